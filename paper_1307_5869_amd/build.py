@@ -50,7 +50,10 @@ HOST_SOURCE_FLAGS = {"simd_host.cpp": ["-O3", "-ffp-contract=off"]}
 # a lane mask and costs three more scalar instructions per group).
 # Tail merging is off so that the repeated tests after each pair of
 # coefficients (mt_pairs.inc) stay in place.
-SOURCE_FLAGS = {"k_mt19937.hip": ["-mllvm", "-structurizecfg-skip-uniform-regions",
+# The GM/GQ kernels work on the matrix instructions' results with the VALU:
+# results in VGPRs, not in accumulation registers, save a copy of every value.
+SOURCE_FLAGS = {"k_gm.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+                "k_mt19937.hip": ["-mllvm", "-structurizecfg-skip-uniform-regions",
                                   "-mllvm", "-simplifycfg-hoist-common=false",
                                   "-mllvm", "-enable-tail-merge=false"]}
 

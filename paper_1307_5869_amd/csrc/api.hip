@@ -480,11 +480,13 @@ int prand_ctx_create(prand_ctx** out, int hip_device) {
   build_gm_ladders(H->gm);
   build_gm_byte_tables(H->gmbyte, H->gmneg);
   build_lfsr_byte_table(H->lfsrbyte);
+  build_gmx_tables(H->gmx);
   hipError_t e = upload(&c->T.mrg, H->mrg, sizeof(H->mrg) / sizeof(H->mrg[0]));
   if (e == hipSuccess) e = upload(&c->T.lfsr, H->lfsr, sizeof(H->lfsr) / sizeof(H->lfsr[0]));
   if (e == hipSuccess) e = upload(&c->T.gm, H->gm, sizeof(H->gm) / sizeof(H->gm[0]));
   if (e == hipSuccess) e = upload(&c->T.gmbyte, H->gmbyte, sizeof(H->gmbyte) / sizeof(H->gmbyte[0]));
   if (e == hipSuccess) e = upload(&c->T.gmneg, H->gmneg, sizeof(H->gmneg) / sizeof(H->gmneg[0]));
+  if (e == hipSuccess) e = upload(&c->T.gmx, H->gmx, sizeof(H->gmx) / sizeof(H->gmx[0]));
   if (e == hipSuccess) e = upload(&c->T.lfsrbyte, H->lfsrbyte, sizeof(H->lfsrbyte) / sizeof(H->lfsrbyte[0]));
   delete H;
   if (e == hipSuccess) e = hipMalloc(&c->T.defaults, kDefaultStride * PRAND_NUM_GENERATORS);
@@ -518,6 +520,7 @@ int prand_ctx_destroy(prand_ctx* c) {
   (void)hipFree(c->T.gm);
   (void)hipFree(c->T.gmbyte);
   (void)hipFree(c->T.gmneg);
+  (void)hipFree(c->T.gmx);
   (void)hipFree(c->T.lfsrbyte);
   release_mt_tables(c);
   (void)hipFree(c->T.defaults);

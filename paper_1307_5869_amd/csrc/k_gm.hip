@@ -5,33 +5,28 @@
 // significant bit first, into 32-bit words (GQ58.3: 36 bits per step, 9 words
 // per 8 steps).
 //
-// v = 1 ensembles (s = 32): one lane per element, half a wavefront per
-// stream, one ballot per step packs a word; each lane keeps the word of one
-// step of every 32, so a flush writes consecutive words from consecutive
-// lanes.  GM55, GQ58.3, GQ58.4: one lane per section, every element stepped
-// in that lane (dev_gmlane.h); a stream is cut into up to 64 sections that
+// Generation by matrix instructions (dev_gmx.h): a wavefront holds the 32
+// elements of one v = 1 stream, or of four 8-element or two 12-element ones;
+// GM19 and GM61 with enough streams to fill the chip keep one lane per element
+// and one ballot per word (dev_gm.h).  Few streams are cut into sections that
 // start by jumps.
 //
-// Arithmetic is exact: special-form reductions (2^29-3, 2^31-1, 2^61-1,
-// 2^51-129) in integers; GM19 (2^19-1) in FP32 FMAs on centred residues,
-// every value an integer below 2^24 (dev_gm.h).  For g = p 2^t (GM55: t = 4, GQ58: t = 29) the even
+// Arithmetic is exact.  For g = p 2^t (GM55: t = 4, GQ58: t = 29) the even
 // k and q kill the 2-adic part within n0 steps; from then on x = 2^t y with y
 // following the same recurrence mod p and the digit equal to
 // floor(2^v y / p), so the kernels run exact mod-g steps only until every
 // element of the wavefront has collapsed and then switch to the mod-p
-// recurrence.  In the steady state an element (GM19 aside) is held as a
-// redundant residue (congruent to the exact value, possibly shifted by a constant, in
-// a range a little wider than the modulus), so no step needs a final
-// conditional subtraction; digits are read off that form and states are
-// written back exact.
+// recurrence.
 #include "dev_gm.h"
-#include "dev_gmlane.h"
+#include "dev_gmx.h"
 
 namespace prand {
 namespace {
 
 using namespace gm;
 
+// GM19 and GM61 with enough streams to fill the chip: half a wavefront per
+// stream, one lane per element, a ballot per word (dev_gm.h)
 template <int G, int DT>
 __global__ void __launch_bounds__(256) gm_gen32_kernel(const GmState* sin, GmState* sout, uint32_t count, uint64_t n,
                                                        void* __restrict__ out) {
@@ -41,35 +36,36 @@ __global__ void __launch_bounds__(256) gm_gen32_kernel(const GmState* sin, GmSta
   gen32_wave<G, DT, false>(live, sin + (live ? s : 0), 0, n, (char*)out + s * n * es, sout + (live ? s : 0), nullptr);
 }
 
-// GM55, GQ58.3, GQ58.4: lane gid owns section gid & (nsec - 1) of stream
-// gid >> nsec_log2; the sections of a stream cover [j seclen, min((j + 1)
-// seclen, n)) and sit in one wavefront (nsec <= 64), so the state read of
-// every section precedes the write-back of the last.  Flush width: 64-byte
-// runs per lane; GQ58.3 whole 128-byte lines (a 48-word ring, 13 KB per
-// wavefront), which measured 4-6 % faster in u32/f32 and 22 % in f64 for
-// it and no faster for GM55 and GQ58.4.
-template <int G>
-constexpr int lane_flush_words() {
-  return G == 6 ? 32 : kLaneFlushWide;
-}
-
-template <int G, int DT>
-__global__ void __launch_bounds__(256) gm_lane_kernel(const GmState* sin, GmState* sout, uint32_t count, uint64_t n,
-                                                      int nsec_log2, uint64_t seclen, void* __restrict__ out,
-                                                      const uint64_t* __restrict__ ladder) {
-  constexpr int FW = lane_flush_words<G>();
-  __shared__ __align__(16) uint32_t stage[4][LaneRing<FW>::kWaveWords];
-  const uint64_t gid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const uint64_t nsec = 1ull << nsec_log2;
-  const uint64_t jlast = (n == 0) ? 0 : (n - 1) / seclen;
-  const uint64_t s = gid >> nsec_log2, j = gid & (nsec - 1);
-  const uint64_t start = j * seclen;
-  const bool live = s < count && j <= jlast;
-  const uint64_t len = live ? ((j == jlast) ? n - start : seclen) : 0;
+// Many streams: a wavefront takes Mx<G>::Q consecutive (stream, section)
+// pairs; the sections of a stream cover [j seclen, min((j + 1) seclen, n)).
+// kSections: several sections per stream, which read the stream's state and
+// jump to their starts; the states are then moved on by a launch of their own
+// (sout null).  Otherwise seclen = n and the states are updated in place.
+template <int G, int DT, bool kSections>
+__global__ void __launch_bounds__(256) gmx_kernel(const GmState* sin, GmState* sout, uint32_t count, uint64_t n,
+                                                  uint32_t nsec, uint64_t seclen, char* __restrict__ out,
+                                                  const GmxTable* __restrict__ table,
+                                                  const uint64_t* __restrict__ ladder) {
+  constexpr int Q = Mx<G>::Q;
   constexpr int es = (DT == PRAND_F64) ? 8 : 4;
-  void* o = (char*)out + (live ? (s * n + start) * es : 0);
-  gmlane_wave<G, DT, true, FW>(stage[threadIdx.x >> 6], live, sin + (live ? s : 0), start, len, o,
-                               (live && j == jlast) ? sout + s : nullptr, ladder);
+  __shared__ uint32_t lds[4][kGmxLds];
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint64_t first = ((uint64_t)blockIdx.x * 4 + w) * Q;
+  const uint64_t all = kSections ? (uint64_t)count * nsec : count;
+  if (first >= all) return;
+  auto sec = [&](int q) {
+    const uint64_t i = first + q;
+    const uint64_t s = kSections ? i / nsec : i, start = kSections ? (i % nsec) * seclen : 0;
+    GmxSec r{nullptr, start, 0, nullptr, nullptr};
+    if (i < all) {
+      r.in = sin + s;
+      r.n = kSections ? (n - start < seclen ? n - start : seclen) : n;
+      r.out = out + (s * n + start) * es;
+      r.sout = kSections ? nullptr : sout + s;
+    }
+    return r;
+  };
+  gmx_wave<G, DT, kSections>(sec, table + G, ladder, lds[w]);
 }
 
 // One lane per element slot (32 per stream): states[s] = base (or states[s])
@@ -79,7 +75,7 @@ __global__ void __launch_bounds__(256) gm_lane_kernel(const GmState* sin, GmStat
 template <int G>
 __global__ void __launch_bounds__(256) gm_jump_kernel(GmState* __restrict__ states, uint32_t count,
                                                       const uint64_t* __restrict__ dist, int nlimbs, int per_stream,
-                                                      const uint64_t* __restrict__ ids, int block_e,
+                                                      uint64_t fixed, const uint64_t* __restrict__ ids, int block_e,
                                                       const GmState* __restrict__ base,
                                                       const uint64_t* __restrict__ ladder,
                                                       const uint64_t* __restrict__ bytetab,
@@ -107,9 +103,11 @@ __global__ void __launch_bounds__(256) gm_jump_kernel(GmState* __restrict__ stat
     const int q = block_e >> 6, r = block_e & 63;   // block in ensemble steps
     N[q] = id << r;
     if (r) N[q + 1] = id >> (64 - r);
-  } else {
+  } else if (dist) {
     const uint64_t* d = dist + (per_stream ? (size_t)s * nlimbs : 0);
     for (int l = 0; l < nlimbs; l++) N[l] = d[l];
+  } else {
+    N[0] = fixed;
   }
   uint32_t new_off = 0;
   if (G == 6) {
@@ -123,52 +121,69 @@ __global__ void __launch_bounds__(256) gm_jump_kernel(GmState* __restrict__ stat
   if (e == 0) { dst->off = new_off; dst->pad = 0; }
 }
 
-template <int G, int DT>
-hipError_t launch_gen(const uint64_t* ladder, const GmState* sin, GmState* sout, uint32_t count, uint64_t n, void* out,
-                      hipStream_t st) {
-  if constexpr (G == 3 || G == 6 || G == 7) {
-    // enough lanes to fill the chip: up to 64 sections per stream, each at
-    // least 64 outputs long; section lengths are multiples of 4 (16-byte
-    // aligned starts) and, for GQ58.3, of 9 (every section starts at the
-    // same place in the 9-word block as the stream)
-    const uint64_t unit = (G == 6) ? 36 : 4;
-    int nsec_log2 = 0;
-    while (nsec_log2 < 6 && ((uint64_t)count << nsec_log2) < (1ull << 19) && (n >> (nsec_log2 + 1)) >= 64)
-      nsec_log2++;
-    uint64_t seclen = (n + (1ull << nsec_log2) - 1) >> nsec_log2;
-    seclen = (seclen + unit - 1) / unit * unit;
-    if (seclen == 0) seclen = unit;
-    const uint64_t lanes = (uint64_t)count << nsec_log2;
-    const uint32_t blocks = (uint32_t)((lanes + 255) / 256);
-    hipLaunchKernelGGL((gm_lane_kernel<G, DT>), dim3(blocks), dim3(256), 0, st, sin, sout, count, n, nsec_log2,
-                       seclen, out, ladder);
-  } else {
-    const uint64_t lanes = (uint64_t)count * 32;
-    const uint32_t blocks = (uint32_t)((lanes + 255) / 256);
-    hipLaunchKernelGGL((gm_gen32_kernel<G, DT>), dim3(blocks), dim3(256), 0, st, sin, sout, count, n, out);
-  }
-  return hipGetLastError();
-}
-
-template <int G>
-hipError_t launch_gen_g(const uint64_t* ladder, int dtype, const GmState* sin, GmState* sout, uint32_t count,
-                        uint64_t n, void* out, hipStream_t st) {
-  switch (dtype) {
-    case PRAND_U32: return launch_gen<G, PRAND_U32>(ladder, sin, sout, count, n, out, st);
-    case PRAND_F32: return launch_gen<G, PRAND_F32>(ladder, sin, sout, count, n, out, st);
-    default: return launch_gen<G, PRAND_F64>(ladder, sin, sout, count, n, out, st);
-  }
-}
-
 template <int G>
 hipError_t launch_jump_g(const DeviceTables& T, GmState* states, uint32_t count, const JumpSpec& js,
                          const GmState* base, hipStream_t st) {
   const uint64_t lanes = (uint64_t)count * 32;
   const uint32_t blocks = (uint32_t)((lanes + 255) / 256);
   hipLaunchKernelGGL(gm_jump_kernel<G>, dim3(blocks), dim3(256), 0, st, states, count, js.dist, js.nlimbs,
-                     js.per_stream, js.ids, js.block_e, base, T.gm,
+                     js.per_stream, js.fixed, js.ids, js.block_e, base, T.gm,
                      T.gmbyte ? T.gmbyte + (size_t)G * 8 * 256 * 4 : nullptr, T.gmneg ? T.gmneg + (size_t)G * 4 : nullptr);
   return hipGetLastError();
+}
+
+// Sections per stream.  With at least kFillWaves wavefronts of whole streams
+// the chip is full (four to five per SIMD, twice over); fewer are cut into
+// sections of whole state advances, as long as there stay enough of them,
+// but no shorter than eight advances (a section's start is one ladder matrix
+// per set bit of its number, about the time of two advances).  Powers of two
+// keep the set bits of the starts few.
+constexpr uint64_t kFillWaves = 8192;
+
+template <int G, int DT>
+hipError_t launch_gen(const DeviceTables& T, const GmState* sin, GmState* sout, uint32_t count, uint64_t n, void* out,
+                      hipStream_t st) {
+  constexpr uint64_t Q = Mx<G>::Q;
+  constexpr uint64_t unit = G == 6 ? kGmxSteps / 8 * 9 : kGmxSteps;   // outputs of a state advance
+  uint64_t seclen = 8 * unit;
+  if constexpr (G == 0 || G == 4) {
+    // half a wavefront per stream: from kFillWaves wavefronts on, or where a
+    // stream is too short to cut, the ballot form is the faster one (2^30
+    // words: GM19 3.9 against 4.0 ms, GM61 10.5 against 12.3 ms)
+    if ((uint64_t)count >= 2 * kFillWaves || n < 2 * seclen) {
+      const uint32_t blocks = (uint32_t)(((uint64_t)count * 32 + 255) / 256);
+      hipLaunchKernelGGL((gm_gen32_kernel<G, DT>), dim3(blocks), dim3(256), 0, st, sin, sout, count, n, out);
+      return hipGetLastError();
+    }
+  }
+  if ((uint64_t)count >= kFillWaves * Q || n < 2 * seclen || sin != sout) {
+    const uint32_t blocks = (uint32_t)(((count + Q - 1) / Q + 3) / 4);
+    hipLaunchKernelGGL((gmx_kernel<G, DT, false>), dim3(blocks), dim3(256), 0, st, sin, sout, count, n, 1u, n,
+                       (char*)out, T.gmx, T.gm);
+    return hipGetLastError();
+  }
+  while ((uint64_t)count * ((n + 2 * seclen - 1) / (2 * seclen)) >= kFillWaves * Q) seclen *= 2;
+  // the grid stays below 2^31 workgroups
+  while ((n + seclen - 1) / seclen > (1ull << 30) / count) seclen *= 2;
+  const uint32_t nsec = (uint32_t)((n + seclen - 1) / seclen);
+  const uint32_t blocks = (uint32_t)((((uint64_t)count * nsec + Q - 1) / Q + 3) / 4);
+  hipLaunchKernelGGL((gmx_kernel<G, DT, true>), dim3(blocks), dim3(256), 0, st, sin, nullptr, count, n, nsec, seclen,
+                     (char*)out, T.gmx, T.gm);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  JumpSpec js;
+  js.fixed = n;
+  return launch_jump_g<G>(T, sout, count, js, nullptr, st);
+}
+
+template <int G>
+hipError_t launch_gen_g(const DeviceTables& T, int dtype, const GmState* sin, GmState* sout, uint32_t count,
+                        uint64_t n, void* out, hipStream_t st) {
+  switch (dtype) {
+    case PRAND_U32: return launch_gen<G, PRAND_U32>(T, sin, sout, count, n, out, st);
+    case PRAND_F32: return launch_gen<G, PRAND_F32>(T, sin, sout, count, n, out, st);
+    default: return launch_gen<G, PRAND_F64>(T, sin, sout, count, n, out, st);
+  }
 }
 
 }  // namespace
@@ -176,14 +191,14 @@ hipError_t launch_jump_g(const DeviceTables& T, GmState* states, uint32_t count,
 hipError_t launch_gm_generate(const DeviceTables& T, int gen, const GmState* sin, GmState* sout, uint32_t count,
                               uint64_t n, int dtype, void* out, hipStream_t st) {
   switch (gen - PRAND_GM19) {
-    case 0: return launch_gen_g<0>(T.gm, dtype, sin, sout, count, n, out, st);
-    case 1: return launch_gen_g<1>(T.gm, dtype, sin, sout, count, n, out, st);
-    case 2: return launch_gen_g<2>(T.gm, dtype, sin, sout, count, n, out, st);
-    case 3: return launch_gen_g<3>(T.gm, dtype, sin, sout, count, n, out, st);
-    case 4: return launch_gen_g<4>(T.gm, dtype, sin, sout, count, n, out, st);
-    case 5: return launch_gen_g<5>(T.gm, dtype, sin, sout, count, n, out, st);
-    case 6: return launch_gen_g<6>(T.gm, dtype, sin, sout, count, n, out, st);
-    default: return launch_gen_g<7>(T.gm, dtype, sin, sout, count, n, out, st);
+    case 0: return launch_gen_g<0>(T, dtype, sin, sout, count, n, out, st);
+    case 1: return launch_gen_g<1>(T, dtype, sin, sout, count, n, out, st);
+    case 2: return launch_gen_g<2>(T, dtype, sin, sout, count, n, out, st);
+    case 3: return launch_gen_g<3>(T, dtype, sin, sout, count, n, out, st);
+    case 4: return launch_gen_g<4>(T, dtype, sin, sout, count, n, out, st);
+    case 5: return launch_gen_g<5>(T, dtype, sin, sout, count, n, out, st);
+    case 6: return launch_gen_g<6>(T, dtype, sin, sout, count, n, out, st);
+    default: return launch_gen_g<7>(T, dtype, sin, sout, count, n, out, st);
   }
 }
 

@@ -66,6 +66,36 @@ constexpr GmParams kGmParams[8] = {
     /* GQ58.3 */ {8, 48, 536870909ull, 29, 3, 12, 16},
     /* GQ58.4 */ {8, 48, 536870909ull, 29, 4, 8, 16},
 };
+
+// ---- GM/GQ generation by matrix instructions (dev_gmx.h) ----
+// p = 2^e - c; base-16 digits per coefficient (16^digits covers p several
+// times over), 11-bit positions of a fraction, offset of the result in
+// units of the fraction's last bit (an inline constant up to 64; the digits
+// of GM55 and GM61 lose more), carries taken in the slow VALU class per 16
+struct GmxShape {
+  int e;
+  uint64_t c;
+  int digits, positions, delta, slow;
+};
+constexpr GmxShape kGmxShape[8] = {
+    /* GM19   */ {19, 1, 5, 3, 64},
+    /* GM29   */ {29, 3, 8, 4, 64},
+    /* GM31   */ {31, 1, 8, 4, 64},
+    /* GM55   */ {51, 129, 13, 6, 128},
+    /* GM61   */ {61, 1, 16, 7, 128},
+    /* GQ58.1 */ {29, 3, 8, 4, 64},
+    /* GQ58.3 */ {29, 3, 8, 4, 64},
+    /* GQ58.4 */ {29, 3, 8, 4, 64},
+};
+constexpr int kGmxBits = 11;     // bits of a position
+constexpr int kGmxSteps = 256;   // steps per state advance
+struct alignas(16) GmxTable {
+  uint64_t mat[(kGmxSteps + 1) * 4];   // M^j mod p, j = 0 .. kGmxSteps
+  // operand of matrix instruction k (of NK = ceil(digits / 8)) for steps
+  // 32 g + 1 .. 32 g + 32: 16 bytes per lane at [(g NK + k) 64 + lane]
+  int8_t coef[(kGmxSteps / 32) * 2 * 64 * 16];
+};
+
 inline bool is_gm(int gen) { return gen >= PRAND_GM19 && gen <= PRAND_GQ58X4; }
 
 // Byte tables for block splitting with each generator's default variant:
@@ -82,6 +112,7 @@ struct DeviceTables {
   uint32_t* lfsr = nullptr;   // [kLadder][4][32]: columns of T_c^(2^b)
   uint64_t* gm = nullptr;     // [8][kLadder][4]: (a b; c d) = M^(2^b) mod p
   uint64_t* gmbyte = nullptr;   // [8][8][256][4]: M^(d 2^(kGmByteE[G] + 8 j)) mod p
+  GmxTable* gmx = nullptr;      // [8]
   uint64_t* gmneg = nullptr;    // [8][4]: M^(-n0) mod p (composite moduli; identity otherwise)
   uint32_t* lfsrbyte = nullptr; // [8][256][4][32]: columns of T_c^(d 2^(kLfsrByteE + 8 j))
   uint32_t* mt = nullptr;     // [kLadder][624]: bits of x^(2^b) mod phi (19937 used)
@@ -134,8 +165,10 @@ __device__ __forceinline__ void store_out16(void* p, uint4 v) {
 // ---- launchers (one per kernel family); all enqueue on `st` ----
 // Distances: `dist` holds nlimbs limbs per stream when per_stream, else one
 // shared distance.  `ids` + `block_e`: distance id * 2^block_e (GQ58.3: in
-// ensemble steps).  Exactly one of (dist, ids) is used.
+// ensemble steps).  Exactly one of (dist, ids) is used; GM/GQ with neither:
+// every stream moves `fixed` outputs.
 struct JumpSpec {
+  uint64_t fixed = 0;
   const uint64_t* dist = nullptr;
   int nlimbs = 0;
   int per_stream = 0;
@@ -185,6 +218,7 @@ struct HostTables {
   uint64_t gm[8 * kLadder * 4];
   uint64_t gmbyte[8 * 8 * 256 * 4];
   uint64_t gmneg[8 * 4];
+  GmxTable gmx[8];
   uint32_t lfsrbyte[8 * 256 * 128];
 };
 void build_mrg_ladder(uint32_t* out);
@@ -201,6 +235,7 @@ void build_mrg_section_table(uint64_t seclen, uint32_t* out);
 void build_lfsr_section_table(uint64_t seclen, uint32_t* out);
 void build_gm_ladders(uint64_t* out);
 void build_gm_byte_tables(uint64_t* out, uint64_t* neg);
+void build_gmx_tables(GmxTable* out);
 void build_lfsr_byte_table(uint32_t* out);
 
 // the calling thread's current device is set to `dev` for the guard's life
