@@ -251,8 +251,8 @@ const uint32_t* section_table(prand_ctx* c, int k, uint64_t seclen, hipStream_t 
 }
 
 // sections per stream (log2) and section length of the many-stream
-// MRG32K3A/LFSR113 kernel: up to 64 sections per stream, section starts
-// 16-byte aligned.  With a section-start table a start costs one matrix
+// MRG32K3A/LFSR113 kernel: up to 64 sections per stream of whole 32-word
+// chunks (regstream.h).  With a section-start table a start costs one matrix
 // application, so streams are cut into as many sections of at least 256
 // outputs as fit in 2^22 lanes (more, shorter sections measured faster: the
 // 64 runs of a wavefront then lie close together in the output); with ladder
@@ -268,8 +268,8 @@ void section_plan(uint32_t count, uint64_t n, bool table, int& nsec_log2, uint64
       nsec_log2++;
   }
   seclen = (n + (1ull << nsec_log2) - 1) >> nsec_log2;
-  seclen = (seclen + 3) & ~3ull;
-  if (seclen == 0) seclen = 4;
+  seclen = (seclen + 31) & ~31ull;
+  if (seclen == 0) seclen = 32;
 }
 
 // many-stream generation; sin/sout may alias (sections of a stream never

@@ -131,7 +131,7 @@ int batch_plan(const prand_task* tasks, uint32_t ntasks, const prand_batch_confi
       continue;
     }
     b.kind = kTileGen;
-    const uint64_t n = t.n, es = t.dtype == PRAND_F64 ? 8 : 4;
+    const uint64_t n = t.n;
     const double c = per_output_cost(t.gen);
     {
       const bool v1 = t.gen == PRAND_GM19 || t.gen == PRAND_GM29 || t.gen == PRAND_GM31 || t.gen == PRAND_GM61 ||
@@ -167,7 +167,6 @@ int batch_plan(const prand_task* tasks, uint32_t ntasks, const prand_batch_confi
       if (n < 64 * sec) sec = std::max<uint64_t>(32, round_up((n + 63) / 64, 32));
       const uint64_t total = (n + sec - 1) / sec;
       b.seclen = sec;
-      b.coalesce = ((uintptr_t)t.out % 16 == 0) && ((sec * es) % 16 == 0);
       for (uint64_t f = 0; f < total; f += 64) {
         b.first = f;
         b.nsec = (uint32_t)std::min<uint64_t>(64, total - f);

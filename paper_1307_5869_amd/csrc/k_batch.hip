@@ -166,8 +166,7 @@ __device__ __forceinline__ void gen_reg(const BatchTile& tl, const BatchTask& tk
   void* o = (char*)tk.out + (s.live ? s.start : 0) * es;
   const typename G::State* in = (const typename G::State*)(scratch + tl.starts) + (threadIdx.x & 63);
   regstream_wave<G, DT, CW, false>(lds, s.live, in, 0, s.len, o,
-                                         s.last ? (typename G::State*)tk.state_out : nullptr, tl.coalesce != 0,
-                                         nullptr);
+                                         s.last ? (typename G::State*)tk.state_out : nullptr, nullptr);
 }
 
 __global__ void __launch_bounds__(256) batch_reg_kernel(const BatchTile* __restrict__ tiles, uint32_t ntiles,

@@ -34,7 +34,7 @@ struct BatchTile {
   uint64_t first;      // first section of the tile
   uint64_t seclen;     // outputs per section (the task's last section may be shorter)
   uint32_t nsec;       // live sections in the tile
-  uint32_t coalesce;   // MRG32K3A/LFSR113: every section start 16-byte aligned
+  uint32_t pad;
   uint64_t len32;      // v = 1 GM/GQ tiles: the common length of the live
                        // sections; copy tiles: 32-bit words of the state
   uint64_t starts;     // byte offset of the tile's section start states in
