@@ -489,8 +489,9 @@ __device__ __forceinline__ void gq3_words_to_steps(uint64_t* N, uint32_t off, ui
     N[l] = old + carry;
     carry = N[l] < old ? 1 : 0;
   }
-  uint64_t r = 0;   // divide by 9 in 32-bit pieces
+  uint64_t r = 0;   // divide by 9 in 32-bit pieces (leading zero limbs stay 0)
   for (int l = kMaxLimbs; l >= 0; l--) {
+    if (!(r | N[l])) continue;
     const uint64_t hi = (r << 32) | (N[l] >> 32);
     const uint64_t qh = hi / 9;
     r = hi % 9;

@@ -68,10 +68,25 @@ __global__ void __launch_bounds__(256) gmx_kernel(const GmState* sin, GmState* s
   gmx_wave<G, DT, kSections>(sec, table + G, ladder, lds[w]);
 }
 
-// One lane per element slot (32 per stream): states[s] = base (or states[s])
-// jumped by the stream's distance; GQ58.3 distances count words.  Block
-// splitting with the default block exponent takes the byte tables (at most
-// eight matrices per stream), other distances the ladder (one per set bit).
+// lanes per stream of the jump: one per element; GQ58.3's twelve in a group of
+// sixteen, so that a stream's lanes share a wavefront (all of them read the
+// state's word offset before one of them writes it)
+template <int G>
+constexpr uint32_t jump_lanes() {
+  return kGmParams[G].s == 12 ? 16 : kGmParams[G].s;
+}
+
+// One lane per element: states[s] = base (or states[s]) jumped by the
+// stream's distance; GQ58.3 distances count words.  Block splitting with the
+// default block exponent takes the byte tables (at most eight matrices per
+// stream), other distances the ladder (one per set bit).  A state's unused
+// element slots are left alone where it moves in place and copied from the
+// base otherwise.  Bound: the modular products (GM55 and GM61: 128-bit) and the
+// state lines.  (With a lane per slot, 32 per stream, a wavefront of the 8-
+// and 12-element ensembles did its products with a quarter or a third of its
+// lanes, and every slot was read and written.  2^20 states moved 2^k: GM55 494
+// -> 180 us, GQ58.4 363 -> 188, GQ58.3 1490 -> 811; started by block splitting:
+// GM55 711 -> 276, GQ58.4 670 -> 220, GQ58.3 669 -> 371.)
 template <int G>
 __global__ void __launch_bounds__(256) gm_jump_kernel(GmState* __restrict__ states, uint32_t count,
                                                       const uint64_t* __restrict__ dist, int nlimbs, int per_stream,
@@ -80,51 +95,53 @@ __global__ void __launch_bounds__(256) gm_jump_kernel(GmState* __restrict__ stat
                                                       const uint64_t* __restrict__ ladder,
                                                       const uint64_t* __restrict__ bytetab,
                                                       const uint64_t* __restrict__ neg) {
+  constexpr uint32_t S = kGmParams[G].s, kLanes = jump_lanes<G>();
   const uint64_t gid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const uint64_t s = gid >> 5;
-  if (s >= count) return;
-  const int e = threadIdx.x & 31;
+  const uint64_t s = gid / kLanes;
+  const uint32_t e = (uint32_t)(gid % kLanes);
+  if (s >= count || e >= S) return;
   const GmState* src = base ? base : states + s;
+  GmState* dst = states + s;
   uint64_t xc = src->xc[e], xp = src->xp[e];
-  const uint32_t off = src->off;
+  uint32_t off = (G == 6) ? src->off : 0;
   if (ids && bytetab && block_e == kGmByteE[G]) {
     // whole blocks: the offset inside a GQ58.3 block is kept
-    if (e < kGmParams[G].s) jump_bytes_elem<G>(xc, xp, ids[s], bytetab, neg);
-    GmState* dst = states + s;
-    dst->xc[e] = xc;
-    dst->xp[e] = xp;
-    if (e == 0) { dst->off = (G == 6) ? off : 0; dst->pad = 0; }
-    return;
-  }
-  uint64_t N[kMaxLimbs + 1];
-  for (int l = 0; l <= kMaxLimbs; l++) N[l] = 0;
-  if (ids) {
-    const uint64_t id = ids[s];
-    const int q = block_e >> 6, r = block_e & 63;   // block in ensemble steps
-    N[q] = id << r;
-    if (r) N[q + 1] = id >> (64 - r);
-  } else if (dist) {
-    const uint64_t* d = dist + (per_stream ? (size_t)s * nlimbs : 0);
-    for (int l = 0; l < nlimbs; l++) N[l] = d[l];
+    jump_bytes_elem<G>(xc, xp, ids[s], bytetab, neg);
   } else {
-    N[0] = fixed;
+    uint64_t N[kMaxLimbs + 1];
+    for (int l = 0; l <= kMaxLimbs; l++) N[l] = 0;
+    if (ids) {
+      const uint64_t id = ids[s];
+      const int q = block_e >> 6, r = block_e & 63;   // block in ensemble steps
+      N[q] = id << r;
+      if (r) N[q + 1] = id >> (64 - r);
+    } else if (dist) {
+      const uint64_t* d = dist + (per_stream ? (size_t)s * nlimbs : 0);
+      for (int l = 0; l < nlimbs; l++) N[l] = d[l];
+    } else {
+      N[0] = fixed;
+    }
+    // whole blocks of an id keep the offset inside the block
+    if (G == 6 && !ids) gq3_words_to_steps(N, off, &off);
+    jump_steps_elem<G>(xc, xp, N, ladder);
   }
-  uint32_t new_off = 0;
-  if (G == 6) {
-    if (ids) new_off = off;   // whole blocks: the offset inside the block is kept
-    else gq3_words_to_steps(N, off, &new_off);
-  }
-  if (e < kGmParams[G].s) jump_steps_elem<G>(xc, xp, N, ladder);
-  GmState* dst = states + s;
   dst->xc[e] = xc;
   dst->xp[e] = xp;
-  if (e == 0) { dst->off = new_off; dst->pad = 0; }
+  if (base)
+    for (uint32_t i = S + e; i < 32; i += S) {
+      dst->xc[i] = base->xc[i];
+      dst->xp[i] = base->xp[i];
+    }
+  if (e == 0) {
+    dst->off = off;
+    dst->pad = 0;
+  }
 }
 
 template <int G>
 hipError_t launch_jump_g(const DeviceTables& T, GmState* states, uint32_t count, const JumpSpec& js,
                          const GmState* base, hipStream_t st) {
-  const uint64_t lanes = (uint64_t)count * 32;
+  const uint64_t lanes = (uint64_t)count * jump_lanes<G>();
   const uint32_t blocks = (uint32_t)((lanes + 255) / 256);
   hipLaunchKernelGGL(gm_jump_kernel<G>, dim3(blocks), dim3(256), 0, st, states, count, js.dist, js.nlimbs,
                      js.per_stream, js.fixed, js.ids, js.block_e, base, T.gm,
