@@ -17,13 +17,12 @@
 // for the low 48 bits of the id and two bytes for the top 16 bits; from the
 // default state the top 16 bits come from a table of precomputed states, so a
 // stream costs at most 3 polynomials.
-// One wavefront does one stream: the sequence is produced 227 words at a time
-// into an LDS ring, and lane l accumulates outputs t = 10l .. 10l+9 while a
-// register window of 10 sequence words slides over the coefficients, so each
+// A workgroup of 4, 8 or 16 wavefronts does one stream: it produces the
+// sequence into LDS, and each wavefront scans its own part of the
+// coefficients: lane l accumulates outputs t = 10l .. 10l+9 while a register
+// window of 10 sequence words slides over the coefficients, so each
 // coefficient costs one LDS read per lane and set coefficients cost 10
-// three-input XORs per two.  Launches of few streams (stream starts served
-// one request at a time) give each stream a workgroup of 12 or 8 wavefronts
-// that scan separate coefficient ranges and XOR their partial windows.
+// three-input XORs per two.  The partial windows are XORed at the end.
 #include "dev_mt.h"
 #include "mt_poly.h"
 #include "prand_batch.h"
@@ -50,72 +49,26 @@ __global__ void __launch_bounds__(64) mt_generate_kernel(MtState* states, uint32
 }
 
 // ------------------------------------------------------------------ jump
-// Launches of few streams jump each stream with several wavefronts (12 up to
-// 512 streams, 8 up to 2048; one-stream starts from the default state measured
-// 0.27 and 0.31 ms against 1.28 ms with one wavefront; at 4096 streams the
-// ranges' repeated recurrence runs cost more than the shorter chains save).
-constexpr uint32_t kMtSplit12MaxCount = 512;
-constexpr uint32_t kMtSplit8MaxCount = 2048;
-constexpr int kRing = 1024;                 // LDS ring of sequence words (< 900 live at a time)
-constexpr int kMask = kRing - 1;
-constexpr int kMirror = 16;                 // ring[0..15] repeated after the end
+// Wavefronts per stream by the launch's streams, all measured for block
+// splitting from the default state (three polynomials; us):
+//   streams      1   256   512  1000  2048  4096  8192  20000  65536
+//   16         119   138   190   350   656  1283  2479   6563  19700
+//   8          179   194   228   318   606  1167  2272   5823  18300
+//   4          335   339   347   372   640  1183  2266   5518  17820
+// (one wavefront per stream with an LDS ring of its own, the former form for
+// more than 2048 streams, took 1231 us for one and 19300 us for 65536; its
+// split forms, in which every wavefront ran the recurrence by itself up to its
+// coefficients, 244 us for one stream and 639 us for 1000).
+constexpr uint32_t kMtSplit16MaxCount = 512;
+constexpr uint32_t kMtSplit8MaxCount = 4096;
 constexpr int kDeg = 19937;
-constexpr int kSeqLen = kDeg - 1 + 624;     // words seq[0..20559] take part
 constexpr int kPer = 10;                    // outputs per lane: 64 * 10 >= 624
 
 // s_waitcnt lgkmcnt(3), the other counters left at their maximum (gfx9
 // encoding: vmcnt in bits 3:0 and 15:14, expcnt 6:4, lgkmcnt 11:8).
 __device__ __forceinline__ void wait_lds_but3() { __builtin_amdgcn_s_waitcnt(0xC37F); }
 
-// Extend the ring to hold seq[0..upto) (227 words per phase).  Words landing
-// in the first kMirror slots are also written after the ring's end, so that
-// kPer consecutive words can be read from any slot without wrapping.  The
-// ring belongs to one wavefront.  kBatched: a phase reads only words of
-// earlier phases (j - 227 and below), so all its reads are issued before its
-// writes, one LDS latency per phase; it takes 12 more registers, so it is
-// used where no scan registers are live (the run up to a range's start).
-template <bool kBatched>
-__device__ __forceinline__ void extend(uint32_t* ring, int& gen_hi, int upto, int lane) {
-  if (upto > kSeqLen) upto = kSeqLen;
-  while (gen_hi < upto) {
-    const int g0 = gen_hi;
-    const int g1 = (g0 + 227 < kSeqLen) ? g0 + 227 : kSeqLen;
-    if constexpr (kBatched) {
-      uint32_t x0[4], x1[4], xm[4];
-#pragma unroll
-      for (int k = 0; k < 4; k++) {
-        const int j = g0 + lane + 64 * k;
-        if (j < g1) {
-          x0[k] = ring[(j - 624) & kMask];
-          x1[k] = ring[(j - 623) & kMask];
-          xm[k] = ring[(j - 227) & kMask];
-        }
-      }
-      asm volatile("" ::: "memory");
-#pragma unroll
-      for (int k = 0; k < 4; k++) {
-        const int j = g0 + lane + 64 * k;
-        if (j < g1) {
-          const uint32_t v = recur(x0[k], x1[k], xm[k]);
-          const int slot = j & kMask;
-          ring[slot] = v;
-          if (slot < kMirror) ring[slot + kRing] = v;
-        }
-      }
-    } else {
-      for (int j = g0 + lane; j < g1; j += 64) {
-        const uint32_t v = recur(ring[(j - 624) & kMask], ring[(j - 623) & kMask], ring[(j - 227) & kMask]);
-        const int slot = j & kMask;
-        ring[slot] = v;
-        if (slot < kMirror) ring[slot + kRing] = v;
-      }
-    }
-    wave_lds_sync();
-    gen_hi = g1;
-  }
-}
-
-// ring[0..623] holds a window (next output = tempered successor); apply_poly
+// buf[0..623] holds a window (next output = tempered successor); apply_poly
 // replaces it by g(A) applied to it, g = poly (624 words of coefficient bits,
 // reduced: no bit at or above 19937 is set).  Lane l accumulates outputs
 // t = 10 l + r.  For the coefficients i0 .. i0 + 9 of a group it holds the
@@ -134,13 +87,14 @@ __device__ __forceinline__ void extend(uint32_t* ring, int& gen_hi, int upto, in
 // pair the remaining nothing-pending tests are repeated in place, one taken
 // branch less per pair), built with the structurizer told to leave uniform
 // regions alone, so every test is one scalar compare and branch.
+// i0 is counted from the buffer's first word.
 template <int kOff>
-__device__ __forceinline__ void group(uint32_t* ring, uint32_t i0, uint32_t lo, uint32_t hi, int lane,
+__device__ __forceinline__ void group(const uint32_t* buf, uint32_t i0, uint32_t lo, uint32_t hi, int lane,
                                       uint32_t (&acc)[kPer],
                                       const uint32_t (&cur)[kPer], const uint32_t (&nxt)[kPer],
                                       uint32_t (&pf)[kPer]) {
   // i0 + 20 + 10 lane is even, so the window is read in 8-byte pairs
-  const uint32_t* src = ring + ((i0 + 2 * kPer + kPer * lane) & (kMask & ~1));   // + k < kRing + kMirror
+  const uint32_t* src = buf + ((i0 + 2 * kPer + kPer * lane) & ~1u);
 #pragma unroll
   for (int k = 0; k < kPer; k++) pf[k] = src[k];
   // the window nxt was read by the previous group: wait for those reads once
@@ -187,107 +141,126 @@ __device__ __forceinline__ uint32_t poly_word(PolyBuf pb, uint32_t w) {
   return __builtin_amdgcn_raw_buffer_load_b32(pb, off, 0, 0);
 }
 
-// The sum over the coefficients c0 <= i < c1 of poly into acc (lane l holds
-// outputs t = 10 l + r) for the window ring[0..623]; c0 a multiple of kStep,
-// c1 one too or kDeg.  The ring is extended as far as the range needs; a
-// range that starts later first runs the recurrence up to it.
-__device__ __forceinline__ void scan_range(uint32_t* ring, const uint32_t* __restrict__ poly, int lane, uint32_t c0,
-                                           uint32_t c1, uint32_t (&sum)[kPer]) {
-  uint32_t acc[kPer];   // local: the groups' code is built on a register array
-  int gen_hi = 624;
-  extend<true>(ring, gen_hi, (int)c0 + kStepReach, lane);
-  uint32_t wa[kPer], wb[kPer], wc[kPer];
-  // the first two windows, read as group() reads the later ones (an even
-  // slot; words past the ring's end are in its mirror)
-  const uint32_t* w0 = ring + ((c0 + kPer * lane) & (kMask & ~1));
-  const uint32_t* w1 = ring + ((c0 + kPer + kPer * lane) & (kMask & ~1));
+// apply_poly by the kParts wavefronts of a workgroup: the sequence is
+// produced by all of them, segment by segment into a linear LDS buffer; of a
+// segment's coefficients each wavefront scans its own kChunk (a multiple of
+// kStep), and at the end the partial sums, which add up to the whole because
+// g(A) Y is linear in the coefficients, are XORed together through LDS.
+// Segments: as few as leave eight wavefronts per SIMD (4 and 8 parts: 19 and
+// 31 KB per workgroup); fewer or more measured 1-5 % slower.
+template <int kParts>
+struct Split {
+  static constexpr int kThreads = 64 * kParts;
+  static constexpr uint32_t kSegs = kParts == 4 ? 6 : 3;
+  static constexpr uint32_t kChunk = ((kDeg + kParts * kSegs - 1) / (kParts * kSegs) + kStep - 1) / kStep * kStep;
+  static constexpr uint32_t kSeg = kChunk * kParts;               // coefficients of a segment
+  static constexpr int kPhase = kThreads < 623 ? kThreads : 623;   // words a phase adds
+  static constexpr int kHold = (int)kSeg + kStepReach + kPhase;
+  static constexpr int kSum = 640 * kParts;
+  static constexpr int kLds = kHold > kSum ? kHold : kSum;        // words
+  static constexpr int kWords = (624 + kThreads - 1) / kThreads;   // combined words per thread
+  static_assert(kSeg * kSegs >= (uint32_t)kDeg, "the segments cover the polynomial");
+  static_assert(kSeg >= (uint32_t)(kStepReach + kPhase), "a segment's words past its end move without overlap");
+};
+
+// words that the recurrence takes from the pair (x_j, x_{j+1})
+__device__ __forceinline__ uint32_t twist_pair(const uint32_t* x) { return recur(x[0], x[1], 0); }
+
+// Extend buf[0 .. have) (have >= 624 words of the sequence) to at least
+// `need` words, kPhase words at a time: word have + t is x_{j+397} + the pair
+// of x_j (j = have - 624 + t), and where x_{j+397} is itself new (t >= 227,
+// again from t >= 454), the recurrence is put in for it, so a phase needs no
+// word of its own and one barrier serves up to 623 words instead of 227.
+template <int kParts>
+__device__ __forceinline__ void extend_shared(uint32_t* buf, int& have, int need) {
+  const int t = (int)threadIdx.x;
+  while (have < need) {
+    if (t < Split<kParts>::kPhase) {
+      const uint32_t* x = buf + have - 624 + t;
+      uint32_t v = twist_pair(x);
+      if (t < 227) {
+        v ^= x[397];
+      } else if (t < 454) {
+        v ^= x[170] ^ twist_pair(x - 227);
+      } else {
+        v ^= x[-57] ^ twist_pair(x - 227) ^ twist_pair(x - 454);
+      }
+      buf[have + t] = v;
+    }
+    have += Split<kParts>::kPhase;
+    __syncthreads();
+  }
+}
+
+// The sum over the coefficients c0 <= i < c1 of poly added to sum (lane l
+// holds outputs t = 10 l + r); buf[0] is word `base` of the sequence, c0 and
+// base multiples of kStep, c1 one too or kDeg
+__device__ __forceinline__ void scan(const uint32_t* buf, const uint32_t* __restrict__ poly, int lane, uint32_t c0,
+                                            uint32_t c1, uint32_t base, uint32_t (&sum)[kPer]) {
+  // acc is local: the groups' code is built on a register array
+  uint32_t acc[kPer], wa[kPer], wb[kPer], wc[kPer];
+  // the first two windows, read as group() reads the later ones
+  const uint32_t* w0 = buf + ((c0 - base + kPer * lane) & ~1u);
 #pragma unroll
   for (int r = 0; r < kPer; r++) {
-    acc[r] = 0;
+    acc[r] = sum[r];
     wa[r] = w0[r];
-    wb[r] = w1[r];
+    wb[r] = w0[kPer + r];
   }
   // bits i1 .. i1 + 59 lie in the words i1 / 32 .. i1 / 32 + 2 (the last
-  // step's third word is past the polynomial and reads as zero).  The ring
-  // is extended 227 words at a time and every step that its words allow runs
-  // before the next extension (near the end the sequence stops at kSeqLen:
-  // the words past it meet only coefficients at or above 19937, which are
-  // zero, or outputs t >= 624, which are dropped).
+  // step's third word is past the polynomial and reads as zero)
   const PolyBuf pb = poly_buffer(poly);
-  uint32_t i1 = c0;
   uint32_t n0 = poly_word(pb, c0 >> 5), n1 = poly_word(pb, (c0 >> 5) + 1), n2 = poly_word(pb, (c0 >> 5) + 2);
-  while (i1 < c1) {
-    extend<false>(ring, gen_hi, (int)i1 + kStepReach, lane);
-    const uint32_t lim = (gen_hi >= kSeqLen) ? (uint32_t)kDeg : (uint32_t)(gen_hi - kStepReach);
-    do {
-      const uint32_t p0 = __builtin_amdgcn_readfirstlane(n0), p1 = __builtin_amdgcn_readfirstlane(n1),
-                     p2 = __builtin_amdgcn_readfirstlane(n2);
-      const uint32_t wn = (i1 + kStep) >> 5;
-      n0 = poly_word(pb, wn);
-      n1 = poly_word(pb, wn + 1);
-      n2 = poly_word(pb, wn + 2);
-      const uint32_t sh = i1 & 31;
-      uint32_t b0 = (uint32_t)((((uint64_t)p1 << 32) | p0) >> sh);   // bits i1 .. i1 + 31
-      uint32_t b1 = (uint32_t)((((uint64_t)p2 << 32) | p1) >> sh);   // bits i1 + 32 .. i1 + 63
-      asm volatile("" : "+s"(b0), "+s"(b1));   // every test reads these two words
-      group<0>(ring, i1, b0, b1, lane, acc, wa, wb, wc);
-      group<kPer>(ring, i1 + kPer, b0, b1, lane, acc, wb, wc, wa);
-      group<2 * kPer>(ring, i1 + 2 * kPer, b0, b1, lane, acc, wc, wa, wb);
-      group<3 * kPer>(ring, i1 + 3 * kPer, b0, b1, lane, acc, wa, wb, wc);
-      group<4 * kPer>(ring, i1 + 4 * kPer, b0, b1, lane, acc, wb, wc, wa);
-      group<5 * kPer>(ring, i1 + 5 * kPer, b0, b1, lane, acc, wc, wa, wb);
-      i1 += kStep;
-    } while (i1 <= lim && i1 < c1);
+  for (uint32_t i1 = c0; i1 < c1; i1 += kStep) {
+    const uint32_t p0 = __builtin_amdgcn_readfirstlane(n0), p1 = __builtin_amdgcn_readfirstlane(n1),
+                   p2 = __builtin_amdgcn_readfirstlane(n2);
+    const uint32_t wn = (i1 + kStep) >> 5;
+    n0 = poly_word(pb, wn);
+    n1 = poly_word(pb, wn + 1);
+    n2 = poly_word(pb, wn + 2);
+    const uint32_t sh = i1 & 31;
+    uint32_t b0 = (uint32_t)((((uint64_t)p1 << 32) | p0) >> sh);
+    uint32_t b1 = (uint32_t)((((uint64_t)p2 << 32) | p1) >> sh);
+    asm volatile("" : "+s"(b0), "+s"(b1));   // every test reads these two words
+    const uint32_t i0 = i1 - base;
+    group<0>(buf, i0, b0, b1, lane, acc, wa, wb, wc);
+    group<kPer>(buf, i0 + kPer, b0, b1, lane, acc, wb, wc, wa);
+    group<2 * kPer>(buf, i0 + 2 * kPer, b0, b1, lane, acc, wc, wa, wb);
+    group<3 * kPer>(buf, i0 + 3 * kPer, b0, b1, lane, acc, wa, wb, wc);
+    group<4 * kPer>(buf, i0 + 4 * kPer, b0, b1, lane, acc, wb, wc, wa);
+    group<5 * kPer>(buf, i0 + 5 * kPer, b0, b1, lane, acc, wc, wa, wb);
   }
 #pragma unroll
   for (int r = 0; r < kPer; r++) sum[r] = acc[r];
 }
 
-__device__ __forceinline__ void apply_poly(uint32_t* ring, const uint32_t* __restrict__ poly, int lane) {
-  uint32_t acc[kPer];
-  scan_range(ring, poly, lane, 0, (uint32_t)kDeg, acc);
-  __syncthreads();
-#pragma unroll
-  for (int r = 0; r < kPer; r++) {
-    const int t = kPer * lane + r;
-    if (t < 624) ring[t] = (t == 0) ? (acc[r] & kUpper) : acc[r];
-  }
-  __syncthreads();
-}
-
-// apply_poly by kParts wavefronts of one workgroup, for few streams: the
-// coefficients are cut into kParts ranges of kChunk (a multiple of kStep),
-// wavefront w scans range w in its own ring rings[w] (first running the
-// recurrence up to the range's start), and the partial sums, which add up to
-// the whole because g(A) Y is linear in the coefficients, are XORed together
-// through LDS and the result copied into every ring.  A lone stream's
-// polynomial then takes the time of one range plus the recurrence up to it
-// instead of the whole scan (the ranges' recurrence runs are repeated work,
-// which is why many streams keep one wavefront each).
+// buf[0 .. 624) holds the window; every thread of the workgroup calls, with
+// the window in place for all of them
 template <int kParts>
-struct Split {
-  static constexpr uint32_t kChunk = ((kDeg + kParts - 1) / kParts + kStep - 1) / kStep * kStep;
-  static constexpr int kThreads = 64 * kParts;
-  static constexpr int kWords = (624 + kThreads - 1) / kThreads;   // combined words per thread
-  static_assert(kChunk * (kParts - 1) < (uint32_t)kDeg, "every range holds coefficients");
-};
-
-template <int kParts>
-__device__ __forceinline__ void apply_poly_split(uint32_t (*rings)[kRing + kMirror], const uint32_t* __restrict__ poly,
-                                                 int lane, int part) {
+__device__ __forceinline__ void apply_poly(uint32_t* buf, const uint32_t* __restrict__ poly, int lane, int part) {
   using S = Split<kParts>;
-  uint32_t* ring = rings[part];
-  const uint32_t c0 = (uint32_t)part * S::kChunk;
-  const uint32_t c1 = c0 + S::kChunk < (uint32_t)kDeg ? c0 + S::kChunk : (uint32_t)kDeg;
-  uint32_t acc[kPer];
-  scan_range(ring, poly, lane, c0, c1, acc);
-  wave_lds_sync();   // the wavefront's reads of its ring are done
+  uint32_t sum[kPer];
 #pragma unroll
-  for (int r = 0; r < kPer; r++) {
-    const int t = kPer * lane + r;
-    if (t < 624) ring[t] = acc[r];
+  for (int r = 0; r < kPer; r++) sum[r] = 0;
+  int have = 624;
+#pragma unroll 1
+  for (uint32_t g = 0; g < S::kSegs; g++) {
+    const uint32_t base = g * S::kSeg;
+    if (g) {
+      // the words past the segment move to the front (fewer than kSeg)
+      have -= (int)S::kSeg;
+      for (int i = (int)threadIdx.x; i < have; i += S::kThreads) buf[i] = buf[S::kSeg + i];
+      __syncthreads();
+    }
+    extend_shared<kParts>(buf, have, (int)S::kSeg + kStepReach);
+    const uint32_t c0 = base + (uint32_t)part * S::kChunk;
+    const uint32_t c1 = c0 + S::kChunk < (uint32_t)kDeg ? c0 + S::kChunk : (uint32_t)kDeg;
+    if (c0 < c1) scan(buf, poly, lane, c0, c1, base, sum);
+    __syncthreads();   // the segment's words are read
   }
-  __syncthreads();   // every partial in place
+#pragma unroll
+  for (int r = 0; r < kPer; r++) buf[640 * part + kPer * lane + r] = sum[r];
+  __syncthreads();   // every partial sum in place
   uint32_t v[S::kWords];
 #pragma unroll
   for (int k = 0; k < S::kWords; k++) {
@@ -295,18 +268,15 @@ __device__ __forceinline__ void apply_poly_split(uint32_t (*rings)[kRing + kMirr
     v[k] = 0;
     if (t < 624) {
 #pragma unroll
-      for (int p = 0; p < kParts; p++) v[k] ^= rings[p][t];
+      for (int p = 0; p < kParts; p++) v[k] ^= buf[640 * p + t];
       if (t == 0) v[k] &= kUpper;
     }
   }
-  __syncthreads();   // every partial read
+  __syncthreads();   // every partial sum read
 #pragma unroll
   for (int k = 0; k < S::kWords; k++) {
     const int t = (int)threadIdx.x + S::kThreads * k;
-    if (t < 624) {
-#pragma unroll
-      for (int p = 0; p < kParts; p++) rings[p][t] = v[k];
-    }
+    if (t < 624) buf[t] = v[k];
   }
   __syncthreads();
 }
@@ -324,8 +294,7 @@ __device__ __forceinline__ int next_bit(const uint64_t (&N)[kMaxLimbs], int from
   return -1;
 }
 
-// kParts = 1: one wavefront per stream; more: a workgroup of kParts
-// wavefronts per stream, each polynomial applied by apply_poly_split.
+// A workgroup of kParts wavefronts per stream.
 template <int kParts>
 __global__ void __launch_bounds__(64 * kParts) mt_jump_kernel(MtState* __restrict__ states, uint32_t count,
                                                      const uint64_t* __restrict__ dist, int nlimbs, int per_stream,
@@ -336,7 +305,7 @@ __global__ void __launch_bounds__(64 * kParts) mt_jump_kernel(MtState* __restric
                                                      const uint32_t* __restrict__ diglo,
                                                      const uint32_t* __restrict__ dig8hi,
                                                      const uint32_t* __restrict__ blk, int blocks) {
-  __shared__ __align__(16) uint32_t rings[kParts][kRing + kMirror];
+  __shared__ __align__(16) uint32_t buf[Split<kParts>::kLds];
   const uint32_t s = blockIdx.x;
   if (s >= count) return;
   // the scan is one long chain of dependent scalar tests and branches: where
@@ -347,8 +316,7 @@ __global__ void __launch_bounds__(64 * kParts) mt_jump_kernel(MtState* __restric
   const int lane = threadIdx.x & 63;
   // the wavefront's part, uniform across it (its coefficient range is scanned
   // by scalar branching)
-  const int part = kParts > 1 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
-  uint32_t* ring = rings[part];
+  const int part = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   // block splitting from the default state: start from the precomputed
   // state of the id's top 16 bits
   const bool digit_path = ids && block_e == kMtDigitE;
@@ -365,9 +333,9 @@ __global__ void __launch_bounds__(64 * kParts) mt_jump_kernel(MtState* __restric
     const uint64_t* d = dist + (per_stream ? (size_t)s * nlimbs : 0);
     for (int l = 0; l < nlimbs; l++) N[l] = d[l];
   }
-  for (int i = lane; i < 624; i += 64) ring[i] = src->mt[i];
+  for (int i = (int)threadIdx.x; i < 624; i += 64 * kParts) buf[i] = src->mt[i];
   uint32_t idx = src->idx < 624u ? src->idx : 624u;
-  wave_lds_sync();
+  __syncthreads();
   // the polynomials to apply, in order: for block splitting from a
   // block-aligned state, id * 2^432 with the low 48 bits of id as 16-bit
   // digits and the top 16 bits as two bytes, one table polynomial
@@ -431,13 +399,11 @@ __global__ void __launch_bounds__(64 * kParts) mt_jump_kernel(MtState* __restric
       }
     }
     if (!poly) break;
-    if constexpr (kParts > 1) apply_poly_split<kParts>(rings, poly, lane, part);
-    else apply_poly(ring, poly, lane);
+    apply_poly<kParts>(buf, poly, lane, part);
   }
-  if (part) return;
   MtState* dst = states + s;
-  for (int i = lane; i < 624; i += 64) dst->mt[i] = ring[i];
-  if (lane == 0) {
+  for (int i = (int)threadIdx.x; i < 624; i += 64 * kParts) dst->mt[i] = buf[i];
+  if (threadIdx.x == 0) {
     dst->idx = idx;
     dst->pad[0] = dst->pad[1] = dst->pad[2] = 0;
   }
@@ -453,33 +419,37 @@ __global__ void __launch_bounds__(64 * kParts) mt_jump_kernel(MtState* __restric
 // back, so that the array's words 1..623 are the exact words 0..622 of the
 // target window, and one step of the recurrence supplies its word 623.
 // Section 0 is a copy.
-__global__ void __launch_bounds__(64) mt_section_start_kernel(const BatchTile* __restrict__ tiles, uint32_t ntiles,
-                                                              const BatchTask* __restrict__ tasks,
-                                                              char* __restrict__ scratch,
-                                                              const uint32_t* __restrict__ blk,
-                                                              const uint32_t* __restrict__ inv) {
-  __shared__ __align__(16) uint32_t ring[kRing + kMirror];
+constexpr int kSectionParts = 8;
+
+__global__ void __launch_bounds__(64 * kSectionParts)
+    mt_section_start_kernel(const BatchTile* __restrict__ tiles, uint32_t ntiles, const BatchTask* __restrict__ tasks,
+                            char* __restrict__ scratch, const uint32_t* __restrict__ blk,
+                            const uint32_t* __restrict__ inv) {
+  __shared__ __align__(16) uint32_t buf[Split<kSectionParts>::kLds];
   const uint32_t t = blockIdx.x;
   if (t >= ntiles) return;
   const BatchTile tl = tiles[t];
   if (tl.kind != kTileMtSection) return;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  const int part = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const MtState* src = (const MtState*)tasks[tl.task].state_in;
   MtState* dst = (MtState*)(scratch + tl.starts);
-  for (int i = lane; i < 624; i += 64) ring[i] = src->mt[i];
+  for (int i = (int)threadIdx.x; i < 624; i += 64 * kSectionParts) buf[i] = src->mt[i];
   const uint32_t idx = src->idx < 624u ? src->idx : 624u;
   __syncthreads();
-  uint64_t sec = tl.first;
-  if (sec == 0) {
-    for (int i = lane; i < 624; i += 64) dst->mt[i] = ring[i];
+  if (tl.first == 0) {
+    for (int i = (int)threadIdx.x; i < 624; i += 64 * kSectionParts) dst->mt[i] = buf[i];
   } else {
-    for (int b = 0; sec; b++, sec >>= 1)
-      if (sec & 1u) apply_poly(ring, blk + (size_t)b * 624, lane);
-    apply_poly(ring, inv, lane);
-    for (int i = lane; i < 623; i += 64) dst->mt[i] = ring[i + 1];
-    if (lane == 0) dst->mt[623] = recur(ring[0], ring[1], ring[397]);
+    // one polynomial per set bit of the section number, then x^(-1)
+    uint64_t sec = tl.first;
+    for (int b = 0, last = 0; !last; b++, sec >>= 1) {
+      last = sec == 0;
+      if (last || (sec & 1u)) apply_poly<kSectionParts>(buf, last ? inv : blk + (size_t)b * 624, lane, part);
+    }
+    for (int i = (int)threadIdx.x; i < 623; i += 64 * kSectionParts) dst->mt[i] = buf[i + 1];
+    if (threadIdx.x == 0) dst->mt[623] = recur(buf[0], buf[1], buf[397]);
   }
-  if (lane == 0) {
+  if (threadIdx.x == 0) {
     dst->idx = idx;
     dst->pad[0] = dst->pad[1] = dst->pad[2] = 0;
   }
@@ -490,7 +460,7 @@ __global__ void __launch_bounds__(64) mt_section_start_kernel(const BatchTile* _
 hipError_t launch_batch_mt_starts(const DeviceTables& T, const BatchTile* tiles, uint32_t ntiles,
                                   const BatchTask* tasks, char* scratch, hipStream_t st) {
   if (!ntiles) return hipSuccess;
-  hipLaunchKernelGGL(mt_section_start_kernel, dim3(ntiles), dim3(64), 0, st, tiles, ntiles, tasks, scratch, T.mtblk,
+  hipLaunchKernelGGL(mt_section_start_kernel, dim3(ntiles), dim3(64 * kSectionParts), 0, st, tiles, ntiles, tasks, scratch, T.mtblk,
                      T.mtinv);
   return hipGetLastError();
 }
@@ -508,8 +478,8 @@ hipError_t launch_mt_jump(const DeviceTables& T, MtState* states, uint32_t count
                           const MtState* base, hipStream_t st) {
   // whole-section distances: one limb per stream
   if (js.mt_blocks && (js.ids || !js.per_stream || js.nlimbs != 1)) return hipErrorInvalidValue;
-  if (count <= kMtSplit12MaxCount)
-    hipLaunchKernelGGL(mt_jump_kernel<12>, dim3(count), dim3(64 * 12), 0, st, states, count, js.dist, js.nlimbs,
+  if (count <= kMtSplit16MaxCount)
+    hipLaunchKernelGGL(mt_jump_kernel<16>, dim3(count), dim3(64 * 16), 0, st, states, count, js.dist, js.nlimbs,
                        js.per_stream, js.ids, js.block_e, base, (const MtState*)js.mt_top, T.mt, T.mtdiglo, T.mtdig8hi,
                        T.mtblk, js.mt_blocks);
   else if (count <= kMtSplit8MaxCount)
@@ -517,7 +487,7 @@ hipError_t launch_mt_jump(const DeviceTables& T, MtState* states, uint32_t count
                        js.per_stream, js.ids, js.block_e, base, (const MtState*)js.mt_top, T.mt, T.mtdiglo, T.mtdig8hi,
                        T.mtblk, js.mt_blocks);
   else
-    hipLaunchKernelGGL(mt_jump_kernel<1>, dim3(count), dim3(64), 0, st, states, count, js.dist, js.nlimbs,
+    hipLaunchKernelGGL(mt_jump_kernel<4>, dim3(count), dim3(64 * 4), 0, st, states, count, js.dist, js.nlimbs,
                        js.per_stream, js.ids, js.block_e, base, (const MtState*)js.mt_top, T.mt, T.mtdiglo, T.mtdig8hi,
                        T.mtblk, js.mt_blocks);
   return hipGetLastError();
