@@ -475,9 +475,9 @@ int prand_ctx_create(prand_ctx** out, int hip_device) {
   std::strncpy(c->arch, prop.gcnArchName, sizeof(c->arch) - 1);
   HostTables* H = new (std::nothrow) HostTables;
   if (!H) { delete c; return PRAND_ENOMEM; }
-  build_mrg_ladder(H->mrg);
-  build_lfsr_ladder(H->lfsr);
-  build_gm_ladders(H->gm);
+  build_mrg_bytes(H->mrg);
+  build_lfsr_jumps(H->lfsr);
+  build_gm_jumps(H->gm);
   build_gm_byte_tables(H->gmbyte, H->gmneg);
   build_lfsr_byte_table(H->lfsrbyte);
   build_gmx_tables(H->gmx);

@@ -382,20 +382,41 @@ __device__ __forceinline__ void prime_form(int G, int& e, uint64_t& c) {
   }
 }
 
-// Jump one element (xc, xp) = (x^(n), x^(n-1)) ahead by N ensemble steps
-// (little-endian limbs, N[kMaxLimbs] must be 0 on entry to the ladder part):
-// one ladder matrix M^(2^b) mod p per set bit b.  Composite moduli first
-// collapse (n0 exact steps) unless the element already has, then jump x/2^t
-// mod p; distances below n0 are taken as exact steps.
-template <int G>
-__device__ __forceinline__ void jump_steps_elem(uint64_t& xc, uint64_t& xp, uint64_t* N,
-                                                const uint64_t* __restrict__ ladder) {
-  using E = Eng<G>;
+// (yc, yp) moved N steps on (little-endian limbs), mod the prime part p:
+// one matrix M^(d 2^(8 j)) per nonzero byte of the lowest limb, one ladder
+// entry M^(2^b) per set bit above it
+template <int G, int kLimbs>
+__device__ __forceinline__ void jump_prime(uint64_t& yc, uint64_t& yp, const uint64_t* N,
+                                           const uint64_t* __restrict__ table) {
   int pe;
   uint64_t pc;
   prime_form(G, pe, pc);
   const uint64_t p = kGmParams[G].p;
-  const uint64_t* L = ladder + (size_t)G * kLadder * 4;
+  const uint64_t* T = table + (size_t)G * kJumpRows * 4;
+  auto apply = [&](const uint64_t* M) {
+    const uint64_t nc = mulsum_mod<G>(M[0], yc, M[1], yp, pe, pc, p);
+    const uint64_t np = mulsum_mod<G>(M[2], yc, M[3], yp, pe, pc, p);
+    yc = nc;
+    yp = np;
+  };
+  for (uint64_t w = N[0]; w;) {
+    uint32_t d;
+    const int j = take_byte(w, d);
+    apply(T + (uint32_t)(kLadder + j * 256 + (int)d) * 4u);
+  }
+#pragma unroll
+  for (int l = 1; l < kLimbs; l++)
+    for (uint64_t w = N[l]; w; w &= w - 1) apply(T + (size_t)(__builtin_ctzll(w) + 64 * l) * 4);
+}
+
+// Jump one element (xc, xp) = (x^(n), x^(n-1)) ahead by N ensemble steps
+// (little-endian limbs, N[kMaxLimbs] must be 0 after the collapse).
+// Composite moduli first collapse (n0 exact steps) unless the element already
+// has, then jump x/2^t mod p; distances below n0 are taken as exact steps.
+template <int G>
+__device__ __forceinline__ void jump_steps_elem(uint64_t& xc, uint64_t& xp, uint64_t* N,
+                                                const uint64_t* __restrict__ table) {
+  using E = Eng<G>;
   if constexpr (E::kComposite) {
     bool small = true;
     for (int l = 1; l <= kMaxLimbs; l++) small = small && N[l] == 0;
@@ -414,31 +435,11 @@ __device__ __forceinline__ void jump_steps_elem(uint64_t& xc, uint64_t& xp, uint
       }
     }
     uint64_t yc = xc >> E::t, yp = xp >> E::t;
-    for (int l = 0; l < kMaxLimbs; l++) {
-      uint64_t wd = N[l];
-      while (wd) {
-        const int b = __builtin_ctzll(wd) + 64 * l;
-        wd &= wd - 1;
-        const uint64_t* M = L + (size_t)b * 4;
-        const uint64_t nc = mulsum_mod<G>(M[0], yc, M[1], yp, pe, pc, p);
-        const uint64_t np = mulsum_mod<G>(M[2], yc, M[3], yp, pe, pc, p);
-        yc = nc; yp = np;
-      }
-    }
+    jump_prime<G, kMaxLimbs>(yc, yp, N, table);
     xc = yc << E::t;
     xp = yp << E::t;
   } else {
-    for (int l = 0; l < kMaxLimbs; l++) {
-      uint64_t wd = N[l];
-      while (wd) {
-        const int b = __builtin_ctzll(wd) + 64 * l;
-        wd &= wd - 1;
-        const uint64_t* M = L + (size_t)b * 4;
-        const uint64_t nc = mulsum_mod<G>(M[0], xc, M[1], xp, pe, pc, p);
-        const uint64_t np = mulsum_mod<G>(M[2], xc, M[3], xp, pe, pc, p);
-        xc = nc; xp = np;
-      }
-    }
+    jump_prime<G, kMaxLimbs>(xc, xp, N, table);
   }
 }
 

@@ -63,20 +63,6 @@ struct FastPair {
   typename Eng<G>::F yc, yp;
 };
 
-// m0 a + m1 b mod p for the prime part of GM55 / GQ58 (all operands < p)
-template <int G>
-__device__ __forceinline__ uint64_t lane_mulsum(uint64_t m0, uint64_t a, uint64_t m1, uint64_t b) {
-  if constexpr (G == 3) {
-    return fold_special<G>((u128)m0 * a + (u128)m1 * b, 51, 129, Eng<3>::p);
-  } else {
-    // p = 2^29 - 3: products below 2^58, folded twice with 2^29 = 3 (mod p)
-    const uint64_t t = m0 * a + m1 * b;                                           // < 2^59
-    const uint64_t u = (t & 0x1FFFFFFFull) + 3ull * (t >> 29);                    // < 2^32 + 2^29
-    const uint32_t w = (uint32_t)(u & 0x1FFFFFFFull) + 3u * (uint32_t)(u >> 29);  // < 2^29 + 24
-    return w >= EngGQ<1>::kP ? w - EngGQ<1>::kP : w;
-  }
-}
-
 // Element e of *in moved nsteps >= n0 ensemble steps ahead, in the fast
 // (collapsed, mod p) representation: exact steps until the element has
 // collapsed, then one ladder matrix M^(2^b) mod p per set bit b of the rest.
@@ -95,16 +81,7 @@ __device__ __forceinline__ FastPair<G> lane_jump_fast(const GmState* in, int e, 
     nsteps -= n0;
   }
   uint64_t yc = xc >> E::t, yp = xp >> E::t;
-  const uint64_t* L = ladder + (size_t)G * kLadder * 4;
-  while (nsteps) {
-    const int b = __builtin_ctzll(nsteps);
-    nsteps &= nsteps - 1;
-    const uint64_t* M = L + (size_t)b * 4;
-    const uint64_t nc = lane_mulsum<G>(M[0], yc, M[1], yp);
-    const uint64_t np = lane_mulsum<G>(M[2], yc, M[3], yp);
-    yc = nc;
-    yp = np;
-  }
+  jump_prime<G, 1>(yc, yp, &nsteps, ladder);
   FastPair<G> r;   // the ladder gives exact residues; the kernels' form may be offset
   r.yc = E::to_fast(yc << E::t);
   r.yp = E::to_fast(yp << E::t);

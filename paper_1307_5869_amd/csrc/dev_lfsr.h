@@ -4,7 +4,8 @@
 // (x_{ns}..x_{ns+31}) advances by ((z & top_p) << s) ^ (((z << q) ^ z) >> (p-s)),
 // and the output word is the XOR of the four components.  One lane owns a
 // (stream, section) pair with the four words in registers; jumps apply the
-// 32x32 F2 matrices T_c^(2^b) of the context ladder for each set bit b.
+// 32x32 F2 matrices T_c^(d 2^(8 j)) of the context table for each nonzero byte
+// d of the distance (above 64 bits: T_c^(2^b) per set bit b).
 // LFSR113 device code (see k_lfsr113.hip).
 #pragma once
 
@@ -35,26 +36,6 @@ __device__ __forceinline__ uint32_t step(LfsrRegs& r) {
   return __builtin_amdgcn_bitop3_b32(r.z0, r.z1, r.z2, 0x96) ^ r.z3;   // 0x96: three-input XOR
 }
 
-__device__ __forceinline__ uint32_t f2_apply(const uint32_t* __restrict__ cols, uint32_t v) {
-  uint32_t r = 0;
-#pragma unroll 4
-  for (int j = 0; j < 32; j++) r ^= ((v >> j) & 1u) ? cols[j] : 0u;
-  return r;
-}
-
-__device__ __forceinline__ void jump_state(const uint32_t* ladder, uint32_t z[4], const uint64_t* limbs,
-                                           int nlimbs) {
-  for (int l = 0; l < nlimbs; l++) {
-    uint64_t w = limbs[l];
-    while (w) {
-      const int b = __builtin_ctzll(w) + 64 * l;
-      w &= w - 1;
-      const uint32_t* M = ladder + (size_t)b * 128;
-      for (int c = 0; c < 4; c++) z[c] = f2_apply(M + 32 * c, z[c]);
-    }
-  }
-}
-
 struct LfsrGen {
   using State = LfsrState;
   using Regs = lfsr::LfsrRegs;
@@ -64,7 +45,6 @@ struct LfsrGen {
     o.z[0] = r.z0; o.z[1] = r.z1; o.z[2] = r.z2; o.z[3] = r.z3;
     return o;
   }
-  __device__ static void jump(LfsrState& st, uint64_t d, const uint32_t* ladder) { jump_state(ladder, st.z, &d, 1); }
   // one jump matrix per component (columns of T_c^d), 4 x 32 words, 16-byte
   // aligned: the columns come in as 16-byte loads, and column j joins the
   // result through bit j of the word spread to a mask (one sign-extending
@@ -89,6 +69,20 @@ struct LfsrGen {
       }
       st.z[c] = r;
     }
+  }
+  // one matrix per nonzero byte of the distance
+  __device__ static void jump(LfsrState& st, uint64_t d, const uint32_t* table) {
+    while (d) {
+      uint32_t v;
+      const int j = take_byte(d, v);
+      apply(st, table + (uint32_t)(kLadder + j * 256 + (int)v) * 128u);
+    }
+  }
+  // of several limbs: one ladder entry per set bit above the lowest limb
+  __device__ static void jump_limbs(LfsrState& st, const uint64_t* limbs, int nlimbs, const uint32_t* table) {
+    if (nlimbs > 0) jump(st, limbs[0], table);
+    for (int l = 1; l < nlimbs; l++)
+      for (uint64_t w = limbs[l]; w; w &= w - 1) apply(st, table + (size_t)(__builtin_ctzll(w) + 64 * l) * 128);
   }
   __device__ static uint32_t next(Regs& r) { return step(r); }
   __device__ static double f64(uint32_t w) { return (double)w * 0x1p-32; }

@@ -11,8 +11,9 @@
 // is five FP64 operations per component.  The output map converts the two
 // centred values to 32-bit integers and forms the canonical z with integer
 // compares and selects (twelve 32-bit operations).
-// Jumps apply A^(2^b), B^(2^b) from the context ladder for each set bit b of
-// the distance (binary decomposition, O(log n)).
+// Jumps apply A^(d 2^(8 j)), B^(d 2^(8 j)) from the context table for each
+// nonzero byte d of the distance (4096 streams k 2^76 ahead: 18 -> 6 us against
+// one matrix pair per set bit).
 #pragma once
 
 #include "prand_impl.h"
@@ -63,40 +64,49 @@ __device__ __forceinline__ uint32_t step(Regs& r) {
   return xc > yc ? d : d - 209u;   // x <= y: x - y + m1 = x - y - 209 (mod 2^32), in [1, m1]
 }
 
-// 2^32 = C (mod 2^32 - C): fold a 64-bit value to its residue
-template <uint32_t C>
-__device__ __forceinline__ uint32_t fold32(uint64_t v) {
-  v = (v >> 32) * C + (v & 0xFFFFFFFFull);
-  v = (v >> 32) * C + (v & 0xFFFFFFFFull);
-  v = (v >> 32) * C + (v & 0xFFFFFFFFull);
-  const uint64_t m = (1ull << 32) - C;
-  return (uint32_t)(v >= m ? v - m : v);
-}
-
+// v = M v mod m = 2^32 - C; M: 9 words.  2^32 = C (mod m): each product is
+// folded once (below 2^32 (C + 1)), the sum of three twice more (below 2 m).
 template <uint32_t C>
 __device__ __forceinline__ void mat3_apply(const uint32_t* M, uint32_t v[3]) {
   const uint64_t m = (1ull << 32) - C;
   uint32_t r[3];
+#pragma unroll
   for (int i = 0; i < 3; i++) {
     uint64_t acc = 0;
-    for (int k = 0; k < 3; k++) acc += fold32<C>((uint64_t)M[3 * i + k] * v[k]);
-    acc = acc >= m ? acc - m : acc;
-    acc = acc >= m ? acc - m : acc;
-    r[i] = (uint32_t)acc;
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+      const uint64_t p = (uint64_t)M[3 * i + k] * v[k];
+      acc += (p >> 32) * C + (uint32_t)p;
+    }
+    acc = (acc >> 32) * C + (uint32_t)acc;
+    acc = (acc >> 32) * C + (uint32_t)acc;
+    r[i] = (uint32_t)(acc >= m ? acc - m : acc);
   }
   v[0] = r[0]; v[1] = r[1]; v[2] = r[2];
 }
 
-__device__ __forceinline__ void jump_state(const uint32_t* ladder, uint32_t x[3], uint32_t y[3],
-                                           const uint64_t* limbs, int nlimbs) {
+// one jump matrix pair (A^d mod m1, B^d mod m2), 18 words, rows 8-byte aligned
+__device__ __forceinline__ void apply_pair(const uint32_t* M, uint32_t x[3], uint32_t y[3]) {
+  uint32_t m[18];
+  const uint2* row = (const uint2*)M;
+#pragma unroll
+  for (int i = 0; i < 9; i++) {
+    const uint2 w = row[i];
+    m[2 * i] = w.x;
+    m[2 * i + 1] = w.y;
+  }
+  mat3_apply<209u>(m, x);
+  mat3_apply<22853u>(m + 9, y);
+}
+
+// one matrix pair per nonzero byte of the distance
+__device__ __forceinline__ void jump_state(const uint32_t* table, uint32_t x[3], uint32_t y[3], const uint64_t* limbs,
+                                           int nlimbs) {
   for (int l = 0; l < nlimbs; l++) {
-    uint64_t w = limbs[l];
-    while (w) {
-      int b = __builtin_ctzll(w) + 64 * l;
-      w &= w - 1;
-      const uint32_t* M = ladder + (size_t)b * 18;
-      mat3_apply<209u>(M, x);
-      mat3_apply<22853u>(M + 9, y);
+    for (uint64_t w = limbs[l]; w;) {
+      uint32_t d;
+      const int j = 8 * l + take_byte(w, d);
+      apply_pair(table + (uint32_t)(j * 256 + (int)d) * 18u, x, y);
     }
   }
 }
@@ -114,13 +124,9 @@ struct MrgGen {
     o.y[0] = canonical<22853u>(r.y0); o.y[1] = canonical<22853u>(r.y1); o.y[2] = canonical<22853u>(r.y2);
     return o;
   }
-  __device__ static void jump(MrgState& st, uint64_t d, const uint32_t* ladder) { jump_state(ladder, st.x, st.y, &d, 1); }
-  // one jump matrix pair (A^d mod m1, B^d mod m2), 18 words
+  __device__ static void jump(MrgState& st, uint64_t d, const uint32_t* table) { jump_state(table, st.x, st.y, &d, 1); }
   static constexpr int kSectionWords = 18;
-  __device__ static void apply(MrgState& st, const uint32_t* M) {
-    mat3_apply<209u>(M, st.x);
-    mat3_apply<22853u>(M + 9, st.y);
-  }
+  __device__ static void apply(MrgState& st, const uint32_t* M) { apply_pair(M, st.x, st.y); }
   __device__ static uint32_t next(Regs& r) { return step(r); }
   __device__ static double f64(uint32_t z) { return (double)z * kNorm; }
 };

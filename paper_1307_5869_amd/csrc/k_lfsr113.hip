@@ -3,8 +3,8 @@
 // relations lfsrRel1 and lfsrOutput).  A component's 32-bit word
 // (x_{ns}..x_{ns+31}) advances by ((z & top_p) << s) ^ (((z << q) ^ z) >> (p-s)),
 // and the output word is the XOR of the four components.  One lane owns a
-// (stream, section) pair with the four words in registers; jumps apply the
-// 32x32 F2 matrices T_c^(2^b) of the context ladder for each set bit b.
+// (stream, section) pair with the four words in registers; jumps apply
+// 32x32 F2 matrices (dev_lfsr.h).
 #include "dev_lfsr.h"
 #include "regstream.h"
 
@@ -47,7 +47,7 @@ __global__ void __launch_bounds__(256) lfsr_jump_kernel(LfsrState* __restrict__ 
     for (int l = 0; l < nlimbs; l++) limbs[l] = d[l];
     nl = nlimbs;
   }
-  jump_state(ladder, st.z, limbs, nl);
+  LfsrGen::jump_limbs(st, limbs, nl, ladder);
   states[i] = st;
 }
 

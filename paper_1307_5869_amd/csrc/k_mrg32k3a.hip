@@ -3,9 +3,9 @@
 // [1, m1].  One lane owns one (stream, section) pair and keeps the six state
 // words in registers (the store path is shared, see regstream.h); the
 // recurrence runs in exact double arithmetic on centred residues (dev_mrg.h).
-// Jumps apply A^(2^b), B^(2^b) from the context ladder for each set bit b of
-// the distance (binary decomposition, O(log n)); the sections of the
-// many-stream kernel start from one application of a section-start table.
+// Jumps apply one pair of matrices per nonzero byte of the distance; the
+// sections of the many-stream kernel start from one application of a
+// section-start table.
 #include "dev_mrg.h"
 #include "regstream.h"
 

@@ -16,6 +16,7 @@ namespace prand {
 
 constexpr int kMaxLimbs = 8;        // distances up to 2^512
 constexpr int kLadder = 512;        // jump tables hold M^(2^b) for b < 512
+constexpr int kJumpRows = kLadder + 8 * 256;   // and M^(d 2^(8 j)) for j < 8, d < 256
 
 // ---- state blobs (layout documented in prand.h) ----
 struct MtState {
@@ -108,9 +109,11 @@ constexpr int kLfsrByteE = 34;
 
 // ---- device-resident jump tables (built once per context) ----
 struct DeviceTables {
-  uint32_t* mrg = nullptr;    // [kLadder][18]: A^(2^b) mod m1 (row major), B^(2^b) mod m2
-  uint32_t* lfsr = nullptr;   // [kLadder][4][32]: columns of T_c^(2^b)
-  uint64_t* gm = nullptr;     // [8][kLadder][4]: (a b; c d) = M^(2^b) mod p
+  // distances: one matrix per nonzero byte (MRG32K3A: of all 512 bits;
+  // LFSR113 and GM/GQ: of the low 64 bits, one per set bit above them)
+  uint32_t* mrg = nullptr;    // [64][256][18]: A^(d 2^(8 j)) mod m1 (row major), B^(d 2^(8 j)) mod m2
+  uint32_t* lfsr = nullptr;   // [kJumpRows][4][32]: columns of T_c^(2^b), b < kLadder, then T_c^(d 2^(8 j)), [8][256]
+  uint64_t* gm = nullptr;     // [8][kJumpRows][4]: (a b; c d) = M^(2^b) mod p, then M^(d 2^(8 j)) mod p
   uint64_t* gmbyte = nullptr;   // [8][8][256][4]: M^(d 2^(kGmByteE[G] + 8 j)) mod p
   GmxTable* gmx = nullptr;      // [8]
   uint64_t* gmneg = nullptr;    // [8][4]: M^(-n0) mod p (composite moduli; identity otherwise)
@@ -140,6 +143,16 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The lowest nonzero byte of w (w != 0), taken out of it: its position is
+// returned, its value left in d.  Lanes whose distances have bytes in different
+// places then go through their matrices together, one per nonzero byte.
+__device__ __forceinline__ int take_byte(uint64_t& w, uint32_t& d) {
+  const int j = __builtin_ctzll(w) >> 3;
+  d = (uint32_t)(w >> (8 * j)) & 255u;
+  w ^= (uint64_t)d << (8 * j);
+  return j;
 }
 
 // 16-byte output store of the bulk generators.  u32/f32 outputs are marked
@@ -213,16 +226,16 @@ void seed_host(int gen, uint64_t seed, void* h_state);
 
 // ---- host-side table construction (context set-up) ----
 struct HostTables {
-  uint32_t mrg[kLadder * 18];
-  uint32_t lfsr[kLadder * 4 * 32];
-  uint64_t gm[8 * kLadder * 4];
+  uint32_t mrg[64 * 256 * 18];
+  uint32_t lfsr[kJumpRows * 4 * 32];
+  uint64_t gm[8 * kJumpRows * 4];
   uint64_t gmbyte[8 * 8 * 256 * 4];
   uint64_t gmneg[8 * 4];
   GmxTable gmx[8];
   uint32_t lfsrbyte[8 * 256 * 128];
 };
-void build_mrg_ladder(uint32_t* out);
-void build_lfsr_ladder(uint32_t* out);
+void build_mrg_bytes(uint32_t* out);
+void build_lfsr_jumps(uint32_t* out);
 // Section-start tables of the many-stream MRG32K3A/LFSR113 kernels: for a
 // section length L, row j - 1 (j = 1 .. kSectionTableRows) holds the jump by
 // j L (MRG32K3A: A^(jL) mod m1 then B^(jL) mod m2, 18 words; LFSR113: the
@@ -233,7 +246,7 @@ constexpr int kMrgSectionWords = 18;
 constexpr int kLfsrSectionWords = 128;
 void build_mrg_section_table(uint64_t seclen, uint32_t* out);
 void build_lfsr_section_table(uint64_t seclen, uint32_t* out);
-void build_gm_ladders(uint64_t* out);
+void build_gm_jumps(uint64_t* out);
 void build_gm_byte_tables(uint64_t* out, uint64_t* neg);
 void build_gmx_tables(GmxTable* out);
 void build_lfsr_byte_table(uint32_t* out);

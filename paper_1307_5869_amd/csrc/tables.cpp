@@ -1,8 +1,9 @@
-// Context set-up: the jump-ahead ladders of MRG32K3A, LFSR113 and the GM/GQ
+// Context set-up: the jump-ahead tables of MRG32K3A, LFSR113 and the GM/GQ
 // ensembles, computed once on the host when a context is created and then
 // uploaded (the MT19937 polynomials are built in mt_poly.cpp).  A distance is
-// applied as one ladder entry M^(2^b) per set bit b (binary decomposition of
-// the distance, as in the paper's jump-ahead sections).
+// applied as one matrix M^(d 2^(8 j)) per nonzero byte d, LFSR113 and GM/GQ
+// distances above 64 bits as one ladder entry M^(2^b) per set bit b (the
+// paper's jump-ahead sections decompose the distance in binary).
 #include <cstring>
 #include <vector>
 
@@ -25,22 +26,6 @@ void mat3_sqr(const uint64_t* a, uint64_t* r, uint64_t m) {
   std::memcpy(r, t, sizeof t);
 }
 
-}  // namespace
-
-void build_mrg_ladder(uint32_t* out) {
-  uint64_t A[9] = {0, kMrgA12, kMrgM1 - kMrgA13n, 1, 0, 0, 0, 1, 0};
-  uint64_t B[9] = {kMrgA21, 0, kMrgM2 - kMrgA23n, 1, 0, 0, 0, 1, 0};
-  for (int b = 0; b < kLadder; b++) {
-    for (int i = 0; i < 9; i++) {
-      out[b * 18 + i] = (uint32_t)A[i];
-      out[b * 18 + 9 + i] = (uint32_t)B[i];
-    }
-    mat3_sqr(A, A, kMrgM1);
-    mat3_sqr(B, B, kMrgM2);
-  }
-}
-
-namespace {
 void mat3_mul(const uint64_t* a, const uint64_t* b, uint64_t* r, uint64_t m) {
   uint64_t t[9];
   for (int i = 0; i < 3; i++)
@@ -62,6 +47,45 @@ void mat3_pow(const uint64_t* a, uint64_t e, uint64_t* r, uint64_t m) {
   std::memcpy(r, acc, sizeof acc);
 }
 }  // namespace
+
+namespace {
+// r = a b mod m (entries below m = 2^32 - c, c < 2^15), in 64-bit folds
+void mat3_mul_fold(const uint32_t* a, const uint32_t* b, uint32_t* r, uint32_t c) {
+  const uint64_t m = (1ull << 32) - c;
+  uint32_t t[9];
+  for (int i = 0; i < 3; i++)
+    for (int j = 0; j < 3; j++) {
+      uint64_t acc = 0;
+      for (int k = 0; k < 3; k++) {
+        const uint64_t v = (uint64_t)a[3 * i + k] * b[3 * k + j];
+        acc += (v >> 32) * c + (uint32_t)v;
+      }
+      acc = (acc >> 32) * c + (uint32_t)acc;
+      acc = (acc >> 32) * c + (uint32_t)acc;
+      t[3 * i + j] = (uint32_t)(acc >= m ? acc - m : acc);
+    }
+  std::memcpy(r, t, sizeof t);
+}
+}  // namespace
+
+// out [64][256][18]: A^(d 2^(8 j)) mod m1, then B^(d 2^(8 j)) mod m2
+void build_mrg_bytes(uint32_t* out) {
+  const uint32_t gen[2][9] = {{0, kMrgA12, kMrgM1 - kMrgA13n, 1, 0, 0, 0, 1, 0},
+                              {kMrgA21, 0, kMrgM2 - kMrgA23n, 1, 0, 0, 0, 1, 0}};
+  for (int h = 0; h < 2; h++) {
+    const uint32_t c = h ? 0u - kMrgM2 : 0u - kMrgM1;
+    uint32_t b[9], t[9];
+    std::memcpy(b, gen[h], sizeof b);
+    for (int j = 0; j < 64; j++) {
+      for (int i = 0; i < 9; i++) t[i] = i % 4 == 0;
+      for (int d = 0; d < 256; d++) {
+        std::memcpy(out + ((size_t)j * 256 + d) * 18 + 9 * h, t, sizeof t);
+        mat3_mul_fold(b, t, t, c);
+      }
+      std::memcpy(b, t, sizeof b);   // t = b^256
+    }
+  }
+}
 
 void build_mrg_section_table(uint64_t seclen, uint32_t* out) {
   const uint64_t A[9] = {0, kMrgA12, kMrgM1 - kMrgA13n, 1, 0, 0, 0, 1, 0};
@@ -102,26 +126,14 @@ uint32_t f2_apply(const uint32_t* cols, uint32_t v) {
 }
 }  // namespace
 
-void build_lfsr_ladder(uint32_t* out) {
-  for (int c = 0; c < 4; c++) {
-    uint32_t cols[32];
-    for (int j = 0; j < 32; j++) cols[j] = lfsr_word_step(1u << j, c);
-    for (int b = 0; b < kLadder; b++) {
-      std::memcpy(out + ((size_t)b * 4 + c) * 32, cols, sizeof cols);
-      uint32_t sq[32];
-      for (int j = 0; j < 32; j++) sq[j] = f2_apply(cols, cols[j]);
-      std::memcpy(cols, sq, sizeof sq);
-    }
-  }
-}
-
-// columns of T_c^(d 2^(kLfsrByteE + 8 j)) for every byte position j and
-// value d (row [j][d], 128 words, the layout of the section tables)
-void build_lfsr_byte_table(uint32_t* out) {
+namespace {
+// columns of T_c^(d 2^(e + 8 j)) for every byte position j < 8 and value d
+// (row [j][d], 128 words, the layout of the section tables)
+void lfsr_bytes(int e, uint32_t* out) {
   for (int c = 0; c < 4; c++) {
     uint32_t b[32], t[32], m[32];
     for (int j = 0; j < 32; j++) b[j] = lfsr_word_step(1u << j, c);
-    for (int i = 0; i < kLfsrByteE; i++) {   // b = T_c^(2^e)
+    for (int i = 0; i < e; i++) {   // b = T_c^(2^e)
       for (int j = 0; j < 32; j++) t[j] = f2_apply(b, b[j]);
       std::memcpy(b, t, sizeof t);
     }
@@ -132,13 +144,27 @@ void build_lfsr_byte_table(uint32_t* out) {
         for (int j = 0; j < 32; j++) t[j] = f2_apply(b, m[j]);
         std::memcpy(m, t, sizeof t);
       }
-      for (int i = 0; i < 8; i++) {   // b = b^256 for the next byte
-        for (int j = 0; j < 32; j++) t[j] = f2_apply(b, b[j]);
-        std::memcpy(b, t, sizeof t);
-      }
+      std::memcpy(b, m, sizeof b);   // m = b^256
     }
   }
 }
+}  // namespace
+
+void build_lfsr_jumps(uint32_t* out) {
+  for (int c = 0; c < 4; c++) {
+    uint32_t cols[32];
+    for (int j = 0; j < 32; j++) cols[j] = lfsr_word_step(1u << j, c);
+    for (int b = 0; b < kLadder; b++) {
+      std::memcpy(out + ((size_t)b * 4 + c) * 32, cols, sizeof cols);
+      uint32_t sq[32];
+      for (int j = 0; j < 32; j++) sq[j] = f2_apply(cols, cols[j]);
+      std::memcpy(cols, sq, sizeof sq);
+    }
+  }
+  lfsr_bytes(0, out + (size_t)kLadder * 128);
+}
+
+void build_lfsr_byte_table(uint32_t* out) { lfsr_bytes(kLfsrByteE, out); }
 
 void build_lfsr_section_table(uint64_t seclen, uint32_t* out) {
   for (int c = 0; c < 4; c++) {
@@ -216,19 +242,29 @@ void build_gm_byte_tables(uint64_t* out, uint64_t* neg) {
   }
 }
 
-void build_gm_ladders(uint64_t* out) {
+void build_gm_jumps(uint64_t* out) {
   for (int g = 0; g < 8; g++) {
     const GmParams& P = kGmParams[g];
     const uint64_t p = P.p;
-    uint64_t a = P.k % p, b = (p - P.q % p) % p, c = 1, d = 0;
+    uint64_t* const o = out + (size_t)g * kJumpRows * 4;
+    auto put = [&](size_t row, const Mat2& m) {
+      const uint64_t v[4] = {m.a, m.b, m.c, m.d};
+      std::memcpy(o + 4 * row, v, sizeof v);
+    };
+    const Mat2 m{P.k % p, (p - P.q % p) % p, 1, 0};
+    Mat2 b = m;
     for (int i = 0; i < kLadder; i++) {
-      uint64_t* o = out + ((size_t)g * kLadder + i) * 4;
-      o[0] = a; o[1] = b; o[2] = c; o[3] = d;
-      uint64_t na = (uint64_t)(((u128)a * a + (u128)b * c) % p);
-      uint64_t nb = (uint64_t)(((u128)a * b + (u128)b * d) % p);
-      uint64_t nc = (uint64_t)(((u128)c * a + (u128)d * c) % p);
-      uint64_t nd = (uint64_t)(((u128)c * b + (u128)d * d) % p);
-      a = na; b = nb; c = nc; d = nd;
+      put(i, b);
+      b = mat2_mul(b, b, p);
+    }
+    b = m;
+    for (int pos = 0; pos < 8; pos++) {
+      Mat2 t{1, 0, 0, 1};
+      for (int d = 0; d < 256; d++) {
+        put(kLadder + 256 * pos + d, t);
+        t = mat2_mul(t, b, p);
+      }
+      b = t;
     }
   }
 }
