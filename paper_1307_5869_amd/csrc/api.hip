@@ -307,6 +307,30 @@ __global__ void section_dist_kernel(uint64_t* d, uint32_t nb, uint64_t seclen, u
   else if (i == nb) d[i] = T;
 }
 
+// a state blob between pinned host memory and the device
+__global__ void copy_state_kernel(uint32_t* dst, const uint32_t* src, uint32_t words) {
+  for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) dst[i] = src[i];
+}
+
+// the host state in pinned slot 0 after `launch` on it, back to h_state (the
+// default stream; the caller holds mu)
+template <class F>
+int on_host_state(prand_ctx* c, int gen, void* h_state, F&& launch) {
+  char* const state = c->pin + kPinOut;
+  std::memcpy(state, h_state, state_bytes(gen));
+  hipError_t e = launch((void*)state);
+  const hipError_t se = hipStreamSynchronize(nullptr);
+  if (e == hipSuccess) e = se;
+  if (e != hipSuccess) return hipfail(c, e);
+  std::memcpy(h_state, state, state_bytes(gen));
+  return PRAND_OK;
+}
+
+// outputs of one GM19/GM61 stream from which its 4096-output sections fill the
+// chip with ballot wavefronts (two sections each); 6.7 * 10^7 GM61 outputs
+// take 850 us either way, 4.2 * 10^7 735 by the ballot and 560 by gmx
+constexpr uint64_t kBallotSingle = 4096ull * 16384;
+
 }  // namespace
 
 int prand::ensure_mt_tables(prand_ctx* c) {
@@ -324,24 +348,65 @@ int prand::ensure_mt_tables(prand_ctx* c) {
 // final section's state is exactly the sequential one.  The section states,
 // their distances and the copied-in base state live in `scratch` when it is
 // given (the plan then uses at most as many sections as fit in
-// scratch_bytes; the output does not depend on the plan), else in memory
-// allocated for the call.  Arguments are checked by the caller; MT19937
-// tables must exist.
+// scratch_bytes; the output does not depend on the plan), else in the
+// context's buffers.  Arguments are checked by the caller; MT19937 tables must
+// exist.
+//
+// That plan of several launches is for MT19937 calls of more than one section
+// and for the GM19/GM61 calls long enough for the ballot kernel.  The others
+// are one launch whose lanes or wavefronts jump to their sections by
+// themselves (a state of 24 or 16 bytes by value, GM/GQ from the pinned slot
+// while few wavefronts read it, else from a device copy).  States come and go
+// through pinned memory that kernels read and write: no copy calls.
 int prand::generate_host_state(prand_ctx* c, int gen, void* h_state, int dtype, void* d_out, uint64_t n,
                                hipStream_t st, void* scratch, size_t scratch_bytes) {
-  uint64_t min_sec, max_secs;
-  switch (gen) {
-    case PRAND_MT19937: min_sec = 1ull << 18; max_secs = 4096; break;
-    case PRAND_MRG32K3A:
-    case PRAND_LFSR113: min_sec = 256; max_secs = 1u << 19; break;
-    default: min_sec = 4096; max_secs = 1u << 16; break;
-  }
   const size_t sb = state_bytes(gen);
   const size_t es = elem_bytes(dtype);
   const size_t base_bytes = (sb + 255) & ~(size_t)255;
+  // base state, then distances, then states, each 256-byte aligned
+  if (scratch && scratch_bytes < base_bytes + 2 * 256 + 2 * (sb + 8)) return PRAND_ERANGE;
+  std::unique_lock<std::mutex> lk(c->mu, std::defer_lock);
+  if (!scratch) lk.lock();
+  char* const pin_in = c->pin + (scratch ? kPinBytes : 0);
+  char* const pin_out = pin_in + kPinOut;
+  std::memcpy(pin_in, h_state, sb);
+  std::memcpy(pin_out, h_state, sb);
+  hipError_t e = hipSuccess;
+  auto finish = [&]() -> int {
+    const hipError_t se = hipStreamSynchronize(st);   // also after an error: what was launched uses the slot
+    if (e == hipSuccess) e = se;
+    if (e != hipSuccess) return hipfail(c, e);
+    std::memcpy(h_state, pin_out, sb);
+    return PRAND_OK;
+  };
+  if (gen == PRAND_MRG32K3A) {
+    e = launch_mrg_single(c->T, (const MrgState*)h_state, (MrgState*)pin_out, n, dtype, d_out, st);
+    return finish();
+  }
+  if (gen == PRAND_LFSR113) {
+    e = launch_lfsr_single(c->T, (const LfsrState*)h_state, (LfsrState*)pin_out, n, dtype, d_out, st);
+    return finish();
+  }
+  // the base state's device copy (without `scratch`: the host calls' scratch)
+  void* const d_base = scratch ? scratch : c->scratch;
+  const uint32_t words = (uint32_t)(sb / 4);
+  const bool ballot = (gen == PRAND_GM19 || gen == PRAND_GM61) && n >= kBallotSingle;
+  if (gen != PRAND_MT19937 && !ballot) {
+    const void* base = pin_in;
+    if (gm_single_wavefronts(gen, n) > 16) {
+      hipLaunchKernelGGL(copy_state_kernel, dim3(1), dim3(256), 0, st, (uint32_t*)d_base, (const uint32_t*)pin_in, words);
+      e = hipGetLastError();
+      base = d_base;
+    }
+    if (e == hipSuccess) e = launch_gm_single(c->T, gen, (const GmState*)base, (GmState*)pin_out, n, dtype, d_out, st);
+    return finish();
+  }
+  uint64_t min_sec, max_secs;
+  switch (gen) {
+    case PRAND_MT19937: min_sec = 1ull << 18; max_secs = 4096; break;
+    default: min_sec = 4096; max_secs = 1u << 16; break;
+  }
   if (scratch) {
-    // base state, then distances, then states, each 256-byte aligned
-    if (scratch_bytes < base_bytes + 2 * 256 + 2 * (sb + 8)) return PRAND_ERANGE;
     const uint64_t fit = (scratch_bytes - base_bytes - 2 * 256) / (sb + 8);   // section states that fit
     max_secs = std::min<uint64_t>(max_secs, fit - 1);
   }
@@ -349,6 +414,11 @@ int prand::generate_host_state(prand_ctx* c, int gen, void* h_state, int dtype, 
   while ((1ull << k) < min_sec) k++;
   while (((n + (1ull << k) - 1) >> k) > max_secs) k++;
   const bool one = (1ull << k) >= n;
+  if (one && gen == PRAND_MT19937) {
+    // one wavefront, in place in the pinned slot
+    e = launch_mt_generate((MtState*)pin_out, 1, n, dtype, d_out, st);
+    return finish();
+  }
   const uint64_t seclen = one ? n : (1ull << k);
   uint64_t T;
   if (one) {
@@ -365,23 +435,15 @@ int prand::generate_host_state(prand_ctx* c, int gen, void* h_state, int dtype, 
   const uint64_t nst = nb + 1;                 // plus the final one
   void* d_states = nullptr;
   uint64_t* d_dist = nullptr;
-  void* d_base = nullptr;
-  hipError_t e = hipSuccess;
-  std::unique_lock<std::mutex> lk(c->mu, std::defer_lock);
+  const size_t st_off = (nst * 8 + 255) & ~(size_t)255;
   if (scratch) {
-    const size_t dist_off = base_bytes;
-    const size_t st_off = dist_off + ((nst * 8 + 255) & ~(size_t)255);
-    if (st_off + nst * sb > scratch_bytes) return PRAND_ERANGE;
-    d_base = scratch;
-    d_dist = (uint64_t*)((char*)scratch + dist_off);
-    d_states = (char*)scratch + st_off;
+    if (base_bytes + st_off + nst * sb > scratch_bytes) return PRAND_ERANGE;
+    d_dist = (uint64_t*)((char*)scratch + base_bytes);
+    d_states = (char*)scratch + base_bytes + st_off;
   } else {
-    // the context's host-call scratch holds the base state; its section
-    // buffer (grown when too small, otherwise reused: no allocation and no
-    // implicit device synchronisation per call) the distances and states
-    lk.lock();
-    d_base = c->scratch;
-    const size_t st_off = (nst * 8 + 255) & ~(size_t)255;
+    // the context's section buffer (grown when too small, otherwise reused:
+    // no allocation and no implicit device synchronisation per call) holds
+    // the distances and states
     const size_t need = st_off + nst * sb;
     if (need > c->sec_buf_bytes) {
       (void)hipFree(c->sec_buf);
@@ -395,8 +457,8 @@ int prand::generate_host_state(prand_ctx* c, int gen, void* h_state, int dtype, 
       d_states = (char*)c->sec_buf + st_off;
     }
   }
-  if (e == hipSuccess) e = hipMemcpyAsync(d_base, h_state, sb, hipMemcpyHostToDevice, st);
   if (e == hipSuccess) {
+    hipLaunchKernelGGL(copy_state_kernel, dim3(1), dim3(256), 0, st, (uint32_t*)d_base, (const uint32_t*)pin_in, words);
     hipLaunchKernelGGL(section_dist_kernel, dim3((uint32_t)((nst + 255) / 256)), dim3(256), 0, st, d_dist,
                        (uint32_t)nb, seclen, T);
     e = hipGetLastError();
@@ -415,9 +477,11 @@ int prand::generate_host_state(prand_ctx* c, int gen, void* h_state, int dtype, 
   void* last = (char*)d_states + nb * sb;
   if (e == hipSuccess)
     e = launch_streams(c, gen, last, last, 1, n - T, dtype, (char*)d_out + T * es, st, !scratch);
-  if (e == hipSuccess) e = hipMemcpyAsync(h_state, last, sb, hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
-  return e == hipSuccess ? PRAND_OK : hipfail(c, e);
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL(copy_state_kernel, dim3(1), dim3(256), 0, st, (uint32_t*)pin_out, (const uint32_t*)last, words);
+    e = hipGetLastError();
+  }
+  return finish();
 }
 
 bool prand::mt_tables_ready(prand_ctx* c) {
@@ -491,6 +555,7 @@ int prand_ctx_create(prand_ctx** out, int hip_device) {
   delete H;
   if (e == hipSuccess) e = hipMalloc(&c->T.defaults, kDefaultStride * PRAND_NUM_GENERATORS);
   if (e == hipSuccess) e = hipMalloc(&c->scratch, kScratch);
+  if (e == hipSuccess) e = hipHostMalloc((void**)&c->pin, kPinSlots * kPinBytes, hipHostMallocMapped);
   if (e == hipSuccess) e = noalloc_setup(hip_device);
   if (e == hipSuccess) {
     // default states: the documented default seed of each generator
@@ -526,6 +591,11 @@ int prand_ctx_destroy(prand_ctx* c) {
   (void)hipFree(c->T.defaults);
   (void)hipFree(c->scratch);
   (void)hipFree(c->sec_buf);
+  (void)hipHostFree(c->pin);
+  (void)hipFree(c->arr_dev);
+  (void)hipHostFree(c->arr_pin);
+  for (hipEvent_t ev : c->arr_ev)
+    if (ev) (void)hipEventDestroy(ev);
   for (auto& v : c->sec_tabs)
     for (auto& t : v) (void)hipFree(t.second);
   delete c;
@@ -545,12 +615,9 @@ int prand_seed(prand_ctx* c, int gen, uint64_t seed, void* h_state) {
   if (!c || !valid_gen(gen) || !h_state) return PRAND_EINVAL;
   DeviceGuard g(c->device);
   std::lock_guard<std::mutex> lk(c->mu);
-  uint64_t* d_seed = (uint64_t*)c->scratch;
-  void* d_state = (char*)c->scratch + 256;
-  hipError_t e = hipMemcpy(d_seed, &seed, 8, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = launch_seed(gen, d_seed, 1, d_state, nullptr);
-  if (e == hipSuccess) e = hipMemcpy(h_state, d_state, state_bytes(gen), hipMemcpyDeviceToHost);
-  return e == hipSuccess ? PRAND_OK : hipfail(c, e);
+  std::memcpy(c->pin, &seed, 8);
+  return on_host_state(c, gen, h_state,
+                       [&](void* state) { return launch_seed(gen, (const uint64_t*)c->pin, 1, state, nullptr); });
 }
 
 int prand_seed_host(int gen, uint64_t seed, void* h_state) {
@@ -618,16 +685,12 @@ int prand_skipahead(prand_ctx* c, int gen, void* h_state, const uint64_t* h_dist
   int rc = ensure_mt_locked(c, gen);
   if (rc) return rc;
   std::lock_guard<std::mutex> lk(c->mu);
-  uint64_t* d_dist = (uint64_t*)c->scratch;
-  void* d_state = (char*)c->scratch + 256;
-  hipError_t e = hipMemcpy(d_dist, h_dist, 8 * (size_t)nlimbs, hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(d_state, h_state, state_bytes(gen), hipMemcpyHostToDevice);
+  std::memcpy(c->pin, h_dist, 8 * (size_t)nlimbs);
   JumpSpec js;
-  js.dist = d_dist;
+  js.dist = (const uint64_t*)c->pin;
   js.nlimbs = nlimbs;
-  if (e == hipSuccess) e = launch_jump(c, gen, d_state, 1, js, nullptr, nullptr);
-  if (e == hipSuccess) e = hipMemcpy(h_state, d_state, state_bytes(gen), hipMemcpyDeviceToHost);
-  return e == hipSuccess ? PRAND_OK : hipfail(c, e);
+  return on_host_state(c, gen, h_state,
+                       [&](void* state) { return launch_jump(c, gen, state, 1, js, nullptr, nullptr); });
 }
 
 int prand_init_streams_dev(prand_ctx* c, int gen, int variant, const void* d_base_state, const uint64_t* d_ids,
@@ -657,17 +720,14 @@ int prand_init_stream(prand_ctx* c, int gen, int variant, uint64_t id, void* h_s
   int rc = ensure_mt_locked(c, gen);
   if (rc) return rc;
   std::lock_guard<std::mutex> lk(c->mu);
-  uint64_t* d_id = (uint64_t*)c->scratch;
-  void* d_state = (char*)c->scratch + 256;
-  hipError_t e = hipMemcpy(d_id, &id, 8, hipMemcpyHostToDevice);
+  std::memcpy(c->pin, &id, 8);
   JumpSpec js;
-  js.ids = d_id;
+  js.ids = (const uint64_t*)c->pin;
   js.block_e = be;
   if (gen == PRAND_MT19937) js.mt_top = c->T.mttop;
-  if (e == hipSuccess)
-    e = launch_jump(c, gen, d_state, 1, js, (const char*)c->T.defaults + kDefaultStride * gen, nullptr);
-  if (e == hipSuccess) e = hipMemcpy(h_state, d_state, state_bytes(gen), hipMemcpyDeviceToHost);
-  return e == hipSuccess ? PRAND_OK : hipfail(c, e);
+  return on_host_state(c, gen, h_state, [&](void* state) {
+    return launch_jump(c, gen, state, 1, js, (const char*)c->T.defaults + kDefaultStride * gen, nullptr);
+  });
 }
 
 int prand_generate_array(prand_ctx* c, int gen, void* h_state, int dtype, void* h_out, uint64_t n) {
@@ -678,25 +738,64 @@ int prand_generate_array(prand_ctx* c, int gen, void* h_state, int dtype, void* 
   DeviceGuard g(c->device);
   int rc = ensure_mt_locked(c, gen);
   if (rc) return rc;
-  // chunks of at most 2^26 values: each is filled on the device by the
-  // sectioned fill (which continues the host state) and copied to the host
+  // Chunks of up to kArrayDevBytes: each is filled on the device by the
+  // sectioned fill (which continues the host state) and goes to the host
+  // array by way of pinned buffers, one piece copied from the device while the
+  // CPU copies the one before on: 10^7 MRG32K3A f32 took 2.4 ms by one copy
+  // into pageable memory, 1.5 so (the copying CPU's rate, 27 GB/s).  A call of
+  // at most 256 KB is generated straight into a pinned buffer.
+  std::lock_guard<std::mutex> lk(c->arr_mu);
   const size_t es = elem_bytes(dtype);
-  const uint64_t chunk = std::min<uint64_t>(n, 1ull << 26);
-  void* d_buf = nullptr;
-  hipError_t e = hipMalloc(&d_buf, chunk * es);
+  hipError_t e = hipSuccess;
+  if (!c->arr_pin) {
+    e = hipHostMalloc((void**)&c->arr_pin, kArrayPins * kArrayPinBytes, hipHostMallocMapped);
+    if (e != hipSuccess) c->arr_pin = nullptr;
+  }
+  for (hipEvent_t& ev : c->arr_ev)
+    if (e == hipSuccess && !ev) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+  const uint64_t chunk = std::min<uint64_t>(n, kArrayDevBytes / es);
+  const bool direct = n * es <= (256u << 10);
+  if (e == hipSuccess && !direct && c->arr_dev_bytes < chunk * es) {
+    (void)hipFree(c->arr_dev);
+    c->arr_dev = nullptr;
+    c->arr_dev_bytes = 0;
+    e = hipMalloc(&c->arr_dev, chunk * es);
+    if (e == hipSuccess) c->arr_dev_bytes = chunk * es;
+  }
   if (e != hipSuccess) {
     (void)hipGetLastError();
     return e == hipErrorOutOfMemory ? PRAND_ENOMEM : hipfail(c, e);
   }
+  if (direct) {
+    rc = generate_host_state(c, gen, h_state, dtype, c->arr_pin, n, nullptr, nullptr, 0);
+    if (rc == PRAND_OK) std::memcpy(h_out, c->arr_pin, n * es);
+    return rc;
+  }
   for (uint64_t done = 0; done < n && rc == PRAND_OK; done += chunk) {
     const uint64_t m = std::min(chunk, n - done);
-    rc = generate_host_state(c, gen, h_state, dtype, d_buf, m, nullptr, nullptr, 0);
-    if (rc == PRAND_OK) {
-      e = hipMemcpy((char*)h_out + done * es, d_buf, m * es, hipMemcpyDeviceToHost);
-      if (e != hipSuccess) rc = hipfail(c, e);
+    rc = generate_host_state(c, gen, h_state, dtype, c->arr_dev, m, nullptr, nullptr, 0);
+    if (rc != PRAND_OK) break;
+    const size_t bytes = m * es, pieces = (bytes + kArrayPinBytes - 1) / kArrayPinBytes;
+    char* const to = (char*)h_out + done * es;
+    auto size_of = [&](size_t k) { return std::min(kArrayPinBytes, bytes - k * kArrayPinBytes); };
+    auto start = [&](size_t k) {
+      if (e == hipSuccess)
+        e = hipMemcpyAsync(c->arr_pin + (k % kArrayPins) * kArrayPinBytes, (char*)c->arr_dev + k * kArrayPinBytes,
+                           size_of(k), hipMemcpyDeviceToHost, nullptr);
+      if (e == hipSuccess) e = hipEventRecord(c->arr_ev[k % kArrayPins], nullptr);
+    };
+    for (size_t k = 0; k < std::min<size_t>(pieces, kArrayPins); k++) start(k);
+    for (size_t k = 0; k < pieces && e == hipSuccess; k++) {
+      e = hipEventSynchronize(c->arr_ev[k % kArrayPins]);
+      if (e != hipSuccess) break;
+      std::memcpy(to + k * kArrayPinBytes, c->arr_pin + (k % kArrayPins) * kArrayPinBytes, size_of(k));
+      if (k + kArrayPins < pieces) start(k + kArrayPins);
+    }
+    if (e != hipSuccess) {
+      (void)hipDeviceSynchronize();   // no copy may outlive the call
+      rc = hipfail(c, e);
     }
   }
-  (void)hipFree(d_buf);
   return rc;
 }
 

@@ -40,7 +40,8 @@ __global__ void __launch_bounds__(256) gm_gen32_kernel(const GmState* sin, GmSta
 // pairs; the sections of a stream cover [j seclen, min((j + 1) seclen, n)).
 // kSections: several sections per stream, which read the stream's state and
 // jump to their starts; the states are then moved on by a launch of their own
-// (sout null).  Otherwise seclen = n and the states are updated in place.
+// (sout null), or, of a single stream, the last section leaves the state in
+// *sout (another object than *sin).  Otherwise seclen = n and the states are updated in place.
 template <int G, int DT, bool kSections>
 __global__ void __launch_bounds__(256) gmx_kernel(const GmState* sin, GmState* sout, uint32_t count, uint64_t n,
                                                   uint32_t nsec, uint64_t seclen, char* __restrict__ out,
@@ -61,7 +62,7 @@ __global__ void __launch_bounds__(256) gmx_kernel(const GmState* sin, GmState* s
       r.in = sin + s;
       r.n = kSections ? (n - start < seclen ? n - start : seclen) : n;
       r.out = out + (s * n + start) * es;
-      r.sout = kSections ? nullptr : sout + s;
+      r.sout = !kSections ? sout + s : (sout && start + r.n == n ? sout : nullptr);
     }
     return r;
   };
@@ -84,9 +85,10 @@ constexpr uint32_t jump_lanes() {
 // base otherwise.  Bound: the modular products (GM55 and GM61: 128-bit) and the
 // state lines.  (With a lane per slot, 32 per stream, a wavefront of the 8-
 // and 12-element ensembles did its products with a quarter or a third of its
-// lanes, and every slot was read and written.  2^20 states moved 2^k: GM55 494
-// -> 180 us, GQ58.4 363 -> 188, GQ58.3 1490 -> 811; started by block splitting:
-// GM55 711 -> 276, GQ58.4 670 -> 220, GQ58.3 669 -> 371.)
+// lanes, and every slot was read and written; GQ58.3 took a matrix per set bit
+// of its distance in elements.  2^20 states moved 2^k: GM55 494 -> 186 us,
+// GQ58.4 363 -> 188, GQ58.3 1490 -> 361; started by block splitting: GM55
+// 711 -> 236, GQ58.4 670 -> 220, GQ58.3 669 -> 369.)
 template <int G>
 __global__ void __launch_bounds__(256) gm_jump_kernel(GmState* __restrict__ states, uint32_t count,
                                                       const uint64_t* __restrict__ dist, int nlimbs, int per_stream,
@@ -193,6 +195,44 @@ hipError_t launch_gen(const DeviceTables& T, const GmState* sin, GmState* sout, 
   return launch_jump_g<G>(T, sout, count, js, nullptr, st);
 }
 
+// One stream: sections from one advance of the states on, so that a short
+// call's time is that of a few; eight or more once they fill the chip's SIMDs.
+// (10^5 outputs by copies, jumps and sections of 4096 in launches of their own,
+// and so: GM61 232 and 21 us, GQ58.3 138 and 24; 10^7: 305 and 148, 190 and 91.)
+template <int G>
+uint64_t single_seclen(uint64_t n) {
+  constexpr uint64_t Q = Mx<G>::Q;
+  constexpr uint64_t unit = G == 6 ? kGmxSteps / 8 * 9 : kGmxSteps;
+  uint64_t seclen = unit;
+  while (seclen < 8 * unit && (n + seclen - 1) / seclen > 1024 * Q) seclen *= 2;
+  while ((n + 2 * seclen - 1) / (2 * seclen) >= kFillWaves * Q) seclen *= 2;
+  return seclen;
+}
+
+template <int G>
+hipError_t launch_single_g(const DeviceTables& T, int dtype, const GmState* base, GmState* sout, uint64_t n, void* out,
+                           hipStream_t st) {
+  constexpr uint64_t Q = Mx<G>::Q;
+  const uint64_t seclen = single_seclen<G>(n);
+  const uint32_t nsec = (uint32_t)((n + seclen - 1) / seclen);
+  const dim3 grid((uint32_t)((nsec + 4 * Q - 1) / (4 * Q))), block(256);
+  switch (dtype) {
+    case PRAND_U32:
+      hipLaunchKernelGGL((gmx_kernel<G, PRAND_U32, true>), grid, block, 0, st, base, sout, 1u, n, nsec, seclen,
+                         (char*)out, T.gmx, T.gm);
+      break;
+    case PRAND_F32:
+      hipLaunchKernelGGL((gmx_kernel<G, PRAND_F32, true>), grid, block, 0, st, base, sout, 1u, n, nsec, seclen,
+                         (char*)out, T.gmx, T.gm);
+      break;
+    default:
+      hipLaunchKernelGGL((gmx_kernel<G, PRAND_F64, true>), grid, block, 0, st, base, sout, 1u, n, nsec, seclen,
+                         (char*)out, T.gmx, T.gm);
+      break;
+  }
+  return hipGetLastError();
+}
+
 template <int G>
 hipError_t launch_gen_g(const DeviceTables& T, int dtype, const GmState* sin, GmState* sout, uint32_t count,
                         uint64_t n, void* out, hipStream_t st) {
@@ -216,6 +256,33 @@ hipError_t launch_gm_generate(const DeviceTables& T, int gen, const GmState* sin
     case 5: return launch_gen_g<5>(T, dtype, sin, sout, count, n, out, st);
     case 6: return launch_gen_g<6>(T, dtype, sin, sout, count, n, out, st);
     default: return launch_gen_g<7>(T, dtype, sin, sout, count, n, out, st);
+  }
+}
+
+hipError_t launch_gm_single(const DeviceTables& T, int gen, const GmState* base, GmState* sout, uint64_t n, int dtype,
+                            void* out, hipStream_t st) {
+  switch (gen - PRAND_GM19) {
+    case 0: return launch_single_g<0>(T, dtype, base, sout, n, out, st);
+    case 1: return launch_single_g<1>(T, dtype, base, sout, n, out, st);
+    case 2: return launch_single_g<2>(T, dtype, base, sout, n, out, st);
+    case 3: return launch_single_g<3>(T, dtype, base, sout, n, out, st);
+    case 4: return launch_single_g<4>(T, dtype, base, sout, n, out, st);
+    case 5: return launch_single_g<5>(T, dtype, base, sout, n, out, st);
+    case 6: return launch_single_g<6>(T, dtype, base, sout, n, out, st);
+    default: return launch_single_g<7>(T, dtype, base, sout, n, out, st);
+  }
+}
+
+uint64_t gm_single_wavefronts(int gen, uint64_t n) {
+  switch (gen - PRAND_GM19) {
+    case 0: return (n / single_seclen<0>(n)) / Mx<0>::Q + 1;
+    case 1: return (n / single_seclen<1>(n)) / Mx<1>::Q + 1;
+    case 2: return (n / single_seclen<2>(n)) / Mx<2>::Q + 1;
+    case 3: return (n / single_seclen<3>(n)) / Mx<3>::Q + 1;
+    case 4: return (n / single_seclen<4>(n)) / Mx<4>::Q + 1;
+    case 5: return (n / single_seclen<5>(n)) / Mx<5>::Q + 1;
+    case 6: return (n / single_seclen<6>(n)) / Mx<6>::Q + 1;
+    default: return (n / single_seclen<7>(n)) / Mx<7>::Q + 1;
   }
 }
 

@@ -61,6 +61,11 @@ hipError_t launch_lfsr_generate(const DeviceTables& T, const LfsrState* sin, Lfs
   return launch_regstream<LfsrGen>(sin, sout, count, n, nsec_log2, seclen, dtype, out, T.lfsr, sectab, st);
 }
 
+hipError_t launch_lfsr_single(const DeviceTables& T, const LfsrState* base, LfsrState* sout, uint64_t n, int dtype,
+                             void* out, hipStream_t st) {
+  return launch_regstream_single<LfsrGen>(base, sout, n, dtype, out, T.lfsr, st);
+}
+
 hipError_t launch_lfsr_jump(const DeviceTables& T, LfsrState* states, uint32_t count, const JumpSpec& js,
                             const LfsrState* base, hipStream_t st) {
   const uint32_t blocks = (count + 255) / 256;

@@ -53,6 +53,11 @@ hipError_t launch_mrg_generate(const DeviceTables& T, const MrgState* sin, MrgSt
   return launch_regstream<MrgGen>(sin, sout, count, n, nsec_log2, seclen, dtype, out, T.mrg, sectab, st);
 }
 
+hipError_t launch_mrg_single(const DeviceTables& T, const MrgState* base, MrgState* sout, uint64_t n, int dtype,
+                             void* out, hipStream_t st) {
+  return launch_regstream_single<MrgGen>(base, sout, n, dtype, out, T.mrg, st);
+}
+
 hipError_t launch_mrg_jump(const DeviceTables& T, MrgState* states, uint32_t count, const JumpSpec& js,
                            const MrgState* base, hipStream_t st) {
   const uint32_t blocks = (count + 255) / 256;

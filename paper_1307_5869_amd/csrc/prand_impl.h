@@ -201,6 +201,18 @@ struct JumpSpec {
 hipError_t launch_mrg_generate(const DeviceTables& T, const MrgState* sin, MrgState* sout, uint32_t count,
                                uint64_t n, int nsec_log2, uint64_t seclen, int dtype, void* out,
                                const uint32_t* sectab, hipStream_t st);
+// one stream cut into sections, a lane each: n outputs of *base (a host
+// object, passed by value) to out, the state after them to *sout (device-
+// accessible memory)
+hipError_t launch_mrg_single(const DeviceTables& T, const MrgState* base, MrgState* sout, uint64_t n, int dtype,
+                             void* out, hipStream_t st);
+hipError_t launch_lfsr_single(const DeviceTables& T, const LfsrState* base, LfsrState* sout, uint64_t n, int dtype,
+                              void* out, hipStream_t st);
+// likewise GM/GQ, a wavefront's share each: base and sout device-accessible
+// and distinct; wavefronts() of them read the base
+hipError_t launch_gm_single(const DeviceTables& T, int gen, const GmState* base, GmState* sout, uint64_t n, int dtype,
+                            void* out, hipStream_t st);
+uint64_t gm_single_wavefronts(int gen, uint64_t n);
 hipError_t launch_mrg_jump(const DeviceTables& T, MrgState* states, uint32_t count, const JumpSpec& js,
                            const MrgState* base, hipStream_t st);
 
@@ -267,6 +279,14 @@ struct DeviceGuard {
 
 }  // namespace prand
 
+namespace prand {
+constexpr size_t kPinBytes = 8192, kPinOut = 4096;
+constexpr int kPinSlots = 2;
+constexpr size_t kArrayDevBytes = 64u << 20, kArrayPinBytes = 2u << 20;
+constexpr int kArrayPins = 3;
+static_assert(sizeof(MtState) <= kPinOut, "a state fits half a slot");
+}  // namespace prand
+
 // the opaque context of the public ABI
 struct prand_ctx {
   int device = 0;
@@ -281,6 +301,18 @@ struct prand_ctx {
   void* sec_buf = nullptr;
   size_t sec_buf_bytes = 0;
   int last_hip = 0;
+  // pinned host memory: kPinSlots slots of kPinBytes for the states that host
+  // calls pass in (at 0) and get back (at kPinOut): slot 0 under mu, slot 1
+  // under the allocation-free entry point's lock of the device
+  char* pin = nullptr;
+  // prand_generate_array: device buffer and pinned copy buffers, kept between
+  // calls (at most kArrayDevBytes and kArrayPins kArrayPinBytes), and the
+  // events of the copies; guarded by arr_mu
+  std::mutex arr_mu;
+  void* arr_dev = nullptr;
+  size_t arr_dev_bytes = 0;
+  char* arr_pin = nullptr;
+  hipEvent_t arr_ev[prand::kArrayPins] = {};
   // section-start tables by section length, [0] MRG32K3A, [1] LFSR113
   // (built on first use, immutable afterwards, freed with the context)
   std::mutex sec_mu;

@@ -195,6 +195,60 @@ __global__ void __launch_bounds__(256) regstream_kernel(const typename G::State*
                             (live && j == jlast) ? sout + s : nullptr, ladder, sec_mat);
 }
 
+// One stream: lane j owns section j (seclen outputs, the last one the rest).
+template <class G, int DT>
+__global__ void __launch_bounds__(256) regstream_single_kernel(typename G::State base, typename G::State* sout,
+                                                               uint64_t n, uint32_t nsec, uint64_t seclen,
+                                                               void* __restrict__ out,
+                                                               const uint32_t* __restrict__ table) {
+  __shared__ __align__(16) uint32_t stage[4][RegStage<32>::kWaveWords];
+  const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
+  const bool live = j < nsec;
+  const uint64_t start = live ? j * seclen : 0;
+  const uint64_t len = live ? (j + 1 < nsec ? seclen : n - start) : 0;
+  constexpr int es = (DT == PRAND_F64) ? 8 : 4;
+  regstream_wave<G, DT, 32>(stage[threadIdx.x >> 6], live, &base, start, len, (char*)out + start * es,
+                            live && j + 1 == nsec ? sout : nullptr, table);
+}
+
+// Sections of 32 outputs up to kSingleLanes of them: a short call's time is the
+// chain of one section (1000 MRG32K3A numbers: 51 us by way of copies, jumps
+// and sections of 256 in launches of their own, 18 us as this one).  Then 64
+// and so on, as the starts (one matrix per nonzero byte of the distance) would
+// come to cost as much as the outputs, up to 2 KB of them: in longer ones the
+// 64 runs of a wavefront lie further apart than the caches join (10^9 f64
+// MRG32K3A: 1.47 ms in sections of 2 KB, 1.79 of 4 KB; 10^9 u32: 0.82 of 2 KB,
+// 1.04 of 4 KB, 0.84 of 1 KB), until the lanes would be more than
+// kSingleMaxLanes.
+constexpr uint64_t kSingleLanes = 1u << 18, kSingleMaxLanes = 1u << 22;
+
+template <class G>
+hipError_t launch_regstream_single(const typename G::State* base, typename G::State* sout, uint64_t n, int dtype,
+                                   void* out, const uint32_t* table, hipStream_t st) {
+  uint64_t seclen = 32;
+  auto lanes = [&]() { return (n + seclen - 1) / seclen; };
+  const uint64_t full = dtype == PRAND_F64 ? 256 : 512;   // 2 KB
+  while (seclen < full && lanes() > kSingleLanes) seclen *= 2;
+  while (lanes() > kSingleMaxLanes) seclen *= 2;
+  const uint32_t nsec = (uint32_t)((n + seclen - 1) / seclen);
+  const dim3 grid((nsec + 255) / 256), block(256);
+  switch (dtype) {
+    case PRAND_U32:
+      hipLaunchKernelGGL((regstream_single_kernel<G, PRAND_U32>), grid, block, 0, st, *base, sout, n, nsec, seclen, out,
+                         table);
+      break;
+    case PRAND_F32:
+      hipLaunchKernelGGL((regstream_single_kernel<G, PRAND_F32>), grid, block, 0, st, *base, sout, n, nsec, seclen, out,
+                         table);
+      break;
+    default:
+      hipLaunchKernelGGL((regstream_single_kernel<G, PRAND_F64>), grid, block, 0, st, *base, sout, n, nsec, seclen, out,
+                         table);
+      break;
+  }
+  return hipGetLastError();
+}
+
 // CW of the register-state kernels: 32 unless PRAND_REG_CHUNK_WORDS=16
 inline int regstream_chunk_words() {
   static int cw = -1;
