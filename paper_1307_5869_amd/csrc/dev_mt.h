@@ -235,5 +235,85 @@ __device__ __forceinline__ void gen_wave(uint32_t* mt, const MtState* in, MtStat
   }
 }
 
+// A workgroup of kGroup threads generates n outputs of one stream: state *in,
+// outputs at out, advanced state to *sout (may be the same object as *in).
+//
+// The sequence continues 227 words at a time, a word per thread: x_{i} is
+// x_{i-227}, this thread's word of the turn before, plus the pair x_{i-624},
+// x_{i-623} of words at least two turns old.  Those come from a ring of 4 * 227
+// LDS words, read a turn ahead, so that a turn's chain is one XOR and the
+// ring's latency, the tempering and the store all lie beside it.  Word i is at
+// ring place (i + 57) % 908: the new words of turn p then fill quarter
+// (p + 3) % 4, and with the turns unrolled by four every LDS address is a
+// constant of the thread.  A turn's writes replace words i - 908, older than
+// any that is still read.  Bound: one LDS round trip and one barrier per 227
+// words.  A lone stream of 100000 u32: 98 us by one wavefront, which waits out
+// the LDS three times per block, 40 so (54 with the LDS instructions where the
+// compiler puts them, the write last).
+//
+// The threads past kTurn repeat the last one's word, so that no turn but the
+// last ones masks anything.  All kGroup threads must call; the ring may be used
+// again after a barrier.
+constexpr int kGroup = 256, kTurn = 227, kRing = 4 * kTurn;
+
+template <int DT>
+__device__ __forceinline__ void gen_group(uint32_t* ring, const MtState* in, MtState* sout, uint64_t n, void* out) {
+  constexpr int es = (DT == PRAND_F64) ? 8 : 4;
+  for (uint32_t i = threadIdx.x; i < 624; i += kGroup) ring[57 + i] = in->mt[i];
+  const uint32_t idx0 = in->idx < 624u ? in->idx : 624u;   // an index past the block means "block used up"
+  __syncthreads();
+  // rest of the current block
+  const uint64_t rest = (uint64_t)(624 - idx0) < n ? (uint64_t)(624 - idx0) : n;
+  for (uint32_t i = threadIdx.x; i < rest; i += kGroup) put<DT>(out, i, temper(ring[57 + idx0 + i]));
+  // then `blocks` whole ones, whose words beyond the n outputs are made too
+  const uint64_t blocks = (n - rest + 623) / 624;
+  uint64_t turns = (624 * blocks + kTurn - 1) / kTurn, left = n - rest;
+  const uint32_t t = threadIdx.x < kTurn ? threadIdx.x : kTurn - 1;
+  uint32_t v = ring[57 + 397 + t];                     // x_{i-227}
+  uint32_t pair = recur(ring[57 + t], ring[58 + t], 0);
+  char* o = (char*)out + (rest + t) * es;
+  // turn q (mod 4): the word is made, the next turn's pair read
+  auto turn = [&](int q, auto&& store) {
+    const int next = (q + 1) % 4;
+    v ^= pair;
+    ring[kTurn * ((q + 3) % 4) + t] = v;
+    const uint32_t a = kTurn * next + 57 + t;
+    const uint32_t x0 = ring[next < 3 ? a : a % kRing], x1 = ring[next < 3 ? a + 1 : (a + 1) % kRing];
+    __builtin_amdgcn_sched_barrier(0);   // the LDS works while the word is tempered and stored
+    store(temper(v));
+    __builtin_amdgcn_sched_barrier(0);
+    pair = recur(x0, x1, 0);
+    __syncthreads();
+  };
+  // four turns at a time (at most 2^30 fours, a 32-bit count, in one go)
+  while (left >= kRing) {
+    const uint64_t fours = left / kRing;
+    const uint32_t m = fours < (1u << 30) ? (uint32_t)fours : 1u << 30;
+    for (uint32_t i = 0; i < m; i++) {
+#pragma unroll
+      for (int q = 0; q < 4; q++) turn(q, [&](uint32_t w) { put<DT>(o, kTurn * q, w); });
+      o += kRing * es;
+    }
+    left -= (uint64_t)kRing * m;
+    turns -= 4ull * m;
+  }
+  // the last ones, fewer than eight
+  for (uint32_t p = 0; p < (uint32_t)turns; p += 4) {
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      if (p + q < (uint32_t)turns)
+        turn(q, [&](uint32_t w) {
+          if (kTurn * (p + q) + t < (uint32_t)left) put<DT>(o, kTurn * (p + q), w);
+        });
+    }
+  }
+  const uint32_t last = (uint32_t)((624 * blocks + 57) % kRing);   // the last block's ring place
+  for (uint32_t i = threadIdx.x; i < 624; i += kGroup) sout->mt[i] = ring[(last + i) % kRing];
+  if (threadIdx.x == 0) {
+    sout->idx = blocks ? (uint32_t)(n - rest - 624 * (blocks - 1)) : idx0 + (uint32_t)rest;
+    sout->pad[0] = sout->pad[1] = sout->pad[2] = 0;
+  }
+}
+
 }  // namespace mt
 }  // namespace prand

@@ -4,7 +4,9 @@
 // renews the block in three dependency phases (words 0..226 read old words
 // 397..623; 227..453 read words renewed in phase one; 454..623 read phase two
 // and word 0), each phase parallel across the 64 lanes; whole blocks are
-// written out two at a time from LDS as 16-byte pieces (dev_mt.h).
+// written out two at a time from LDS as 16-byte pieces (dev_mt.h).  Where the
+// streams are too few to fill the chip so, a workgroup of four wavefronts per
+// stream makes 227 words at a time.
 //
 // Jump-ahead (paper, section on MT19937 jump-ahead, equation g_v):
 // A^v Y = g_v(A) Y = sum_i a_i A^(i-1) Y with g_v = x^v mod phi.  A^(i-1) Y is
@@ -47,6 +49,23 @@ __global__ void __launch_bounds__(64) mt_generate_kernel(MtState* states, uint32
   constexpr int es = (DT == PRAND_F64) ? 8 : 4;
   gen_wave<DT, true>(mt, states + s, states + s, n, (char*)out + (uint64_t)s * n * es);
 }
+
+// a workgroup per stream (dev_mt.h)
+template <int DT>
+__global__ void __launch_bounds__(kGroup) mt_generate_group_kernel(MtState* states, uint64_t n, void* __restrict__ out) {
+  __shared__ uint32_t ring[kRing];
+  constexpr int es = (DT == PRAND_F64) ? 8 : 4;
+  const uint32_t s = blockIdx.x;
+  gen_group<DT>(ring, states + s, states + s, n, (char*)out + (uint64_t)s * n * es);
+}
+
+// Streams up to which a workgroup each is faster than a wavefront each, us for
+// 100000 u32 / f64 per stream:
+//   streams       1      256      512     1000     1500     2048
+//   wavefront   98/106  104/113  113/124  113/169  141/259  189/326
+//   workgroup   40/45    46/50    48/89    96/167  145/243  180/320
+// (8192 streams of 20000 u32: 153 and 170; 65536 of 16384: 909 and 1080).
+constexpr uint32_t kMtGroupMaxCount = 1024;
 
 // ------------------------------------------------------------------ jump
 // Wavefronts per stream by the launch's streams, all measured for block
@@ -466,6 +485,15 @@ hipError_t launch_batch_mt_starts(const DeviceTables& T, const BatchTile* tiles,
 }
 
 hipError_t launch_mt_generate(MtState* states, uint32_t count, uint64_t n, int dtype, void* out, hipStream_t st) {
+  if (count <= kMtGroupMaxCount) {
+    const dim3 grid(count), block(kGroup);
+    switch (dtype) {
+      case PRAND_U32: hipLaunchKernelGGL(mt_generate_group_kernel<PRAND_U32>, grid, block, 0, st, states, n, out); break;
+      case PRAND_F32: hipLaunchKernelGGL(mt_generate_group_kernel<PRAND_F32>, grid, block, 0, st, states, n, out); break;
+      default: hipLaunchKernelGGL(mt_generate_group_kernel<PRAND_F64>, grid, block, 0, st, states, n, out); break;
+    }
+    return hipGetLastError();
+  }
   switch (dtype) {
     case PRAND_U32: hipLaunchKernelGGL(mt_generate_kernel<PRAND_U32>, dim3(count), dim3(64), 0, st, states, count, n, out); break;
     case PRAND_F32: hipLaunchKernelGGL(mt_generate_kernel<PRAND_F32>, dim3(count), dim3(64), 0, st, states, count, n, out); break;
