@@ -236,15 +236,12 @@ int prand_generate_noalloc(prand_ctx* ctx, int gen, void* h_state, int dtype, vo
  * Batched launch: many streams of uneven lengths and mixed generators and
  * dtypes in one launch, replayed from a HIP graph.  Each task is cut into
  * sections that jump to their first output (the sectioning of "Multi-threaded
- * generation"), grouped into per-wavefront tiles; a first kernel computes
- * every section's start state, then three persistent kernels, one per
- * register class (the lane-per-section GM55/GQ58.3/GQ58.4 tiles;
- * MRG32K3A/LFSR113; MT19937 with the v = 1 GM/GQ ensembles), work through
- * their tile lists longest first, every wavefront taking the next tile from
- * its class's device counter -- one after another, each with as many
- * wavefronts as the chip holds, or side by side, each with a share of the
- * chip sized by its work, or the MRG32K3A/LFSR113 class first and then the
- * other two side by side (prand_batch_config.overlap).
+ * generation"), grouped into tiles; a first kernel computes every section's
+ * start state, then two persistent kernels (MT19937 and GM/GQ; MRG32K3A and
+ * LFSR113) work through their tile lists longest first, taking the next tile
+ * from a device counter -- one after the other, each with as many wavefronts
+ * as the chip holds, in either order, or side by side
+ * (prand_batch_config.overlap).
  * ------------------------------------------------------------------------ */
 typedef struct prand_task {
   int32_t gen;           /* enum prand_gen */
@@ -257,16 +254,17 @@ typedef struct prand_task {
 } prand_task;
 
 typedef struct prand_batch_config {
-  uint32_t waves_per_block; /* wavefronts per workgroup: 1, 2 or 4 (0: 4) */
-  uint32_t reg_section;    /* MRG32K3A/LFSR113 outputs per lane section, multiple of 32 (0: 2048) */
-  uint32_t gm_section;     /* GM/GQ outputs per element-group section (0: 4096) */
+  uint32_t waves_per_block; /* wavefronts per workgroup of the section starts and MRG32K3A/LFSR113
+                               kernels: 1, 2 or 4 (0: 4) */
+  uint32_t reg_section;    /* MRG32K3A/LFSR113 outputs per lane section, multiple of 32 (0: 128 .. 2048 by
+                               the batch's outputs) */
+  uint32_t gm_section;     /* GM/GQ outputs per tile (0: 1024 .. 16384 by the batch's outputs) */
   uint32_t use_graph;      /* 1: capture the launch in a HIP graph and replay it */
   uint32_t lds_chunk_words; /* LDS staging of MRG32K3A/LFSR113 lanes, 16 or 32 words (0: 32):
                                5 or 9 KB per wavefront of their kernel */
-  uint32_t overlap;        /* 0: the three class kernels run one after another; 1: side by side,
-                              each class's share of the chip sized by its work; 2: the
-                              MRG32K3A/LFSR113 class first with the whole chip, then the other
-                              two side by side */
+  uint32_t overlap;        /* 0: MT19937 and GM/GQ first, then MRG32K3A/LFSR113; 1: side by side,
+                              MRG32K3A/LFSR113 with the share of the chip its work takes;
+                              2: MRG32K3A/LFSR113 first */
 } prand_batch_config;
 
 typedef struct prand_batch prand_batch;
@@ -285,7 +283,7 @@ int prand_batch_create(prand_ctx* ctx, const prand_task* h_tasks, uint32_t ntask
    the same batch must not overlap each other (they share the batch's tile
    counters and scratch). */
 int prand_batch_launch(prand_batch* batch, void* stream);
-/* Number of tiles (wavefront work items) the plan holds. */
+/* Number of tiles (work items of a wavefront or, MT19937, a workgroup) the plan holds. */
 int prand_batch_tiles(const prand_batch* batch, uint32_t* ntiles);
 int prand_batch_destroy(prand_batch* batch);
 

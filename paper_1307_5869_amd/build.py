@@ -53,6 +53,7 @@ HOST_SOURCE_FLAGS = {"simd_host.cpp": ["-O3", "-ffp-contract=off"]}
 # The GM/GQ kernels work on the matrix instructions' results with the VALU:
 # results in VGPRs, not in accumulation registers, save a copy of every value.
 SOURCE_FLAGS = {"k_gm.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+                "k_batch.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
                 "k_mt19937.hip": ["-mllvm", "-structurizecfg-skip-uniform-regions",
                                   "-mllvm", "-simplifycfg-hoist-common=false",
                                   "-mllvm", "-enable-tail-merge=false"]}

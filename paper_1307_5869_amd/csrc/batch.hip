@@ -1,18 +1,16 @@
 // Batched launch: planning, HIP-graph replay and the autotuner.
 //
 // The planner cuts each task into sections that jump to their first output
-// and groups them into per-wavefront tiles (see k_batch.hip), family by
-// family.  Every MRG32K3A/LFSR113 and GM/GQ tile gets a slot in the batch's
-// scratch area for its sections' start states.  The tiles of each register
-// class (light: v = 1 GM/GQ, MT19937, copies; reg: MRG32K3A/LFSR113; heavy:
-// the lane-per-section GM/GQ shapes) form one list, longest first by
-// estimated wavefront time, which the class's persistent kernel works
-// through.  The launch -- counter reset and section starts, then the three
-// persistent kernels side by side on forked streams -- is captured once in a
-// HIP graph on a private stream and replayed on the caller's stream.  The autotuner times a small grid of
-// (MRG32K3A/LFSR113 lane section, GM/GQ group section, LDS chunk width of
-// the light kernel, class order) on the actual task mix and re-times the
-// best three before it picks one.
+// and groups them into tiles (see k_batch.hip), family by family.  Every
+// MRG32K3A/LFSR113 and GM/GQ tile gets a slot in the batch's scratch area for
+// its sections' start states.  The tiles form three lists (MT19937 and
+// copies, MRG32K3A/LFSR113, GM/GQ), longest first by estimated time, which the
+// persistent kernels work through.  The launch -- counter reset and section
+// starts, then the two persistent kernels -- is captured once in a HIP graph
+// on a private stream and replayed on the caller's stream.  The autotuner
+// times a small grid of (MRG32K3A/LFSR113 lane section, LDS chunk width of the
+// reg kernel, kernel order) on the actual task mix and re-times the best three
+// before it picks one.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -36,14 +34,14 @@ struct prand_batch {
   BatchCounts n;
   BatchTask* d_tasks = nullptr;
   char* d_scratch = nullptr;
-  uint32_t* d_order = nullptr;      // the class lists, one after the other
-  uint32_t* d_counters = nullptr;   // kBatchCounters tile counters
-  uint32_t n_cls[kBatchCounters] = {0, 0, 0};
-  uint32_t off_cls[kBatchCounters] = {0, 0, 0};
-  uint32_t blocks_cls[kBatchCounters] = {0, 0, 0};
+  uint32_t* d_order = nullptr;      // the lists, one after the other
+  uint32_t* d_counters = nullptr;   // a tile counter per list
+  uint32_t n_list[kBatchLists] = {0, 0, 0};
+  uint32_t off_list[kBatchLists] = {0, 0, 0};
+  uint32_t main_blocks = 0, reg_blocks = 0;
   hipStream_t cap = nullptr;
-  hipStream_t side[2] = {nullptr, nullptr};    // heavy and reg branches
-  hipEvent_t ev[3] = {nullptr, nullptr, nullptr};   // fork, joins
+  hipStream_t side = nullptr;               // reg branch
+  hipEvent_t ev[2] = {nullptr, nullptr};    // fork, join
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
 };
@@ -59,29 +57,36 @@ size_t state_size(int g) {
   }
 }
 
-// relative wavefront time per output of a tile's longest lane sequence
+// relative wavefront time per output of a tile's longest section (compared
+// within a class only); GM/GQ: the chip time below times the sections that a
+// wavefront runs side by side
 double per_output_cost(int gen) {
   switch (gen) {
-    case PRAND_MT19937: return 0.35;   // 64 lanes share one stream
+    case PRAND_MT19937: return 1;
     case PRAND_MRG32K3A: return 32;
     case PRAND_LFSR113: return 27;
-    case PRAND_GM19: return 6;
-    case PRAND_GM29: return 11;
-    case PRAND_GM31: return 16;
-    case PRAND_GM61: return 24;
-    case PRAND_GQ58X1: return 15;
-    case PRAND_GQ58X3: return 20;
-    default: return 25;   // GM55, GQ58.4
+    case PRAND_GM19: return 4;
+    case PRAND_GM61: return 12.3;
+    case PRAND_GM55: return 12.2;
+    case PRAND_GQ58X3: return 6.6;
+    case PRAND_GQ58X4: return 6.6;
+    default: return 5.4;   // GM29, GM31, GQ58.1
   }
 }
 
+// GM/GQ sections of a tile (the streams of a wavefront in dev_gmx.h)
+uint32_t gm_groups(int gen) {
+  return gen == PRAND_GM55 || gen == PRAND_GQ58X4 ? 4 : (gen == PRAND_GQ58X3 ? 2 : 1);
+}
+
 // whole-chip time per output of the plain many-stream kernels (ms per 2^30
-// outputs, 65536 streams, MI355X; u32 and f32 alike, then f64): the work a
-// class of tiles holds, from which the side-by-side launch sizes its share
+// outputs, 65536 streams, MI355X; u32 and f32 alike, then f64; GM19 and GM61
+// by the matrix form the tiles run): the work a class of tiles holds, from
+// which the side-by-side launch sizes its share
 double chip_cost(int gen, int dtype) {
   static const double t[PRAND_NUM_GENERATORS][2] = {
-      {0.89, 1.77}, {0.94, 1.59}, {0.84, 1.61}, {3.93, 4.03}, {7.31, 7.38}, {7.31, 7.35},
-      {3.72, 4.26}, {10.55, 10.61}, {7.30, 7.40}, {4.05, 5.17}, {2.52, 3.05}};
+      {0.89, 1.77}, {0.94, 1.59}, {0.84, 1.61}, {4.0, 4.0}, {5.4, 5.4}, {5.4, 5.4},
+      {3.05, 3.1}, {12.3, 12.3}, {5.4, 5.4}, {3.3, 3.4}, {1.65, 2.0}};
   return t[gen][dtype == PRAND_F64 ? 1 : 0];
 }
 
@@ -89,13 +94,11 @@ uint64_t round_up(uint64_t x, uint64_t m) { return (x + m - 1) / m * m; }
 
 void fill_defaults(prand_batch_config& c) {
   if (!c.waves_per_block) c.waves_per_block = 4;
-  if (!c.reg_section) c.reg_section = 2048;
-  if (!c.gm_section) c.gm_section = 4096;
   c.lds_chunk_words = c.lds_chunk_words == 16 ? 16 : 32;
   c.overlap = c.overlap > 2 ? 2 : c.overlap;
   c.waves_per_block = c.waves_per_block >= 4 ? 4 : (c.waves_per_block >= 2 ? 2 : 1);
-  c.reg_section = (uint32_t)std::max<uint64_t>(32, round_up(c.reg_section, 32));
-  c.gm_section = std::max<uint32_t>(32, c.gm_section);
+  if (c.reg_section) c.reg_section = (uint32_t)round_up(c.reg_section, 32);
+  if (c.gm_section) c.gm_section = std::max<uint32_t>(32, c.gm_section);
 }
 
 bool is_reg(int g) { return g == PRAND_MRG32K3A || g == PRAND_LFSR113; }
@@ -112,10 +115,24 @@ void batch_fill_defaults(prand_batch_config& c) { fill_defaults(c); }
 
 int batch_plan(const prand_task* tasks, uint32_t ntasks, const prand_batch_config& cfg, BatchPlan& plan,
                uint64_t mt_section_min) {
-  // families in BatchCounts order: MRG32K3A/LFSR113, GM/GQ v = 1, v = 4,
-  // GQ58.3, MT19937, copies (n = 0)
   std::vector<std::pair<double, BatchTile>> work[kBatchFamilies];
-  plan.cost[0] = plan.cost[1] = plan.cost[2] = 0;
+  for (double& c : plan.cost) c = 0;
+  // Section lengths that the configuration leaves open: the lanes (262144) and
+  // wavefronts (16384, four for each the chip holds) they spread a family's
+  // outputs over, up to lengths where the starts are a small part of the work.
+  // (A serving iteration of 16 MRG32K3A/LFSR113 requests of 10^3 .. 10^6: 165 us
+  // in sections of 2048, 16 so; 2000 mixed tasks with GM/GQ tiles of 4096 outputs
+  // 9.45 ms, of 16384 8.6.)
+  uint64_t reg_total = 0, gm_total = 0;
+  for (uint32_t k = 0; k < ntasks; k++) {
+    if (is_reg(tasks[k].gen)) reg_total += std::min<uint64_t>(tasks[k].n, 1ull << 40);
+    else if (tasks[k].gen != PRAND_MT19937) gm_total += std::min<uint64_t>(tasks[k].n, 1ull << 40);
+  }
+  const uint64_t reg_section =
+      cfg.reg_section ? cfg.reg_section
+                      : round_up(std::min<uint64_t>(std::max<uint64_t>(reg_total >> 18, 128), 2048), 32);
+  const uint64_t gm_section =
+      cfg.gm_section ? cfg.gm_section : std::min<uint64_t>(std::max<uint64_t>(gm_total >> 14, 1024), 16384);
   for (uint32_t k = 0; k < ntasks; k++) {
     const prand_task& t = tasks[k];
     if (t.gen < 0 || t.gen >= PRAND_NUM_GENERATORS || t.dtype < PRAND_U32 || t.dtype > PRAND_F64)
@@ -126,19 +143,15 @@ int batch_plan(const prand_task* tasks, uint32_t ntasks, const prand_batch_confi
     b.task = k;
     if (t.n == 0) {
       b.kind = kTileCopy;
-      b.len32 = state_size(t.gen) / 4;
-      work[5].push_back({0.0, b});
+      b.words = state_size(t.gen) / 4;
+      work[kFamCopy].push_back({0.0, b});
       continue;
     }
     b.kind = kTileGen;
     const uint64_t n = t.n;
     const double c = per_output_cost(t.gen);
-    {
-      const bool v1 = t.gen == PRAND_GM19 || t.gen == PRAND_GM29 || t.gen == PRAND_GM31 || t.gen == PRAND_GM61 ||
-                      t.gen == PRAND_GQ58X1;
-      const int cls = (is_reg(t.gen)) ? kClassReg : (t.gen == PRAND_MT19937 || v1) ? kClassLight : kClassHeavy;
-      plan.cost[cls] += (double)n * chip_cost(t.gen, t.dtype);
-    }
+    plan.cost[is_reg(t.gen) ? kListReg : (t.gen == PRAND_MT19937 ? kListMt : kListGm)] +=
+        (double)n * chip_cost(t.gen, t.dtype);
     if (t.gen == PRAND_MT19937) {
       // one wavefront per task, or, for a long task, per kMtSection-output
       // section (each section starts from a jump of the task state)
@@ -147,7 +160,7 @@ int batch_plan(const prand_task* tasks, uint32_t ntasks, const prand_batch_confi
         b.first = 0;
         b.seclen = n;
         b.nsec = 1;
-        work[4].push_back({c * (double)n, b});
+        work[kFamMt].push_back({c * (double)n, b});
       } else {
         // a section's start applies the whole-block ladder entry of every set
         // bit of its number: the numbers must stay below 2^kMtBlkPolys
@@ -157,61 +170,37 @@ int batch_plan(const prand_task* tasks, uint32_t ntasks, const prand_batch_confi
         b.nsec = 1;
         for (uint64_t f = 0; f * sec < n; f++) {
           b.first = f;
-          work[4].push_back({c * (double)std::min(sec, n - f * sec), b});
+          work[kFamMt].push_back({c * (double)std::min(sec, n - f * sec), b});
         }
       }
       continue;
     }
     if (is_reg(t.gen)) {
-      uint64_t sec = cfg.reg_section;
+      uint64_t sec = reg_section;
       if (n < 64 * sec) sec = std::max<uint64_t>(32, round_up((n + 63) / 64, 32));
       const uint64_t total = (n + sec - 1) / sec;
       b.seclen = sec;
       for (uint64_t f = 0; f < total; f += 64) {
         b.first = f;
         b.nsec = (uint32_t)std::min<uint64_t>(64, total - f);
-        work[0].push_back({c * (double)sec, b});
+        work[kFamReg].push_back({c * (double)sec, b});
       }
       continue;
     }
-    const bool v1 = t.gen == PRAND_GM19 || t.gen == PRAND_GM29 || t.gen == PRAND_GM31 || t.gen == PRAND_GM61 ||
-                    t.gen == PRAND_GQ58X1;
-    // v = 1: two 32-lane sections per tile; GM55, GQ58.3, GQ58.4: one lane
-    // per section, section lengths a multiple of 4 (16-byte aligned starts)
-    // and, for GQ58.3, of 9 (every section at the task's place in the
-    // 9-word block)
-    // (a lane then steps all 8 or 12 elements of its section: a lane's
-    // section is an eighth of gm_section, which keeps a tile's time near a
-    // v = 1 tile's)
-    const uint64_t groups = v1 ? 2 : 64;
-    const uint64_t unit = v1 ? 32 : (t.gen == PRAND_GQ58X3 ? 36 : 4);
-    const int fam = v1 ? 1 : (t.gen == PRAND_GQ58X3 ? 3 : 2);
-    uint64_t sec = round_up(v1 ? cfg.gm_section : std::max<uint32_t>(cfg.gm_section / 8, 32), unit);
+    // GM/GQ: the sections of a wavefront share gm_section, so that a tile of
+    // any shape makes as many outputs; a short task spreads over its tile's
+    // sections.  Lengths are whole turns of the generation loop (64 steps,
+    // 72 words of GQ58.3)
+    const uint64_t groups = gm_groups(t.gen);
+    const uint64_t unit = t.gen == PRAND_GQ58X3 ? 72 : 64;
+    uint64_t sec = round_up(std::max<uint64_t>(gm_section / groups, unit), unit);
     if (n < groups * sec) sec = std::max<uint64_t>(unit, round_up((n + groups - 1) / groups, unit));
+    const uint64_t secs = (n + sec - 1) / sec;
     b.seclen = sec;
-    if (v1) {
-      // both halves of a wavefront run the same number of steps: pair the
-      // full sections, give the ragged last section a tile of its own
-      const uint64_t full = n / sec, part = n % sec;
-      for (uint64_t f = 0; f < full; f += 2) {
-        b.first = f;
-        b.nsec = (uint32_t)std::min<uint64_t>(2, full - f);
-        b.len32 = sec;
-        work[fam].push_back({c * (double)sec, b});
-      }
-      if (part) {
-        b.first = full;
-        b.nsec = 1;
-        b.len32 = part;
-        work[fam].push_back({c * (double)part, b});
-      }
-    } else {
-      const uint64_t total = (n + sec - 1) / sec;
-      for (uint64_t f = 0; f < total; f += groups) {
-        b.first = f;
-        b.nsec = (uint32_t)std::min<uint64_t>(groups, total - f);
-        work[fam].push_back({c * (double)sec, b});
-      }
+    for (uint64_t f = 0; f < secs; f += groups) {
+      b.first = f;
+      b.nsec = (uint32_t)std::min<uint64_t>(groups, secs - f);
+      work[kFamGm].push_back({c * (double)std::min(sec, n - f * sec), b});
     }
   }
   size_t total = 0;
@@ -220,41 +209,35 @@ int batch_plan(const prand_task* tasks, uint32_t ntasks, const prand_batch_confi
   plan.tiles.resize(total);
   plan.scratch_bytes = 0;
   plan.n.mtsec = 0;
-  std::vector<std::pair<double, uint32_t>> light, reg, heavy;
+  std::vector<std::pair<double, uint32_t>> list[kBatchLists];
   size_t at = 0;
   for (int f = 0; f < kBatchFamilies; f++) {
     std::stable_sort(work[f].begin(), work[f].end(), [](const auto& a, const auto& b) { return a.first > b.first; });
     for (auto& w : work[f]) {
-      (f == 0 ? reg : (f == 2 || f == 3) ? heavy : light).push_back({w.first, (uint32_t)at});
+      list[f == kFamReg ? kListReg : f == kFamGm ? kListGm : kListMt].push_back({w.first, (uint32_t)at});
       BatchTile& tl = plan.tiles[at++];
       tl = w.second;
-      if (f <= 3 || tl.kind == kTileMtSection) {
+      if (f == kFamReg || f == kFamGm || tl.kind == kTileMtSection) {
         // section start states: 64 register states, one GmState per
         // section, or the MT19937 section's state
         const int gen = tasks[tl.task].gen;
-        const uint64_t bytes = f == 0   ? 64 * state_size(gen)
-                               : f == 4 ? (uint64_t)sizeof(MtState)
-                                        : (uint64_t)tl.nsec * sizeof(GmState);
+        const uint64_t bytes = f == kFamReg ? 64 * state_size(gen) : (uint64_t)tl.nsec * state_size(gen);
         tl.starts = plan.scratch_bytes;
         plan.scratch_bytes += round_up(bytes, 64);
-        if (f == 4) plan.n.mtsec++;
+        if (f == kFamMt) plan.n.mtsec++;
       }
     }
   }
-  // each class's list longest first (ties: family order, then placement)
-  const std::pair<std::vector<std::pair<double, uint32_t>>*, std::vector<uint32_t>*> lists[] = {
-      {&light, &plan.order_light}, {&reg, &plan.order_reg}, {&heavy, &plan.order_heavy}};
-  for (auto& l : lists) {
-    std::stable_sort(l.first->begin(), l.first->end(), [](const auto& a, const auto& b) { return a.first > b.first; });
-    l.second->resize(l.first->size());
-    for (size_t i = 0; i < l.first->size(); i++) (*l.second)[i] = (*l.first)[i].second;
+  // each list longest first (ties: family order, then placement)
+  for (int l = 0; l < kBatchLists; l++) {
+    std::stable_sort(list[l].begin(), list[l].end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+    plan.order[l].resize(list[l].size());
+    for (size_t i = 0; i < list[l].size(); i++) plan.order[l][i] = list[l][i].second;
   }
-  plan.n.reg = (uint32_t)work[0].size();
-  plan.n.g32 = (uint32_t)work[1].size();
-  plan.n.g8 = (uint32_t)work[2].size();
-  plan.n.g3 = (uint32_t)work[3].size();
-  plan.n.mt = (uint32_t)work[4].size();
-  plan.n.copy = (uint32_t)work[5].size();
+  plan.n.reg = (uint32_t)work[kFamReg].size();
+  plan.n.gm = (uint32_t)work[kFamGm].size();
+  plan.n.mt = (uint32_t)work[kFamMt].size();
+  plan.n.copy = (uint32_t)work[kFamCopy].size();
   return PRAND_OK;
 }
 
@@ -268,8 +251,7 @@ void free_batch(prand_batch* b) {
   if (b->graph) (void)hipGraphDestroy(b->graph);
   for (hipEvent_t e : b->ev)
     if (e) (void)hipEventDestroy(e);
-  for (hipStream_t s : b->side)
-    if (s) (void)hipStreamDestroy(s);
+  if (b->side) (void)hipStreamDestroy(b->side);
   if (b->cap) (void)hipStreamDestroy(b->cap);
   (void)hipFree(b->d_tiles);
   (void)hipFree(b->d_tasks);
@@ -281,52 +263,49 @@ void free_batch(prand_batch* b) {
 
 // The batch's kernels: on stream a the tile counters are cleared and every
 // section jumped to its start (and the MT19937 section starts, when a task
-// is long enough to have sections); then the three persistent kernels run,
-// either one after another on stream a, each with the whole chip's worth of
-// workgroups (mode 0), or side by side -- heavy and reg on two forked
-// streams, each with the share of the chip its work takes, light on stream a
-// with the whole chip's worth (those that do not fit at first are
-// dispatched as the other two classes' wavefronts finish) -- and the forks
-// join back into a (mode 1), or reg first with the whole chip and then heavy
-// beside light (mode 2).
+// is long enough to have sections); then the two persistent kernels run, each
+// with the whole chip's worth of workgroups, main then reg (mode 0) or reg
+// then main (mode 2), or side by side (mode 1): reg on a forked stream with
+// the share of the chip its work takes, main on stream a with the whole chip's
+// worth (those that do not fit at first are dispatched as the other's finish).
 hipError_t enqueue_persistent(prand_batch* b, hipStream_t a) {
   const DeviceTables& T = b->ctx->T;
   const uint32_t w = b->cfg.waves_per_block;
-  const int cw = (int)b->cfg.lds_chunk_words;
   const BatchCounts& n = b->n;
-  const BatchTile* mt = b->d_tiles + n.reg + n.g32 + n.g8 + n.g3;
+  const BatchTile* mt = b->d_tiles + n.with_starts();
   hipError_t e = launch_batch_reset(b->d_counters, a);
   if (e == hipSuccess) e = launch_batch_starts(T, b->d_tiles, n.with_starts(), b->d_tasks, b->d_scratch, w, a);
   if (e == hipSuccess && n.mtsec) e = launch_batch_mt_starts(T, mt, n.mt, b->d_tasks, b->d_scratch, a);
-  if (!b->cfg.overlap) {
-    for (int cls : {kClassHeavy, kClassReg, kClassLight})
-      if (e == hipSuccess)
-        e = launch_batch_persistent(cls, cw, b->d_tiles, b->d_order + b->off_cls[cls], b->n_cls[cls], b->d_tasks,
-                                    b->d_scratch, b->d_counters + cls, w, b->blocks_cls[cls], a);
-    return e;
-  }
-  // mode 2: the reg class first, alone, with the whole chip (its work is a
-  // few percent of a mixed batch, and beside many light wavefronts a small
-  // share of it runs behind), then heavy and light side by side
-  const bool reg_first = b->cfg.overlap == 2;
-  if (reg_first && e == hipSuccess)
-    e = launch_batch_persistent(kClassReg, cw, b->d_tiles, b->d_order + b->off_cls[kClassReg], b->n_cls[kClassReg],
-                                b->d_tasks, b->d_scratch, b->d_counters + kClassReg, w, b->blocks_cls[kClassReg], a);
-  if (e == hipSuccess) e = hipEventRecord(b->ev[0], a);
-  const int side_cls[2] = {kClassHeavy, kClassReg};
-  for (int i = 0; i < (reg_first ? 1 : 2) && e == hipSuccess; i++) {
-    const int cls = side_cls[i];
-    e = hipStreamWaitEvent(b->side[i], b->ev[0], 0);
+  auto main = [&](hipStream_t st) {
     if (e == hipSuccess)
-      e = launch_batch_persistent(cls, cw, b->d_tiles, b->d_order + b->off_cls[cls], b->n_cls[cls], b->d_tasks,
-                                  b->d_scratch, b->d_counters + cls, w, b->blocks_cls[cls], b->side[i]);
-    if (e == hipSuccess) e = hipEventRecord(b->ev[1 + i], b->side[i]);
+      e = launch_batch_main(T, b->d_tiles, b->d_order + b->off_list[kListMt], b->n_list[kListMt],
+                            b->d_order + b->off_list[kListGm], b->n_list[kListGm], b->d_tasks, b->d_scratch,
+                            b->d_counters, b->main_blocks, st);
+  };
+  auto reg = [&](hipStream_t st) {
+    if (e == hipSuccess)
+      e = launch_batch_reg_persistent((int)b->cfg.lds_chunk_words, b->d_tiles, b->d_order + b->off_list[kListReg],
+                                      b->n_list[kListReg], b->d_tasks, b->d_scratch, b->d_counters, w, b->reg_blocks,
+                                      st);
+  };
+  switch (b->cfg.overlap) {
+    case 0:
+      main(a);
+      reg(a);
+      break;
+    case 1:
+      if (e == hipSuccess) e = hipEventRecord(b->ev[0], a);
+      if (e == hipSuccess) e = hipStreamWaitEvent(b->side, b->ev[0], 0);
+      reg(b->side);
+      if (e == hipSuccess) e = hipEventRecord(b->ev[1], b->side);
+      main(a);
+      if (e == hipSuccess) e = hipStreamWaitEvent(a, b->ev[1], 0);
+      break;
+    default:
+      reg(a);
+      main(a);
+      break;
   }
-  if (e == hipSuccess)
-    e = launch_batch_persistent(kClassLight, cw, b->d_tiles, b->d_order + b->off_cls[kClassLight],
-                                b->n_cls[kClassLight], b->d_tasks, b->d_scratch, b->d_counters + kClassLight, w,
-                                b->blocks_cls[kClassLight], a);
-  for (int i = 0; i < (reg_first ? 1 : 2) && e == hipSuccess; i++) e = hipStreamWaitEvent(a, b->ev[1 + i], 0);
   return e;
 }
 
@@ -413,34 +392,29 @@ int prand_batch_create(prand_ctx* c, const prand_task* h_tasks, uint32_t ntasks,
   if (e == hipSuccess && !plan.tiles.empty())
     e = hipMemcpy(b->d_tiles, plan.tiles.data(), plan.tiles.size() * sizeof(BatchTile), hipMemcpyHostToDevice);
   if (e == hipSuccess && ntasks) e = hipMemcpy(b->d_tasks, h_tasks, ntasks * sizeof(BatchTask), hipMemcpyHostToDevice);
-  const std::vector<uint32_t>* ord[kBatchCounters] = {&plan.order_light, &plan.order_reg, &plan.order_heavy};
   uint32_t total_order = 0;
-  const double all = plan.cost[0] + plan.cost[1] + plan.cost[2];
-  for (int cls = 0; cls < kBatchCounters; cls++) {
-    b->n_cls[cls] = (uint32_t)ord[cls]->size();
-    b->off_cls[cls] = total_order;
-    total_order += b->n_cls[cls];
-    const uint32_t full = batch_persistent_blocks(cls, (int)conf.lds_chunk_words, conf.waves_per_block, c->num_cus);
-    // one after another, every class gets the whole chip; side by side, the
-    // light class gets the whole chip's worth and the forked classes the
-    // share their work takes of the batch's (a tenth more, so that they
-    // rather finish before the light class than after it)
-    // (mode 2: the reg class runs alone first, so the heavy class's share is
-    // of the work of heavy and light)
-    const double rest = conf.overlap == 2 ? plan.cost[kClassHeavy] + plan.cost[kClassLight] : all;
-    const double share = (!conf.overlap || cls == kClassLight || rest <= 0 || (conf.overlap == 2 && cls == kClassReg))
-                             ? 1.0
-                             : std::min(1.0, 1.1 * plan.cost[cls] / rest);
-    b->blocks_cls[cls] = std::max<uint32_t>(1, (uint32_t)std::ceil(share * full));
+  double all = 0;
+  for (int l = 0; l < kBatchLists; l++) {
+    b->n_list[l] = (uint32_t)plan.order[l].size();
+    b->off_list[l] = total_order;
+    total_order += b->n_list[l];
+    all += plan.cost[l];
   }
+  // side by side, main gets the whole chip's worth and reg the share its work
+  // takes of the batch's (a tenth more, so that it rather finishes before
+  // main than after it); one after the other, each gets the whole chip
+  const double share = conf.overlap != 1 || all <= 0 ? 1.0 : std::min(1.0, 1.1 * plan.cost[kListReg] / all);
+  const uint32_t full = batch_reg_blocks((int)conf.lds_chunk_words, conf.waves_per_block, c->num_cus);
+  b->reg_blocks = std::max<uint32_t>(1, (uint32_t)std::ceil(share * full));
+  b->main_blocks = batch_main_blocks(c->num_cus);
   if (e == hipSuccess) e = hipMalloc((void**)&b->d_order, std::max<size_t>(1, total_order) * 4);
   if (e == hipSuccess) e = hipMalloc((void**)&b->d_counters, 256);
-  for (int cls = 0; cls < kBatchCounters && e == hipSuccess; cls++)
-    if (b->n_cls[cls])
-      e = hipMemcpy(b->d_order + b->off_cls[cls], ord[cls]->data(), b->n_cls[cls] * 4, hipMemcpyHostToDevice);
+  for (int l = 0; l < kBatchLists && e == hipSuccess; l++)
+    if (b->n_list[l])
+      e = hipMemcpy(b->d_order + b->off_list[l], plan.order[l].data(), b->n_list[l] * 4, hipMemcpyHostToDevice);
   if (e == hipSuccess && conf.use_graph) e = hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking);
-  for (int i = 0; i < 2 && e == hipSuccess; i++) e = hipStreamCreateWithFlags(&b->side[i], hipStreamNonBlocking);
-  for (int i = 0; i < 3 && e == hipSuccess; i++) e = hipEventCreateWithFlags(&b->ev[i], hipEventDisableTiming);
+  if (e == hipSuccess) e = hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking);
+  for (int i = 0; i < 2 && e == hipSuccess; i++) e = hipEventCreateWithFlags(&b->ev[i], hipEventDisableTiming);
   if (e != hipSuccess) {
     free_batch(b);
     if (e == hipErrorOutOfMemory) {
@@ -533,9 +507,9 @@ int prand_batch_autotune(prand_ctx* c, const prand_task* h_tasks, uint32_t ntask
     *out = slowest ? worst : sum / reps;
     return rc;
   };
-  // tile sizes of the two section kinds, and the LDS footprint of the light
+  // tile sizes of the two section kinds, and the LDS footprint of the reg
   // kernel (staging chunk of 16 or 32 words per MRG32K3A/LFSR113 lane: 5 or
-  // 9 KB per wavefront, which sets how many light wavefronts a CU holds).
+  // 9 KB per wavefront, which sets how many of its wavefronts a CU holds).
   // First pass: each configuration scored by the slowest of three launches
   // (a configuration whose classes sometimes finish far apart, a
   // launch-to-launch spread of 10 % was seen, loses to a steadier one).

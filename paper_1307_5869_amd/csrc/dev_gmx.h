@@ -239,16 +239,34 @@ __device__ __forceinline__ uint32_t gmx_pack3(uint32_t p) {
   return (y & 0x3Fu) | (y >> 10);
 }
 
+// output word i in the element type DT, or in `dtype` where DT is kAnyType (a
+// kernel for tasks of every generator and type: one copy of each generator's
+// code)
+constexpr int kAnyType = -1;
+template <int DT>
+__device__ __forceinline__ void gmx_put(void* out, uint64_t i, uint32_t w, int dtype) {
+  if constexpr (DT != kAnyType) {
+    put<DT>(out, i, w);
+  } else {
+    if (dtype == PRAND_F64) {
+      put<PRAND_F64>(out, i, w);
+    } else {
+      const uint32_t f = __float_as_uint((float)(w >> 8) * 0x1p-24f);
+      put<PRAND_U32>(out, i, dtype == PRAND_F32 ? f : w);
+    }
+  }
+}
+
 // Generate the wavefront's streams; sec(q) gives stream q < Mx<G>::Q.  A
 // stream's input state is read before its output state is written, so they
 // may be the same object.  kJump = false: every start is 0.  lds: kGmxLds
-// words of this wavefront.  All 64 lanes must call.
+// words of this wavefront.  dtype (uniform): read where DT is kAnyType.  All 64
+// lanes must call.
 template <int G, int DT, bool kJump, class SecOf>
 __device__ __forceinline__ void gmx_wave(SecOf&& sec, const GmxTable* __restrict__ table,
-                                         const uint64_t* __restrict__ ladder, uint32_t* lds) {
+                                         const uint64_t* __restrict__ ladder, uint32_t* lds, int dtype = DT) {
   using M = Mx<G>;
   using E = Eng<G>;
-  constexpr int es = (DT == PRAND_F64) ? 8 : 4;
   constexpr int J = kGmxSteps;
   const int lane = threadIdx.x & 63;
   const bool upper = lane >= 32;
@@ -334,7 +352,7 @@ __device__ __forceinline__ void gmx_wave(SecOf&& sec, const GmxTable* __restrict
         uint64_t o0, tot;
         frame_of(k, o0, tot);
         if (lane < KW && (uint64_t)lane >= o0 && (uint64_t)lane < tot)
-          put<DT>(sec(k).out, lane - o0, lds[k * KW + lane]);
+          gmx_put<DT>(sec(k).out, lane - o0, lds[k * KW + lane], dtype);
       }
       wave_lds_sync();
       t = K;
@@ -371,7 +389,7 @@ __device__ __forceinline__ void gmx_wave(SecOf&& sec, const GmxTable* __restrict
         }
         const Swapped s = gmx_swap(w[0], w[1]);
         const uint64_t i = t + 32 * g + lane;
-        if (i < total) put<DT>(mine.out, i, gmx_select(s.a, s.b >> 4, 0xF0F0F0F0u));
+        if (i < total) gmx_put<DT>(mine.out, i, gmx_select(s.a, s.b >> 4, 0xF0F0F0F0u), dtype);
       } else if constexpr (M::S == 8) {
         uint32_t w[2][4];
 #pragma unroll
@@ -380,12 +398,27 @@ __device__ __forceinline__ void gmx_wave(SecOf&& sec, const GmxTable* __restrict
 #pragma unroll
           for (int k = 0; k < 4; k++) w[i][k] = gmx_bytes(c, k);
         }
+        uint64_t i = t + 32 * g + lane;
+        // GQ58.4, and kernels of every type: no address of each stream (and
+        // type) is kept across turns
+        if constexpr (G == 7 || DT == kAnyType) asm volatile("" : "+v"(i));
 #pragma unroll
         for (int k = 0; k < 4; k++) {
           const Swapped s = gmx_swap(w[0][k], w[1][k]);
-          const GmxSec o = sec(k);
-          const uint64_t i = t + 32 * g + lane;
-          if (i < o.n) put<DT>(o.out, i, gmx_select(s.a, s.b >> 4, 0xF0F0F0F0u));
+          w[0][k] = gmx_select(s.a, s.b >> 4, 0xF0F0F0F0u);
+        }
+        if (DT != kAnyType || dtype != PRAND_F64) {
+#pragma unroll
+          for (int k = 0; k < 4; k++) {
+            const GmxSec o = sec(k);
+            if (i < o.n) gmx_put<DT>(o.out, i, w[0][k], dtype);
+          }
+        } else {
+#pragma unroll
+          for (int k = 0; k < 4; k++) {
+            const GmxSec o = sec(k);
+            if (i < o.n) put<PRAND_F64>(o.out, i, w[0][k]);
+          }
         }
       } else {
         uint32_t w[2][2];
@@ -410,8 +443,8 @@ __device__ __forceinline__ void gmx_wave(SecOf&& sec, const GmxTable* __restrict
           frame_of(k, o0, tot);
           char* const out = sec(k).out;
           const uint64_t i = (t + 32 * g) / 8 * 9 + lane + (lane >> 3);
-          if (i >= o0 && i < tot) put<DT>(out, i - o0, r4 ? (prev | end) : end);
-          if (r4 == 28 && i + 1 >= o0 && i + 1 < tot) put<DT>(out, i + 1 - o0, begin);
+          if (i >= o0 && i < tot) gmx_put<DT>(out, i - o0, r4 ? (prev | end) : end, dtype);
+          if (r4 == 28 && i + 1 >= o0 && i + 1 < tot) gmx_put<DT>(out, i + 1 - o0, begin, dtype);
         }
       }
     }

@@ -38,9 +38,7 @@ __device__ __forceinline__ void put(void* out, uint64_t i, uint32_t w) {
 // become recur(mt[j], mt[j + 1], mt[j + off]) (word 623's successor is word
 // 0).  Every word a phase reads is either untouched by it or renewed by an
 // earlier phase, so a piece issues all its loads before any of its stores:
-// one LDS latency per K slices of 64 words instead of one per slice (a lone
-// wavefront, as in batched and served MT19937 tasks, is bound by that
-// latency).  kOut: renewed words below `want` are also tempered and stored
+// one LDS latency per K slices of 64 words instead of one per slice.  kOut: renewed words below `want` are also tempered and stored
 // at out[pos + j] straight from registers.
 template <int DT, int K, bool kOut = true>
 __device__ __forceinline__ void twist_phase(uint32_t* mt, int j0, int j1, int off, int want, uint64_t pos, void* out) {
@@ -162,7 +160,7 @@ __device__ __forceinline__ void write_block(const uint32_t* mt, char* out) {
 }
 
 // One wavefront generates n outputs of one stream: state *in (copied into
-// the LDS block mt[624], 16-byte aligned), outputs at out, advanced state to
+// mt[0 .. 623] of 1248 LDS words, 16-byte aligned), outputs at out, advanced state to
 // *sout (may be the same object as *in).  A twist renews the block in three
 // dependency phases (words 0..226 read old words 397..623; 227..453 read
 // words renewed in phase one; 454..623 read phase two and word 0), each
@@ -170,13 +168,12 @@ __device__ __forceinline__ void write_block(const uint32_t* mt, char* out) {
 // aligned is twisted first (one piece per phase) and then tempered and
 // written out from LDS as 16-byte pieces (one vector store per four words
 // instead of four); a partial block tempers and stores renewed words
-// straight from registers.  kPairs (mt then holds 1248 words): while two
-// whole blocks remain, the first is twisted from mt into mt + 624 and the
-// second back into mt, and the two are written out together (1248 words:
-// whole 128-byte lines, where a single block ends in the middle of one;
-// measured about 5 % faster for 65536 streams).  The LDS block is private to
-// the wavefront (wavefront-level ordering only).
-template <int DT, bool kPairs = false>
+// straight from registers.  While two whole blocks remain, the first is
+// twisted from mt into mt + 624 and the second back into mt, and the two are
+// written out together (1248 words: whole 128-byte lines, where a single block
+// ends in the middle of one; measured about 5 % faster for 65536 streams).  The
+// LDS blocks are private to the wavefront (wavefront-level ordering only).
+template <int DT>
 __device__ __forceinline__ void gen_wave(uint32_t* mt, const MtState* in, MtState* sout, uint64_t n, void* out) {
   constexpr int es = (DT == PRAND_F64) ? 8 : 4;
   const int lane = threadIdx.x & 63;
@@ -192,7 +189,7 @@ __device__ __forceinline__ void gen_wave(uint32_t* mt, const MtState* in, MtStat
   const bool vec = (((uintptr_t)out + pos * es) & 15) == 0;
   while (pos < n) {
     const uint64_t left = n - pos;
-    if (kPairs && vec && left >= 1248) {
+    if (vec && left >= 1248) {
       twist_oop(mt, mt + 624);
       twist_oop(mt + 624, mt);
       write_pair<DT>(mt + 624, mt, (char*)out + pos * es);
@@ -211,10 +208,6 @@ __device__ __forceinline__ void gen_wave(uint32_t* mt, const MtState* in, MtStat
       wave_lds_sync();
       write_block<DT>(mt, (char*)out + pos * es);
     } else {
-      // phases in pieces of two 64-word slices: the loads of four slices at
-      // once measured the same for a lone wavefront but took 60 instead of 56
-      // VGPRs in the batch kernel that shares this code with the v = 1 GM/GQ
-      // tiles, which upset the balance of the batch's concurrent kernels
       twist_phase<DT, 2>(mt, 0, 128, 397, want, pos, out);
       twist_phase<DT, 2>(mt, 128, 227, 397, want, pos, out);
       wave_lds_sync();

@@ -47,7 +47,7 @@ __global__ void __launch_bounds__(64) mt_generate_kernel(MtState* states, uint32
   const uint32_t s = b < 8 * per ? (b % 8) * per + b / 8 : b;
   if (s >= count) return;
   constexpr int es = (DT == PRAND_F64) ? 8 : 4;
-  gen_wave<DT, true>(mt, states + s, states + s, n, (char*)out + (uint64_t)s * n * es);
+  gen_wave<DT>(mt, states + s, states + s, n, (char*)out + (uint64_t)s * n * es);
 }
 
 // a workgroup per stream (dev_mt.h)
