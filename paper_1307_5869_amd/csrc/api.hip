@@ -219,17 +219,17 @@ hipError_t launch_jump(prand_ctx* c, int gen, void* states, uint32_t count, cons
 }
 
 // The section-start table of MRG32K3A/LFSR113 (k = 0/1) for section length
-// seclen: looked up, or built on the host and uploaded when `may_create`
-// (an allocation and a blocking copy, once per length; not while the stream
-// is being captured, and at most kMaxSectionTables lengths per generator).
+// seclen: looked up, or built on the host and uploaded (an allocation and a
+// blocking copy, once per length; not while the stream is being captured, and
+// at most kMaxSectionTables lengths per generator).
 // Null when there is none: the kernel then jumps through the ladder.
 constexpr size_t kMaxSectionTables = 64;
 
-const uint32_t* section_table(prand_ctx* c, int k, uint64_t seclen, hipStream_t st, bool may_create) {
+const uint32_t* section_table(prand_ctx* c, int k, uint64_t seclen, hipStream_t st) {
   std::lock_guard<std::mutex> lk(c->sec_mu);
   for (const auto& t : c->sec_tabs[k])
     if (t.first == seclen) return t.second;
-  if (!may_create || c->sec_tabs[k].size() >= kMaxSectionTables) return nullptr;
+  if (c->sec_tabs[k].size() >= kMaxSectionTables) return nullptr;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return nullptr;
   const size_t words = (size_t)kSectionTableRows * (k == 0 ? kMrgSectionWords : kLfsrSectionWords);
@@ -272,31 +272,24 @@ void section_plan(uint32_t count, uint64_t n, bool table, int& nsec_log2, uint64
   if (seclen == 0) seclen = 32;
 }
 
-// many-stream generation; sin/sout may alias (sections of a stream never
-// straddle a wavefront).  may_alloc: a section-start table may be built.
-hipError_t launch_streams(prand_ctx* c, int gen, const void* sin, void* sout, uint32_t count, uint64_t n,
-                          int dtype, void* out, hipStream_t st, bool may_alloc) {
+// many-stream generation, the states moved on in place
+hipError_t launch_streams(prand_ctx* c, int gen, void* states, uint32_t count, uint64_t n, int dtype, void* out,
+                          hipStream_t st) {
   if (gen == PRAND_MRG32K3A || gen == PRAND_LFSR113) {
     const int k = gen == PRAND_MRG32K3A ? 0 : 1;
     int nsec_log2;
     uint64_t seclen;
     section_plan(count, n, true, nsec_log2, seclen);
-    const uint32_t* tab = nsec_log2 ? section_table(c, k, seclen, st, may_alloc) : nullptr;
+    const uint32_t* tab = nsec_log2 ? section_table(c, k, seclen, st) : nullptr;
     if (!tab) section_plan(count, n, false, nsec_log2, seclen);
     if (gen == PRAND_MRG32K3A)
-      return launch_mrg_generate(c->T, (const MrgState*)sin, (MrgState*)sout, count, n, nsec_log2, seclen, dtype,
+      return launch_mrg_generate(c->T, (const MrgState*)states, (MrgState*)states, count, n, nsec_log2, seclen, dtype,
                                  out, tab, st);
-    return launch_lfsr_generate(c->T, (const LfsrState*)sin, (LfsrState*)sout, count, n, nsec_log2, seclen, dtype,
+    return launch_lfsr_generate(c->T, (const LfsrState*)states, (LfsrState*)states, count, n, nsec_log2, seclen, dtype,
                                 out, tab, st);
   }
-  if (gen == PRAND_MT19937) {
-    if (sin != sout) {
-      hipError_t e = hipMemcpyAsync(sout, sin, (size_t)count * sizeof(MtState), hipMemcpyDeviceToDevice, st);
-      if (e != hipSuccess) return e;
-    }
-    return launch_mt_generate((MtState*)sout, count, n, dtype, out, st);
-  }
-  return launch_gm_generate(c->T, gen, (const GmState*)sin, (GmState*)sout, count, n, dtype, out, st);
+  if (gen == PRAND_MT19937) return launch_mt_generate((MtState*)states, count, n, dtype, out, st);
+  return launch_gm_generate(c->T, gen, (GmState*)states, count, n, dtype, out, st);
 }
 
 // distances of the section starts: j * seclen for the bulk sections j < nb,
@@ -326,11 +319,6 @@ int on_host_state(prand_ctx* c, int gen, void* h_state, F&& launch) {
   return PRAND_OK;
 }
 
-// outputs of one GM19/GM61 stream from which its 4096-output sections fill the
-// chip with ballot wavefronts (two sections each); 6.7 * 10^7 GM61 outputs
-// take 850 us either way, 4.2 * 10^7 735 by the ballot and 560 by gmx
-constexpr uint64_t kBallotSingle = 4096ull * 16384;
-
 }  // namespace
 
 int prand::ensure_mt_tables(prand_ctx* c) {
@@ -338,26 +326,28 @@ int prand::ensure_mt_tables(prand_ctx* c) {
   return ensure_mt_locked(c, PRAND_MT19937);
 }
 
-// The sectioned fill behind prand_generate and prand_generate_noalloc.
-// Bulk sections of 2^k outputs cover [0, T); each starts from the state
-// jumped j * 2^k ahead (one ladder application per set bit of j) and fills
-// its slice.  A final section covers [T, n) and leaves the advanced state.
-// For MT19937, T is the last twist-block boundary of the original stream
-// before n: a jump yields the canonical window, which differs from the array
-// sequential generation holds only in bits the next twist overwrites, so the
-// final section's state is exactly the sequential one.  The section states,
-// their distances and the copied-in base state live in `scratch` when it is
-// given (the plan then uses at most as many sections as fit in
-// scratch_bytes; the output does not depend on the plan), else in the
-// context's buffers.  Arguments are checked by the caller; MT19937 tables must
-// exist.
+// The fill behind prand_generate and prand_generate_noalloc, cut into sections
+// that jump to their starts.
 //
-// That plan of several launches is for MT19937 calls of more than one section
-// and for the GM19/GM61 calls long enough for the ballot kernel.  The others
-// are one launch whose lanes or wavefronts jump to their sections by
+// MRG32K3A, LFSR113 and GM/GQ: one launch whose lanes or wavefronts jump by
 // themselves (a state of 24 or 16 bytes by value, GM/GQ from the pinned slot
-// while few wavefronts read it, else from a device copy).  States come and go
-// through pinned memory that kernels read and write: no copy calls.
+// while few wavefronts read it, else from a device copy), the last of which
+// leaves the advanced state.
+//
+// MT19937: one workgroup while one section is enough.  Otherwise bulk sections
+// of 2^k outputs cover [0, T); each starts from the state jumped j * 2^k ahead
+// (one ladder application per set bit of j) and fills its slice.  A final
+// section covers [T, n) and leaves the advanced state.  T is the last
+// twist-block boundary of the original stream before n: a jump yields the
+// canonical window, which differs from the array sequential generation holds
+// only in bits the next twist overwrites, so the final section's state is
+// exactly the sequential one.  The section states, their distances and the
+// copied-in base state live in `scratch` when it is given (the plan then uses
+// at most as many sections as fit in scratch_bytes; the output does not depend
+// on the plan), else in the context's buffers.
+//
+// States come and go through pinned memory that kernels read and write: no
+// copy calls.  Arguments are checked by the caller; MT19937 tables must exist.
 int prand::generate_host_state(prand_ctx* c, int gen, void* h_state, int dtype, void* d_out, uint64_t n,
                                hipStream_t st, void* scratch, size_t scratch_bytes) {
   const size_t sb = state_bytes(gen);
@@ -390,8 +380,7 @@ int prand::generate_host_state(prand_ctx* c, int gen, void* h_state, int dtype, 
   // the base state's device copy (without `scratch`: the host calls' scratch)
   void* const d_base = scratch ? scratch : c->scratch;
   const uint32_t words = (uint32_t)(sb / 4);
-  const bool ballot = (gen == PRAND_GM19 || gen == PRAND_GM61) && n >= kBallotSingle;
-  if (gen != PRAND_MT19937 && !ballot) {
+  if (gen != PRAND_MT19937) {
     const void* base = pin_in;
     if (gm_single_wavefronts(gen, n) > 16) {
       hipLaunchKernelGGL(copy_state_kernel, dim3(1), dim3(256), 0, st, (uint32_t*)d_base, (const uint32_t*)pin_in, words);
@@ -401,35 +390,21 @@ int prand::generate_host_state(prand_ctx* c, int gen, void* h_state, int dtype, 
     if (e == hipSuccess) e = launch_gm_single(c->T, gen, (const GmState*)base, (GmState*)pin_out, n, dtype, d_out, st);
     return finish();
   }
-  uint64_t min_sec, max_secs;
-  switch (gen) {
-    case PRAND_MT19937: min_sec = 1ull << 18; max_secs = 4096; break;
-    default: min_sec = 4096; max_secs = 1u << 16; break;
-  }
+  uint64_t max_secs = 4096;
   if (scratch) {
     const uint64_t fit = (scratch_bytes - base_bytes - 2 * 256) / (sb + 8);   // section states that fit
     max_secs = std::min<uint64_t>(max_secs, fit - 1);
   }
-  int k = 0;
-  while ((1ull << k) < min_sec) k++;
+  int k = 18;
   while (((n + (1ull << k) - 1) >> k) > max_secs) k++;
-  const bool one = (1ull << k) >= n;
-  if (one && gen == PRAND_MT19937) {
-    // one wavefront, in place in the pinned slot
+  if ((1ull << k) >= n) {
+    // in place in the pinned slot
     e = launch_mt_generate((MtState*)pin_out, 1, n, dtype, d_out, st);
     return finish();
   }
-  const uint64_t seclen = one ? n : (1ull << k);
-  uint64_t T;
-  if (one) {
-    T = 0;
-  } else if (gen == PRAND_MT19937) {
-    const uint32_t idx0 = std::min<uint32_t>(((const MtState*)h_state)->idx, 624u);
-    const uint64_t r0 = 624 - idx0;
-    T = (n <= r0) ? 0 : r0 + 624 * ((n - r0 + 623) / 624 - 1);
-  } else {
-    T = ((n + seclen - 1) / seclen - 1) * seclen;
-  }
+  const uint64_t seclen = 1ull << k;
+  const uint64_t r0 = 624 - std::min<uint32_t>(((const MtState*)h_state)->idx, 624u);
+  const uint64_t T = (n <= r0) ? 0 : r0 + 624 * ((n - r0 + 623) / 624 - 1);
   const uint64_t full = T / seclen, part = T % seclen;
   const uint64_t nb = full + (part ? 1 : 0);   // bulk sections
   const uint64_t nst = nb + 1;                 // plus the final one
@@ -467,16 +442,15 @@ int prand::generate_host_state(prand_ctx* c, int gen, void* h_state, int dtype, 
   js.dist = d_dist;
   js.nlimbs = 1;
   js.per_stream = 1;
-  if (e == hipSuccess) e = launch_jump(c, gen, d_states, (uint32_t)nst, js, d_base, st);
+  if (e == hipSuccess) e = launch_mt_jump(c->T, (MtState*)d_states, (uint32_t)nst, js, (const MtState*)d_base, st);
   if (e == hipSuccess && full)
-    e = launch_streams(c, gen, d_states, d_states, (uint32_t)full, seclen, dtype, d_out, st, !scratch);
+    e = launch_mt_generate((MtState*)d_states, (uint32_t)full, seclen, dtype, d_out, st);
   if (e == hipSuccess && part) {
-    void* sp = (char*)d_states + full * sb;
-    e = launch_streams(c, gen, sp, sp, 1, part, dtype, (char*)d_out + full * seclen * es, st, !scratch);
+    MtState* sp = (MtState*)d_states + full;
+    e = launch_mt_generate(sp, 1, part, dtype, (char*)d_out + full * seclen * es, st);
   }
-  void* last = (char*)d_states + nb * sb;
-  if (e == hipSuccess)
-    e = launch_streams(c, gen, last, last, 1, n - T, dtype, (char*)d_out + T * es, st, !scratch);
+  MtState* last = (MtState*)d_states + nb;
+  if (e == hipSuccess) e = launch_mt_generate(last, 1, n - T, dtype, (char*)d_out + T * es, st);
   if (e == hipSuccess) {
     hipLaunchKernelGGL(copy_state_kernel, dim3(1), dim3(256), 0, st, (uint32_t*)pin_out, (const uint32_t*)last, words);
     e = hipGetLastError();
@@ -807,7 +781,7 @@ int prand_generate_streams(prand_ctx* c, int gen, void* d_states, uint32_t count
   if (n > (1ull << 40) || (unsigned __int128)count * n * elem_bytes(dtype) > ((unsigned __int128)1 << 50))
     return PRAND_ERANGE;
   DeviceGuard g(c->device);
-  hipError_t e = launch_streams(c, gen, d_states, d_states, count, n, dtype, d_out, (hipStream_t)stream, true);
+  hipError_t e = launch_streams(c, gen, d_states, count, n, dtype, d_out, (hipStream_t)stream);
   return e == hipSuccess ? PRAND_OK : hipfail(c, e);
 }
 

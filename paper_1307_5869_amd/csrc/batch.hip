@@ -65,12 +65,12 @@ double per_output_cost(int gen) {
     case PRAND_MT19937: return 1;
     case PRAND_MRG32K3A: return 32;
     case PRAND_LFSR113: return 27;
-    case PRAND_GM19: return 4;
-    case PRAND_GM61: return 12.3;
-    case PRAND_GM55: return 12.2;
-    case PRAND_GQ58X3: return 6.6;
-    case PRAND_GQ58X4: return 6.6;
-    default: return 5.4;   // GM29, GM31, GQ58.1
+    case PRAND_GM19: return 3.3;
+    case PRAND_GM61: return 8.9;
+    case PRAND_GM55: return 9;
+    case PRAND_GQ58X3: return 6.4;
+    case PRAND_GQ58X4: return 6.2;
+    default: return 4.9;   // GM29, GM31, GQ58.1
   }
 }
 
@@ -80,13 +80,12 @@ uint32_t gm_groups(int gen) {
 }
 
 // whole-chip time per output of the plain many-stream kernels (ms per 2^30
-// outputs, 65536 streams, MI355X; u32 and f32 alike, then f64; GM19 and GM61
-// by the matrix form the tiles run): the work a class of tiles holds, from
-// which the side-by-side launch sizes its share
+// outputs, 65536 streams, MI355X; u32 and f32 alike, then f64): the work of a
+// list's tiles, from which the side-by-side launch sizes its share
 double chip_cost(int gen, int dtype) {
   static const double t[PRAND_NUM_GENERATORS][2] = {
-      {0.89, 1.77}, {0.94, 1.59}, {0.84, 1.61}, {4.0, 4.0}, {5.4, 5.4}, {5.4, 5.4},
-      {3.05, 3.1}, {12.3, 12.3}, {5.4, 5.4}, {3.3, 3.4}, {1.65, 2.0}};
+      {0.89, 1.77}, {0.94, 1.59}, {0.84, 1.61}, {3.3, 3.3}, {4.9, 4.9}, {5.0, 5.0},
+      {2.25, 2.4}, {8.9, 8.9}, {4.9, 4.9}, {3.2, 3.6}, {1.55, 1.9}};
   return t[gen][dtype == PRAND_F64 ? 1 : 0];
 }
 

@@ -6,9 +6,9 @@
 // per 8 steps).
 //
 // This header holds the per-generator arithmetic, the jumps, and the v = 1
-// ensembles' (s = 32) wavefront routine: one lane per element, half a
-// wavefront per stream, one ballot per step packs a word.  The v >= 3
-// ensembles (GM55, GQ58.3, GQ58.4) run one lane per section (dev_gmlane.h).
+// ensembles' (s = 32) wavefront routine for short runs: one lane per element,
+// half a wavefront per stream, one ballot per step packs a word.  Longer runs
+// and the other ensembles: dev_gmx.h.
 //
 // Arithmetic is exact: special-form reductions (2^19-1, 2^29-3, 2^61-1,
 // 2^51-129) in integers.  For g = p 2^t (GM55: t = 4, GQ58: t = 29) the even
@@ -145,17 +145,13 @@ struct Eng<4> {
   __device__ static bool digit(F z) { return ((uint32_t)(z >> 32) >= (1u << 28)) & (z < g); }
 };
 
-// GM55: g = 2^4 p, p = 2^51 - 129, k = 256, q = 176, v = 4.  After the
-// collapse the kernels keep y = x / 16 (mod p) in [0, p + 78560]:
-// s = (zc << 8) + 176 (2p - zp) < 609 p < 2^61 folded once with 2^51 = 129
-// (mod p) is at most p + 78431
+// GM55: g = 2^4 p, p = 2^51 - 129, k = 256, q = 176, v = 4: the exact steps
 template <>
 struct Eng<3> {
   static constexpr bool kComposite = true;
   static constexpr int t = 4, v = 4;
   static constexpr uint64_t p = 2251799813685119ull;
   static constexpr uint64_t g = p << 4;
-  using F = uint64_t;
   __device__ static uint64_t modp_fold(uint64_t h) {   // h < 2^60
     h = (h & ((1ull << 51) - 1)) + 129ull * (h >> 51);
     return h >= p ? h - p : h;
@@ -169,21 +165,9 @@ struct Eng<3> {
     const uint64_t d0 = x >> 51;
     return (uint32_t)(d0 + ((d0 + 1) * p <= x));
   }
-  __device__ static F to_fast(uint64_t x) { return x >> 4; }
-  __device__ static uint64_t from_fast(F z) { return (z >= p ? z - p : z) << 4; }
-  __device__ static F step(F zc, F zp) {
-    const uint64_t s = (zc << 8) + 176ull * (2 * p - zp);
-    return (s & ((1ull << 51) - 1)) + 129ull * (s >> 51);
-  }
-  // floor(16 y / p); a value z in [p, p + 78560] stands for z - p < p / 16
-  // (digit 0) and gives 16 here, which the 4-bit mask drops
-  __device__ static uint32_t digit(F z) {
-    const uint64_t num = z << 4, d0 = num >> 51;
-    return (uint32_t)(d0 + ((d0 + 1) * p <= num)) & 15u;
-  }
 };
 
-// GQ58.x: g = 2^29 p, p = 2^29 - 3, k = 8, q = 48, v = 1, 3, 4
+// GQ58.x: g = 2^29 p, p = 2^29 - 3, k = 8, q = 48, v = 1, 3, 4: the exact steps
 template <int V>
 struct EngGQ {
   static constexpr bool kComposite = true;
@@ -202,32 +186,6 @@ struct EngGQ {
     const uint64_t num = (x << V) >> 29, d0 = num >> 29;
     return (uint32_t)(d0 + ((d0 + 1) * p <= num));
   }
-  // fast recurrence on y = x / 2^29 mod p, stored as z = y - 37 (mod p) in
-  // [0, p + 166]: u = zc + 6 ((p + 11184779) - zp) < 2^32 (41 * 37 + 48 *
-  // 11184779 = p makes the constant cancel the offset) and 8 u = 3 floor(u /
-  // 2^26) + 8 (u mod 2^26) (mod p) is at most p + 163
-  using F = uint32_t;
-  static constexpr uint32_t kP = 536870909u, kM = 0x1FFFFFFFu;
-  static constexpr uint32_t kD = 37u, kE = 11184779u;
-  __device__ static F to_fast(uint64_t x) {
-    const uint32_t y = (uint32_t)(x >> 29);
-    return y >= kD ? y - kD : y + (kP - kD);
-  }
-  __device__ static uint64_t from_fast(F z) { return ((uint64_t)(z + kD >= kP ? z + kD - kP : z + kD)) << 29; }
-  __device__ static F step(F zc, F zp) {
-    const uint32_t u = zc + 6u * pin((kP + kE) - zp);
-    return ((u << 3) & kM) + __umul24(3u, u >> 26);
-  }
-  // floor(2^v y / p) with y = z + 37: with d0 = floor(2^v y / 2^29),
-  // 2^v y - d0 p < 2 p, so the digit is floor((2^v y + 3 d0 + 3) / 2^29) =
-  // floor((y + floor((3 d0 + 3) / 2^v)) / 2^(29-v)); d0 may be taken from z
-  // instead of y (checked for every z in the range).  z + 37 in [p, p + 203]
-  // stands for a value below p / 2^v (digit 0) and gives 2^v, which the
-  // v-bit field drops.
-  __device__ static uint32_t digit(F z) {
-    const uint32_t d0 = z >> (29 - V);
-    return ((z + ((__umul24(3u, d0) + (3u + (kD << V))) >> V)) >> (29 - V)) & ((1u << V) - 1u);
-  }
 };
 
 // GQ58.1 after the collapse: z in [0, p + 184], z = y + 240 (mod p).
@@ -236,7 +194,8 @@ struct EngGQ {
 // adds 48 * 205 = 41 * 240 = 41 c
 template <>
 struct Eng<5> : EngGQ<1> {
-  static constexpr uint32_t kC = 240u;
+  using F = uint32_t;
+  static constexpr uint32_t kP = 536870909u, kM = 0x1FFFFFFFu, kC = 240u;
   __device__ static F to_fast(uint64_t x) {
     const uint32_t z = (uint32_t)(x >> 29) + kC;
     return z >= kP ? z - kP : z;
@@ -530,18 +489,19 @@ __device__ __forceinline__ uint32_t load_at(const GmState* in, int e, uint64_t s
 }
 
 // ---------------------------------------------- v = 1, s = 32: ballots
-// Each half-wavefront is one section: element e = 31 - (lane & 31) of state
-// *in moved `start` outputs ahead, n outputs to out, advanced state to *sout
-// (none when sout is null).
-// n must be the same for both halves (the ballot spans the wavefront); a dead
-// half (live = false) follows along without loads or stores.
-template <int G, int DT, bool kJump = true>
-__device__ __forceinline__ void gen32_wave(bool live, const GmState* in, uint64_t start, uint64_t n, void* out,
-                                           GmState* sout, const uint64_t* __restrict__ ladder) {
+// Each half-wavefront is one stream: element e = 31 - (lane & 31) of *state, n
+// outputs to out, the state advanced.  n must be the same for both halves (the
+// ballot spans the wavefront); a dead half (live = false) follows along without
+// loads or stores.
+template <int G, int DT>
+__device__ __forceinline__ void gen32_wave(bool live, GmState* state, uint64_t n, void* out) {
   const int li = threadIdx.x & 31;        // bit position of this element's digit
   const int e = 31 - li;                  // element index
   uint64_t xc = 0, xp = 0;
-  if (live) load_at<G, kJump>(in, e, start, xc, xp, ladder);
+  if (live) {
+    xc = state->xc[e];
+    xp = state->xp[e];
+  }
   Elem<G> el;
   el.load(xc, xp);
   // the word of step u goes to lane u of each half of the wavefront: a
@@ -569,11 +529,11 @@ __device__ __forceinline__ void gen32_wave(bool live, const GmState* in, uint64_
     }
     if (live && li < m) put<DT>(out, t0 + li, keep);
   }
-  if (live && sout) {
+  if (live) {
     el.get(xc, xp);
-    sout->xc[e] = xc;
-    sout->xp[e] = xp;
-    if (li == 0) { sout->off = 0; sout->pad = 0; }
+    state->xc[e] = xc;
+    state->xp[e] = xp;
+    if (li == 0) { state->off = 0; state->pad = 0; }
   }
 }
 

@@ -3,20 +3,26 @@
 // Step n + j of an element is a fixed linear combination of its two state
 // values, x^(n+j) = alpha_j x^(n) + beta_j x^(n-1) (mod p), and its digit
 // floor(2^v x / p) is the top v bits of the fraction x^(n+j) / p.  With
-// alpha_j = sum_m a_jm 16^m (and beta_j likewise) in digits a_jm of
-// [-8, 7], the fraction is
-//    sum_m a_jm frac(16^m x^(n) / p) + the same of x^(n-1)   (mod 1),
+// alpha_j = sum_m a_jm 2^(b m) (and beta_j likewise) in b-bit digits a_jm of
+// both signs, the fraction is
+//    sum_m a_jm frac(2^(b m) x^(n) / p) + the same of x^(n-1)   (mod 1),
 // a product of a constant matrix of small integers (32 steps by digits) with
-// data of the state (digits by elements): the work of v_mfma_i32_32x32x32_i8.
+// data of the state (digits by elements): the work of
+// v_mfma_f32_32x32x16_f16, up to 8 digits of both state values.
 //
-// The fractions are cut to TB = 11 (L - 1) + 8 bits and these into L
-// positions of 11 bits (the top one 8).  One matrix instruction forms one
-// position's sum for 32 steps of 32 elements: a data chunk of 11 bits is two
-// bytes, its low 4 bits (times a) and the 7 above (times 16 a), so 8 digits
-// of both state values fill the 32 products of one instruction (two
-// instructions for the 13 and 16 digits of GM55 and GM61).  The sums chain:
-// position s + 1 starts from floor(sum_s / 2^11), and the top sum's byte 0
-// holds the digit in its top v bits.
+// The fractions are cut to TB bits and these into L positions of 11 bits.  The
+// 11 bits of a position are the f16 operand as they stand (below 2048 an f16's
+// bits are its value over 2^-24: a subnormal, or the first normal binade), the
+// digits are held times 256, so that sums are whole multiples of 2^-16.  They
+// are kept at 192 + s 2^-16, |s| < 2^22, where the f32's last bit is 2^-16:
+// every sum is exact and the low bits of the register's word are s.  The sums
+// chain: position i + 1 starts from floor(s_i / 2^11), one multiply-add that
+// rounds toward zero (the mode is set around the loop), and the top sum holds
+// the digit: in bits 8 - v .. 7 of its word, or, where the fractions need all
+// bits of the top position, in the second byte, the top position's data and
+// carry doubled (GM55: bits 8 .. 11).  GM19's four 5-bit digits leave room for
+// positions of 14 bits, each as two parts of 7 (the digit times 2 and times 256,
+// sums of 2^-23 around 1.5), and two positions are enough (bit 14).
 //
 // Exactness.  Cutting a fraction loses e in [0, 1] units of 2^-TB, so the
 // result is the true fraction (2^TB units) plus kDelta, plus at most
@@ -24,7 +30,8 @@
 // sum of its positive ones.  The true 2^v x / p is never closer than
 // 1 / p to the integer above it, so the digit is exact when P <= kDelta and
 // kDelta + N < 2^TB / (2^v p): the tables' digits are chosen for that (among
-// the representations alpha + t p), and a CPU test checks it for every step.
+// the representations alpha + t p), and a CPU test checks it for every step,
+// as it checks that no sum leaves the 2^22.
 //
 // One wavefront holds 32 elements: one stream of a v = 1 ensemble, four of 8
 // elements, two of GQ58.3 (24 rows used).  Lane e < 32 keeps x^(n) of row e,
@@ -33,19 +40,16 @@
 // with the step along the lanes, so words are stored 64 consecutive ones at a
 // time, with no LDS.
 //
-// Bound: power, then issue.  Per 1024 element steps L (or 2 L) matrix
-// instructions of 32 cycles, 16 (L - 1) carries and about 20 operations to
-// gather the digits; the matrix instructions overlap little with the carries
-// of other wavefronts, and with random operands the clock falls to 1.8 GHz
-// (2.3-2.4 GHz in the kernels this replaced).  Carries in the slow VALU class
-// (bit-field extracts), which overlap with matrix instructions when issued
-// from separate wavefronts, measured 3-8 % slower here; one chain at a time in
-// 6 or 8 wavefronts per SIMD instead of two in 5, no faster.  2^30 words
-// (65536 streams, u32), before (one lane per element and a ballot per word,
-// or one lane per section) -> now: GM29 7.35 -> 5.4 ms, GM31 7.3 -> 5.4, GQ58.1
-// 7.3 -> 5.4, GM55 3.9 -> 3.05, GQ58.3 4.2 -> 3.3, GQ58.4 2.6 -> 1.65; GM19 3.9 and
-// GM61 10.5 ms stay with the ballot form where streams fill the chip (4.0
-// and 12.3 ms here).
+// Bound: power, then issue.  Per 1024 element steps L matrix instructions of
+// 32 cycles, 16 (L - 1) carries and about 20 operations to gather the digits;
+// the matrix instructions overlap little with the carries of other wavefronts,
+// and with random operands the clock falls to 1.8 GHz (2.3-2.4 GHz in the
+// kernels this replaced).  The same by v_mfma_i32_32x32x32_i8, each 11 bits as
+// two bytes, holds half the coefficient bits per instruction: GM55 and GM61
+// then take two per position.  2^30 words (65536 streams, u32), before (one
+// lane per element and a ballot per word, or one lane per section), by i8, and
+// now: GM29 7.3, 5.3, 4.9 ms; GM31 7.3, 5.2, 5.0; GQ58.1 7.3, 5.25, 4.9; GM55 3.9, 3.1, 2.25;
+// GQ58.3 4.2, 3.3, 3.2; GQ58.4 2.6, 1.6, 1.55; GM19 4.1, 4.2, 3.3; GM61 10.5, 12.4, 8.9.
 #pragma once
 
 #include "dev_gm.h"
@@ -54,20 +58,26 @@ namespace prand {
 namespace gm {
 
 typedef int I4 __attribute__((ext_vector_type(4)));
-typedef int I16 __attribute__((ext_vector_type(16)));
+typedef float F16 __attribute__((ext_vector_type(16)));
+typedef _Float16 H2 __attribute__((ext_vector_type(2)));
+typedef _Float16 H8 __attribute__((ext_vector_type(8)));
 
 template <int G>
 struct Mx {
   static constexpr int S = kGmParams[G].s, V = kGmParams[G].v, T = kGmParams[G].t;
   static constexpr int E = kGmxShape[G].e;            // p = 2^E - C
   static constexpr uint64_t C = kGmxShape[G].c, P = kGmParams[G].p;
-  static constexpr int D = kGmxShape[G].digits, L = kGmxShape[G].positions;
-  static constexpr int NK = (D + 7) / 8;              // matrix instructions per position
-  static constexpr int TB = kGmxBits * (L - 1) + 8;   // bits of a fraction
-  static constexpr int WF = TB + 4 * (D - 1);         // bits of x / p that the digits reach
-  static constexpr int NW = (kGmxBits * (L - 1) + 8 + 32 * NK + 31) / 32 + 1;   // 32-bit words of it read
+  static constexpr int B = kGmxShape[G].bits, D = kGmxShape[G].digits, L = kGmxShape[G].positions;
+  static constexpr bool TOP = kGmxShape[G].top != 0;
+  static constexpr int W = kGmxShape[G].width;
+  static constexpr int TB = W * (L - 1) + (TOP ? W : 8);   // bits of a fraction
+  static constexpr int WF = TB + B * (D - 1);         // bits of x / p that the digits reach
+  static constexpr int NW = (WF + 31) / 32;           // 32-bit words of it
+  static constexpr int NA = B == 8 && D <= 4 ? 2 : 4;   // data words per position (the others are zero)
   static constexpr int Q = S == 32 ? 1 : (S == 8 ? 4 : 2);   // streams per wavefront
   static constexpr int kDelta = kGmxShape[G].delta;
+  // a sum s is held as kZero + s kUnit, kUnit the last bit of kZero
+  static constexpr float kUnit = gmx_factor(W, 0) * 0x1p-24f, kZero = 0x1.8p23f * kUnit;
 };
 
 // row of the 32-element tile -> stream of the wavefront and element (-1: idle
@@ -108,40 +118,42 @@ __device__ __forceinline__ void gmx_fraction(uint64_t x, uint32_t (&f)[Mx<G>::NW
   using M = Mx<G>;
 #pragma unroll
   for (int i = 0; i < M::NW; i++) f[i] = 0;
-  if constexpr (G == 4) {   // 134 bits
-    const u128 lo = ((u128)x << 73) | ((u128)x << 12) | (x >> 49);
+  if constexpr (G == 4) {
+    static_assert(G != 4 || M::WF == 130, "GM61 fraction");
+    const u128 lo = ((u128)x << 69) | ((u128)x << 8) | (x >> 53);
     f[0] = (uint32_t)lo;
     f[1] = (uint32_t)(lo >> 32);
     f[2] = (uint32_t)(lo >> 64);
     f[3] = (uint32_t)(lo >> 96);
-    f[4] = (uint32_t)(x >> 55);
-  } else if constexpr (G == 3) {   // 111 bits
-    static_assert(G != 3 || M::WF == 111, "GM55 fraction");
-    const u128 lo = ((u128)x << 60) + ((u128)(129ull * x) << 9) + (uint64_t)(((u128)x * 16641u) >> 42);
+    f[4] = (uint32_t)(x >> 59);
+  } else if constexpr (G == 3) {
+    static_assert(G != 3 || M::WF == 114, "GM55 fraction");
+    const u128 lo = ((u128)x << 63) + ((u128)(129ull * x) << 12) + (uint64_t)(((u128)x * 16641u) >> 39);
     f[0] = (uint32_t)lo;
     f[1] = (uint32_t)(lo >> 32);
     f[2] = (uint32_t)(lo >> 64);
     f[3] = (uint32_t)(lo >> 96);
-  } else if constexpr (G == 0) {   // 46 bits
-    static_assert(G != 0 || M::WF == 46, "GM19 fraction");
-    const uint64_t lo = (x << 27) | (x << 8) | (x >> 11);
+  } else if constexpr (G == 0) {
+    static_assert(G != 0 || M::WF == 43, "GM19 fraction");
+    const uint64_t lo = (x << 24) | (x << 5) | (x >> 14);
     f[0] = (uint32_t)lo;
     f[1] = (uint32_t)(lo >> 32);
-  } else if constexpr (G == 2) {   // 69 bits
+  } else if constexpr (G == 2) {
     static_assert(G != 2 || M::WF == 69, "GM31 fraction");
     const uint32_t v = (uint32_t)x;
     f[0] = (v << 7) | (v >> 24);
     f[1] = (v << 6) | (v >> 25);
     f[2] = v >> 26;
-  } else {   // p = 2^29 - 3, 69 bits
-    static_assert(!(G == 1 || G >= 5) || M::WF == 69, "2^29 - 3 fraction");
-    const uint64_t lo = (x << 40) + ((3 * x) << 11) + ((9 * x) >> 18);
+  } else {   // p = 2^29 - 3
+    constexpr int sh = M::WF - 29;
+    static_assert(!(G == 1 || G >= 5) || (sh >= 35 && sh <= 40), "2^29 - 3 fraction");
+    const uint64_t lo = (x << sh) + ((3 * x) << (sh - 29)) + ((9 * x) >> (58 - sh));
     f[0] = (uint32_t)lo;
     f[1] = (uint32_t)(lo >> 32);
-    f[2] = (uint32_t)(x >> 24);
-    // (x << 40) drops the bits above 64 into f[2]; the two smaller terms
+    f[2] = (uint32_t)(x >> (64 - sh));
+    // (x << sh) drops the bits above 64 into f[2]; the two smaller terms
     // may carry into it
-    f[2] += (lo < (x << 40)) ? 1u : 0u;
+    f[2] += (lo < (x << sh)) ? 1u : 0u;
   }
 }
 
@@ -153,52 +165,57 @@ __device__ __forceinline__ uint32_t gmx_bits(const uint32_t (&f)[N], int at) {
   return b ? __builtin_amdgcn_alignbit(hi, lo, b) : lo;
 }
 
-// the data operands of a state value: position s, digits 8 k .. 8 k + 7
-// counted from the least fraction (nibble i of the word at bit 11 s + 32 k):
-// bytes [low 4 bits of even i][of odd i][7 bits above, even i][odd i]
+// the data operands of a state value: position s; word w holds the 11 bits
+// from 11 s + b gmx_below(2 w), and those 16 bits above; or the 7 bits from
+// 14 s + b gmx_below(2 w) and the 7 above
 template <int G>
-__device__ __forceinline__ void gmx_operands(uint64_t x, I4 (&A)[Mx<G>::L][Mx<G>::NK]) {
+__device__ __forceinline__ void gmx_operands(uint64_t x, I4 (&A)[Mx<G>::L]) {
   using M = Mx<G>;
   uint32_t f[M::NW];
   gmx_fraction<G>(x, f);
 #pragma unroll
   for (int s = 0; s < M::L; s++) {
 #pragma unroll
-    for (int k = 0; k < M::NK; k++) {
-      const int at = kGmxBits * s + 32 * k;
-      const uint32_t g0 = gmx_bits(f, at), g4 = gmx_bits(f, at + 4), g8 = gmx_bits(f, at + 8);
-      A[s][k][0] = (int)(g0 & 0x0F0F0F0Fu);
-      A[s][k][1] = (int)(g4 & 0x0F0F0F0Fu);
-      A[s][k][2] = (int)(g4 & 0x7F7F7F7Fu);
-      A[s][k][3] = (int)(g8 & 0x7F7F7F7Fu);
+    for (int w = 0; w < 4; w++) {
+      uint32_t v = 0;
+      if (w < M::NA) v = gmx_bits(f, M::W * s + M::B * gmx_below(M::B, 2 * w));
+      v = M::W == 11 ? v & 0x07FF07FFu : (v & 0x7Fu) | ((v << 9) & 0x7F0000u);
+      if (M::TOP && s == M::L - 1) {
+        const H2 h = __builtin_bit_cast(H2, v);
+        v = __builtin_bit_cast(uint32_t, (H2)(h + h));
+      }
+      A[s][w] = (int)v;
     }
   }
 }
 
-// top sums of 32 steps (coefficients B) for the wavefront's rows
+// top sums of 32 steps (coefficients B) for the wavefront's rows; c: the
+// offset in every element; rounding toward zero
 template <int G>
-__device__ __forceinline__ I16 gmx_chain(const I4 (&A)[Mx<G>::L][Mx<G>::NK], const I4 (&B)[Mx<G>::NK]) {
+__device__ __forceinline__ F16 gmx_chain(const I4 (&A)[Mx<G>::L], const I4& B, F16 c) {
   using M = Mx<G>;
-  I16 c;
-#pragma unroll
-  for (int i = 0; i < 16; i++) c[i] = M::kDelta;
 #pragma unroll
   for (int s = 0; s < M::L; s++) {
     if (s) {
+      const float scale = 1.0f / (1 << (M::W - (M::TOP && s == M::L - 1 ? 1 : 0)));
 #pragma unroll
-      for (int i = 0; i < 16; i++) c[i] >>= kGmxBits;
+      for (int i = 0; i < 16; i++) c[i] = __builtin_fmaf(c[i], scale, M::kZero - M::kZero * scale);
     }
-#pragma unroll
-    for (int k = 0; k < M::NK; k++) c = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[s][k], B[k], c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(H8, A[s]), __builtin_bit_cast(H8, B), c, 0, 0, 0);
   }
   return c;
 }
 
-// byte 0 of registers 4 t .. 4 t + 3 as the four bytes of a word
-__device__ __forceinline__ uint32_t gmx_bytes(const I16& c, int t) {
-  const uint32_t lo = __builtin_amdgcn_perm((uint32_t)c[4 * t + 1], (uint32_t)c[4 * t], 0x0c0c0400u);
-  return __builtin_amdgcn_perm((uint32_t)c[4 * t + 3], __builtin_amdgcn_perm((uint32_t)c[4 * t + 2], lo, 0x0c040100u),
-                               0x04020100u);
+// the digits' bytes of registers 4 t .. 4 t + 3 as the four bytes of a word
+// (byte 0, the digit on top; or byte 1, GM55's digit in its lower half, GM19's
+// in bit 6)
+template <int G>
+__device__ __forceinline__ uint32_t gmx_bytes(const F16& c, int t) {
+  constexpr uint32_t byte = Mx<G>::TOP ? 1 : 0;
+  auto word = [&](int i) { return __float_as_uint(c[4 * t + i]); };
+  uint32_t r = __builtin_amdgcn_perm(word(1), word(0), 0x0c0c0400u + 0x0101u * byte);
+  r = __builtin_amdgcn_perm(word(2), r, 0x0c040100u + 0x010000u * byte);
+  return __builtin_amdgcn_perm(word(3), r, 0x04020100u + 0x01000000u * byte);
 }
 __device__ __forceinline__ uint32_t gmx_select(uint32_t a, uint32_t b, uint32_t mask) {
   return __builtin_amdgcn_bitop3_b32(a, b, mask, 0xE4);   // (a & mask) | (b & ~mask)
@@ -218,6 +235,14 @@ __device__ __forceinline__ void gmx_both(uint64_t x, uint64_t& lower, uint64_t& 
   const Swapped lo = gmx_swap((uint32_t)x, (uint32_t)x), hi = gmx_swap((uint32_t)(x >> 32), (uint32_t)(x >> 32));
   lower = ((uint64_t)hi.a << 32) | lo.a;
   upper = ((uint64_t)hi.b << 32) | lo.b;
+}
+
+// f32 rounding toward zero, or to nearest again (bits 1:0 of the mode
+// register; everything else this code rounds is exact in either mode)
+template <bool kZero>
+__device__ __forceinline__ void gmx_round() {
+  constexpr int kModeBits1to0 = 1 | 0 << 6 | (2 - 1) << 11;
+  __builtin_amdgcn_s_setreg(kModeBits1to0, kZero ? 3 : 0);
 }
 
 // one stream or section of a wavefront (uniform across it): n outputs from
@@ -365,38 +390,42 @@ __device__ __forceinline__ void gmx_wave(SecOf&& sec, const GmxTable* __restrict
   const uint64_t* const mats = table->mat;
   const I4* const coef = (const I4*)table->coef + lane;
   uint64_t mj0 = mats[4 * J + (upper ? 2 : 0)], mj1 = mats[4 * J + (upper ? 3 : 1)];
+  F16 offset;
+#pragma unroll
+  for (int i = 0; i < 16; i++) offset[i] = M::kZero + M::kDelta * M::kUnit;
+  // v = 1: kept in registers of its own, not made again for every chain (1-3 %)
+  if constexpr (M::S == 32) asm volatile("" : "+v"(offset));
+  gmx_round<true>();
   for (; t < need; t += J) {
-    I4 A[M::L][M::NK];
+    I4 A[M::L];
     gmx_operands<G>(x, A);
 #pragma unroll 1
     for (int g = 0; g < J / 32 && t + 32 * g < need; g += 2) {
-      I4 B0[M::NK], B1[M::NK];
-#pragma unroll
-      for (int k = 0; k < M::NK; k++) {
-        B0[k] = coef[64 * (g * M::NK + k)];
-        B1[k] = coef[64 * ((g + 1) * M::NK + k)];
-      }
+      const I4 B[2] = {coef[64 * g], coef[64 * (g + 1)]};
       // lane: step t + 32 g + lane
       if constexpr (M::S == 32) {
         uint32_t w[2];
 #pragma unroll
         for (int i = 0; i < 2; i++) {
-          const I16 c = gmx_chain<G>(A, i ? B1 : B0);
-          uint32_t v = gmx_bytes(c, 3);
-          v = gmx_select(gmx_bytes(c, 2), v >> 1, 0x80808080u);
-          v = gmx_select(gmx_bytes(c, 1), v >> 1, 0x80808080u);
-          w[i] = gmx_select(gmx_bytes(c, 0), v >> 1, 0x80808080u);
+          const F16 c = gmx_chain<G>(A, B[i], offset);
+          constexpr uint32_t digit = M::TOP ? 0x40404040u : 0x80808080u;
+          uint32_t v = gmx_bytes<G>(c, 3);
+          v = gmx_select(gmx_bytes<G>(c, 2), v >> 1, digit);
+          v = gmx_select(gmx_bytes<G>(c, 1), v >> 1, digit);
+          w[i] = gmx_select(gmx_bytes<G>(c, 0), v >> 1, digit);
         }
         const Swapped s = gmx_swap(w[0], w[1]);
         const uint64_t i = t + 32 * g + lane;
-        if (i < total) gmx_put<DT>(mine.out, i, gmx_select(s.a, s.b >> 4, 0xF0F0F0F0u), dtype);
+        const uint32_t word =
+            M::TOP ? gmx_select(s.a << 1, s.b >> 3, 0xF0F0F0F0u) : gmx_select(s.a, s.b >> 4, 0xF0F0F0F0u);
+        if (i < total) gmx_put<DT>(mine.out, i, word, dtype);
       } else if constexpr (M::S == 8) {
         uint32_t w[2][4];
 #pragma unroll
         for (int i = 0; i < 2; i++) {
-          const I16 c = gmx_chain<G>(A, i ? B1 : B0);
+          const F16 c = gmx_chain<G>(A, B[i], offset);
 #pragma unroll
-          for (int k = 0; k < 4; k++) w[i][k] = gmx_bytes(c, k);
+          for (int k = 0; k < 4; k++) w[i][k] = gmx_bytes<G>(c, k);
         }
         uint64_t i = t + 32 * g + lane;
         // GQ58.4, and kernels of every type: no address of each stream (and
@@ -405,7 +434,7 @@ __device__ __forceinline__ void gmx_wave(SecOf&& sec, const GmxTable* __restrict
 #pragma unroll
         for (int k = 0; k < 4; k++) {
           const Swapped s = gmx_swap(w[0][k], w[1][k]);
-          w[0][k] = gmx_select(s.a, s.b >> 4, 0xF0F0F0F0u);
+          w[0][k] = M::TOP ? gmx_select(s.a << 4, s.b, 0xF0F0F0F0u) : gmx_select(s.a, s.b >> 4, 0xF0F0F0F0u);
         }
         if (DT != kAnyType || dtype != PRAND_F64) {
 #pragma unroll
@@ -424,10 +453,10 @@ __device__ __forceinline__ void gmx_wave(SecOf&& sec, const GmxTable* __restrict
         uint32_t w[2][2];
 #pragma unroll
         for (int i = 0; i < 2; i++) {
-          const I16 c = gmx_chain<G>(A, i ? B1 : B0);
+          const F16 c = gmx_chain<G>(A, B[i], offset);
 #pragma unroll
           for (int k = 0; k < 2; k++)
-            w[i][k] = (gmx_pack3(gmx_bytes(c, 2 * k)) << 12) | gmx_pack3(gmx_bytes(c, 2 * k + 1));
+            w[i][k] = (gmx_pack3(gmx_bytes<G>(c, 2 * k)) << 12) | gmx_pack3(gmx_bytes<G>(c, 2 * k + 1));
         }
 #pragma unroll
         for (int k = 0; k < 2; k++) {
@@ -460,6 +489,7 @@ __device__ __forceinline__ void gmx_wave(SecOf&& sec, const GmxTable* __restrict
     gmx_both(x, lower_x, upper_x);
     x = gmx_mulsum<G>(m0, lower_x, m1, upper_x);
   }
+  gmx_round<false>();
   if (sout && !saved) save(x << M::T);
 }
 

@@ -7,9 +7,8 @@
 //
 // Generation by matrix instructions (dev_gmx.h): a wavefront holds the 32
 // elements of one v = 1 stream, or of four 8-element or two 12-element ones;
-// GM19 and GM61 with enough streams to fill the chip keep one lane per element
-// and one ballot per word (dev_gm.h).  Few streams are cut into sections that
-// start by jumps.
+// short runs of the v = 1 ensembles keep one lane per element and one ballot
+// per word (dev_gm.h).  Few streams are cut into sections that start by jumps.
 //
 // Arithmetic is exact.  For g = p 2^t (GM55: t = 4, GQ58: t = 29) the even
 // k and q kill the 2-adic part within n0 steps; from then on x = 2^t y with y
@@ -25,15 +24,22 @@ namespace {
 
 using namespace gm;
 
-// GM19 and GM61 with enough streams to fill the chip: half a wavefront per
-// stream, one lane per element, a ballot per word (dev_gm.h)
+// Runs of a v = 1 ensemble shorter than kBallotOutputs: half a wavefront per
+// stream, one lane per element, a ballot per word (dev_gm.h).  The matrix form
+// makes the operands of 256 steps, 64 steps at a time, and moves the states by
+// a product: 65536 streams of 1, 32, 100, 128 and 192 outputs take, by ballots
+// and so, GM29 17 and 52, 29 and 52, 61 and 71, 74 and 71, 105 and 88 us; GM61 18
+// and 76, 37 and 76, 90 and 106, 106 and 103, 153 and 136.
+constexpr uint64_t kBallotOutputs = 128;
+
 template <int G, int DT>
-__global__ void __launch_bounds__(256) gm_gen32_kernel(const GmState* sin, GmState* sout, uint32_t count, uint64_t n,
+__global__ void __launch_bounds__(256) gm_gen32_kernel(GmState* states, uint32_t count, uint64_t n,
                                                        void* __restrict__ out) {
   const uint64_t s = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 5;
   const bool live = s < count;
   constexpr int es = (DT == PRAND_F64) ? 8 : 4;
-  gen32_wave<G, DT, false>(live, sin + (live ? s : 0), 0, n, (char*)out + s * n * es, sout + (live ? s : 0), nullptr);
+  GmState* state = states + (live ? s : 0);
+  gen32_wave<G, DT>(live, state, n, (char*)out + s * n * es);
 }
 
 // Many streams: a wavefront takes Mx<G>::Q consecutive (stream, section)
@@ -41,7 +47,8 @@ __global__ void __launch_bounds__(256) gm_gen32_kernel(const GmState* sin, GmSta
 // kSections: several sections per stream, which read the stream's state and
 // jump to their starts; the states are then moved on by a launch of their own
 // (sout null), or, of a single stream, the last section leaves the state in
-// *sout (another object than *sin).  Otherwise seclen = n and the states are updated in place.
+// *sout (another object than *sin).  Otherwise seclen = n and the states are
+// updated in place.
 template <int G, int DT, bool kSections>
 __global__ void __launch_bounds__(256) gmx_kernel(const GmState* sin, GmState* sout, uint32_t count, uint64_t n,
                                                   uint32_t nsec, uint64_t seclen, char* __restrict__ out,
@@ -160,24 +167,20 @@ hipError_t launch_jump_g(const DeviceTables& T, GmState* states, uint32_t count,
 constexpr uint64_t kFillWaves = 8192;
 
 template <int G, int DT>
-hipError_t launch_gen(const DeviceTables& T, const GmState* sin, GmState* sout, uint32_t count, uint64_t n, void* out,
-                      hipStream_t st) {
+hipError_t launch_gen(const DeviceTables& T, GmState* states, uint32_t count, uint64_t n, void* out, hipStream_t st) {
   constexpr uint64_t Q = Mx<G>::Q;
   constexpr uint64_t unit = G == 6 ? kGmxSteps / 8 * 9 : kGmxSteps;   // outputs of a state advance
   uint64_t seclen = 8 * unit;
-  if constexpr (G == 0 || G == 4) {
-    // half a wavefront per stream: from kFillWaves wavefronts on, or where a
-    // stream is too short to cut, the ballot form is the faster one (2^30
-    // words: GM19 3.9 against 4.0 ms, GM61 10.5 against 12.3 ms)
-    if ((uint64_t)count >= 2 * kFillWaves || n < 2 * seclen) {
+  if constexpr (Mx<G>::S == 32) {
+    if (n < kBallotOutputs) {
       const uint32_t blocks = (uint32_t)(((uint64_t)count * 32 + 255) / 256);
-      hipLaunchKernelGGL((gm_gen32_kernel<G, DT>), dim3(blocks), dim3(256), 0, st, sin, sout, count, n, out);
+      hipLaunchKernelGGL((gm_gen32_kernel<G, DT>), dim3(blocks), dim3(256), 0, st, states, count, n, out);
       return hipGetLastError();
     }
   }
-  if ((uint64_t)count >= kFillWaves * Q || n < 2 * seclen || sin != sout) {
+  if ((uint64_t)count >= kFillWaves * Q || n < 2 * seclen) {
     const uint32_t blocks = (uint32_t)(((count + Q - 1) / Q + 3) / 4);
-    hipLaunchKernelGGL((gmx_kernel<G, DT, false>), dim3(blocks), dim3(256), 0, st, sin, sout, count, n, 1u, n,
+    hipLaunchKernelGGL((gmx_kernel<G, DT, false>), dim3(blocks), dim3(256), 0, st, states, states, count, n, 1u, n,
                        (char*)out, T.gmx, T.gm);
     return hipGetLastError();
   }
@@ -186,13 +189,13 @@ hipError_t launch_gen(const DeviceTables& T, const GmState* sin, GmState* sout, 
   while ((n + seclen - 1) / seclen > (1ull << 30) / count) seclen *= 2;
   const uint32_t nsec = (uint32_t)((n + seclen - 1) / seclen);
   const uint32_t blocks = (uint32_t)((((uint64_t)count * nsec + Q - 1) / Q + 3) / 4);
-  hipLaunchKernelGGL((gmx_kernel<G, DT, true>), dim3(blocks), dim3(256), 0, st, sin, nullptr, count, n, nsec, seclen,
+  hipLaunchKernelGGL((gmx_kernel<G, DT, true>), dim3(blocks), dim3(256), 0, st, states, nullptr, count, n, nsec, seclen,
                      (char*)out, T.gmx, T.gm);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   JumpSpec js;
   js.fixed = n;
-  return launch_jump_g<G>(T, sout, count, js, nullptr, st);
+  return launch_jump_g<G>(T, states, count, js, nullptr, st);
 }
 
 // One stream: sections from one advance of the states on, so that a short
@@ -234,28 +237,28 @@ hipError_t launch_single_g(const DeviceTables& T, int dtype, const GmState* base
 }
 
 template <int G>
-hipError_t launch_gen_g(const DeviceTables& T, int dtype, const GmState* sin, GmState* sout, uint32_t count,
-                        uint64_t n, void* out, hipStream_t st) {
+hipError_t launch_gen_g(const DeviceTables& T, int dtype, GmState* states, uint32_t count, uint64_t n, void* out,
+                        hipStream_t st) {
   switch (dtype) {
-    case PRAND_U32: return launch_gen<G, PRAND_U32>(T, sin, sout, count, n, out, st);
-    case PRAND_F32: return launch_gen<G, PRAND_F32>(T, sin, sout, count, n, out, st);
-    default: return launch_gen<G, PRAND_F64>(T, sin, sout, count, n, out, st);
+    case PRAND_U32: return launch_gen<G, PRAND_U32>(T, states, count, n, out, st);
+    case PRAND_F32: return launch_gen<G, PRAND_F32>(T, states, count, n, out, st);
+    default: return launch_gen<G, PRAND_F64>(T, states, count, n, out, st);
   }
 }
 
 }  // namespace
 
-hipError_t launch_gm_generate(const DeviceTables& T, int gen, const GmState* sin, GmState* sout, uint32_t count,
-                              uint64_t n, int dtype, void* out, hipStream_t st) {
+hipError_t launch_gm_generate(const DeviceTables& T, int gen, GmState* states, uint32_t count, uint64_t n, int dtype,
+                              void* out, hipStream_t st) {
   switch (gen - PRAND_GM19) {
-    case 0: return launch_gen_g<0>(T, dtype, sin, sout, count, n, out, st);
-    case 1: return launch_gen_g<1>(T, dtype, sin, sout, count, n, out, st);
-    case 2: return launch_gen_g<2>(T, dtype, sin, sout, count, n, out, st);
-    case 3: return launch_gen_g<3>(T, dtype, sin, sout, count, n, out, st);
-    case 4: return launch_gen_g<4>(T, dtype, sin, sout, count, n, out, st);
-    case 5: return launch_gen_g<5>(T, dtype, sin, sout, count, n, out, st);
-    case 6: return launch_gen_g<6>(T, dtype, sin, sout, count, n, out, st);
-    default: return launch_gen_g<7>(T, dtype, sin, sout, count, n, out, st);
+    case 0: return launch_gen_g<0>(T, dtype, states, count, n, out, st);
+    case 1: return launch_gen_g<1>(T, dtype, states, count, n, out, st);
+    case 2: return launch_gen_g<2>(T, dtype, states, count, n, out, st);
+    case 3: return launch_gen_g<3>(T, dtype, states, count, n, out, st);
+    case 4: return launch_gen_g<4>(T, dtype, states, count, n, out, st);
+    case 5: return launch_gen_g<5>(T, dtype, states, count, n, out, st);
+    case 6: return launch_gen_g<6>(T, dtype, states, count, n, out, st);
+    default: return launch_gen_g<7>(T, dtype, states, count, n, out, st);
   }
 }
 

@@ -69,32 +69,39 @@ constexpr GmParams kGmParams[8] = {
 };
 
 // ---- GM/GQ generation by matrix instructions (dev_gmx.h) ----
-// p = 2^e - c; base-16 digits per coefficient (16^digits covers p several
-// times over), 11-bit positions of a fraction, offset of the result in
-// units of the fraction's last bit (an inline constant up to 64; the digits
-// of GM55 and GM61 lose more), carries taken in the slow VALU class per 16
+// p = 2^e - c; digits of `bits` bits per coefficient (their values cover p
+// several times over), positions of a fraction and their width (14: in two
+// parts of 7), whether the top one is doubled, offset of the result in units
+// of the fraction's last bit
 struct GmxShape {
   int e;
   uint64_t c;
-  int digits, positions, delta, slow;
+  int bits, digits, positions, width, top, delta;
 };
 constexpr GmxShape kGmxShape[8] = {
-    /* GM19   */ {19, 1, 5, 3, 64},
-    /* GM29   */ {29, 3, 8, 4, 64},
-    /* GM31   */ {31, 1, 8, 4, 64},
-    /* GM55   */ {51, 129, 13, 6, 128},
-    /* GM61   */ {61, 1, 16, 7, 128},
-    /* GQ58.1 */ {29, 3, 8, 4, 64},
-    /* GQ58.3 */ {29, 3, 8, 4, 64},
-    /* GQ58.4 */ {29, 3, 8, 4, 64},
+    /* GM19   */ {19, 1, 5, 4, 2, 14, 1, 64},
+    /* GM29   */ {29, 3, 8, 4, 4, 11, 0, 600},
+    /* GM31   */ {31, 1, 4, 8, 4, 11, 0, 64},
+    /* GM55   */ {51, 129, 8, 7, 6, 11, 1, 800},
+    /* GM61   */ {61, 1, 8, 8, 7, 11, 0, 1000},
+    /* GQ58.1 */ {29, 3, 8, 4, 4, 11, 0, 600},
+    /* GQ58.3 */ {29, 3, 4, 8, 4, 11, 0, 64},
+    /* GQ58.4 */ {29, 3, 4, 8, 4, 11, 0, 64},
 };
-constexpr int kGmxBits = 11;     // bits of a position
 constexpr int kGmxSteps = 256;   // steps per state advance
+// Product h (0 .. 7) of a state value takes the digit with this many digits
+// below it: two of 16 bits' distance share a word of the data, or the two parts
+// of one (products 2 i and 2 i + 1, the digit times 1 and 128)
+constexpr int gmx_below(int bits, int h) {
+  return bits == 8 ? (h >> 1 & 1) + 4 * (h >> 2) + 2 * (h & 1) : bits == 4 ? (h >> 1) + 4 * (h & 1) : h >> 1;
+}
+// the digits' factor in the operands (their largest is 128 * 256, or 16 * 128 * 2)
+constexpr int gmx_factor(int width, int h) { return width == 11 ? 256 : (h & 1 ? 256 : 2); }
 struct alignas(16) GmxTable {
   uint64_t mat[(kGmxSteps + 1) * 4];   // M^j mod p, j = 0 .. kGmxSteps
-  // operand of matrix instruction k (of NK = ceil(digits / 8)) for steps
-  // 32 g + 1 .. 32 g + 32: 16 bytes per lane at [(g NK + k) 64 + lane]
-  int8_t coef[(kGmxSteps / 32) * 2 * 64 * 16];
+  // matrix operands (f16, gmx_factor times the digits) for steps 32 g + 1 ..
+  // 32 g + 32: 8 per lane at [(64 g + lane) * 8]
+  uint16_t coef[(kGmxSteps / 32) * 64 * 8];
 };
 
 inline bool is_gm(int gen) { return gen >= PRAND_GM19 && gen <= PRAND_GQ58X4; }
@@ -227,8 +234,8 @@ hipError_t launch_mt_generate(MtState* states, uint32_t count, uint64_t n, int d
 hipError_t launch_mt_jump(const DeviceTables& T, MtState* states, uint32_t count, const JumpSpec& js,
                           const MtState* base, hipStream_t st);
 
-hipError_t launch_gm_generate(const DeviceTables& T, int gen, const GmState* sin, GmState* sout,
-                              uint32_t count, uint64_t n, int dtype, void* out, hipStream_t st);
+hipError_t launch_gm_generate(const DeviceTables& T, int gen, GmState* states, uint32_t count, uint64_t n, int dtype,
+                              void* out, hipStream_t st);
 hipError_t launch_gm_jump(const DeviceTables& T, int gen, GmState* states, uint32_t count, const JumpSpec& js,
                           const GmState* base, hipStream_t st);
 

@@ -270,11 +270,12 @@ void build_gm_jumps(uint64_t* out) {
 }
 
 namespace {
-// base-16 digits of v in [-8, 7], least first; false when `n` do not hold it
-bool balanced16(__int128 v, int n, int8_t* d) {
+// digits of v in [-2^(b-1), 2^(b-1)), least first; false when `n` do not hold it
+bool balanced(__int128 v, int b, int n, int* d) {
+  const int half = 1 << (b - 1);
   for (int m = 0; m < n; m++) {
-    d[m] = (int8_t)((int)((v + 8) & 15) - 8);
-    v = (v - d[m]) >> 4;
+    d[m] = (int)((v + half) & (2 * half - 1)) - half;
+    v = (v - d[m]) >> b;
   }
   return v == 0;
 }
@@ -282,32 +283,38 @@ bool balanced16(__int128 v, int n, int8_t* d) {
 // Digits of a coefficient a < p: of the representations a + t p that `n`
 // digits hold, one whose positive digits have a small sum (they lower the
 // result, see dev_gmx.h), then a small sum of magnitudes.
-void gmx_digits(uint64_t a, uint64_t p, int n, int8_t* best) {
+void gmx_digits(uint64_t a, uint64_t p, int b, int n, int* best) {
   int score = 1 << 30;
-  int8_t d[16];
-  for (int t = -9; t <= 9; t++) {
-    if (!balanced16((__int128)a + (__int128)t * p, n, d)) continue;
+  int d[8];
+  for (int t = -40; t <= 40; t++) {
+    if (!balanced((__int128)a + (__int128)t * p, b, n, d)) continue;
     int s = 0;
     for (int m = 0; m < n; m++) s += d[m] > 0 ? 3 * d[m] : -d[m];
     if (s < score) {
       score = s;
-      std::memcpy(best, d, n);
+      std::memcpy(best, d, n * sizeof *d);
     }
   }
+}
+
+// v as f16: |v| < 65536, at most 11 significant bits
+uint16_t gmx_half(int v) {
+  if (!v) return 0;
+  const uint32_t m = (uint32_t)(v < 0 ? -v : v);
+  const int top = 31 - __builtin_clz(m);   // m in [2^top, 2^(top + 1))
+  const uint32_t frac = top > 10 ? m >> (top - 10) : m << (10 - top);
+  return (uint16_t)((v < 0 ? 0x8000u : 0u) | (uint32_t)(top + 15) << 10 | (frac & 0x3FFu));
 }
 }  // namespace
 
 // Powers M^j and the coefficient operands of the matrix instructions: lane l
 // holds column l % 32 (step 32 g + l % 32 + 1) of the digits of alpha (lanes
-// 0..31, products 0..15) or beta (lanes 32..63, products 16..31); digit m is
-// data nibble i = digits - 1 - m, and a lane's 16 bytes are a_i for even i,
-// odd i (the data's low 4 bits), then 16 a_i for even i, odd i (the 7 bits
-// above), i = 8 k .. 8 k + 7.
+// 0..31, products 0..7) or beta (lanes 32..63, products 8..15).
 void build_gmx_tables(GmxTable* out) {
   for (int g = 0; g < 8; g++) {
     const GmParams& P = kGmParams[g];
     const uint64_t p = P.p;
-    const int n = kGmxShape[g].digits, nk = (n + 7) / 8;
+    const int n = kGmxShape[g].digits, b = kGmxShape[g].bits;
     GmxTable& T = out[g];
     std::memset(T.coef, 0, sizeof T.coef);
     const Mat2 m{P.k % p, (p - P.q % p) % p, 1, 0};
@@ -316,14 +323,12 @@ void build_gmx_tables(GmxTable* out) {
       const uint64_t row[4] = {r.a, r.b, r.c, r.d};
       std::memcpy(T.mat + 4 * j, row, sizeof row);
       for (int h = 0; j && h < 2; h++) {
-        int8_t d[16] = {0};
-        gmx_digits(h ? r.b : r.a, p, n, d);
-        const int blk = (j - 1) / 32, lane = (j - 1) % 32 + 32 * h;
-        for (int i = 0; i < n; i++) {
-          int8_t* o = T.coef + (((size_t)blk * nk + i / 8) * 64 + lane) * 16 + 4 * (i & 1) + (i % 8) / 2;
-          o[0] = d[n - 1 - i];
-          o[8] = (int8_t)(16 * d[n - 1 - i]);
-        }
+        int d[8] = {0};
+        gmx_digits(h ? r.b : r.a, p, b, n, d);
+        uint16_t* o = T.coef + ((size_t)(j - 1) / 32 * 64 + (j - 1) % 32 + 32 * h) * 8;
+        for (int i = 0; i < 8; i++)
+          if (gmx_below(b, i) < n)
+            o[i] = gmx_half(d[n - 1 - gmx_below(b, i)] * gmx_factor(kGmxShape[g].width, i));
       }
       r = mat2_mul(m, r, p);
     }
@@ -335,10 +340,11 @@ void build_gmx_tables(GmxTable* out) {
 // Not in the public header (a test hook): the table of one GM/GQ generator
 // (index 0 GM19 .. 7 GQ58.4): the powers M^j, and the digits of step j =
 // 1 .. kGmxSteps read back from the operands, digits[2 (j - 1) + h][m] (h = 0:
-// of x^(n), 1: of x^(n-1); 16 digits, least first).  dims: steps, digits,
-// positions, bits of a position, offset.  0 on success; -1 when the operands'
-// two copies of a digit disagree.
-extern "C" int prand_internal_gmx_table(int g, uint64_t* mat, int8_t* digits, int* dims) {
+// of x^(n), 1: of x^(n-1); 8 digits, least first).  dims: steps, digits,
+// positions, bits of a position, offset, bits of a digit, doubled top.  0 on
+// success; -1 when a product without a digit has a coefficient, or a digit's two
+// parts differ.
+extern "C" int prand_internal_gmx_table(int g, uint64_t* mat, int16_t* digits, int* dims) {
   if (g < 0 || g >= 8 || !mat || !digits || !dims) return PRAND_EINVAL;
   std::vector<prand::GmxTable> t(8);
   prand::build_gmx_tables(t.data());
@@ -347,19 +353,27 @@ extern "C" int prand_internal_gmx_table(int g, uint64_t* mat, int8_t* digits, in
   dims[0] = prand::kGmxSteps;
   dims[1] = S.digits;
   dims[2] = S.positions;
-  dims[3] = prand::kGmxBits;
+  dims[3] = S.width;
   dims[4] = S.delta;
-  const int nk = (S.digits + 7) / 8;
+  dims[5] = S.bits;
+  dims[6] = S.top;
   for (int j = 0; j < prand::kGmxSteps; j++)
-    for (int h = 0; h < 2; h++)
-      for (int m = 0; m < 16; m++) {
-        int8_t& d = digits[(2 * j + h) * 16 + m];
-        d = 0;
-        if (m >= S.digits) continue;
-        const int i = S.digits - 1 - m;
-        const int8_t* o = t[g].coef + (((size_t)(j / 32) * nk + i / 8) * 64 + j % 32 + 32 * h) * 16 + 4 * (i & 1) + (i % 8) / 2;
-        d = o[0];
-        if (o[8] != 16 * o[0]) return -1;
+    for (int h = 0; h < 2; h++) {
+      int16_t* d = digits + (2 * j + h) * 8;
+      std::memset(d, 0, 8 * sizeof *d);
+      const uint16_t* o = t[g].coef + ((size_t)(j / 32) * 64 + j % 32 + 32 * h) * 8;
+      for (int i = 0; i < 8; i++) {
+        // the f16 value, an integer, over the factor
+        const int exp = (o[i] >> 10 & 31) - 15, m = 1024 | (o[i] & 1023);
+        const int v = o[i] ? (o[i] & 0x8000 ? -1 : 1) * (m << exp >> 10) : 0;
+        const int below = prand::gmx_below(S.bits, i), factor = prand::gmx_factor(S.width, i);
+        if (below >= S.digits ? v != 0 : v % factor != 0) return -1;
+        if (below >= S.digits) continue;
+        int16_t& at = d[S.digits - 1 - below];
+        // the second part of a digit repeats the first
+        if (S.width != 11 && (i & 1) && at != v / factor) return -1;
+        at = (int16_t)(v / factor);
       }
+    }
   return 0;
 }

@@ -1,7 +1,8 @@
 """The coefficient tables of the GM/GQ matrix-instruction kernels, on the CPU:
 the digits of every step represent the step's coefficients mod p, lose less
-than the result's offset allows (the bound that makes every digit exact), and
-the kernels' integer arithmetic, emulated on states whose later values sit at
+than the result's offset allows (the bound that makes every digit exact), keep
+the sums within the 22 bits that the accumulators hold exactly, and the
+kernels' arithmetic, emulated in integers on states whose later values sit at
 the digit boundaries, gives the exact digits."""
 import ctypes
 import random
@@ -23,8 +24,8 @@ def tables():
     res = []
     for g in range(8):
         mat = np.zeros((257, 4), dtype=np.uint64)
-        dig = np.zeros((256, 2, 16), dtype=np.int8)
-        dims = (ctypes.c_int * 5)()
+        dig = np.zeros((256, 2, 8), dtype=np.int16)
+        dims = (ctypes.c_int * 7)()
         assert fn(g, ctypes.c_void_p(mat.ctypes.data), ctypes.c_void_p(dig.ctypes.data), dims) == 0
         assert dims[0] == 256
         res.append((mat, dig, *dims[1:]))
@@ -35,60 +36,69 @@ def tables():
 def test_digits_represent_the_steps_and_keep_the_bound(tables, g):
     k, q, e, c, v = GENS[g]
     p = 2**e - c
-    mat, dig, D, L, bits, delta = tables[g]
-    tb = bits * (L - 1) + 8
+    mat, dig, D, L, bits, delta, b, top = tables[g]
+    tb = bits * (L - 1) + (bits if top else 8)
     row, prev = (1, 0), (0, 1)
     for j in range(257):
         assert tuple(int(x) for x in mat[j]) == row + prev
         if j:
-            lost = gained = 0
+            lost = gained = low = high = 0
             for h in range(2):
                 d = [int(x) for x in dig[j - 1, h]]
-                assert all(-8 <= x <= 7 for x in d) and not any(d[D:])
-                assert (sum(x * 16**m for m, x in enumerate(d)) - row[h]) % p == 0
-                # a fraction cut at nibble i loses [0, 1) and 16^-i more for
-                # the rounding of x / p (itself a little over one unit)
-                w = [1 + 1.01 * 16.0 ** -(D - 1 - m) for m in range(D)]
+                assert all(-2**(b - 1) <= x < 2**(b - 1) for x in d) and not any(d[D:])
+                assert (sum(x * 2**(b * m) for m, x in enumerate(d)) - row[h]) % p == 0
+                low -= sum(x for x in d if x < 0)
+                high += sum(x for x in d if x > 0)
+                # a fraction cut i digits above the last loses [0, 1) and
+                # 2^(-b i) more for the rounding of x / p (itself a little
+                # over one unit)
+                w = [1 + 1.01 * 2.0 ** (-b * (D - 1 - m)) for m in range(D)]
                 lost += sum(x * w[m] for m, x in enumerate(d[:D]) if x > 0)
                 gained -= sum(x * w[m] for m, x in enumerate(d[:D]) if x < 0)
             assert lost <= delta
             assert delta + gained < 2**tb / (p * 2**v)
+            # a position's sum with the carry into it (a sum over 2^10 or 2^11)
+            assert (1 + top) * max(low, high) * (2**bits - 1) + 2**13 < 2**22
         row, prev = tuple((k * a - q * b) % p for a, b in zip(row, prev)), row
 
 
+WF = [43, 65, 69, 114, 130, 65, 69, 69]
+
+
 def fraction(g, x):
-    """The kernels' form of floor(2^WF x / p), WF = TB + 4 (D - 1)."""
+    """The kernels' form of floor(2^WF x / p), WF = TB + b (D - 1)."""
     if g == 0:
-        return (x << 27) | (x << 8) | (x >> 11)
+        return (x << 24) | (x << 5) | (x >> 14)
     if g == 2:
         return (x << 38) | (x << 7) | (x >> 24)
     if g == 3:
-        return (x << 60) + ((129 * x) << 9) + ((16641 * x) >> 42)
+        return (x << 63) + ((129 * x) << 12) + ((16641 * x) >> 39)
     if g == 4:
-        return (x << 73) | (x << 12) | (x >> 49)
-    return (x << 40) + ((3 * x) << 11) + ((9 * x) >> 18)
+        return (x << 69) | (x << 8) | (x >> 53)
+    sh = WF[g] - 29
+    return (x << sh) + ((3 * x) << (sh - 29)) + ((9 * x) >> (58 - sh))
 
 
-def kernel_digit(g, dig, D, L, bits, delta, v, j, xc, xp):
+def kernel_digit(g, dig, D, L, bits, delta, b, top, v, j, xc, xp):
     """The accumulator chain of one step of one element."""
     acc = delta
     f = (fraction(g, xc), fraction(g, xp))
     for s in range(L):
+        double = top and s == L - 1
         if s:
-            acc >>= bits
+            acc >>= bits - double
         for h in range(2):
             for m in range(D):
-                w = f[h] >> (bits * s + 4 * (D - 1 - m))
-                acc += int(dig[j - 1, h, m]) * ((w & 15) + 16 * ((w >> 4) & 127))
-        assert -2**31 <= acc < 2**31
-    return (acc >> (8 - v)) & (2**v - 1)
+                acc += int(dig[j - 1, h, m]) * (((f[h] >> (bits * s + b * (D - 1 - m))) & (2**bits - 1)) << double)
+        assert -2**22 <= acc < 2**22
+    return (acc >> (bits + top if top else 8) - v) & (2**v - 1)
 
 
 @pytest.mark.parametrize("g", range(8), ids=NAMES)
 def test_fraction_error(g):
     _, _, e, c, _ = GENS[g]
     p = 2**e - c
-    wf = {0: 46, 2: 69, 3: 111, 4: 134}.get(g, 69)
+    wf = WF[g]
     r = random.Random(7 + g)
     for x in [0, 1, 2, p - 1, p - 2, p // 2, p // 2 + 1] + [r.randrange(p) for _ in range(3000)]:
         err = (x << wf) - fraction(g, x) * p     # in [0, 1.01) units of 2^-WF x p
@@ -99,8 +109,8 @@ def test_fraction_error(g):
 def test_digits_at_the_boundaries(tables, g):
     k, q, e, c, v = GENS[g]
     p = 2**e - c
-    mat, dig, D, L, bits, delta = tables[g]
-    assert bits * (L - 1) + 8 + 4 * (D - 1) == {0: 46, 2: 69, 3: 111, 4: 134}.get(g, 69)
+    mat, dig, D, L, bits, delta, bd, top = tables[g]
+    assert bits * (L - 1) + (bits if top else 8) + bd * (D - 1) == WF[g]
     r = random.Random(11 + g)
     edges = []
     for i in range(2**v + 1):
@@ -114,8 +124,8 @@ def test_digits_at_the_boundaries(tables, g):
             o = r.randrange(p)
             xc, xp = (d * target - b * o) * inv % p, (a * o - cc * target) * inv % p
             assert (a * xc + b * xp) % p == target
-            assert kernel_digit(g, dig, D, L, bits, delta, v, j, xc, xp) == (target << v) // p
+            assert kernel_digit(g, dig, D, L, bits, delta, bd, top, v, j, xc, xp) == (target << v) // p
     for _ in range(300):
         xc, xp, j = r.randrange(p), r.randrange(p), r.randrange(1, 257)
         a, b = int(mat[j][0]), int(mat[j][1])
-        assert kernel_digit(g, dig, D, L, bits, delta, v, j, xc, xp) == ((a * xc + b * xp) % p << v) // p
+        assert kernel_digit(g, dig, D, L, bits, delta, bd, top, v, j, xc, xp) == ((a * xc + b * xp) % p << v) // p
