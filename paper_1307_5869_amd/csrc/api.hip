@@ -250,26 +250,39 @@ const uint32_t* section_table(prand_ctx* c, int k, uint64_t seclen, hipStream_t 
   return d;
 }
 
-// sections per stream (log2) and section length of the many-stream
+// Sections per stream (log2) and section length of the many-stream
 // MRG32K3A/LFSR113 kernel: up to 64 sections per stream of whole 32-word
-// chunks (regstream.h).  With a section-start table a start costs one matrix
-// application, so streams are cut into as many sections of at least 256
-// outputs as fit in 2^22 lanes (more, shorter sections measured faster: the
-// 64 runs of a wavefront then lie close together in the output); with ladder
-// jumps a start costs one application per set bit of its distance, so the
-// cut stops at 2^19 lanes and sections of at least 64 outputs.
-void section_plan(uint32_t count, uint64_t n, bool table, int& nsec_log2, uint64_t& seclen) {
+// chunks (regstream.h).
+//
+// short_plan: starts by the byte tables, anywhere (one matrix per nonzero byte
+// of the distance), so sections may be short and begin on lines of the output
+// (`lines`: every stream does): from 16 outputs of a stream on while the lanes
+// leave SIMDs idle (up to 2^16 of them), MRG32K3A from 128 on up to 2^18 (its
+// matrix costs 25 outputs, LFSR113's, of 128 bits, more than 100).  In a short
+// call the time is the chain of one lane: 5574 MRG32K3A streams of 820 u32 in
+// two sections of 416 by the table 42 us, in 32 sections of 32 26 us; 20000 of
+// 1000 f64 60 us in two, 48 us in four; but 4096 LFSR113 streams of 4096 u32
+// 28 us in 16 sections, 33 in 32.
+// long_plan, where those sections would be longer than 256: starts by a
+// section-start table (one matrix), sections of at least 256 outputs, as many
+// as fit in 2^22 lanes (more, shorter sections measured faster: the 64 runs of
+// a wavefront then lie close together in the output).
+void short_plan(int gen, uint32_t count, uint64_t n, bool lines, int& nsec_log2, uint64_t& seclen) {
+  const uint64_t max_lanes = gen == PRAND_MRG32K3A ? 1ull << 18 : 1ull << 16;
   nsec_log2 = 0;
-  if (table) {
-    while (nsec_log2 < 6 && ((uint64_t)count << (nsec_log2 + 1)) <= (1ull << 22) && (n >> (nsec_log2 + 1)) >= 256)
-      nsec_log2++;
-  } else {
-    while (nsec_log2 < 6 && ((uint64_t)count << nsec_log2) < (1ull << 19) && (n >> (nsec_log2 + 1)) >= 64)
-      nsec_log2++;
+  while (nsec_log2 < 6) {
+    const uint64_t lanes = (uint64_t)count << (nsec_log2 + 1);
+    if (lanes > max_lanes || (lines ? n : n + 31) >> (nsec_log2 + 1) < (lanes <= (1u << 16) ? 16 : 128)) break;
+    nsec_log2++;
   }
-  seclen = (n + (1ull << nsec_log2) - 1) >> nsec_log2;
-  seclen = (seclen + 31) & ~31ull;
-  if (seclen == 0) seclen = 32;
+  const uint64_t reach = nsec_log2 && !lines ? n + 31 : n;   // room to begin the sections on lines
+  seclen = (((reach + (1ull << nsec_log2) - 1) >> nsec_log2) + 31) & ~31ull;
+}
+void long_plan(uint32_t count, uint64_t n, int& nsec_log2, uint64_t& seclen) {
+  nsec_log2 = 0;
+  while (nsec_log2 < 6 && ((uint64_t)count << (nsec_log2 + 1)) <= (1ull << 22) && (n >> (nsec_log2 + 1)) >= 256)
+    nsec_log2++;
+  seclen = (((n + (1ull << nsec_log2) - 1) >> nsec_log2) + 31) & ~31ull;
 }
 
 // many-stream generation, the states moved on in place
@@ -279,9 +292,12 @@ hipError_t launch_streams(prand_ctx* c, int gen, void* states, uint32_t count, u
     const int k = gen == PRAND_MRG32K3A ? 0 : 1;
     int nsec_log2;
     uint64_t seclen;
-    section_plan(count, n, true, nsec_log2, seclen);
-    const uint32_t* tab = nsec_log2 ? section_table(c, k, seclen, st) : nullptr;
-    if (!tab) section_plan(count, n, false, nsec_log2, seclen);
+    short_plan(gen, count, n, ((uintptr_t)out | n * elem_bytes(dtype)) % 128 == 0, nsec_log2, seclen);
+    const uint32_t* tab = nullptr;
+    if (seclen > 256) {
+      long_plan(count, n, nsec_log2, seclen);
+      tab = nsec_log2 ? section_table(c, k, seclen, st) : nullptr;
+    }
     if (gen == PRAND_MRG32K3A)
       return launch_mrg_generate(c->T, (const MrgState*)states, (MrgState*)states, count, n, nsec_log2, seclen, dtype,
                                  out, tab, st);

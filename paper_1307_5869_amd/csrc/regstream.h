@@ -10,11 +10,12 @@
 // eight whole 128-byte lines per instruction).  A lane's chunks are the
 // aligned 4 CW-byte blocks of memory that its run touches, whatever the run's
 // address (any multiple of the element size): only its first and last chunk
-// may be partial, and in these the 16-byte pieces that the run covers are
-// stored as the others are, the words of a piece it covers in part one by
-// one.  (Runs that did not start on 16 bytes used to be stored word by word,
-// lane by lane: 10007 LFSR113 streams of 4999 f32 took 252 us, now 73 us.)
-// A lane whose run is shorter sits out the later rounds.
+// may be partial.  A round in which a lane's chunk is partial makes its words
+// one by one, all lanes together; the 16-byte pieces that the run covers are
+// stored as the others are, the words of a piece it covers in part by the lane.
+// (Runs that did not start on 16 bytes used to be stored word by word, lane by
+// lane: 10007 LFSR113 streams of 4999 f32 took 252 us, now 75 us.)  A lane
+// whose run is shorter sits out the later rounds.
 //
 // regstream_wave() is the wavefront routine shared by the many-stream kernel
 // below and by the batched generation kernel.
@@ -44,6 +45,8 @@ __device__ __forceinline__ void put_word(void* out, uint64_t i, uint32_t w, doub
 // ladder), write `len` values at `out` (element pointer of the run) and, when
 // `sout` is set, store the advanced state there.  All 64 lanes must call.
 // kJump = false: the caller guarantees start == 0 (no jump code is built).
+// unit: bytes that the chunks are aligned to (16: short runs, which then touch
+// fewer of them).
 //
 // G: State, Regs, static load(State) -> Regs, static save(Regs) -> State,
 // static jump(State&, uint64_t distance, const uint32_t* ladder),
@@ -53,7 +56,8 @@ template <class G, int DT, int CW, bool kJump = true>
 __device__ __forceinline__ void regstream_wave(uint32_t* rows, bool live, const typename G::State* in, uint64_t start,
                                                uint64_t len, void* out, typename G::State* sout,
                                                const uint32_t* __restrict__ ladder,
-                                               const uint32_t* __restrict__ sec_mat = nullptr) {
+                                               const uint32_t* __restrict__ sec_mat = nullptr,
+                                               uint32_t unit = 4 * CW) {
   constexpr int kPieces = CW / 4;                            // 16-byte pieces per chunk
   constexpr int kw = (DT == PRAND_F64) ? 2 : 1;               // words per value
   constexpr int es = 4 * kw;
@@ -68,7 +72,7 @@ __device__ __forceinline__ void regstream_wave(uint32_t* rows, bool live, const 
   // the run's frame: its chunks, the first of which it enters `head` words
   // on and the last of which it fills up to `tail` words (1 .. CW)
   const bool framed = __all(!live || (uintptr_t)out % es == 0);
-  const uint32_t head = live ? (uint32_t)((uintptr_t)out % (4 * CW)) / 4 : 0;
+  const uint32_t head = live ? (uint32_t)((uintptr_t)out % unit) / 4 : 0;
   const uint64_t total = (live && framed) ? head + len * kw : 0;   // words from the frame's start
   const uint32_t mine = (uint32_t)((total + CW - 1) / CW);         // chunks (0: none)
   const uint32_t tail = mine ? (uint32_t)(total - (uint64_t)(mine - 1) * CW) : 0;
@@ -83,55 +87,65 @@ __device__ __forceinline__ void regstream_wave(uint32_t* rows, bool live, const 
   if (rounds) {
     const uint32_t skip = __any(head != 0) ? 1 : 0;   // chunks 0 .. skip - 1 may have a head
     // piece (lane % kPieces) of each source lane's chunk, one source lane per
-    // store instruction: its address in chunk 0, the chunks in which the run
-    // reaches the piece's end, and where the run begins and ends in the first
-    // and the last piece
+    // store instruction: its address in chunk 0, and the chunks in which the
+    // run covers it
     const int p4 = 4 * (lane % kPieces);
     char* const base = live ? (char*)out - 4 * (uint64_t)head : nullptr;
     char* dst[kPieces];
-    uint32_t whole[kPieces], ends[kPieces];   // ends: begin in chunk 0 | words in chunk `whole` << 4
+    uint32_t from[kPieces], whole[kPieces];   // from <= chunk < whole
 #pragma unroll
     for (int i = 0; i < kPieces; i++) {
       const int src = i * (64 / kPieces) + lane / kPieces;
       dst[i] = (char*)__shfl((unsigned long long)base, src) + 4 * p4;
       const uint32_t chunks = __shfl(mine, src), ht = __shfl(head | tail << 8, src);
-      const int hd = (int)(ht & 255) - p4, over = (int)(ht >> 8) - p4;
-      whole[i] = chunks - (chunks && over < 4 ? 1 : 0);
-      ends[i] = (uint32_t)(hd < 0 ? 0 : (hd > 4 ? 4 : hd)) | (uint32_t)(over > 0 && over < 4 ? over : 0) << 4;
+      from[i] = (int)(ht & 255) > p4 ? 1 : 0;
+      whole[i] = chunks - (chunks && (int)(ht >> 8) < p4 + 4 ? 1 : 0);
     }
     uint32_t* row = rows + lane * RegStage<CW>::kRowWords;
     for (uint32_t rd = 0; rd < rounds; rd++) {
-      if ((rd || !head) && (rd + 1 < mine || (rd + 1 == mine && tail == CW))) {
+      // all: this chunk is whole for every live lane; parts: partial for one;
+      // otherwise whole for the lanes that have it
+      const bool all = rd >= skip && rd < even;
+      const bool parts = !all && __any((rd == 0 && head) || (rd + 1 == mine && tail < CW));
+      if (!parts) {
+        if (rd < mine) {
 #pragma unroll
-        for (int q = 0; q < kPieces; q++) {
-          uint4 v;
-          if (DT == PRAND_F64) {
-            const double a = G::f64(G::next(r)), b = G::f64(G::next(r));
-            const uint64_t ua = __double_as_longlong(a), ub = __double_as_longlong(b);
-            v = make_uint4((uint32_t)ua, (uint32_t)(ua >> 32), (uint32_t)ub, (uint32_t)(ub >> 32));
-          } else if (DT == PRAND_F32) {
-            const uint32_t a = G::next(r), b = G::next(r), c = G::next(r), d = G::next(r);
-            v = make_uint4(__float_as_uint((float)(a >> 8) * 0x1p-24f), __float_as_uint((float)(b >> 8) * 0x1p-24f),
-                           __float_as_uint((float)(c >> 8) * 0x1p-24f), __float_as_uint((float)(d >> 8) * 0x1p-24f));
-          } else {
-            const uint32_t a = G::next(r), b = G::next(r), c = G::next(r), d = G::next(r);
-            v = make_uint4(a, b, c, d);
+          for (int q = 0; q < kPieces; q++) {
+            uint4 v;
+            if (DT == PRAND_F64) {
+              const double a = G::f64(G::next(r)), b = G::f64(G::next(r));
+              const uint64_t ua = __double_as_longlong(a), ub = __double_as_longlong(b);
+              v = make_uint4((uint32_t)ua, (uint32_t)(ua >> 32), (uint32_t)ub, (uint32_t)(ub >> 32));
+            } else if (DT == PRAND_F32) {
+              const uint32_t a = G::next(r), b = G::next(r), c = G::next(r), d = G::next(r);
+              v = make_uint4(__float_as_uint((float)(a >> 8) * 0x1p-24f), __float_as_uint((float)(b >> 8) * 0x1p-24f),
+                             __float_as_uint((float)(c >> 8) * 0x1p-24f), __float_as_uint((float)(d >> 8) * 0x1p-24f));
+            } else {
+              const uint32_t a = G::next(r), b = G::next(r), c = G::next(r), d = G::next(r);
+              v = make_uint4(a, b, c, d);
+            }
+            *(uint4*)(row + 4 * q) = v;
           }
-          *(uint4*)(row + 4 * q) = v;
         }
-      } else if (rd < mine) {
-        // a partial chunk: the words of the run in it
-        const uint32_t w0 = rd ? 0 : head;
-        const uint32_t w1 = rd + 1 < mine ? CW : tail;
-#pragma unroll 1
-        for (uint32_t w = w0; w < w1; w += kw) {
-          const uint32_t v = G::next(r);
-          put_word<DT>(row + w, 0, v, DT == PRAND_F64 ? G::f64(v) : 0.0);
+      } else {
+        // word by word, the lanes together: the words of the run in this chunk;
+        // those of a 16-byte piece that the run covers in part are stored here
+        const uint32_t w0 = rd ? 0 : head, w1 = rd + 1 < mine ? CW : (rd + 1 == mine ? tail : 0);
+        const uint32_t h4 = (w0 + 3) & ~3u, t4 = w1 & ~3u;
+        char* const at = base + (uint64_t)rd * (4 * CW);
+#pragma unroll
+        for (uint32_t w = 0; w < CW; w += kw) {
+          if (w >= w0 && w < w1) {
+            const uint32_t v = G::next(r);
+            const double f = DT == PRAND_F64 ? G::f64(v) : 0.0;
+            put_word<DT>(row + w, 0, v, f);
+            if (w < h4 || w >= t4) put_word<DT>(at + 4 * w, 0, v, f);
+          }
         }
       }
       wave_lds_sync();
       const uint64_t adv = (uint64_t)rd * (4 * CW);
-      if (rd >= skip && rd < even) {
+      if (all) {
 #pragma unroll
         for (int i = 0; i < kPieces; i++) {
           const int src = i * (64 / kPieces) + lane / kPieces;
@@ -142,18 +156,8 @@ __device__ __forceinline__ void regstream_wave(uint32_t* rows, bool live, const 
 #pragma unroll
         for (int i = 0; i < kPieces; i++) {
           const int src = i * (64 / kPieces) + lane / kPieces;
-          const uint32_t* from = rows + src * RegStage<CW>::kRowWords + p4;
-          const uint4 v = *(const uint4*)from;
-          const uint32_t begin = rd ? 0 : ends[i] & 15;
-          if (rd < whole[i] && begin == 0) {
-            store_out16<DT, (CW >= 32)>(dst[i] + adv, v);
-          } else if (rd <= whole[i]) {
-            const uint32_t end = rd < whole[i] ? 4 : ends[i] >> 4;
-            for (uint32_t w = begin; w < end; w += kw) {
-              if (DT == PRAND_F64) *(uint2*)(dst[i] + adv + 4 * w) = *(const uint2*)(from + w);
-              else *(uint32_t*)(dst[i] + adv + 4 * w) = from[w];
-            }
-          }
+          const uint4 v = *(const uint4*)(rows + src * RegStage<CW>::kRowWords + p4);
+          if (rd >= from[i] && rd < whole[i]) store_out16<DT, (CW >= 32)>(dst[i] + adv, v);
         }
       }
       wave_lds_sync();
@@ -183,16 +187,25 @@ __global__ void __launch_bounds__(256) regstream_kernel(const typename G::State*
   __shared__ __align__(16) uint32_t stage[4][RegStage<CW>::kWaveWords];
   const uint64_t gid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const uint64_t nsec = 1ull << nsec_log2;
-  const uint64_t jlast = (n == 0) ? 0 : (n - 1) / seclen;
   const uint64_t s = gid >> nsec_log2, j = gid & (nsec - 1);
-  const uint64_t start = j * seclen;
-  const bool live = s < count && j <= jlast;
-  const uint64_t len = live ? ((j == jlast) ? n - start : seclen) : 0;
   constexpr int es = (DT == PRAND_F64) ? 8 : 4;
+  // where starts may lie anywhere (jumps by bytes) and the sections leave room
+  // for it, they begin on chunks of the output: the first is shorter by as much
+  // as the stream's output begins inside one
+  const bool any = !sectab && (seclen << nsec_log2) >= n + CW - 1;
+  const uint64_t short_by = any ? ((uintptr_t)out + s * n * es) % (4 * CW) / es : 0;
+  const uint64_t jlast = (n - 1 + short_by) / seclen;
+  const uint64_t start = j ? j * seclen - short_by : 0;
+  const bool live = s < count && j <= jlast;
+  const uint64_t len = live ? (j == jlast ? n : (j + 1) * seclen - short_by) - start : 0;
   void* o = (char*)out + (s * n + start) * es;
+  // Runs of up to a line, and of up to eight where the whole output is small
+  // and the time is that of the rounds (65536 streams of 100 f32: 22 us in
+  // chunks on 16 bytes, 24 on lines; 300000 of 100: 101 and 60)
+  const uint32_t unit = n * es <= 128 || (n * es <= 1024 && count * n * es <= (1u << 25)) ? 16 : 4 * CW;
   const uint32_t* sec_mat = (sectab && j) ? sectab + (j - 1) * G::kSectionWords : nullptr;
   regstream_wave<G, DT, CW>(stage[threadIdx.x >> 6], live, sin + (live ? s : 0), start, len, o,
-                            (live && j == jlast) ? sout + s : nullptr, ladder, sec_mat);
+                            (live && j == jlast) ? sout + s : nullptr, ladder, sec_mat, unit);
 }
 
 // One stream: lane j owns section j (seclen outputs, the last one the rest).

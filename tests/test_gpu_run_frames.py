@@ -21,7 +21,8 @@ def ctx():
     c.close()
 
 
-@pytest.mark.parametrize("count,n", [(1, 1), (3, 31), (2, 33), (65, 5), (5, 255), (4, 257), (3, 999), (2, 4999), (1, 20003)])
+@pytest.mark.parametrize("count,n", [(1, 1), (3, 31), (2, 33), (65, 5), (5, 255), (4, 257), (3, 999), (2, 4999), (1, 20003),
+                                     (300, 60), (107, 123), (64, 128), (33, 820), (9, 2080), (129, 513)])
 @pytest.mark.parametrize("dtype", [P.U32, P.F32, P.F64])
 @pytest.mark.parametrize("gen", [P.MRG32K3A, P.LFSR113])
 def test_any_address(ctx, oracle, gen, dtype, count, n):
