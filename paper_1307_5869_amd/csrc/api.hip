@@ -264,9 +264,11 @@ const uint32_t* section_table(prand_ctx* c, int k, uint64_t seclen, hipStream_t 
 // 1000 f64 60 us in two, 48 us in four; but 4096 LFSR113 streams of 4096 u32
 // 28 us in 16 sections, 33 in 32.
 // long_plan, where those sections would be longer than 256: starts by a
-// section-start table (one matrix), sections of at least 256 outputs, as many
-// as fit in 2^22 lanes (more, shorter sections measured faster: the 64 runs of
-// a wavefront then lie close together in the output).
+// section-start table (one matrix), sections of at least 1 KB, as many as fit
+// in 2^22 lanes (more, shorter sections measured faster: the 64 runs of a
+// wavefront then lie close together in the output; 10007 streams of 4999 f64
+// in sections of 2 KB 112 us, of 1 KB 101-109, of u32 in sections of 512 bytes
+// 72-74, 75 in those of 1 KB).
 void short_plan(int gen, uint32_t count, uint64_t n, bool lines, int& nsec_log2, uint64_t& seclen) {
   const uint64_t max_lanes = gen == PRAND_MRG32K3A ? 1ull << 18 : 1ull << 16;
   nsec_log2 = 0;
@@ -278,9 +280,9 @@ void short_plan(int gen, uint32_t count, uint64_t n, bool lines, int& nsec_log2,
   const uint64_t reach = nsec_log2 && !lines ? n + 31 : n;   // room to begin the sections on lines
   seclen = (((reach + (1ull << nsec_log2) - 1) >> nsec_log2) + 31) & ~31ull;
 }
-void long_plan(uint32_t count, uint64_t n, int& nsec_log2, uint64_t& seclen) {
+void long_plan(uint32_t count, uint64_t n, int dtype, int& nsec_log2, uint64_t& seclen) {
   nsec_log2 = 0;
-  while (nsec_log2 < 6 && ((uint64_t)count << (nsec_log2 + 1)) <= (1ull << 22) && (n >> (nsec_log2 + 1)) >= 256)
+  while (nsec_log2 < 6 && ((uint64_t)count << (nsec_log2 + 1)) <= (1ull << 22) && (n >> (nsec_log2 + 1)) * elem_bytes(dtype) >= 1024)
     nsec_log2++;
   seclen = (((n + (1ull << nsec_log2) - 1) >> nsec_log2) + 31) & ~31ull;
 }
@@ -295,7 +297,7 @@ hipError_t launch_streams(prand_ctx* c, int gen, void* states, uint32_t count, u
     short_plan(gen, count, n, ((uintptr_t)out | n * elem_bytes(dtype)) % 128 == 0, nsec_log2, seclen);
     const uint32_t* tab = nullptr;
     if (seclen > 256) {
-      long_plan(count, n, nsec_log2, seclen);
+      long_plan(count, n, dtype, nsec_log2, seclen);
       tab = nsec_log2 ? section_table(c, k, seclen, st) : nullptr;
     }
     if (gen == PRAND_MRG32K3A)

@@ -46,7 +46,7 @@ __device__ __forceinline__ void put_word(void* out, uint64_t i, uint32_t w, doub
 // `sout` is set, store the advanced state there.  All 64 lanes must call.
 // kJump = false: the caller guarantees start == 0 (no jump code is built).
 // unit: bytes that the chunks are aligned to (16: short runs, which then touch
-// fewer of them).
+// fewer of them).  drop: outputs to leave out before the first.
 //
 // G: State, Regs, static load(State) -> Regs, static save(Regs) -> State,
 // static jump(State&, uint64_t distance, const uint32_t* ladder),
@@ -57,7 +57,7 @@ __device__ __forceinline__ void regstream_wave(uint32_t* rows, bool live, const 
                                                uint64_t len, void* out, typename G::State* sout,
                                                const uint32_t* __restrict__ ladder,
                                                const uint32_t* __restrict__ sec_mat = nullptr,
-                                               uint32_t unit = 4 * CW) {
+                                               uint32_t unit = 4 * CW, uint32_t drop = 0) {
   constexpr int kPieces = CW / 4;                            // 16-byte pieces per chunk
   constexpr int kw = (DT == PRAND_F64) ? 2 : 1;               // words per value
   constexpr int es = 4 * kw;
@@ -69,6 +69,7 @@ __device__ __forceinline__ void regstream_wave(uint32_t* rows, bool live, const 
     else if (kJump && start) G::jump(st, start, ladder);
   }
   typename G::Regs r = G::load(st);
+  for (uint32_t i = 0; i < drop; i++) (void)G::next(r);
   // the run's frame: its chunks, the first of which it enters `head` words
   // on and the last of which it fills up to `tail` words (1 .. CW)
   const bool framed = __all(!live || (uintptr_t)out % es == 0);
@@ -189,15 +190,22 @@ __global__ void __launch_bounds__(256) regstream_kernel(const typename G::State*
   const uint64_t nsec = 1ull << nsec_log2;
   const uint64_t s = gid >> nsec_log2, j = gid & (nsec - 1);
   constexpr int es = (DT == PRAND_F64) ? 8 : 4;
-  // where starts may lie anywhere (jumps by bytes) and the sections leave room
-  // for it, they begin on chunks of the output: the first is shorter by as much
-  // as the stream's output begins inside one
+  // Sections begin on chunks of the output, for all but the first to be whole.
+  // Where starts may lie anywhere (jumps by bytes) and the sections leave room
+  // for it, the first is shorter by as much as the stream's output begins
+  // inside a chunk; with starts by the table it is longer by the rest of that
+  // chunk, which the others drop: at most 15 of 128 f64 (65536 streams of 16383
+  // 2.38 ms with partial chunks at every section's ends, 1.65 so), but not up
+  // to 31 of 256 u32, which costs what it saves (10007 LFSR113 streams of 4999
+  // f32 70 us without, 71.5 so).
+  const uint64_t inside = ((uintptr_t)out + s * n * es) % (4 * CW) / es;
   const bool any = !sectab && (seclen << nsec_log2) >= n + CW - 1;
-  const uint64_t short_by = any ? ((uintptr_t)out + s * n * es) % (4 * CW) / es : 0;
-  const uint64_t jlast = (n - 1 + short_by) / seclen;
-  const uint64_t start = j ? j * seclen - short_by : 0;
+  const uint64_t less = any ? inside : 0;
+  const uint64_t more = sectab && DT == PRAND_F64 && inside ? 4 * CW / es - inside : 0;
+  const uint64_t jlast = n > more ? (n - 1 - more + less) / seclen : 0;
+  const uint64_t start = j ? j * seclen + more - less : 0;
   const bool live = s < count && j <= jlast;
-  const uint64_t len = live ? (j == jlast ? n : (j + 1) * seclen - short_by) - start : 0;
+  const uint64_t len = live ? (j == jlast ? n : (j + 1) * seclen + more - less) - start : 0;
   void* o = (char*)out + (s * n + start) * es;
   // Runs of up to a line, and of up to eight where the whole output is small
   // and the time is that of the rounds (65536 streams of 100 f32: 22 us in
@@ -205,7 +213,8 @@ __global__ void __launch_bounds__(256) regstream_kernel(const typename G::State*
   const uint32_t unit = n * es <= 128 || (n * es <= 1024 && count * n * es <= (1u << 25)) ? 16 : 4 * CW;
   const uint32_t* sec_mat = (sectab && j) ? sectab + (j - 1) * G::kSectionWords : nullptr;
   regstream_wave<G, DT, CW>(stage[threadIdx.x >> 6], live, sin + (live ? s : 0), start, len, o,
-                            (live && j == jlast) ? sout + s : nullptr, ladder, sec_mat, unit);
+                            (live && j == jlast) ? sout + s : nullptr, ladder, sec_mat, unit,
+                            live && j ? (uint32_t)more : 0);
 }
 
 // One stream: lane j owns section j (seclen outputs, the last one the rest).
