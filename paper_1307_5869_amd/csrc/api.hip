@@ -158,9 +158,10 @@ hipError_t ensure_mt(prand_ctx* c) {
   }
   std::vector<uint32_t> mt((size_t)kLadder * 624), dlo((size_t)kMtLoDigits * kMtLoSize * 624),
       d8((size_t)2 * 256 * 624);
-  std::vector<uint32_t> blk((size_t)kMtBlkPolys * 624), inv(624);
+  constexpr int kBits = 4 * kMtBlkDigits;
+  std::vector<uint32_t> bits((size_t)kBits * 624), blk((size_t)kMtBlkDigits * 16 * 624), inv(624);
   if (!mt_build_polys(mt.data(), kLadder, dlo.data(), d8.data(), kMtDigitE)) return hipErrorUnknown;
-  if (!mt_build_block_polys(kMtBlkFirst + kMtBlkPolys + 9, kMtBlkFirst, kMtBlkPolys, blk.data(), inv.data()))
+  if (!mt_build_block_polys(kMtBlkUnit + kBits + 9, kMtBlkUnit, kBits, bits.data(), inv.data(), blk.data()))
     return hipErrorUnknown;
   hipError_t e = upload(&c->T.mt, mt.data(), mt.size());
   if (e == hipSuccess) e = upload(&c->T.mtblk, blk.data(), blk.size());
@@ -310,13 +311,15 @@ hipError_t launch_streams(prand_ctx* c, int gen, void* states, uint32_t count, u
   return launch_gm_generate(c->T, gen, (GmState*)states, count, n, dtype, out, st);
 }
 
-// distances of the section starts: j * seclen for the bulk sections j < nb,
-// then T for the final section
-__global__ void section_dist_kernel(uint64_t* d, uint32_t nb, uint64_t seclen, uint64_t T) {
+// distances of the section starts: (i + 1) units
+__global__ void section_dist_kernel(uint64_t* d, uint32_t count, uint64_t unit) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < nb) d[i] = (uint64_t)i * seclen;
-  else if (i == nb) d[i] = T;
+  if (i < count) d[i] = (i + 1) * unit;
 }
+
+// MT19937 outputs that one section makes in no more time than sections with
+// their jumps: 200000 u32 80 us, 300000 111; 310000 to 10^6 in sections 103-110
+constexpr uint64_t kMtSingle = 1u << 18;
 
 // a state blob between pinned host memory and the device
 __global__ void copy_state_kernel(uint32_t* dst, const uint32_t* src, uint32_t words) {
@@ -352,24 +355,25 @@ int prand::ensure_mt_tables(prand_ctx* c) {
 // while few wavefronts read it, else from a device copy), the last of which
 // leaves the advanced state.
 //
-// MT19937: one workgroup while one section is enough.  Otherwise bulk sections
-// of 2^k outputs cover [0, T); each starts from the state jumped j * 2^k ahead
-// (one ladder application per set bit of j) and fills its slice.  A final
-// section covers [T, n) and leaves the advanced state.  T is the last
-// twist-block boundary of the original stream before n: a jump yields the
+// MT19937: one workgroup while one section is enough.  Otherwise sections that
+// start on the stream's block boundaries: the first from the state itself, the
+// rest of its block and L outputs, section j from the state moved j L outputs
+// on from the end of its block (L = 624 * 2^8 * 2^k: a jump per nonzero
+// hexadecimal digit of j 2^k), the last one what is left.  A jump yields the
 // canonical window, which differs from the array sequential generation holds
-// only in bits the next twist overwrites, so the final section's state is
-// exactly the sequential one.  The section states, their distances and the
-// copied-in base state live in `scratch` when it is given (the plan then uses
-// at most as many sections as fit in scratch_bytes; the output does not depend
-// on the plan), else in the context's buffers.
+// only in bits that the next twist overwrites, and every section begins with a
+// twist: the last one's state is exactly the sequential one.  The section
+// states, their distances and the copied-in base state live in `scratch` when
+// it is given (the plan then uses at most as many sections as fit in
+// scratch_bytes; the output does not depend on the plan), else in the
+// context's buffers.  (Sections off the boundaries, by the ladder, and one more
+// from the last boundary: 10^6 u32 538 us, 110 so; 10^7 650 and 152.)
 //
 // States come and go through pinned memory that kernels read and write: no
 // copy calls.  Arguments are checked by the caller; MT19937 tables must exist.
 int prand::generate_host_state(prand_ctx* c, int gen, void* h_state, int dtype, void* d_out, uint64_t n,
                                hipStream_t st, void* scratch, size_t scratch_bytes) {
   const size_t sb = state_bytes(gen);
-  const size_t es = elem_bytes(dtype);
   const size_t base_bytes = (sb + 255) & ~(size_t)255;
   // base state, then distances, then states, each 256-byte aligned
   if (scratch && scratch_bytes < base_bytes + 2 * 256 + 2 * (sb + 8)) return PRAND_ERANGE;
@@ -408,24 +412,23 @@ int prand::generate_host_state(prand_ctx* c, int gen, void* h_state, int dtype, 
     if (e == hipSuccess) e = launch_gm_single(c->T, gen, (const GmState*)base, (GmState*)pin_out, n, dtype, d_out, st);
     return finish();
   }
-  uint64_t max_secs = 4096;
+  // up to 512 sections of the shortest length: 80 million outputs
+  uint64_t max_secs = 512;
   if (scratch) {
     const uint64_t fit = (scratch_bytes - base_bytes - 2 * 256) / (sb + 8);   // section states that fit
-    max_secs = std::min<uint64_t>(max_secs, fit - 1);
+    max_secs = std::min<uint64_t>(max_secs, fit);
   }
-  int k = 18;
-  while (((n + (1ull << k) - 1) >> k) > max_secs) k++;
-  if ((1ull << k) >= n) {
+  const uint64_t r0 = 624 - std::min<uint32_t>(((const MtState*)h_state)->idx, 624u);
+  int k = 0;
+  auto seclen = [&]() { return 624ull << (kMtBlkUnit + k); };
+  auto sections = [&]() { return n > r0 ? (n - r0 + seclen() - 1) / seclen() : 1; };
+  while (sections() > max_secs) k++;
+  if (n <= kMtSingle || sections() == 1) {
     // in place in the pinned slot
     e = launch_mt_generate((MtState*)pin_out, 1, n, dtype, d_out, st);
     return finish();
   }
-  const uint64_t seclen = 1ull << k;
-  const uint64_t r0 = 624 - std::min<uint32_t>(((const MtState*)h_state)->idx, 624u);
-  const uint64_t T = (n <= r0) ? 0 : r0 + 624 * ((n - r0 + 623) / 624 - 1);
-  const uint64_t full = T / seclen, part = T % seclen;
-  const uint64_t nb = full + (part ? 1 : 0);   // bulk sections
-  const uint64_t nst = nb + 1;                 // plus the final one
+  const uint64_t nst = sections() - 1;   // states: of every section but the first
   void* d_states = nullptr;
   uint64_t* d_dist = nullptr;
   const size_t st_off = (nst * 8 + 255) & ~(size_t)255;
@@ -453,26 +456,18 @@ int prand::generate_host_state(prand_ctx* c, int gen, void* h_state, int dtype, 
   if (e == hipSuccess) {
     hipLaunchKernelGGL(copy_state_kernel, dim3(1), dim3(256), 0, st, (uint32_t*)d_base, (const uint32_t*)pin_in, words);
     hipLaunchKernelGGL(section_dist_kernel, dim3((uint32_t)((nst + 255) / 256)), dim3(256), 0, st, d_dist,
-                       (uint32_t)nb, seclen, T);
+                       (uint32_t)nst, 1ull << k);
     e = hipGetLastError();
   }
   JumpSpec js;
   js.dist = d_dist;
   js.nlimbs = 1;
   js.per_stream = 1;
+  js.mt_blocks = kMtUnits;
   if (e == hipSuccess) e = launch_mt_jump(c->T, (MtState*)d_states, (uint32_t)nst, js, (const MtState*)d_base, st);
-  if (e == hipSuccess && full)
-    e = launch_mt_generate((MtState*)d_states, (uint32_t)full, seclen, dtype, d_out, st);
-  if (e == hipSuccess && part) {
-    MtState* sp = (MtState*)d_states + full;
-    e = launch_mt_generate(sp, 1, part, dtype, (char*)d_out + full * seclen * es, st);
-  }
-  MtState* last = (MtState*)d_states + nb;
-  if (e == hipSuccess) e = launch_mt_generate(last, 1, n - T, dtype, (char*)d_out + T * es, st);
-  if (e == hipSuccess) {
-    hipLaunchKernelGGL(copy_state_kernel, dim3(1), dim3(256), 0, st, (uint32_t*)pin_out, (const uint32_t*)last, words);
-    e = hipGetLastError();
-  }
+  if (e == hipSuccess)
+    e = launch_mt_sections((const MtState*)d_base, (const MtState*)d_states, (MtState*)pin_out, (uint32_t)nst + 1,
+                           r0 + seclen(), seclen(), n, dtype, d_out, st);
   return finish();
 }
 
@@ -648,7 +643,7 @@ int prand_internal_mt_jump_sections(prand_ctx* c, void* d_states, uint32_t count
   js.dist = d_sections;
   js.nlimbs = 1;
   js.per_stream = 1;
-  js.mt_blocks = 1;
+  js.mt_blocks = kMtSections;
   hipError_t e = launch_mt_jump(c->T, (MtState*)d_states, count, js, nullptr, (hipStream_t)stream);
   return e == hipSuccess ? PRAND_OK : hipfail(c, e);
 }

@@ -229,7 +229,8 @@ __device__ __forceinline__ void gen_wave(uint32_t* mt, const MtState* in, MtStat
 }
 
 // A workgroup of kGroup threads generates n outputs of one stream: state *in,
-// outputs at out, advanced state to *sout (may be the same object as *in).
+// outputs at out, advanced state to *sout (may be the same object as *in; null:
+// not wanted).
 //
 // The sequence continues 227 words at a time, a word per thread: x_{i} is
 // x_{i-227}, this thread's word of the turn before, plus the pair x_{i-624},
@@ -300,6 +301,7 @@ __device__ __forceinline__ void gen_group(uint32_t* ring, const MtState* in, MtS
         });
     }
   }
+  if (!sout) return;
   const uint32_t last = (uint32_t)((624 * blocks + 57) % kRing);   // the last block's ring place
   for (uint32_t i = threadIdx.x; i < 624; i += kGroup) sout->mt[i] = ring[(last + i) % kRing];
   if (threadIdx.x == 0) {

@@ -59,6 +59,22 @@ __global__ void __launch_bounds__(kGroup) mt_generate_group_kernel(MtState* stat
   gen_group<DT>(ring, states + s, states + s, n, (char*)out + (uint64_t)s * n * es);
 }
 
+// sections of one stream, a workgroup each: section 0 starts from *base and has
+// `first` outputs, section j from states[j - 1] and has seclen, the last one
+// the rest; the state after it goes to *last
+template <int DT>
+__global__ void __launch_bounds__(kGroup) mt_sections_kernel(const MtState* base, const MtState* states, MtState* last,
+                                                             uint64_t first, uint64_t seclen, uint64_t n,
+                                                             void* __restrict__ out) {
+  __shared__ uint32_t ring[kRing];
+  constexpr int es = (DT == PRAND_F64) ? 8 : 4;
+  const uint32_t j = blockIdx.x;
+  const bool end = j + 1 == gridDim.x;
+  const uint64_t start = j ? first + (j - 1) * seclen : 0;
+  gen_group<DT>(ring, j ? states + (j - 1) : base, end ? last : nullptr, end ? n - start : (j ? seclen : first),
+                (char*)out + start * es);
+}
+
 // Streams up to which a workgroup each is faster than a wavefront each, us for
 // 100000 u32 / f64 per stream:
 //   streams       1      256      512     1000     1500     2048
@@ -366,11 +382,13 @@ __global__ void __launch_bounds__(64 * kParts) mt_jump_kernel(MtState* __restric
   const bool use_digits = digit_path && idx == 624;
   const uint64_t id = ids ? ids[s] : 0;
   // distances D in whole sections: from a block boundary, and D within the
-  // table, one whole-block polynomial per set bit of D (the state stays on a
-  // boundary); otherwise the distance in outputs, D (624 2^kMtBlkFirst),
-  // through the ladder
-  const bool sec_units = blocks && !ids;
-  const bool use_blocks = sec_units && idx == 624 && (N[0] >> kMtBlkPolys) == 0;
+  // table, one whole-block polynomial per nonzero hexadecimal digit of the
+  // distance in units (the state stays on a boundary); otherwise the distance
+  // in outputs, D (624 2^kMtBlkFirst), through the ladder
+  if (blocks == kMtUnits) idx = 624;
+  const bool sec_units = blocks == kMtSections && !ids;
+  const bool use_blocks = blocks == kMtUnits || (sec_units && idx == 624 && (N[0] >> kMtBlkPolys) == 0);
+  if (sec_units && use_blocks) N[0] <<= kMtBlkFirst - kMtBlkUnit;
   if (sec_units && !use_blocks) {
     constexpr uint64_t kSec = 624ull << kMtBlkFirst;
     const uint64_t d = N[0];
@@ -410,10 +428,15 @@ __global__ void __launch_bounds__(64 * kParts) mt_jump_kernel(MtState* __restric
           if (d) poly = dig8hi + ((size_t)j * 256 + d) * 624;
         }
       }
+    } else if (use_blocks) {
+      for (; pos < kMtBlkDigits && !poly; pos++) {
+        const uint32_t d = (uint32_t)(N[0] >> (4 * pos)) & 15u;
+        if (d) poly = blk + ((size_t)pos * 16 + d) * 624;
+      }
     } else {
       const int b = next_bit(N, pos);
       if (b >= 0) {
-        poly = (use_blocks ? blk : ladder) + (size_t)b * 624;
+        poly = ladder + (size_t)b * 624;
         pos = b + 1;
       }
     }
@@ -432,7 +455,7 @@ __global__ void __launch_bounds__(64 * kParts) mt_jump_kernel(MtState* __restric
 // D = first * kMtSection outputs on, a whole number of 624-word blocks, so
 // the state keeps the task's block grid and its place in the block (idx)
 // and equals the state sequential generation would reach.  x^D (one
-// whole-block ladder polynomial per set bit of the section number) moves
+// whole-block polynomial per nonzero digit of the distance) moves
 // every word of the array D places along the sequence but leaves only the
 // top bit of the oldest word exact; x^(-1) then steps the window one word
 // back, so that the array's words 1..623 are the exact words 0..622 of the
@@ -459,11 +482,11 @@ __global__ void __launch_bounds__(64 * kSectionParts)
   if (tl.first == 0) {
     for (int i = (int)threadIdx.x; i < 624; i += 64 * kSectionParts) dst->mt[i] = buf[i];
   } else {
-    // one polynomial per set bit of the section number, then x^(-1)
-    uint64_t sec = tl.first;
-    for (int b = 0, last = 0; !last; b++, sec >>= 1) {
-      last = sec == 0;
-      if (last || (sec & 1u)) apply_poly<kSectionParts>(buf, last ? inv : blk + (size_t)b * 624, lane, part);
+    // one polynomial per nonzero digit of the distance in units, then x^(-1)
+    const uint64_t units = tl.first << (kMtBlkFirst - kMtBlkUnit);
+    for (int k = 0; k <= kMtBlkDigits; k++) {
+      const uint32_t d = k < kMtBlkDigits ? (uint32_t)(units >> (4 * k)) & 15u : 1u;
+      if (d) apply_poly<kSectionParts>(buf, k < kMtBlkDigits ? blk + ((size_t)k * 16 + d) * 624 : inv, lane, part);
     }
     for (int i = (int)threadIdx.x; i < 623; i += 64 * kSectionParts) dst->mt[i] = buf[i + 1];
     if (threadIdx.x == 0) dst->mt[623] = recur(buf[0], buf[1], buf[397]);
@@ -498,6 +521,23 @@ hipError_t launch_mt_generate(MtState* states, uint32_t count, uint64_t n, int d
     case PRAND_U32: hipLaunchKernelGGL(mt_generate_kernel<PRAND_U32>, dim3(count), dim3(64), 0, st, states, count, n, out); break;
     case PRAND_F32: hipLaunchKernelGGL(mt_generate_kernel<PRAND_F32>, dim3(count), dim3(64), 0, st, states, count, n, out); break;
     default: hipLaunchKernelGGL(mt_generate_kernel<PRAND_F64>, dim3(count), dim3(64), 0, st, states, count, n, out); break;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_mt_sections(const MtState* base, const MtState* states, MtState* last, uint32_t count, uint64_t first,
+                              uint64_t seclen, uint64_t n, int dtype, void* out, hipStream_t st) {
+  const dim3 grid(count), block(kGroup);
+  switch (dtype) {
+    case PRAND_U32:
+      hipLaunchKernelGGL(mt_sections_kernel<PRAND_U32>, grid, block, 0, st, base, states, last, first, seclen, n, out);
+      break;
+    case PRAND_F32:
+      hipLaunchKernelGGL(mt_sections_kernel<PRAND_F32>, grid, block, 0, st, base, states, last, first, seclen, n, out);
+      break;
+    default:
+      hipLaunchKernelGGL(mt_sections_kernel<PRAND_F64>, grid, block, 0, st, base, states, last, first, seclen, n, out);
+      break;
   }
   return hipGetLastError();
 }

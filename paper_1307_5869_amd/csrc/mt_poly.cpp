@@ -298,7 +298,7 @@ bool mt_build_polys(uint32_t* ladder, int nladder, uint32_t* dig_lo, uint32_t* d
   return true;
 }
 
-bool mt_build_block_polys(int nladder, int first, int nblk, uint32_t* blk, uint32_t* inv) {
+bool mt_build_block_polys(int nladder, int first, int nblk, uint32_t* blk, uint32_t* inv, uint32_t* digits) {
   if (first + nblk + 9 > nladder) return false;
   Field F;
   if (!F.init()) return false;
@@ -306,13 +306,21 @@ bool mt_build_block_polys(int nladder, int first, int nblk, uint32_t* blk, uint3
   lad[0] = 2;   // x
   for (int b = 0; b + 1 < nladder; b++) F.mulmod(&lad[(size_t)b * kW], &lad[(size_t)b * kW], &lad[(size_t)(b + 1) * kW]);
   // 624 2^k = 2^(k+9) + 2^(k+6) + 2^(k+5) + 2^(k+4)
-  std::vector<uint64_t> g(kW), t(kW);
+  std::vector<uint64_t> g(kW), t(kW), p((size_t)16 * kW);   // p: the digits at hand
   for (int i = 0; i < nblk; i++) {
     const int k = first + i;
     F.mulmod(&lad[(size_t)(k + 9) * kW], &lad[(size_t)(k + 6) * kW], g.data());
     F.mulmod(g.data(), &lad[(size_t)(k + 5) * kW], t.data());
     F.mulmod(t.data(), &lad[(size_t)(k + 4) * kW], g.data());
     store(g.data(), blk + (size_t)i * kMtPolyWords);
+    if (!digits || nblk / 4 <= i / 4) continue;
+    // digits with this bit on top: its own, times those below
+    for (int d = 0; d < 1 << (i & 3); d++) {
+      uint64_t* const q = &p[(size_t)(d + (1 << (i & 3))) * kW];
+      if (d) F.mulmod(g.data(), &p[(size_t)d * kW], q);
+      else std::copy(g.begin(), g.end(), q);
+      store(q, digits + ((size_t)(i / 4) * 16 + d + (1 << (i & 3))) * kMtPolyWords);
+    }
   }
   // (phi - 1) / x: phi's bits 1 .. n moved down one place (degree n - 1)
   std::vector<uint64_t> q(kW, 0);

@@ -129,17 +129,19 @@ struct DeviceTables {
   uint32_t* mtdiglo = nullptr;  // [3][65536][624]: x^(d 2^(kMtDigitE + 16k)) mod phi
   uint32_t* mtdig8hi = nullptr; // [2][256][624]: x^(d 2^(kMtDigitE + 48 + 8j)) mod phi
   void* mttop = nullptr;        // [65536] MtState: the default state jumped t 2^(kMtDigitE + 48)
-  uint32_t* mtblk = nullptr;    // [kMtBlkPolys][624]: x^(624 2^(kMtBlkFirst + i)) mod phi
+  uint32_t* mtblk = nullptr;    // [kMtBlkDigits][16][624]: x^(d 624 2^(kMtBlkUnit + 4 k)) mod phi
   uint32_t* mtinv = nullptr;    // [624]: x^(-1) mod phi
   void* defaults = nullptr;   // default state of each generator, 11 x 2560 bytes
 };
 constexpr size_t kDefaultStride = 2560;
 // exponent of the MT19937 digit tables: the block-splitting block 2^432
 constexpr int kMtDigitE = 432;
-// whole-block MT19937 jumps for batched sections of 624 2^kMtBlkFirst outputs
-// (tasks up to 2^40 outputs: section numbers below 2^22)
+// whole-block MT19937 jumps, in units of 624 2^kMtBlkUnit outputs by hexadecimal
+// digits (calls and tasks of up to 2^40 outputs); sections of batched and
+// served tasks have 624 2^kMtBlkFirst outputs
+constexpr int kMtBlkUnit = 8, kMtBlkDigits = 6;
 constexpr int kMtBlkFirst = 10;
-constexpr int kMtBlkPolys = 22;
+constexpr int kMtBlkPolys = 4 * kMtBlkDigits - (kMtBlkFirst - kMtBlkUnit);   // bits of a section number
 
 // Order a wavefront's LDS writes before its later LDS reads (and reads before
 // later writes) when the LDS block is private to the wavefront: LDS
@@ -187,6 +189,7 @@ __device__ __forceinline__ void store_out16(void* p, uint4 v) {
 // shared distance.  `ids` + `block_e`: distance id * 2^block_e (GQ58.3: in
 // ensemble steps).  Exactly one of (dist, ids) is used; GM/GQ with neither:
 // every stream moves `fixed` outputs.
+constexpr int kMtSections = 1, kMtUnits = 2;
 struct JumpSpec {
   uint64_t fixed = 0;
   const uint64_t* dist = nullptr;
@@ -197,10 +200,12 @@ struct JumpSpec {
   // MT19937 block splitting from the default state: the states of the top
   // 16 bits of an id (DeviceTables::mttop), or null
   const void* mt_top = nullptr;
-  // MT19937, per-stream one-limb distances: counted in whole sections of
-  // 624 2^kMtBlkFirst outputs (jumped by the whole-block table, one
-  // polynomial per set bit, where the state sits on a block boundary and the
-  // distance is below 2^kMtBlkPolys sections; otherwise through the ladder)
+  // MT19937, per-stream one-limb distances.  kMtSections: counted in whole
+  // sections of 624 2^kMtBlkFirst outputs (by the whole-block digits where the
+  // state sits on a block boundary and the distance is below 2^kMtBlkPolys
+  // sections; otherwise through the ladder).  kMtUnits: counted in units of
+  // 624 2^kMtBlkUnit outputs from the end of the state's block, which is taken
+  // as used up (by the digits; fewer than 16^kMtBlkDigits units)
   int mt_blocks = 0;
 };
 
@@ -229,6 +234,11 @@ hipError_t launch_lfsr_generate(const DeviceTables& T, const LfsrState* sin, Lfs
 hipError_t launch_lfsr_jump(const DeviceTables& T, LfsrState* states, uint32_t count, const JumpSpec& js,
                             const LfsrState* base, hipStream_t st);
 
+// n outputs of one stream by `count` sections: the first from *base, `first`
+// outputs; the others from states[0 .. count - 2], seclen each, the last one the
+// rest; the advanced state to *last
+hipError_t launch_mt_sections(const MtState* base, const MtState* states, MtState* last, uint32_t count, uint64_t first,
+                              uint64_t seclen, uint64_t n, int dtype, void* out, hipStream_t st);
 hipError_t launch_mt_generate(MtState* states, uint32_t count, uint64_t n, int dtype, void* out,
                               hipStream_t st);
 hipError_t launch_mt_jump(const DeviceTables& T, MtState* states, uint32_t count, const JumpSpec& js,

@@ -414,7 +414,7 @@ int admit_and_init(prand_server* s, int li) {
     js.dist = ib.d_dist + d0;
     js.nlimbs = 1;
     js.per_stream = 1;
-    js.mt_blocks = 1;
+    js.mt_blocks = kMtSections;
     e = launch_mt_jump(s->ctx->T, (MtState*)r->secs[0].st[0], (uint32_t)r->secs.size(), js, nullptr, L.init_st);
     d0 += (uint32_t)r->secs.size();
   }

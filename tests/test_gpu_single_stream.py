@@ -18,7 +18,7 @@ GUARD = 256
 SIZES = [(g, n) for g in (P.MRG32K3A, P.LFSR113) for n in (1, 31, 32, 33, 8191, 8193, (1 << 23) - 1, (1 << 23) + 1)]
 SIZES += [(g, n) for g in range(P.GM19, P.NUM_GENERATORS) for n in (1, 255, 257, 289, 4097, 65537, 300007, 4200001)]
 SIZES += [(g, (1 << 26) + d) for g in (P.GM19, P.GM61) for d in (-1, 0)]
-SIZES += [(P.MT19937, n) for n in (1, 623, 625, 1 << 18, (1 << 18) + 1)]
+SIZES += [(P.MT19937, n) for n in (1, 623, 625, 1 << 18, (1 << 18) + 1, 624 * 513 - 1, 624 * 512, 624 * 512 + 1, 1000003)]
 
 
 @pytest.fixture(scope="module")
@@ -53,6 +53,23 @@ def test_device_output(ctx, oracle, gen, n):
             np.testing.assert_array_equal(raw[at:at + n * es].view(NPDT[dtype]), ref)
             assert (raw[:at] == 0x5A).all() and (raw[at + n * es:] == 0x5A).all()
             np.testing.assert_array_equal(st, end)
+
+
+@pytest.mark.parametrize("used", [1, 300, 623])
+def test_mt_sections_from_inside_a_block(ctx, oracle, used):
+    """the first section ends on the state's own block grid, wherever in its
+    block the state is"""
+    st = oracle.seed(P.MT19937, SEED)
+    oracle.generate(P.MT19937, st, used, P.U32)
+    for n in (624 * 256 + 624 - used, 300007, 624 * 512 + 624 - used, 624 * 512 + 625 - used):
+        ref = st.copy()
+        want = oracle.generate(P.MT19937, ref, n, P.U32)
+        for call in (ctx.generate, ctx.generate_noalloc):
+            s = st.copy()
+            out = torch.empty(n, dtype=torch.int32, device="cuda")
+            call(P.MT19937, s, P.U32, out, n)
+            np.testing.assert_array_equal(out.cpu().numpy().view(np.uint32), want)
+            np.testing.assert_array_equal(s, ref)
 
 
 @pytest.mark.parametrize("size", [1, 65535, 65536, 65537, 3 << 19, (3 << 19) + 1, (1 << 24) - 1, (1 << 24) + 5])
