@@ -113,7 +113,7 @@ static_assert(((1ull << 40) - 1) / kMtSection < (1ull << kMtBlkPolys), "MT19937 
 void batch_fill_defaults(prand_batch_config& c) { fill_defaults(c); }
 
 int batch_plan(const prand_task* tasks, uint32_t ntasks, const prand_batch_config& cfg, BatchPlan& plan,
-               uint64_t mt_section_min) {
+               uint64_t mt_section_min, bool may_cut) {
   std::vector<std::pair<double, BatchTile>> work[kBatchFamilies];
   for (double& c : plan.cost) c = 0;
   // Section lengths that the configuration leaves open: the lanes (262144) and
@@ -123,7 +123,10 @@ int batch_plan(const prand_task* tasks, uint32_t ntasks, const prand_batch_confi
   // in sections of 2048, 16 so; 2000 mixed tasks with GM/GQ tiles of 4096 outputs
   // 9.45 ms, of 16384 8.6.)
   uint64_t reg_total = 0, gm_total = 0;
+  double chip = 0;   // ms of the whole chip, 2^30-fold
   for (uint32_t k = 0; k < ntasks; k++) {
+    if (tasks[k].gen >= 0 && tasks[k].gen < PRAND_NUM_GENERATORS)
+      chip += (double)tasks[k].n * chip_cost(tasks[k].gen, tasks[k].dtype);
     if (is_reg(tasks[k].gen)) reg_total += std::min<uint64_t>(tasks[k].n, 1ull << 40);
     else if (tasks[k].gen != PRAND_MT19937) gm_total += std::min<uint64_t>(tasks[k].n, 1ull << 40);
   }
@@ -152,24 +155,29 @@ int batch_plan(const prand_task* tasks, uint32_t ntasks, const prand_batch_confi
     plan.cost[is_reg(t.gen) ? kListReg : (t.gen == PRAND_MT19937 ? kListMt : kListGm)] +=
         (double)n * chip_cost(t.gen, t.dtype);
     if (t.gen == PRAND_MT19937) {
-      // one wavefront per task, or, for a long task, per kMtSection-output
-      // section (each section starts from a jump of the task state)
+      // one workgroup per task, or, for a long task, per kMtSection-output
+      // section (each section starts from a jump of the task state).  Long: by
+      // itself, or where its workgroup's run (0.45 ns per output beside other
+      // work) is longer than the whole batch takes the chip and than three
+      // sections' (the starts take 0.2 ms): 451 tasks of 10^3 .. 10^7 outputs
+      // 4.9 ms whole, 1.9 so; 52 of them 5.0 and 0.9
       const uint64_t sec = kMtSection;
-      if (n <= std::max(sec, mt_section_min)) {
+      const bool cut = may_cut && n > 3 * sec && (double)n * 0.45e-6 * (double)(1u << 30) > chip;
+      if (n <= std::max(sec, mt_section_min) && !cut) {
         b.first = 0;
         b.seclen = n;
         b.nsec = 1;
         work[kFamMt].push_back({c * (double)n, b});
       } else {
-        // a section's start applies the whole-block ladder entry of every set
-        // bit of its number: the numbers must stay below 2^kMtBlkPolys
+        // a section's start applies a whole-block polynomial per nonzero digit
+        // of its number, which must stay below 2^kMtBlkPolys
         if ((n - 1) / sec >= (1ull << kMtBlkPolys)) return PRAND_ERANGE;
         b.kind = kTileMtSection;
         b.seclen = sec;
         b.nsec = 1;
         for (uint64_t f = 0; f * sec < n; f++) {
           b.first = f;
-          work[kFamMt].push_back({c * (double)std::min(sec, n - f * sec), b});
+          work[f && n <= mt_section_min ? kFamCut : kFamMt].push_back({c * (double)std::min(sec, n - f * sec), b});
         }
       }
       continue;
@@ -223,7 +231,7 @@ int batch_plan(const prand_task* tasks, uint32_t ntasks, const prand_batch_confi
         const uint64_t bytes = f == kFamReg ? 64 * state_size(gen) : (uint64_t)tl.nsec * state_size(gen);
         tl.starts = plan.scratch_bytes;
         plan.scratch_bytes += round_up(bytes, 64);
-        if (f == kFamMt) plan.n.mtsec++;
+        if (f == kFamMt || f == kFamCut) plan.n.mtsec++;
       }
     }
   }
@@ -237,6 +245,7 @@ int batch_plan(const prand_task* tasks, uint32_t ntasks, const prand_batch_confi
   plan.n.gm = (uint32_t)work[kFamGm].size();
   plan.n.mt = (uint32_t)work[kFamMt].size();
   plan.n.copy = (uint32_t)work[kFamCopy].size();
+  plan.n.cut = (uint32_t)work[kFamCut].size();
   return PRAND_OK;
 }
 
@@ -274,7 +283,7 @@ hipError_t enqueue_persistent(prand_batch* b, hipStream_t a) {
   const BatchTile* mt = b->d_tiles + n.with_starts();
   hipError_t e = launch_batch_reset(b->d_counters, a);
   if (e == hipSuccess) e = launch_batch_starts(T, b->d_tiles, n.with_starts(), b->d_tasks, b->d_scratch, w, a);
-  if (e == hipSuccess && n.mtsec) e = launch_batch_mt_starts(T, mt, n.mt, b->d_tasks, b->d_scratch, a);
+  if (e == hipSuccess && n.mtsec) e = launch_batch_mt_starts(T, mt, n.mt + n.copy + n.cut, b->d_tasks, b->d_scratch, a);
   auto main = [&](hipStream_t st) {
     if (e == hipSuccess)
       e = launch_batch_main(T, b->d_tiles, b->d_order + b->off_list[kListMt], b->n_list[kListMt],
@@ -375,7 +384,7 @@ int prand_batch_create(prand_ctx* c, const prand_task* h_tasks, uint32_t ntasks,
   if (cfg) conf = *cfg;
   fill_defaults(conf);
   BatchPlan plan;
-  int rc = batch_plan(h_tasks, ntasks, conf, plan, kMtBatchSectionMin);
+  int rc = batch_plan(h_tasks, ntasks, conf, plan, kMtBatchSectionMin, mt_tables_ready(c));
   if (rc) return rc;
   // MT19937 sections start from ladder jumps: the context's MT19937 tables
   if (plan.n.mtsec && (rc = ensure_mt_tables(c)) != PRAND_OK) return rc;

@@ -40,15 +40,17 @@ struct BatchTile {
                        // the batch scratch (MRG32K3A/LFSR113 and GM/GQ tiles)
 };
 
-// tiles are stored family by family: [reg | gm | mt | copy]
-// (MRG32K3A/LFSR113; GM/GQ; MT19937; n = 0)
+// tiles are stored family by family: [reg | gm | mt | copy | cut]
+// (MRG32K3A/LFSR113; GM/GQ; MT19937; n = 0; the further sections of MT19937
+// tasks that are cut because the rest of the batch is shorter than they are,
+// each of them one tile to the caller)
 struct BatchCounts {
-  uint32_t reg = 0, gm = 0, mt = 0, copy = 0;
-  uint32_t mtsec = 0;   // MT19937 section tiles among the mt ones
+  uint32_t reg = 0, gm = 0, mt = 0, copy = 0, cut = 0;
+  uint32_t mtsec = 0;   // MT19937 section tiles among the mt and cut ones
   uint32_t with_starts() const { return reg + gm; }
   uint32_t total() const { return with_starts() + mt + copy; }
 };
-constexpr int kFamReg = 0, kFamGm = 1, kFamMt = 2, kFamCopy = 3, kBatchFamilies = 4;
+constexpr int kFamReg = 0, kFamGm = 1, kFamMt = 2, kFamCopy = 3, kFamCut = 4, kBatchFamilies = 5;
 
 // lists of the persistent launch: MT19937 and copies, MRG32K3A/LFSR113, GM/GQ
 constexpr int kListMt = 0, kListReg = 1, kListGm = 2, kBatchLists = 3;
@@ -67,12 +69,12 @@ struct BatchPlan {
 void batch_fill_defaults(prand_batch_config& c);
 // cut tasks into tiles, family by family, each family longest first
 // (PRAND_OK or an error code); MT19937 tasks longer than mt_section_min
-// outputs are cut into kMtSection-output sections
+// outputs are cut into kMtSection-output sections, and (may_cut: the MT19937
+// tables are at hand) shorter ones that would outlast the rest of the batch
 int batch_plan(const prand_task* tasks, uint32_t ntasks, const prand_batch_config& cfg, BatchPlan& plan,
-               uint64_t mt_section_min);
-// MT19937 tasks of a batched launch above this many outputs (about 16 ms of
-// one wavefront) run as sections; below it the jumps cost more than the
-// wavefront's run, which the batch's other work covers
+               uint64_t mt_section_min, bool may_cut);
+// MT19937 tasks of a batched launch above this many outputs (about 6 ms of a
+// workgroup) run as sections
 constexpr uint64_t kMtBatchSectionMin = 1ull << 24;
 
 // the kernels of a batch, `waves` wavefronts (tiles) per workgroup

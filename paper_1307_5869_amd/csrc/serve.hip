@@ -459,7 +459,7 @@ int enqueue_iteration(prand_server* s, Lane& L, IterSlot& sl, bool* launched) {
   }
   BatchPlan& plan = s->plan;
   // MT19937 requests are sectioned at admission; their chunks stay whole
-  int rc = batch_plan(s->tasks.data(), (uint32_t)s->tasks.size(), s->bcfg, plan, UINT64_MAX);
+  int rc = batch_plan(s->tasks.data(), (uint32_t)s->tasks.size(), s->bcfg, plan, UINT64_MAX, false);
   if (rc) return rc;
   hipError_t e = grow_slot(s, sl, (uint32_t)s->tasks.size(), (uint32_t)plan.tiles.size(), plan.scratch_bytes);
   if (e != hipSuccess) return hipfail(s->ctx, e);
