@@ -160,10 +160,13 @@ hipError_t launch_jump_g(const DeviceTables& T, GmState* states, uint32_t count,
 
 // Sections per stream.  With at least kFillWaves wavefronts of whole streams
 // the chip is full (four to five per SIMD, twice over); fewer are cut into
-// sections of whole state advances, as long as there stay enough of them,
-// but no shorter than eight advances (a section's start is one ladder matrix
-// per set bit of its number, about the time of two advances).  Powers of two
-// keep the set bits of the starts few.
+// sections of whole state advances, as long as there stay enough of them: of
+// eight advances (a section's start is one matrix per nonzero byte of its
+// distance, about the time of two advances), or down to one where there would
+// be less than a wavefront per SIMD, for streams of at least three (the states
+// then move on by a launch of their own: 4 us.  196 GM55 streams of 5148 u32 in
+// sections of eight advances 56 us, of one 20; 61 GM31 of 2792 36 us whole, 15
+// so; 100 GM61 of 1000 24 and 16)
 constexpr uint64_t kFillWaves = 8192;
 
 template <int G, int DT>
@@ -178,7 +181,8 @@ hipError_t launch_gen(const DeviceTables& T, GmState* states, uint32_t count, ui
       return hipGetLastError();
     }
   }
-  if ((uint64_t)count >= kFillWaves * Q || n < 2 * seclen) {
+  while (seclen > unit && (uint64_t)count * ((n + seclen - 1) / seclen) < 1024 * Q) seclen /= 2;
+  if ((uint64_t)count >= kFillWaves * Q || n < 2 * seclen || n < 3 * unit) {
     const uint32_t blocks = (uint32_t)(((count + Q - 1) / Q + 3) / 4);
     hipLaunchKernelGGL((gmx_kernel<G, DT, false>), dim3(blocks), dim3(256), 0, st, states, states, count, n, 1u, n,
                        (char*)out, T.gmx, T.gm);

@@ -41,7 +41,8 @@ def check(ctx, oracle, gen, states, n, dtype):
         assert np.array_equal(got_st[i], st), f"{P.NAMES[gen]} state {i} of {count}, n {n}"
 
 
-@pytest.mark.parametrize("n", [1, 31, 33, 64, 65, 255, 256, 257, 511, 513, 4607, 4608, 5000, 9216, 20011])
+@pytest.mark.parametrize("n", [1, 31, 33, 64, 65, 127, 128, 255, 256, 257, 511, 513, 767, 768, 863, 864, 1025, 2881, 4607, 4608, 5000,
+                               9216, 20011])
 @pytest.mark.parametrize("gen", GENS)
 def test_lengths(ctx, oracle, gen, n):
     count = 5 if n < 1000 else 2
