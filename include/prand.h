@@ -204,11 +204,11 @@ int prand_generate_array(prand_ctx* ctx, int gen, void* h_state, int dtype, void
    each d_states[s] is advanced by n_per_stream in place.  PRAND_ERANGE when
    n_per_stream > 2^40 or the output exceeds 2^50 bytes.  Asynchronous on
    `stream`, except that the first MRG32K3A or LFSR113 call with a given
-   section length (a function of count and n_per_stream) builds that length's
-   section-start table (up to 32 KB of device memory, kept until the context
+   section length (a function of count and n_per_stream; short calls have none)
+   builds that length's section-start table (up to 32 KB of device memory, kept until the context
    is destroyed; a blocking copy), unless `stream` is being captured into a
    graph: calls under capture, and calls past 64 such lengths per generator,
-   jump every section through the ladder instead (same outputs, more work). */
+   jump every section by the byte tables instead (same outputs, more work). */
 int prand_generate_streams(prand_ctx* ctx, int gen, void* d_states, uint32_t count,
                            uint64_t n_per_stream, int dtype, void* d_out, void* stream);
 
@@ -315,7 +315,7 @@ typedef struct prand_server_config {
                                reserved by prand_server_create */
   uint64_t iter_numbers;    /* outputs per loop iteration over all requests (0: 2^28) */
   uint64_t min_chunk;       /* smallest per-request share of an iteration (0: 2^16) */
-  uint64_t mt_chunk;        /* largest MT19937 chunk per iteration (one wavefront each; 0: 2^20) */
+  uint64_t mt_chunk;        /* largest MT19937 chunk per iteration (one workgroup each; 0: 2^20) */
   uint64_t mt_section;      /* MT19937 requests longer than this are cut into up to 256 sections of
                                624 * 2^k outputs (k >= 10) that start from jumped states and run in
                                parallel (0: 2^20) */

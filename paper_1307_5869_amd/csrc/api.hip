@@ -223,7 +223,7 @@ hipError_t launch_jump(prand_ctx* c, int gen, void* states, uint32_t count, cons
 // seclen: looked up, or built on the host and uploaded (an allocation and a
 // blocking copy, once per length; not while the stream is being captured, and
 // at most kMaxSectionTables lengths per generator).
-// Null when there is none: the kernel then jumps through the ladder.
+// Null when there is none: the kernel then jumps by the byte tables.
 constexpr size_t kMaxSectionTables = 64;
 
 const uint32_t* section_table(prand_ctx* c, int k, uint64_t seclen, hipStream_t st) {

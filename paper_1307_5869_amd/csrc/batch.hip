@@ -106,9 +106,9 @@ bool is_reg(int g) { return g == PRAND_MRG32K3A || g == PRAND_LFSR113; }
 
 namespace prand {
 
-// tasks of up to 2^40 outputs (checked below) never need a whole-block ladder
-// entry beyond the table
-static_assert(((1ull << 40) - 1) / kMtSection < (1ull << kMtBlkPolys), "MT19937 block ladder too short");
+// the section starts of tasks of up to 2^40 outputs (checked below) lie within
+// the reach of the whole-block polynomials
+static_assert(((1ull << 40) - 1) / kMtSection < (1ull << kMtBlkPolys), "MT19937 block polynomials too few");
 
 void batch_fill_defaults(prand_batch_config& c) { fill_defaults(c); }
 
@@ -386,7 +386,7 @@ int prand_batch_create(prand_ctx* c, const prand_task* h_tasks, uint32_t ntasks,
   BatchPlan plan;
   int rc = batch_plan(h_tasks, ntasks, conf, plan, kMtBatchSectionMin, mt_tables_ready(c));
   if (rc) return rc;
-  // MT19937 sections start from ladder jumps: the context's MT19937 tables
+  // MT19937 sections start from whole-block jumps: the context's MT19937 tables
   if (plan.n.mtsec && (rc = ensure_mt_tables(c)) != PRAND_OK) return rc;
   DeviceGuard g(c->device);
   prand_batch* b = new (std::nothrow) prand_batch;

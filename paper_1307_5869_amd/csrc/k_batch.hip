@@ -13,7 +13,7 @@
 //  - batch_starts_kernel jumps every MRG32K3A/LFSR113/GM/GQ section to its
 //    start and writes the state to the batch's scratch area (the jump code
 //    needs many registers, so it runs apart from the generation loops);
-//    sections of MT19937 tasks above 2^24 outputs get theirs from
+//    sections of long MT19937 tasks (batch.hip) get theirs from
 //    mt_section_start_kernel (k_mt19937.hip);
 //  - two persistent kernels, each launched with as many workgroups as the
 //    chip holds at once, which take the next tile of a list from a device
@@ -26,7 +26,7 @@
 // Each tile runs the same routines as the one-generator kernels; the GM/GQ ones
 // with the element type as a value, so that the kernel holds each generator's
 // code once.  2000 tasks of 10^3 .. 10^7 outputs of all generators: 20.9 ms with
-// a ballot or a lane per section for GM/GQ and a wavefront per MT19937 task, 8.5
+// a ballot or a lane per section for GM/GQ and a wavefront per MT19937 task, 7.0
 // so.
 //
 // The serving loop keeps one grid kernel per family (batch_reg_kernel,

@@ -14,6 +14,8 @@
 // of the result is the XOR of seq[i + t] over the set coefficients i, seq
 // being the raw-word sequence continued from the state.  A distance is applied
 // as one polynomial x^(2^b) mod phi (from the context ladder) per set bit b;
+// sections on block boundaries start by x^(d 624 2^(8 + 4 j)) mod phi per
+// nonzero hexadecimal digit d of their distance in units of 2^8 blocks;
 // block splitting by id * 2^432 from a block-aligned state uses the context's
 // digit tables x^(d 2^(432 + position)) mod phi instead: three 16-bit digits
 // for the low 48 bits of the id and two bytes for the top 16 bits; from the

@@ -27,7 +27,7 @@ constexpr uint32_t kTileCopy = 1;   // n = 0: copy state_in to state_out
 constexpr uint32_t kTileMtSection = 2;
 constexpr uint64_t kMtSection = 624ull << kMtBlkFirst;
 
-// the work of one wavefront
+// the work of one wavefront (an MT19937 tile's: of one workgroup)
 struct BatchTile {
   uint32_t task;
   uint32_t kind;
@@ -88,7 +88,7 @@ hipError_t launch_batch_gm(const DeviceTables& T, const BatchTile* tiles, uint32
 hipError_t launch_batch_mt(const BatchTile* tiles, uint32_t ntiles, const BatchTask* tasks, char* scratch,
                            hipStream_t st);
 // start states of the MT19937 section tiles among tiles[0 .. ntiles): the
-// task state moved first * kMtSection outputs on (one wavefront each)
+// task state moved first * kMtSection outputs on (one workgroup each)
 hipError_t launch_batch_mt_starts(const DeviceTables& T, const BatchTile* tiles, uint32_t ntiles,
                                   const BatchTask* tasks, char* scratch, hipStream_t st);
 // persistent launch: one tile counter per list, cleared by a small kernel

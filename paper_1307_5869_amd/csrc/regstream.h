@@ -179,7 +179,7 @@ __device__ __forceinline__ void regstream_wave(uint32_t* rows, bool live, const 
 // [j * seclen, min((j + 1) * seclen, n)) and sit in one wavefront (nsec <= 64),
 // so the state read of every section precedes the write-back of the last.
 // With sectab (the section-start table of seclen), section j > 0 starts from
-// row j - 1 of it, else from ladder jumps.
+// row j - 1 of it, else from jumps by the byte tables.
 template <class G, int DT, int CW>
 __global__ void __launch_bounds__(256) regstream_kernel(const typename G::State* sin, typename G::State* sout,
                                                         uint32_t count, uint64_t n, int nsec_log2, uint64_t seclen,

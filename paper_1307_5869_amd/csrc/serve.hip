@@ -1,8 +1,8 @@
 // Serving loop: continuous batching of generate requests over one device.
 //
 // One worker thread owns the device work.  Requests are served in two lanes
-// that run concurrently on their own HIP streams: MT19937 (one wavefront per
-// chunk, so its chunks are long) and every other generator.  Each turn of
+// that run concurrently on their own HIP streams: MT19937 (one workgroup per
+// chunk, so its chunks take long) and every other generator.  Each turn of
 // the worker's loop it
 //  1. takes newly submitted requests into a FIFO of waiting requests and
 //     applies the releases clients have made;
@@ -131,8 +131,8 @@ struct Req {
 };
 
 constexpr uint32_t kMaxSections = 256;
-// shortest MT19937 section: 624 * 2^kMinSectionLog2 outputs, about 1.3 ms
-// on the one wavefront that generates a section
+// shortest MT19937 section: 624 * 2^kMinSectionLog2 outputs, about 0.25 ms
+// on the one workgroup that generates a section
 constexpr int kMinSectionLog2 = 10;
 static_assert(kMinSectionLog2 >= kMtBlkFirst, "sections are whole-block-table units");
 
