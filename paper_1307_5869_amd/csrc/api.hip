@@ -269,7 +269,11 @@ const uint32_t* section_table(prand_ctx* c, int k, uint64_t seclen, hipStream_t 
 // in 2^22 lanes (more, shorter sections measured faster: the 64 runs of a
 // wavefront then lie close together in the output; 10007 streams of 4999 f64
 // in sections of 2 KB 112 us, of 1 KB 101-109, of u32 in sections of 512 bytes
-// 72-74, 75 in those of 1 KB).
+// 72-74, 75 in those of 1 KB).  LFSR113's start costs as much as a hundred
+// outputs: f64 sections have 240 or more where a stream's output is 8 KB at
+// most, so that its runs lie together in any case (65536 streams of 600 f64 in
+// sections of 150 79 us, of 300 72; but of 5001 545 us in sections of 157, 555
+// of 313, and 10007 of 4999 102 and 107).
 void short_plan(int gen, uint32_t count, uint64_t n, bool lines, int& nsec_log2, uint64_t& seclen) {
   const uint64_t max_lanes = gen == PRAND_MRG32K3A ? 1ull << 18 : 1ull << 16;
   nsec_log2 = 0;
@@ -281,9 +285,10 @@ void short_plan(int gen, uint32_t count, uint64_t n, bool lines, int& nsec_log2,
   const uint64_t reach = nsec_log2 && !lines ? n + 31 : n;   // room to begin the sections on lines
   seclen = (((reach + (1ull << nsec_log2) - 1) >> nsec_log2) + 31) & ~31ull;
 }
-void long_plan(uint32_t count, uint64_t n, int dtype, int& nsec_log2, uint64_t& seclen) {
+void long_plan(int gen, uint32_t count, uint64_t n, int dtype, int& nsec_log2, uint64_t& seclen) {
+  const uint64_t least = gen == PRAND_LFSR113 && dtype == PRAND_F64 && n <= 1024 ? 1920 : 1024;
   nsec_log2 = 0;
-  while (nsec_log2 < 6 && ((uint64_t)count << (nsec_log2 + 1)) <= (1ull << 22) && (n >> (nsec_log2 + 1)) * elem_bytes(dtype) >= 1024)
+  while (nsec_log2 < 6 && ((uint64_t)count << (nsec_log2 + 1)) <= (1ull << 22) && (n >> (nsec_log2 + 1)) * elem_bytes(dtype) >= least)
     nsec_log2++;
   seclen = (((n + (1ull << nsec_log2) - 1) >> nsec_log2) + 31) & ~31ull;
 }
@@ -298,7 +303,7 @@ hipError_t launch_streams(prand_ctx* c, int gen, void* states, uint32_t count, u
     short_plan(gen, count, n, ((uintptr_t)out | n * elem_bytes(dtype)) % 128 == 0, nsec_log2, seclen);
     const uint32_t* tab = nullptr;
     if (seclen > 256) {
-      long_plan(count, n, dtype, nsec_log2, seclen);
+      long_plan(gen, count, n, dtype, nsec_log2, seclen);
       tab = nsec_log2 ? section_table(c, k, seclen, st) : nullptr;
     }
     if (gen == PRAND_MRG32K3A)
