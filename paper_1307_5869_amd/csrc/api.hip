@@ -653,6 +653,23 @@ int prand_internal_mt_jump_sections(prand_ctx* c, void* d_states, uint32_t count
   return e == hipSuccess ? PRAND_OK : hipfail(c, e);
 }
 
+// Not in the public header (a test hook): the ranges in which a launch over
+// `count` streams goes out (launch_ranges); returns their number, the first
+// `max` of them in ranges[3 i ..]: first stream, streams, workgroups.
+int prand_internal_launch_ranges(uint64_t count, uint32_t block, uint32_t per_block, uint64_t* ranges, int max) {
+  int k = 0;
+  (void)launch_ranges(count, block, per_block, [&](uint64_t first, uint32_t m, uint32_t blocks) {
+    if (k < max) {
+      ranges[3 * k] = first;
+      ranges[3 * k + 1] = m;
+      ranges[3 * k + 2] = blocks;
+    }
+    k++;
+    return hipSuccess;
+  });
+  return k;
+}
+
 int prand_skipahead_dev(prand_ctx* c, int gen, void* d_states, uint32_t count, const uint64_t* d_dist, int nlimbs,
                         int per_stream, void* stream) {
   if (!c || !valid_gen(gen) || nlimbs < 0 || nlimbs > kMaxLimbs) return PRAND_EINVAL;

@@ -386,33 +386,34 @@ hipError_t launch_batch_reg_persistent(int cw, const BatchTile* tiles, const uin
 
 hipError_t launch_batch_starts(const DeviceTables& T, const BatchTile* tiles, uint32_t ntiles, const BatchTask* tasks,
                                char* scratch, uint32_t waves, hipStream_t st) {
-  if (!ntiles) return hipSuccess;
-  hipLaunchKernelGGL(batch_starts_kernel, dim3(blocks_for(ntiles, waves)), dim3(64 * waves), 0, st, tiles, ntiles,
-                     tasks, scratch, T);
-  return hipGetLastError();
+  return launch_ranges(ntiles, 64 * waves, waves, [&](uint64_t first, uint32_t m, uint32_t blocks) {
+    hipLaunchKernelGGL(batch_starts_kernel, dim3(blocks), dim3(64 * waves), 0, st, tiles + first, m, tasks, scratch, T);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_batch_reg(const BatchTile* tiles, uint32_t ntiles, const BatchTask* tasks, const char* scratch,
                             uint32_t waves, hipStream_t st) {
-  if (!ntiles) return hipSuccess;
-  hipLaunchKernelGGL(batch_reg_kernel, dim3(blocks_for(ntiles, waves)), dim3(64 * waves), 0, st, tiles, ntiles,
-                     tasks, scratch);
-  return hipGetLastError();
+  return launch_ranges(ntiles, 64 * waves, waves, [&](uint64_t first, uint32_t m, uint32_t blocks) {
+    hipLaunchKernelGGL(batch_reg_kernel, dim3(blocks), dim3(64 * waves), 0, st, tiles + first, m, tasks, scratch);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_batch_gm(const DeviceTables& T, const BatchTile* tiles, uint32_t ntiles, const BatchTask* tasks,
                            const char* scratch, uint32_t waves, hipStream_t st) {
-  if (!ntiles) return hipSuccess;
-  hipLaunchKernelGGL(batch_gmx_kernel, dim3(blocks_for(ntiles, waves)), dim3(64 * waves), 0, st, tiles, ntiles, tasks,
-                     scratch, T.gmx);
-  return hipGetLastError();
+  return launch_ranges(ntiles, 64 * waves, waves, [&](uint64_t first, uint32_t m, uint32_t blocks) {
+    hipLaunchKernelGGL(batch_gmx_kernel, dim3(blocks), dim3(64 * waves), 0, st, tiles + first, m, tasks, scratch, T.gmx);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_batch_mt(const BatchTile* tiles, uint32_t ntiles, const BatchTask* tasks, char* scratch,
                            hipStream_t st) {
-  if (!ntiles) return hipSuccess;
-  hipLaunchKernelGGL(batch_mt_kernel, dim3(ntiles), dim3(mt::kGroup), 0, st, tiles, tasks, scratch);
-  return hipGetLastError();
+  return launch_ranges(ntiles, mt::kGroup, 1, [&](uint64_t first, uint32_t, uint32_t blocks) {
+    hipLaunchKernelGGL(batch_mt_kernel, dim3(blocks), dim3(mt::kGroup), 0, st, tiles + first, tasks, scratch);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_batch_serial(const DeviceTables& T, const BatchTile* tiles, const BatchCounts& n,

@@ -150,12 +150,14 @@ __global__ void __launch_bounds__(256) gm_jump_kernel(GmState* __restrict__ stat
 template <int G>
 hipError_t launch_jump_g(const DeviceTables& T, GmState* states, uint32_t count, const JumpSpec& js,
                          const GmState* base, hipStream_t st) {
-  const uint64_t lanes = (uint64_t)count * jump_lanes<G>();
-  const uint32_t blocks = (uint32_t)((lanes + 255) / 256);
-  hipLaunchKernelGGL(gm_jump_kernel<G>, dim3(blocks), dim3(256), 0, st, states, count, js.dist, js.nlimbs,
-                     js.per_stream, js.fixed, js.ids, js.block_e, base, T.gm,
-                     T.gmbyte ? T.gmbyte + (size_t)G * 8 * 256 * 4 : nullptr, T.gmneg ? T.gmneg + (size_t)G * 4 : nullptr);
-  return hipGetLastError();
+  return launch_ranges(count, 256, 256 / jump_lanes<G>(), [&](uint64_t first, uint32_t m, uint32_t blocks) {
+    hipLaunchKernelGGL(gm_jump_kernel<G>, dim3(blocks), dim3(256), 0, st, states + first, m,
+                       js.per_stream ? js.dist + first * js.nlimbs : js.dist, js.nlimbs, js.per_stream, js.fixed,
+                       js.ids ? js.ids + first : nullptr, js.block_e, base, T.gm,
+                       T.gmbyte ? T.gmbyte + (size_t)G * 8 * 256 * 4 : nullptr,
+                       T.gmneg ? T.gmneg + (size_t)G * 4 : nullptr);
+    return hipGetLastError();
+  });
 }
 
 // Sections per stream.  With at least kFillWaves wavefronts of whole streams
@@ -171,26 +173,28 @@ constexpr uint64_t kFillWaves = 8192;
 
 template <int G, int DT>
 hipError_t launch_gen(const DeviceTables& T, GmState* states, uint32_t count, uint64_t n, void* out, hipStream_t st) {
-  constexpr uint64_t Q = Mx<G>::Q;
+  constexpr uint64_t Q = Mx<G>::Q, es = DT == PRAND_F64 ? 8 : 4;
   constexpr uint64_t unit = G == 6 ? kGmxSteps / 8 * 9 : kGmxSteps;   // outputs of a state advance
   uint64_t seclen = 8 * unit;
   if constexpr (Mx<G>::S == 32) {
     if (n < kBallotOutputs) {
-      const uint32_t blocks = (uint32_t)(((uint64_t)count * 32 + 255) / 256);
-      hipLaunchKernelGGL((gm_gen32_kernel<G, DT>), dim3(blocks), dim3(256), 0, st, states, count, n, out);
-      return hipGetLastError();
+      return launch_ranges(count, 256, 8, [&](uint64_t first, uint32_t m, uint32_t blocks) {
+        hipLaunchKernelGGL((gm_gen32_kernel<G, DT>), dim3(blocks), dim3(256), 0, st, states + first, m, n,
+                           (char*)out + first * n * es);
+        return hipGetLastError();
+      });
     }
   }
   while (seclen > unit && (uint64_t)count * ((n + seclen - 1) / seclen) < 1024 * Q) seclen /= 2;
   if ((uint64_t)count >= kFillWaves * Q || n < 2 * seclen || n < 3 * unit) {
-    const uint32_t blocks = (uint32_t)(((count + Q - 1) / Q + 3) / 4);
-    hipLaunchKernelGGL((gmx_kernel<G, DT, false>), dim3(blocks), dim3(256), 0, st, states, states, count, n, 1u, n,
-                       (char*)out, T.gmx, T.gm);
-    return hipGetLastError();
+    return launch_ranges(count, 256, 4 * Q, [&](uint64_t first, uint32_t m, uint32_t blocks) {
+      hipLaunchKernelGGL((gmx_kernel<G, DT, false>), dim3(blocks), dim3(256), 0, st, states + first, states + first, m,
+                         n, 1u, n, (char*)out + first * n * es, T.gmx, T.gm);
+      return hipGetLastError();
+    });
   }
+  // (at most 2 kFillWaves wavefronts from here on)
   while ((uint64_t)count * ((n + 2 * seclen - 1) / (2 * seclen)) >= kFillWaves * Q) seclen *= 2;
-  // the grid stays below 2^31 workgroups
-  while ((n + seclen - 1) / seclen > (1ull << 30) / count) seclen *= 2;
   const uint32_t nsec = (uint32_t)((n + seclen - 1) / seclen);
   const uint32_t blocks = (uint32_t)((((uint64_t)count * nsec + Q - 1) / Q + 3) / 4);
   hipLaunchKernelGGL((gmx_kernel<G, DT, true>), dim3(blocks), dim3(256), 0, st, states, nullptr, count, n, nsec, seclen,

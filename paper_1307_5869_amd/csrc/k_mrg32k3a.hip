@@ -60,10 +60,12 @@ hipError_t launch_mrg_single(const DeviceTables& T, const MrgState* base, MrgSta
 
 hipError_t launch_mrg_jump(const DeviceTables& T, MrgState* states, uint32_t count, const JumpSpec& js,
                            const MrgState* base, hipStream_t st) {
-  const uint32_t blocks = (count + 255) / 256;
-  hipLaunchKernelGGL(mrg_jump_kernel, dim3(blocks), dim3(256), 0, st, states, count, js.dist, js.nlimbs,
-                     js.per_stream, js.ids, js.block_e, base, T.mrg);
-  return hipGetLastError();
+  return launch_ranges(count, 256, 256, [&](uint64_t first, uint32_t m, uint32_t blocks) {
+    hipLaunchKernelGGL(mrg_jump_kernel, dim3(blocks), dim3(256), 0, st, states + first, m,
+                       js.per_stream ? js.dist + first * js.nlimbs : js.dist, js.nlimbs, js.per_stream,
+                       js.ids ? js.ids + first : nullptr, js.block_e, base, T.mrg);
+    return hipGetLastError();
+  });
 }
 
 }  // namespace prand

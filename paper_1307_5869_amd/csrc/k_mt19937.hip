@@ -503,10 +503,11 @@ __global__ void __launch_bounds__(64 * kSectionParts)
 
 hipError_t launch_batch_mt_starts(const DeviceTables& T, const BatchTile* tiles, uint32_t ntiles,
                                   const BatchTask* tasks, char* scratch, hipStream_t st) {
-  if (!ntiles) return hipSuccess;
-  hipLaunchKernelGGL(mt_section_start_kernel, dim3(ntiles), dim3(64 * kSectionParts), 0, st, tiles, ntiles, tasks, scratch, T.mtblk,
-                     T.mtinv);
-  return hipGetLastError();
+  return launch_ranges(ntiles, 64 * kSectionParts, 1, [&](uint64_t first, uint32_t m, uint32_t blocks) {
+    hipLaunchKernelGGL(mt_section_start_kernel, dim3(blocks), dim3(64 * kSectionParts), 0, st, tiles + first, m, tasks,
+                       scratch, T.mtblk, T.mtinv);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_mt_generate(MtState* states, uint32_t count, uint64_t n, int dtype, void* out, hipStream_t st) {
@@ -519,12 +520,17 @@ hipError_t launch_mt_generate(MtState* states, uint32_t count, uint64_t n, int d
     }
     return hipGetLastError();
   }
-  switch (dtype) {
-    case PRAND_U32: hipLaunchKernelGGL(mt_generate_kernel<PRAND_U32>, dim3(count), dim3(64), 0, st, states, count, n, out); break;
-    case PRAND_F32: hipLaunchKernelGGL(mt_generate_kernel<PRAND_F32>, dim3(count), dim3(64), 0, st, states, count, n, out); break;
-    default: hipLaunchKernelGGL(mt_generate_kernel<PRAND_F64>, dim3(count), dim3(64), 0, st, states, count, n, out); break;
-  }
-  return hipGetLastError();
+  return launch_ranges(count, 64, 1, [&](uint64_t first, uint32_t m, uint32_t blocks) {
+    const dim3 grid(blocks), block(64);
+    MtState* const s = states + first;
+    char* const o = (char*)out + first * n * (dtype == PRAND_F64 ? 8 : 4);
+    switch (dtype) {
+      case PRAND_U32: hipLaunchKernelGGL(mt_generate_kernel<PRAND_U32>, grid, block, 0, st, s, m, n, o); break;
+      case PRAND_F32: hipLaunchKernelGGL(mt_generate_kernel<PRAND_F32>, grid, block, 0, st, s, m, n, o); break;
+      default: hipLaunchKernelGGL(mt_generate_kernel<PRAND_F64>, grid, block, 0, st, s, m, n, o); break;
+    }
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_mt_sections(const MtState* base, const MtState* states, MtState* last, uint32_t count, uint64_t first,
@@ -548,19 +554,17 @@ hipError_t launch_mt_jump(const DeviceTables& T, MtState* states, uint32_t count
                           const MtState* base, hipStream_t st) {
   // whole-section distances: one limb per stream
   if (js.mt_blocks && (js.ids || !js.per_stream || js.nlimbs != 1)) return hipErrorInvalidValue;
-  if (count <= kMtSplit16MaxCount)
-    hipLaunchKernelGGL(mt_jump_kernel<16>, dim3(count), dim3(64 * 16), 0, st, states, count, js.dist, js.nlimbs,
-                       js.per_stream, js.ids, js.block_e, base, (const MtState*)js.mt_top, T.mt, T.mtdiglo, T.mtdig8hi,
-                       T.mtblk, js.mt_blocks);
-  else if (count <= kMtSplit8MaxCount)
-    hipLaunchKernelGGL(mt_jump_kernel<8>, dim3(count), dim3(64 * 8), 0, st, states, count, js.dist, js.nlimbs,
-                       js.per_stream, js.ids, js.block_e, base, (const MtState*)js.mt_top, T.mt, T.mtdiglo, T.mtdig8hi,
-                       T.mtblk, js.mt_blocks);
-  else
-    hipLaunchKernelGGL(mt_jump_kernel<4>, dim3(count), dim3(64 * 4), 0, st, states, count, js.dist, js.nlimbs,
-                       js.per_stream, js.ids, js.block_e, base, (const MtState*)js.mt_top, T.mt, T.mtdiglo, T.mtdig8hi,
-                       T.mtblk, js.mt_blocks);
-  return hipGetLastError();
+  const uint32_t parts = count <= kMtSplit16MaxCount ? 16 : count <= kMtSplit8MaxCount ? 8 : 4;
+  return launch_ranges(count, 64 * parts, 1, [&](uint64_t first, uint32_t m, uint32_t blocks) {
+    auto launch = [&](auto* kernel) {
+      hipLaunchKernelGGL(kernel, dim3(blocks), dim3(64 * parts), 0, st, states + first, m,
+                         js.per_stream ? js.dist + first * js.nlimbs : js.dist, js.nlimbs, js.per_stream,
+                         js.ids ? js.ids + first : nullptr, js.block_e, base, (const MtState*)js.mt_top, T.mt, T.mtdiglo,
+                         T.mtdig8hi, T.mtblk, js.mt_blocks);
+      return hipGetLastError();
+    };
+    return parts == 16 ? launch(mt_jump_kernel<16>) : parts == 8 ? launch(mt_jump_kernel<8>) : launch(mt_jump_kernel<4>);
+  });
 }
 
 }  // namespace prand

@@ -138,9 +138,11 @@ __global__ void __launch_bounds__(256) seed_kernel(int gen, const uint64_t* __re
 void seed_host(int gen, uint64_t seed, void* h_state) { seed_one(gen, seed, h_state); }
 
 hipError_t launch_seed(int gen, const uint64_t* seeds, uint32_t count, void* states, hipStream_t st) {
-  if (count == 0) return hipSuccess;
-  hipLaunchKernelGGL(seed_kernel, dim3((count + 255) / 256), dim3(256), 0, st, gen, seeds, count, states);
-  return hipGetLastError();
+  return launch_ranges(count, 256, 256, [&](uint64_t first, uint32_t m, uint32_t blocks) {
+    hipLaunchKernelGGL(seed_kernel, dim3(blocks), dim3(256), 0, st, gen, seeds + first, m,
+                       (char*)states + first * state_size(gen));
+    return hipGetLastError();
+  });
 }
 
 }  // namespace prand

@@ -184,6 +184,21 @@ __device__ __forceinline__ void store_out16(void* p, uint4 v) {
   }
 }
 
+// A dispatch holds fewer than 2^32 work-items.  Launches of more than one per
+// stream (or tile) go out in ranges of streams that each fit: `per_block` of them
+// to a workgroup of `block` threads; launch(first, m, blocks) -> hipError_t takes
+// streams first .. first + m - 1.
+template <class F>
+hipError_t launch_ranges(uint64_t count, uint32_t block, uint32_t per_block, F&& launch) {
+  const uint64_t most = (uint64_t)(0xFFFFFFFFu / block) * per_block;
+  hipError_t e = hipSuccess;
+  for (uint64_t first = 0; first < count && e == hipSuccess; first += most) {
+    const uint64_t m = count - first < most ? count - first : most;
+    e = launch(first, (uint32_t)m, (uint32_t)((m + per_block - 1) / per_block));
+  }
+  return e;
+}
+
 // ---- launchers (one per kernel family); all enqueue on `st` ----
 // Distances: `dist` holds nlimbs limbs per stream when per_stream, else one
 // shared distance.  `ids` + `block_e`: distance id * 2^block_e (GQ58.3: in

@@ -291,23 +291,16 @@ template <class G, int CW>
 hipError_t launch_regstream_cw(const typename G::State* sin, typename G::State* sout, uint32_t count, uint64_t n,
                                int nsec_log2, uint64_t seclen, int dtype, void* out, const uint32_t* ladder,
                                const uint32_t* sectab, hipStream_t st) {
-  const uint64_t lanes = (uint64_t)count << nsec_log2;
-  const uint32_t blocks = (uint32_t)((lanes + 255) / 256);
-  switch (dtype) {
-    case PRAND_U32:
-      hipLaunchKernelGGL((regstream_kernel<G, PRAND_U32, CW>), dim3(blocks), dim3(256), 0, st, sin, sout, count, n,
-                         nsec_log2, seclen, out, ladder, sectab);
-      break;
-    case PRAND_F32:
-      hipLaunchKernelGGL((regstream_kernel<G, PRAND_F32, CW>), dim3(blocks), dim3(256), 0, st, sin, sout, count, n,
-                         nsec_log2, seclen, out, ladder, sectab);
-      break;
-    default:
-      hipLaunchKernelGGL((regstream_kernel<G, PRAND_F64, CW>), dim3(blocks), dim3(256), 0, st, sin, sout, count, n,
-                         nsec_log2, seclen, out, ladder, sectab);
-      break;
-  }
-  return hipGetLastError();
+  return launch_ranges(count, 256, 256u >> nsec_log2, [&](uint64_t first, uint32_t m, uint32_t blocks) {
+    auto launch = [&](auto* kernel, size_t es) {
+      hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, st, sin + first, sout + first, m, n, nsec_log2, seclen,
+                         (void*)((char*)out + first * n * es), ladder, sectab);
+      return hipGetLastError();
+    };
+    return dtype == PRAND_U32   ? launch(regstream_kernel<G, PRAND_U32, CW>, 4)
+           : dtype == PRAND_F32 ? launch(regstream_kernel<G, PRAND_F32, CW>, 4)
+                                : launch(regstream_kernel<G, PRAND_F64, CW>, 8);
+  });
 }
 
 template <class G>
