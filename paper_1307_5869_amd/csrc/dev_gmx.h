@@ -238,11 +238,19 @@ __device__ __forceinline__ void gmx_both(uint64_t x, uint64_t& lower, uint64_t& 
 }
 
 // f32 rounding toward zero, or to nearest again (bits 1:0 of the mode
-// register; everything else this code rounds is exact in either mode)
+// register).  What else rounds in f32 in between, the conversions of outputs, is
+// exact in either mode; no integer is divided there (the compiler's division is
+// by f32 reciprocals), so sec() of gmx_wave must be made beforehand.
 template <bool kZero>
 __device__ __forceinline__ void gmx_round() {
   constexpr int kModeBits1to0 = 1 | 0 << 6 | (2 - 1) << 11;
   __builtin_amdgcn_s_setreg(kModeBits1to0, kZero ? 3 : 0);
+}
+
+// a value that is the same in every lane, in scalar registers
+__device__ __forceinline__ uint64_t gmx_uniform(uint64_t v) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return ((uint64_t)hi << 32) | lo;
 }
 
 // one stream or section of a wavefront (uniform across it): n outputs from
@@ -285,7 +293,8 @@ __device__ __forceinline__ void gmx_put(void* out, uint64_t i, uint32_t w, int d
 // Generate the wavefront's streams; sec(q) gives stream q < Mx<G>::Q.  A
 // stream's input state is read before its output state is written, so they
 // may be the same object.  kJump = false: every start is 0.  lds: kGmxLds
-// words of this wavefront.  dtype (uniform): read where DT is kAnyType.  All 64
+// words of this wavefront.  sec() is called in the loop too, under its rounding
+// mode: it divides nothing.  dtype (uniform): read where DT is kAnyType.  All 64
 // lanes must call.
 template <int G, int DT, bool kJump, class SecOf>
 __device__ __forceinline__ void gmx_wave(SecOf&& sec, const GmxTable* __restrict__ table,

@@ -158,19 +158,13 @@ __global__ void __launch_bounds__(256) batch_reg_kernel(const BatchTile* __restr
 }
 
 // ------------------------------------------------------------------ GM/GQ
-// a value that is the same in every lane, in scalar registers
-__device__ __forceinline__ uint64_t uniform(uint64_t v) {
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return ((uint64_t)hi << 32) | lo;
-}
-
 template <int G>
 __device__ __forceinline__ void gen_gm(const BatchTile* tile, const BatchTask* tasks, const char* scratch,
                                     const GmxTable* tables, uint32_t* lds) {
   const BatchTask& tk = tasks[tile->task];
-  const uint64_t first = uniform(tile->first * tile->seclen), seclen = uniform(tile->seclen), n = uniform(tk.n);
-  const uint64_t out = uniform((uint64_t)tk.out), sout = uniform((uint64_t)tk.state_out);
-  const uint64_t starts = uniform((uint64_t)(scratch + tile->starts)), table = uniform((uint64_t)(tables + G));
+  const uint64_t first = gm::gmx_uniform(tile->first * tile->seclen), seclen = gm::gmx_uniform(tile->seclen), n = gm::gmx_uniform(tk.n);
+  const uint64_t out = gm::gmx_uniform((uint64_t)tk.out), sout = gm::gmx_uniform((uint64_t)tk.state_out);
+  const uint64_t starts = gm::gmx_uniform((uint64_t)(scratch + tile->starts)), table = gm::gmx_uniform((uint64_t)(tables + G));
   const uint32_t nsec = __builtin_amdgcn_readfirstlane(tile->nsec);
   const int dtype = __builtin_amdgcn_readfirstlane(tk.dtype);
   const uint64_t es = dtype == PRAND_F64 ? 8 : 4;

@@ -61,11 +61,26 @@ __global__ void __launch_bounds__(256) gmx_kernel(const GmState* sin, GmState* s
   const uint64_t first = ((uint64_t)blockIdx.x * 4 + w) * Q;
   const uint64_t all = kSections ? (uint64_t)count * nsec : count;
   if (first >= all) return;
+  // one division, here: sec() is called in the generation loop too (with a
+  // division per pair and turn left there and now: 300 GM55 streams of 20000 u32
+  // 35 and 28 us, 10^7 GQ58.3 numbers of one state 86 and 75, 10^8 GQ58.4 226 and
+  // 171).  In 64 bits, which the compiler branches around: by a 32-bit division
+  // the v = 1 kernels came out with 4-20 registers more, GM61's a wavefront less
+  const uint32_t s0 = kSections ? (uint32_t)(first / nsec) : 0;
+  const uint32_t j0 = kSections ? (uint32_t)first - s0 * nsec : 0;   // (count nsec < 2^32: launch_gen)
   auto sec = [&](int q) {
-    const uint64_t i = first + q;
-    const uint64_t s = kSections ? i / nsec : i, start = kSections ? (i % nsec) * seclen : 0;
+    uint32_t s1 = s0, j = j0 + q;
+    if (kSections) {
+#pragma unroll
+      for (int c = 1; c < Q; c++)
+        if (c <= q && j >= nsec) {
+          j -= nsec;
+          s1++;
+        }
+    }
+    const uint64_t s = kSections ? s1 : first + q, start = kSections ? j * seclen : 0;
     GmxSec r{nullptr, start, 0, nullptr, nullptr};
-    if (i < all) {
+    if (first + q < all) {
       r.in = sin + s;
       r.n = kSections ? (n - start < seclen ? n - start : seclen) : n;
       r.out = out + (s * n + start) * es;
