@@ -102,6 +102,25 @@ void fill_defaults(prand_batch_config& c) {
 
 bool is_reg(int g) { return g == PRAND_MRG32K3A || g == PRAND_LFSR113; }
 
+// Section lengths that a configuration leaves open: the lanes (262144) and
+// wavefronts (16384, four for each the chip holds) that a family's outputs
+// spread over, up to lengths where the starts are a small part of the work.
+// (A serving iteration of 16 MRG32K3A/LFSR113 requests of 10^3 .. 10^6: 165 us
+// in sections of 2048, 16 so; 2000 mixed tasks with GM/GQ tiles of 4096 outputs
+// 9.45 ms, of 16384 8.6.)
+struct OpenSections {
+  uint32_t reg, gm;
+};
+OpenSections open_sections(const prand_task* tasks, uint32_t ntasks) {
+  uint64_t reg = 0, gm = 0;
+  for (uint32_t k = 0; k < ntasks; k++) {
+    if (is_reg(tasks[k].gen)) reg += std::min<uint64_t>(tasks[k].n, 1ull << 40);
+    else if (tasks[k].gen != PRAND_MT19937) gm += std::min<uint64_t>(tasks[k].n, 1ull << 40);
+  }
+  return {(uint32_t)round_up(std::min<uint64_t>(std::max<uint64_t>(reg >> 18, 128), 2048), 32),
+          (uint32_t)std::min<uint64_t>(std::max<uint64_t>(gm >> 14, 1024), 16384)};
+}
+
 }  // namespace
 
 namespace prand {
@@ -116,25 +135,13 @@ int batch_plan(const prand_task* tasks, uint32_t ntasks, const prand_batch_confi
                uint64_t mt_section_min, bool may_cut) {
   std::vector<std::pair<double, BatchTile>> work[kBatchFamilies];
   for (double& c : plan.cost) c = 0;
-  // Section lengths that the configuration leaves open: the lanes (262144) and
-  // wavefronts (16384, four for each the chip holds) they spread a family's
-  // outputs over, up to lengths where the starts are a small part of the work.
-  // (A serving iteration of 16 MRG32K3A/LFSR113 requests of 10^3 .. 10^6: 165 us
-  // in sections of 2048, 16 so; 2000 mixed tasks with GM/GQ tiles of 4096 outputs
-  // 9.45 ms, of 16384 8.6.)
-  uint64_t reg_total = 0, gm_total = 0;
   double chip = 0;   // ms of the whole chip, 2^30-fold
-  for (uint32_t k = 0; k < ntasks; k++) {
+  for (uint32_t k = 0; k < ntasks; k++)
     if (tasks[k].gen >= 0 && tasks[k].gen < PRAND_NUM_GENERATORS)
       chip += (double)tasks[k].n * chip_cost(tasks[k].gen, tasks[k].dtype);
-    if (is_reg(tasks[k].gen)) reg_total += std::min<uint64_t>(tasks[k].n, 1ull << 40);
-    else if (tasks[k].gen != PRAND_MT19937) gm_total += std::min<uint64_t>(tasks[k].n, 1ull << 40);
-  }
-  const uint64_t reg_section =
-      cfg.reg_section ? cfg.reg_section
-                      : round_up(std::min<uint64_t>(std::max<uint64_t>(reg_total >> 18, 128), 2048), 32);
-  const uint64_t gm_section =
-      cfg.gm_section ? cfg.gm_section : std::min<uint64_t>(std::max<uint64_t>(gm_total >> 14, 1024), 16384);
+  const OpenSections open = open_sections(tasks, ntasks);
+  const uint64_t reg_section = cfg.reg_section ? cfg.reg_section : open.reg;
+  const uint64_t gm_section = cfg.gm_section ? cfg.gm_section : open.gm;
   for (uint32_t k = 0; k < ntasks; k++) {
     const prand_task& t = tasks[k];
     if (t.gen < 0 || t.gen >= PRAND_NUM_GENERATORS || t.dtype < PRAND_U32 || t.dtype > PRAND_F64)
@@ -515,7 +522,8 @@ int prand_batch_autotune(prand_ctx* c, const prand_task* h_tasks, uint32_t ntask
     *out = slowest ? worst : sum / reps;
     return rc;
   };
-  // tile sizes of the two section kinds, and the LDS footprint of the reg
+  // tile sizes of the two section kinds, the ones that a default configuration
+  // takes for these tasks among them, and the LDS footprint of the reg
   // kernel (staging chunk of 16 or 32 words per MRG32K3A/LFSR113 lane: 5 or
   // 9 KB per wavefront, which sets how many of its wavefronts a CU holds).
   // First pass: each configuration scored by the slowest of three launches
@@ -524,8 +532,10 @@ int prand_batch_autotune(prand_ctx* c, const prand_task* h_tasks, uint32_t ntask
   // Second pass: the three best re-timed over six launches each and ranked
   // by their mean, so that one lucky or unlucky first pass does not decide.
   const uint32_t cws[] = {16, 32};
-  const uint32_t regs[] = {2048, 8192};
-  const uint32_t gms[] = {16384};
+  const OpenSections open = open_sections(h_tasks, ntasks);
+  std::vector<uint32_t> regs = {2048, 8192}, gms = {16384};
+  if (open.reg != 2048) regs.insert(regs.begin(), open.reg);
+  if (open.gm != 16384) gms.insert(gms.begin(), open.gm);
   const uint32_t ovs[] = {0, 1, 2};
   std::vector<std::pair<float, prand_batch_config>> scored;
   int rc = PRAND_OK;
