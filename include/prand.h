@@ -293,7 +293,8 @@ int prand_batch_destroy(prand_batch* batch);
    six launches each and ranked by their mean.  The section lengths that a
    default configuration takes for these tasks are among the candidates.  When the
    environment variable PRAND_TUNE_CACHE names a file, results are kept there
-   keyed by the device and a signature of the task mix, and reused.  Blocks. */
+   keyed by the version of the plans, the device and a signature of the task
+   mix, and reused.  Blocks. */
 int prand_batch_autotune(prand_ctx* ctx, const prand_task* h_tasks, uint32_t ntasks, prand_batch_config* best);
 
 

@@ -325,7 +325,9 @@ hipError_t enqueue_persistent(prand_batch* b, hipStream_t a) {
 }
 
 std::string signature(prand_ctx* c, const prand_task* tasks, uint32_t ntasks) {
-  // task count, then per (generator, dtype): tasks and total outputs (2 digits)
+  // the version of the plans that the cached fields configure (2: GM/GQ sections
+  // counted per tile, three launch modes), the device and the task count, then
+  // per (generator, dtype): tasks and total outputs (2 digits)
   std::map<int, std::pair<uint64_t, double>> mix;
   for (uint32_t k = 0; k < ntasks; k++) {
     auto& m = mix[tasks[k].gen * 4 + tasks[k].dtype];
@@ -333,7 +335,7 @@ std::string signature(prand_ctx* c, const prand_task* tasks, uint32_t ntasks) {
     m.second += (double)tasks[k].n;
   }
   char buf[96];
-  std::string s = std::string(c->arch) + "/" + std::to_string(c->num_cus) + "/" + std::to_string(ntasks);
+  std::string s = std::string("2/") + c->arch + "/" + std::to_string(c->num_cus) + "/" + std::to_string(ntasks);
   for (auto& kv : mix) {
     std::snprintf(buf, sizeof buf, "/%d.%d:%llu:%.1e", kv.first / 4, kv.first % 4, (unsigned long long)kv.second.first,
                   kv.second.second);

@@ -1,5 +1,6 @@
 """The batch autotuner: its pick is no slower than a default configuration,
-also where the tasks are few and short."""
+also where the tasks are few and short, and a cache file of a library with
+other plans is not taken."""
 import numpy as np
 import pytest
 import torch
@@ -48,3 +49,19 @@ def test_pick_is_no_slower_than_the_default(ctx, monkeypatch):
     # a section length of 2048 takes three times the default's here
     assert _time(ctx, tasks, best) <= 1.5 * default
 
+
+def test_cache_of_other_plans_is_not_taken(ctx, tmp_path, monkeypatch):
+    path = tmp_path / "tune.txt"
+    monkeypatch.setenv("PRAND_TUNE_CACHE", str(path))
+    tasks = _tasks(ctx, [(P.GM29, 5000), (P.MRG32K3A, 7000)])
+    P.autotune(ctx, tasks)
+    key = path.read_text().split("\t")[0]
+    old = key[key.index("gfx950"):]   # the key as it was before plans had a version
+    path.write_text(f"{old}\t1 32 64 16 1\n")
+    best = P.autotune(ctx, tasks)
+    assert (best.waves_per_block, best.reg_section, best.gm_section) != (1, 32, 64)
+    assert path.read_text().count("\n") == 2
+    # what this library wrote is taken
+    path.write_text(f"{key}\t2 64 128 16 2\n")
+    best = P.autotune(ctx, tasks)
+    assert (best.waves_per_block, best.reg_section, best.gm_section, best.overlap) == (2, 64, 128, 2)
