@@ -275,7 +275,9 @@ typedef struct prand_batch prand_batch;
    per tile).  MT19937 tasks longer than 2^24 outputs are run as sections of
    624 * 2^10 outputs, whose start states come from whole-block jumps of the
    task state; a batch with such a task makes the context build its MT19937
-   jump tables first, if no earlier call has (a few seconds, once). */
+   jump tables first, if no earlier call has (a few seconds, once).  Where the
+   tables are there already, shorter tasks that would outlast the rest of the
+   batch are cut so too. */
 int prand_batch_create(prand_ctx* ctx, const prand_task* h_tasks, uint32_t ntasks, const prand_batch_config* cfg,
                        prand_batch** batch);
 /* Enqueue the batch on `stream` (a hipStream_t, NULL = default stream), as
@@ -283,7 +285,9 @@ int prand_batch_create(prand_ctx* ctx, const prand_task* h_tasks, uint32_t ntask
    the same batch must not overlap each other (they share the batch's tile
    counters and scratch). */
 int prand_batch_launch(prand_batch* batch, void* stream);
-/* Number of tiles (work items of a wavefront or, MT19937, a workgroup) the plan holds. */
+/* Number of tiles (work items of a wavefront or, MT19937, a workgroup) the plan
+   holds; an MT19937 task of up to 2^24 outputs counts as one, also where it is
+   cut into sections. */
 int prand_batch_tiles(const prand_batch* batch, uint32_t* ntiles);
 int prand_batch_destroy(prand_batch* batch);
 

@@ -450,6 +450,10 @@ int prand_batch_tiles(const prand_batch* b, uint32_t* ntiles) {
   return PRAND_OK;
 }
 
+// Not in the public header (a test hook): the sections beyond the first of the
+// MT19937 tasks that are cut because the rest of the batch is shorter than they are
+uint32_t prand_internal_batch_cut(const prand_batch* b) { return b ? b->n.cut : 0; }
+
 int prand_batch_launch(prand_batch* b, void* stream) {
   if (!b) return PRAND_EINVAL;
   if (b->n.total() == 0) return PRAND_OK;
