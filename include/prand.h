@@ -204,7 +204,8 @@ int prand_generate_array(prand_ctx* ctx, int gen, void* h_state, int dtype, void
    each d_states[s] is advanced by n_per_stream in place.  PRAND_ERANGE when
    n_per_stream > 2^40 or the output exceeds 2^50 bytes.  Asynchronous on
    `stream`, except that the first MRG32K3A or LFSR113 call with a given
-   section length (a function of count and n_per_stream; short calls have none)
+   section length (a function of the sizes, the type and whether the rows lie on
+   128-byte lines; calls of few outputs have none)
    builds that length's section-start table (up to 32 KB of device memory, kept until the context
    is destroyed; a blocking copy), unless `stream` is being captured into a
    graph: calls under capture, and calls past 64 such lengths per generator,

@@ -251,21 +251,33 @@ const uint32_t* section_table(prand_ctx* c, int k, uint64_t seclen, hipStream_t 
   return d;
 }
 
-// Sections per stream (log2) and section length of the many-stream
-// MRG32K3A/LFSR113 kernel: up to 64 sections per stream of whole 32-word
-// chunks (regstream.h).
+// How a many-stream MRG32K3A/LFSR113 call is cut and stored (regstream.h).
 //
-// short_plan: starts by the byte tables, anywhere (one matrix per nonzero byte
-// of the distance), so sections may be short and begin on lines of the output
-// (`lines`: every stream does): from 16 outputs of a stream on while the lanes
-// leave SIMDs idle (up to 2^16 of them), MRG32K3A from 128 on up to 2^18 (its
-// matrix costs 25 outputs, LFSR113's, of 128 bits, more than 100).  In a short
-// call the time is the chain of one lane: 5574 MRG32K3A streams of 820 u32 in
-// two sections of 416 by the table 42 us, in 32 sections of 32 26 us; 20000 of
-// 1000 f64 60 us in two, 48 us in four; but 4096 LFSR113 streams of 4096 u32
-// 28 us in 16 sections, 33 in 32.
-// long_plan, where those sections would be longer than 256: starts by a
-// section-start table (one matrix), sections of at least 1 KB, as many as fit
+// Lanes store by themselves (unit 0) runs of up to 32 bytes, and rows off the
+// output's lines that are not much longer while there are few: a frame of chunks
+// costs 2 us of set-up and partial rounds (LFSR113, 5574 streams of 9 u32 3.4 us
+// so and 6.9 in a frame, of 33 u32 7.0 and 7.6; but 300000 of 9 u32 12.0 and
+// 11.6, 33000 of 16 u32 5.9 and 5.4).
+//
+// few_plan: in a call of up to 10 * 2^20 outputs (f64 or rows on lines: 12) the
+// time is the chain of one lane, and the caches join partial lines, so a stream
+// is cut into short sections whose starts jump by the byte tables (one matrix per
+// nonzero byte of the distance), on 16 bytes and in chunks on 16 bytes; where
+// every row is on lines, sections are whole chunks.  Up to 2^16 lanes (while
+// they leave SIMDs idle) of 12 outputs or more, on lines 24 (MRG32K3A) and 16,
+// where a row is longer than a section's start: from 64 outputs, MRG32K3A from 32
+// (LFSR113's matrix, of 128 bits, costs more than 100 outputs, MRG32K3A's 25);
+// MRG32K3A also up to 2^19 lanes of 512 bytes (on lines 384).  us, with sections that begin on
+// lines wherever the row begins, and so: MRG32K3A 20000 streams of 100 u32 13.7
+// and 8.9, 10007 of 1000 26 and 22, of 300 f64 17 and 14; LFSR113 20000 of 100 u32
+// 13.9 and 9.6, 10007 of 1000 37 and 27; and with one section per stream, or two
+// by the table: MRG32K3A 20000 of 100 u32 10.9, 10007 of 1000 39.
+//
+// short_plan, of more outputs: short sections that begin on lines, up to 2^16 lanes
+// of 16 outputs or more, MRG32K3A up to 2^18 of 128 (20000 streams of 1000 u32
+// 35 us, 39 by the table; 10007 of 2500 36 and 44).
+// long_plan, where those sections would be longer than 256: starts by a section-start
+// table (one matrix), sections of at least 1 KB, as many as fit
 // in 2^22 lanes (more, shorter sections measured faster: the 64 runs of a
 // wavefront then lie close together in the output; 10007 streams of 4999 f64
 // in sections of 2 KB 112 us, of 1 KB 101-109, of u32 in sections of 512 bytes
@@ -273,44 +285,85 @@ const uint32_t* section_table(prand_ctx* c, int k, uint64_t seclen, hipStream_t 
 // outputs: f64 sections have 240 or more where a stream's output is 8 KB at
 // most, so that its runs lie together in any case (65536 streams of 600 f64 in
 // sections of 150 79 us, of 300 72; but of 5001 545 us in sections of 157, 555
-// of 313, and 10007 of 4999 102 and 107).
-void short_plan(int gen, uint32_t count, uint64_t n, bool lines, int& nsec_log2, uint64_t& seclen) {
-  const uint64_t max_lanes = gen == PRAND_MRG32K3A ? 1ull << 18 : 1ull << 16;
-  nsec_log2 = 0;
-  while (nsec_log2 < 6) {
-    const uint64_t lanes = (uint64_t)count << (nsec_log2 + 1);
-    if (lanes > max_lanes || (lines ? n : n + 31) >> (nsec_log2 + 1) < (lanes <= (1u << 16) ? 16 : 128)) break;
-    nsec_log2++;
-  }
-  const uint64_t reach = nsec_log2 && !lines ? n + 31 : n;   // room to begin the sections on lines
-  seclen = (((reach + (1ull << nsec_log2) - 1) >> nsec_log2) + 31) & ~31ull;
+// of 313, and 10007 of 4999 102 and 107).  f64 sections begin on lines, by
+// dropping up to 15 outputs (65536 streams of 16383 2.38 ms with partial chunks
+// at every section's ends, 1.65 so); u32 and f32 ones do not, as dropping up to
+// 31 of 256 costs what it saves (10007 LFSR113 streams of 4999 f32 70 us
+// without, 71.5 so).
+//
+// One section: chunks on 16 bytes for runs of up to a line, and of up to eight
+// where the outputs are few (65536 streams of 100 f32 22 us in chunks on 16
+// bytes, 24 on lines, of 100 f64 17.3 and 19.9; but 40000 of 250 u32 31.3 and
+// 28.8, 300000 of 100 f32 101 and 60).
+bool lane_stores(uint32_t count, uint64_t n, uint64_t bytes, bool lines) {
+  if (lines || bytes > 272) return false;
+  const uint64_t all = count * bytes;
+  return bytes < 32 || count <= 128 || (bytes == 32 && all <= (16u << 20)) || (bytes <= 136 && all <= (3u << 19)) ||
+         (bytes <= 100 && all <= (bytes % 16 || n <= 8 ? 4u << 20 : 2u << 20));
 }
-void long_plan(int gen, uint32_t count, uint64_t n, int dtype, int& nsec_log2, uint64_t& seclen) {
+bool few_plan(int gen, uint32_t count, uint64_t n, size_t es, bool lines, RegPlan& p) {
+  if (n > (16u << 20) || count * n > (lines || es == 8 ? 12u << 20 : 10u << 20)) return false;
+  const bool mrg = gen == PRAND_MRG32K3A;
+  const uint64_t least = !lines ? 12 : mrg ? 24 : n <= 64 ? 32 : 16;
+  while (p.nsec_log2 < 6 && (lines || n >= (mrg ? 32 : 64))) {
+    const uint64_t lanes = (uint64_t)count << (p.nsec_log2 + 1), more = 1ull << (p.nsec_log2 + 1);
+    if (!(lanes <= (1u << 16) && n >= least * more) &&
+        !(mrg && lanes <= (1u << 19) && n * es >= (lines ? 384 : 512) * more))
+      break;
+    p.nsec_log2++;
+  }
+  const uint64_t whole = lines ? 31 : 3;   // sections of whole chunks, or 16-byte pieces
+  p.seclen = (((n + (1ull << p.nsec_log2) - 1) >> p.nsec_log2) + whole) & ~whole;
+  if (p.nsec_log2 && !lines) {
+    p.unit = 16;
+    return true;
+  }
+  return p.seclen <= 256;
+}
+bool short_plan(int gen, uint32_t count, uint64_t n, bool lines, RegPlan& p) {
+  const uint64_t max_lanes = gen == PRAND_MRG32K3A ? 1ull << 18 : 1ull << 16;
+  const uint64_t reach = lines ? n : n + 31;   // room to begin the sections on lines
+  p.nsec_log2 = 0;
+  while (p.nsec_log2 < 6) {
+    const uint64_t lanes = (uint64_t)count << (p.nsec_log2 + 1);
+    if (lanes > max_lanes || reach >> (p.nsec_log2 + 1) < (lanes <= (1u << 16) ? 16 : 128)) break;
+    p.nsec_log2++;
+  }
+  p.seclen = ((((p.nsec_log2 ? reach : n) + (1ull << p.nsec_log2) - 1) >> p.nsec_log2) + 31) & ~31ull;
+  return p.seclen <= 256;
+}
+void long_plan(int gen, uint32_t count, uint64_t n, int dtype, RegPlan& p) {
   const uint64_t least = gen == PRAND_LFSR113 && dtype == PRAND_F64 && n <= 1024 ? 1920 : 1024;
-  nsec_log2 = 0;
-  while (nsec_log2 < 6 && ((uint64_t)count << (nsec_log2 + 1)) <= (1ull << 22) && (n >> (nsec_log2 + 1)) * elem_bytes(dtype) >= least)
-    nsec_log2++;
-  seclen = (((n + (1ull << nsec_log2) - 1) >> nsec_log2) + 31) & ~31ull;
+  p.nsec_log2 = 0;
+  while (p.nsec_log2 < 6 && ((uint64_t)count << (p.nsec_log2 + 1)) <= (1ull << 22) &&
+         (n >> (p.nsec_log2 + 1)) * elem_bytes(dtype) >= least)
+    p.nsec_log2++;
+  const uint64_t whole = dtype == PRAND_F64 ? 15 : 31;
+  p.seclen = (((n + (1ull << p.nsec_log2) - 1) >> p.nsec_log2) + whole) & ~whole;
 }
 
 // many-stream generation, the states moved on in place
 hipError_t launch_streams(prand_ctx* c, int gen, void* states, uint32_t count, uint64_t n, int dtype, void* out,
                           hipStream_t st) {
   if (gen == PRAND_MRG32K3A || gen == PRAND_LFSR113) {
-    const int k = gen == PRAND_MRG32K3A ? 0 : 1;
-    int nsec_log2;
-    uint64_t seclen;
-    short_plan(gen, count, n, ((uintptr_t)out | n * elem_bytes(dtype)) % 128 == 0, nsec_log2, seclen);
-    const uint32_t* tab = nullptr;
-    if (seclen > 256) {
-      long_plan(gen, count, n, dtype, nsec_log2, seclen);
-      tab = nsec_log2 ? section_table(c, k, seclen, st) : nullptr;
+    const size_t es = elem_bytes(dtype);
+    const bool lines = ((uintptr_t)out | n * es) % 128 == 0;
+    RegPlan p;
+    p.seclen = n;
+    if (lane_stores(count, n, n * es, lines)) {
+      p.unit = 0;
+    } else if (few_plan(gen, count, n, es, lines, p)) {
+      p.lines = lines;
+    } else if (short_plan(gen, count, n, lines, p)) {
+      p.lines = true;
+    } else {
+      long_plan(gen, count, n, dtype, p);
+      if (p.nsec_log2) p.sectab = section_table(c, gen == PRAND_MRG32K3A ? 0 : 1, p.seclen, st);
+      p.lines = dtype == PRAND_F64 || !p.sectab;
     }
-    if (gen == PRAND_MRG32K3A)
-      return launch_mrg_generate(c->T, (const MrgState*)states, (MrgState*)states, count, n, nsec_log2, seclen, dtype,
-                                 out, tab, st);
-    return launch_lfsr_generate(c->T, (const LfsrState*)states, (LfsrState*)states, count, n, nsec_log2, seclen, dtype,
-                                out, tab, st);
+    if (p.unit && !p.nsec_log2 && (n * es <= 128 || (n * es <= 1024 && count * n <= (1u << 23)))) p.unit = 16;
+    if (gen == PRAND_MRG32K3A) return launch_mrg_generate(c->T, (MrgState*)states, count, n, p, dtype, out, st);
+    return launch_lfsr_generate(c->T, (LfsrState*)states, count, n, p, dtype, out, st);
   }
   if (gen == PRAND_MT19937) return launch_mt_generate((MtState*)states, count, n, dtype, out, st);
   return launch_gm_generate(c->T, gen, (GmState*)states, count, n, dtype, out, st);

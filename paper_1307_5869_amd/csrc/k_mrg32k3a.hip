@@ -47,10 +47,9 @@ __global__ void __launch_bounds__(256) mrg_jump_kernel(MrgState* __restrict__ st
 
 static_assert(MrgGen::kSectionWords == kMrgSectionWords, "section-start table row size");
 
-hipError_t launch_mrg_generate(const DeviceTables& T, const MrgState* sin, MrgState* sout, uint32_t count,
-                               uint64_t n, int nsec_log2, uint64_t seclen, int dtype, void* out,
-                               const uint32_t* sectab, hipStream_t st) {
-  return launch_regstream<MrgGen>(sin, sout, count, n, nsec_log2, seclen, dtype, out, T.mrg, sectab, st);
+hipError_t launch_mrg_generate(const DeviceTables& T, MrgState* states, uint32_t count, uint64_t n, const RegPlan& plan,
+                               int dtype, void* out, hipStream_t st) {
+  return launch_regstream<MrgGen>(states, count, n, plan, dtype, out, T.mrg, st);
 }
 
 hipError_t launch_mrg_single(const DeviceTables& T, const MrgState* base, MrgState* sout, uint64_t n, int dtype,

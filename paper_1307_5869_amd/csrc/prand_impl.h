@@ -224,10 +224,16 @@ struct JumpSpec {
   int mt_blocks = 0;
 };
 
-// sectab: the section-start table of seclen, or null (ladder jumps)
-hipError_t launch_mrg_generate(const DeviceTables& T, const MrgState* sin, MrgState* sout, uint32_t count,
-                               uint64_t n, int nsec_log2, uint64_t seclen, int dtype, void* out,
-                               const uint32_t* sectab, hipStream_t st);
+// how the many-stream MRG32K3A/LFSR113 kernels cut and store (regstream.h)
+struct RegPlan {
+  int nsec_log2 = 0;                  // sections per stream
+  uint64_t seclen = 0;
+  bool lines = false;                 // sections begin on lines of the output
+  uint32_t unit = 128;                // bytes that a run's chunks are aligned to (0: the lanes store by themselves)
+  const uint32_t* sectab = nullptr;   // the section-start table of seclen (null: jumps by bytes)
+};
+hipError_t launch_mrg_generate(const DeviceTables& T, MrgState* states, uint32_t count, uint64_t n, const RegPlan& plan,
+                               int dtype, void* out, hipStream_t st);
 // one stream cut into sections, a lane each: n outputs of *base (a host
 // object, passed by value) to out, the state after them to *sout (device-
 // accessible memory)
@@ -243,9 +249,8 @@ uint64_t gm_single_wavefronts(int gen, uint64_t n);
 hipError_t launch_mrg_jump(const DeviceTables& T, MrgState* states, uint32_t count, const JumpSpec& js,
                            const MrgState* base, hipStream_t st);
 
-hipError_t launch_lfsr_generate(const DeviceTables& T, const LfsrState* sin, LfsrState* sout, uint32_t count,
-                                uint64_t n, int nsec_log2, uint64_t seclen, int dtype, void* out,
-                                const uint32_t* sectab, hipStream_t st);
+hipError_t launch_lfsr_generate(const DeviceTables& T, LfsrState* states, uint32_t count, uint64_t n,
+                                const RegPlan& plan, int dtype, void* out, hipStream_t st);
 hipError_t launch_lfsr_jump(const DeviceTables& T, LfsrState* states, uint32_t count, const JumpSpec& js,
                             const LfsrState* base, hipStream_t st);
 

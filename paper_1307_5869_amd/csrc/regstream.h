@@ -11,10 +11,11 @@
 // aligned 4 CW-byte blocks of memory that its run touches, whatever the run's
 // address (any multiple of the element size): only its first and last chunk
 // may be partial.  A round in which a lane's chunk is partial makes its words
-// one by one, all lanes together; the 16-byte pieces that the run covers are
-// stored as the others are, the words of a piece it covers in part by the lane.
+// one by one, all lanes together (four at a time left out that no lane's run
+// covers); the 16-byte pieces that the run covers are stored as the others are,
+// the words of a piece it covers in part by the lane.
 // (Runs that did not start on 16 bytes used to be stored word by word, lane by
-// lane: 10007 LFSR113 streams of 4999 f32 took 252 us, now 75 us.)  A lane
+// lane: 10007 LFSR113 streams of 4999 f32 took 252 us, now 70 us.)  A lane
 // whose run is shorter sits out the later rounds.
 //
 // regstream_wave() is the wavefront routine shared by the many-stream kernel
@@ -22,6 +23,7 @@
 #pragma once
 
 #include <cstdlib>
+#include <type_traits>
 
 #include "prand_impl.h"
 
@@ -46,7 +48,7 @@ __device__ __forceinline__ void put_word(void* out, uint64_t i, uint32_t w, doub
 // `sout` is set, store the advanced state there.  All 64 lanes must call.
 // kJump = false: the caller guarantees start == 0 (no jump code is built).
 // unit: bytes that the chunks are aligned to (16: short runs, which then touch
-// fewer of them).  drop: outputs to leave out before the first.
+// fewer of them; 0: the lanes store their words by themselves).  drop: outputs to leave out before the first.
 //
 // G: State, Regs, static load(State) -> Regs, static save(Regs) -> State,
 // static jump(State&, uint64_t distance, const uint32_t* ladder),
@@ -72,8 +74,8 @@ __device__ __forceinline__ void regstream_wave(uint32_t* rows, bool live, const 
   for (uint32_t i = 0; i < drop; i++) (void)G::next(r);
   // the run's frame: its chunks, the first of which it enters `head` words
   // on and the last of which it fills up to `tail` words (1 .. CW)
-  const bool framed = __all(!live || (uintptr_t)out % es == 0);
-  const uint32_t head = live ? (uint32_t)((uintptr_t)out % unit) / 4 : 0;
+  const bool framed = unit && __all(!live || (uintptr_t)out % es == 0);
+  const uint32_t head = live ? (uint32_t)((uintptr_t)out & (unit - 1)) / 4 : 0;
   const uint64_t total = (live && framed) ? head + len * kw : 0;   // words from the frame's start
   const uint32_t mine = (uint32_t)((total + CW - 1) / CW);         // chunks (0: none)
   const uint32_t tail = mine ? (uint32_t)(total - (uint64_t)(mine - 1) * CW) : 0;
@@ -137,16 +139,24 @@ __device__ __forceinline__ void regstream_wave(uint32_t* rows, bool live, const 
         // word by word, the lanes together: the words of the run in this chunk;
         // those of a 16-byte piece that the run covers in part are stored here
         const uint32_t w0 = rd ? 0 : head, w1 = rd + 1 < mine ? CW : (rd + 1 == mine ? tail : 0);
-        const uint32_t h4 = (w0 + 3) & ~3u, t4 = w1 & ~3u;
         char* const at = base + (uint64_t)rd * (4 * CW);
 #pragma unroll
-        for (uint32_t w = 0; w < CW; w += kw) {
-          if (w >= w0 && w < w1) {
-            const uint32_t v = G::next(r);
-            const double f = DT == PRAND_F64 ? G::f64(v) : 0.0;
-            put_word<DT>(row + w, 0, v, f);
-            if (w < h4 || w >= t4) put_word<DT>(at + 4 * w, 0, v, f);
-          }
+        for (uint32_t w4 = 0; w4 < CW; w4 += 4) {
+          if (!__any(w4 + 4 > w0 && w4 < w1)) continue;   // no lane's
+#pragma unroll
+          for (uint32_t w = w4; w < w4 + 4; w += kw)
+            if (w >= w0 && w < w1) {
+              const uint32_t v = G::next(r);
+              put_word<DT>(row + w, 0, v, DT == PRAND_F64 ? G::f64(v) : 0.0);
+            }
+        }
+        // of the pieces covered in part: up to 3 words at the run's front and end
+        const uint32_t h4 = (w0 + 3) / 4 * 4 < w1 ? (w0 + 3) / 4 * 4 : w1, t4 = w1 / 4 * 4 > h4 ? w1 / 4 * 4 : h4;
+        typedef typename std::conditional<DT == PRAND_F64, uint64_t, uint32_t>::type Value;
+#pragma unroll
+        for (uint32_t k = 0; k < 4 - kw; k += kw) {
+          if (w0 + k < h4) *(Value*)(at + 4 * (w0 + k)) = *(const Value*)(row + w0 + k);
+          if (t4 + k < w1) *(Value*)(at + 4 * (t4 + k)) = *(const Value*)(row + t4 + k);
         }
       }
       wave_lds_sync();
@@ -170,7 +180,7 @@ __device__ __forceinline__ void regstream_wave(uint32_t* rows, bool live, const 
     }
   }
   if (live) {
-    if (!framed)   // an address that is no multiple of the element size
+    if (!framed)   // a very short run, or an address that is no multiple of the element size
       for (uint64_t i = 0; i < len; i++) {
         const uint32_t w = G::next(r);
         put_word<DT>(out, i, w, DT == PRAND_F64 ? G::f64(w) : 0.0);
@@ -185,9 +195,15 @@ __device__ __forceinline__ void regstream_wave(uint32_t* rows, bool live, const 
 // so the state read of every section precedes the write-back of the last.
 // With sectab (the section-start table of seclen), section j > 0 starts from
 // row j - 1 of it, else from jumps by the byte tables.
+//
+// lines: sections begin on chunks of the output, for all but the first to be
+// whole.  Where starts may lie anywhere (jumps by bytes) and the sections leave
+// room for it, the first is shorter by as much as the stream's output begins
+// inside a chunk; with starts by the table it is longer by the rest of that
+// chunk, which the others drop.
 template <class G, int DT, int CW>
-__global__ void __launch_bounds__(256) regstream_kernel(const typename G::State* sin, typename G::State* sout,
-                                                        uint32_t count, uint64_t n, int nsec_log2, uint64_t seclen,
+__global__ void __launch_bounds__(256) regstream_kernel(typename G::State* states, uint32_t count, uint64_t n,
+                                                        int nsec_log2, uint64_t seclen, bool lines, uint32_t unit,
                                                         void* __restrict__ out, const uint32_t* __restrict__ ladder,
                                                         const uint32_t* __restrict__ sectab) {
   __shared__ __align__(16) uint32_t stage[4][RegStage<CW>::kWaveWords];
@@ -195,32 +211,18 @@ __global__ void __launch_bounds__(256) regstream_kernel(const typename G::State*
   const uint64_t nsec = 1ull << nsec_log2;
   const uint64_t s = gid >> nsec_log2, j = gid & (nsec - 1);
   constexpr int es = (DT == PRAND_F64) ? 8 : 4;
-  // Sections begin on chunks of the output, for all but the first to be whole.
-  // Where starts may lie anywhere (jumps by bytes) and the sections leave room
-  // for it, the first is shorter by as much as the stream's output begins
-  // inside a chunk; with starts by the table it is longer by the rest of that
-  // chunk, which the others drop: at most 15 of 128 f64 (65536 streams of 16383
-  // 2.38 ms with partial chunks at every section's ends, 1.65 so), but not up
-  // to 31 of 256 u32, which costs what it saves (10007 LFSR113 streams of 4999
-  // f32 70 us without, 71.5 so).
-  const uint64_t inside = ((uintptr_t)out + s * n * es) % (4 * CW) / es;
+  const uint64_t inside = lines ? ((uintptr_t)out + s * n * es) % (4 * CW) / es : 0;
   const bool any = !sectab && (seclen << nsec_log2) >= n + CW - 1;
   const uint64_t less = any ? inside : 0;
-  const uint64_t more = sectab && DT == PRAND_F64 && inside ? 4 * CW / es - inside : 0;
+  const uint64_t more = sectab && inside ? 4 * CW / es - inside : 0;
   const uint64_t start = j ? j * seclen + more - less : 0, next = (j + 1) * seclen + more - less;
   const bool live = s < count && (!j || start < n);
   const bool last = live && next >= n;
   const uint64_t len = live ? (last ? n : next) - start : 0;
   void* o = (char*)out + (s * n + start) * es;
-  // Runs of up to a line, and of up to eight where the outputs are few and the
-  // time is that of the rounds (65536 streams of 100 f32: 22 us in chunks on 16
-  // bytes, 24 on lines, of 100 f64 17.3 and 19.9; but 40000 of 250 u32 31.3 and
-  // 28.8, 300000 of 100 f32 101 and 60)
-  const uint32_t unit = n * es <= 128 || (n * es <= 1024 && count * n <= (1u << 23)) ? 16 : 4 * CW;
   const uint32_t* sec_mat = (sectab && j) ? sectab + (j - 1) * G::kSectionWords : nullptr;
-  regstream_wave<G, DT, CW>(stage[threadIdx.x >> 6], live, sin + (live ? s : 0), start, len, o,
-                            last ? sout + s : nullptr, ladder, sec_mat, unit,
-                            live && j ? (uint32_t)more : 0);
+  regstream_wave<G, DT, CW>(stage[threadIdx.x >> 6], live, states + (live ? s : 0), start, len, o,
+                            last ? states + s : nullptr, ladder, sec_mat, unit, live && j ? (uint32_t)more : 0);
 }
 
 // One stream: lane j owns section j (seclen outputs, the last one the rest).
@@ -288,13 +290,13 @@ inline int regstream_chunk_words() {
 }
 
 template <class G, int CW>
-hipError_t launch_regstream_cw(const typename G::State* sin, typename G::State* sout, uint32_t count, uint64_t n,
-                               int nsec_log2, uint64_t seclen, int dtype, void* out, const uint32_t* ladder,
-                               const uint32_t* sectab, hipStream_t st) {
-  return launch_ranges(count, 256, 256u >> nsec_log2, [&](uint64_t first, uint32_t m, uint32_t blocks) {
+hipError_t launch_regstream_cw(typename G::State* states, uint32_t count, uint64_t n, const RegPlan& plan, int dtype,
+                               void* out, const uint32_t* ladder, hipStream_t st) {
+  const uint32_t unit = plan.unit > 4 * CW ? 4 * CW : plan.unit;
+  return launch_ranges(count, 256, 256u >> plan.nsec_log2, [&](uint64_t first, uint32_t m, uint32_t blocks) {
     auto launch = [&](auto* kernel, size_t es) {
-      hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, st, sin + first, sout + first, m, n, nsec_log2, seclen,
-                         (void*)((char*)out + first * n * es), ladder, sectab);
+      hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, st, states + first, m, n, plan.nsec_log2, plan.seclen,
+                         plan.lines, unit, (void*)((char*)out + first * n * es), ladder, plan.sectab);
       return hipGetLastError();
     };
     return dtype == PRAND_U32   ? launch(regstream_kernel<G, PRAND_U32, CW>, 4)
@@ -304,12 +306,10 @@ hipError_t launch_regstream_cw(const typename G::State* sin, typename G::State* 
 }
 
 template <class G>
-hipError_t launch_regstream(const typename G::State* sin, typename G::State* sout, uint32_t count, uint64_t n,
-                            int nsec_log2, uint64_t seclen, int dtype, void* out, const uint32_t* ladder,
-                            const uint32_t* sectab, hipStream_t st) {
-  if (regstream_chunk_words() == 16)
-    return launch_regstream_cw<G, 16>(sin, sout, count, n, nsec_log2, seclen, dtype, out, ladder, sectab, st);
-  return launch_regstream_cw<G, 32>(sin, sout, count, n, nsec_log2, seclen, dtype, out, ladder, sectab, st);
+hipError_t launch_regstream(typename G::State* states, uint32_t count, uint64_t n, const RegPlan& plan, int dtype,
+                            void* out, const uint32_t* ladder, hipStream_t st) {
+  return regstream_chunk_words() == 16 ? launch_regstream_cw<G, 16>(states, count, n, plan, dtype, out, ladder, st)
+                                       : launch_regstream_cw<G, 32>(states, count, n, plan, dtype, out, ladder, st);
 }
 
 }  // namespace prand
