@@ -24,22 +24,48 @@ namespace {
 
 using namespace gm;
 
-// Runs of a v = 1 ensemble shorter than kBallotOutputs: half a wavefront per
-// stream, one lane per element, a ballot per word (dev_gm.h).  The matrix form
-// makes the operands of 256 steps, 64 steps at a time, and moves the states by
-// a product: 65536 streams of 1, 32, 100, 128 and 192 outputs take, by ballots
-// and so, GM29 17 and 52, 29 and 52, 61 and 71, 74 and 71, 105 and 88 us; GM61 18
-// and 76, 37 and 76, 90 and 106, 106 and 103, 153 and 136.
-constexpr uint64_t kBallotOutputs = 128;
+// wavefronts that fill the chip (four to five per SIMD, twice over)
+constexpr uint64_t kFillWaves = 8192;
+
+// Short runs of a v = 1 ensemble: half a wavefront per stream, one lane per
+// element, a ballot per word (dev_gm.h).  The matrix form makes the operands of
+// 256 steps, turns of 64 steps, and moves the states by a product: 65536 GM29
+// streams of 1, 32 and 100 outputs take 17, 29 and 61 us by ballots, 52, 52 and 71
+// so.  From 128 outputs on it costs, in ballot outputs, a fixed part and parts per
+// 256 steps and per turn, more where states and outputs are well beyond the
+// memory-side cache (256 MB): it has half as many streams in a wavefront, waiting
+// for their states.  Ballots where that is more than n: 65536 GM61 streams of 144 outputs
+// 104 us (by the matrix form 116), of 192 134 (118); 300000 GM19 streams of 128 f64
+// 169 (273), of 512 587 (640), of 800 964 (923).  (The v >= 3 ensembles are
+// faster by the matrix form at any length: 65536 streams of 1, 32 and 128 u32,
+// GM55 30, 40 and 69 us by a lane per section, 24, 25 and 31 so; GQ58.3 48, 54 and
+// 88, 37, 39 and 51; GQ58.4 30, 38 and 55, 21, 22 and 26.)
+struct BallotCost {
+  uint32_t fixed, advance, turn;
+};
+struct BallotRule {
+  BallotCost small, large, large64;   // 64: f64
+};
+template <int G>
+bool ballots(uint64_t count, uint64_t n, uint64_t es) {
+  static_assert(Mx<G>::S == 32, "a lane per element");
+  constexpr BallotRule r = G == 0   ? BallotRule{{45, 15, 40}, {85, 0, 50}, {120, 0, 54}}
+                           : G == 4 ? BallotRule{{18, 15, 43}, {45, 0, 47}, {60, 0, 45}}
+                                    : BallotRule{{46, 0, 34}, {44, 0, 45}, {62, 0, 44}};
+  if (n < 128) return true;
+  if (n >= 1024 || count < 2 * kFillWaves) return false;
+  const bool large = count * (2 * sizeof(GmState) + n * es) > (440u << 20);
+  const BallotCost c = !large ? r.small : es == 8 ? r.large64 : r.large;
+  return n < c.fixed + c.advance * ((n + 255) / 256) + c.turn * ((n + 63) / 64);
+}
 
 template <int G, int DT>
-__global__ void __launch_bounds__(256) gm_gen32_kernel(GmState* states, uint32_t count, uint64_t n,
+__global__ void __launch_bounds__(256) gm_gen32_kernel(const GmState* sin, GmState* sout, uint32_t count, uint64_t n,
                                                        void* __restrict__ out) {
   const uint64_t s = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 5;
   const bool live = s < count;
   constexpr int es = (DT == PRAND_F64) ? 8 : 4;
-  GmState* state = states + (live ? s : 0);
-  gen32_wave<G, DT>(live, state, n, (char*)out + s * n * es);
+  gen32_wave<G, DT>(live, sin + (live ? s : 0), sout + (live ? s : 0), n, (char*)out + s * n * es);
 }
 
 // Many streams: a wavefront takes Mx<G>::Q consecutive (stream, section)
@@ -175,8 +201,8 @@ hipError_t launch_jump_g(const DeviceTables& T, GmState* states, uint32_t count,
   });
 }
 
-// Sections per stream.  With at least kFillWaves wavefronts of whole streams
-// the chip is full (four to five per SIMD, twice over); fewer are cut into
+// Sections per stream.  At least kFillWaves wavefronts of whole streams stay
+// whole; fewer are cut into
 // sections of whole state advances, as long as there stay enough of them: of
 // eight advances (a section's start is one matrix per nonzero byte of its
 // distance, about the time of two advances), or down to one where there would
@@ -184,18 +210,16 @@ hipError_t launch_jump_g(const DeviceTables& T, GmState* states, uint32_t count,
 // then move on by a launch of their own: 4 us.  196 GM55 streams of 5148 u32 in
 // sections of eight advances 56 us, of one 20; 61 GM31 of 2792 36 us whole, 15
 // so; 100 GM61 of 1000 24 and 16)
-constexpr uint64_t kFillWaves = 8192;
-
 template <int G, int DT>
 hipError_t launch_gen(const DeviceTables& T, GmState* states, uint32_t count, uint64_t n, void* out, hipStream_t st) {
   constexpr uint64_t Q = Mx<G>::Q, es = DT == PRAND_F64 ? 8 : 4;
   constexpr uint64_t unit = G == 6 ? kGmxSteps / 8 * 9 : kGmxSteps;   // outputs of a state advance
   uint64_t seclen = 8 * unit;
   if constexpr (Mx<G>::S == 32) {
-    if (n < kBallotOutputs) {
+    if (ballots<G>(count, n, es)) {
       return launch_ranges(count, 256, 8, [&](uint64_t first, uint32_t m, uint32_t blocks) {
-        hipLaunchKernelGGL((gm_gen32_kernel<G, DT>), dim3(blocks), dim3(256), 0, st, states + first, m, n,
-                           (char*)out + first * n * es);
+        hipLaunchKernelGGL((gm_gen32_kernel<G, DT>), dim3(blocks), dim3(256), 0, st, states + first,
+                           states + first, m, n, (char*)out + first * n * es);
         return hipGetLastError();
       });
     }
