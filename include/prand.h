@@ -238,11 +238,9 @@ int prand_generate_noalloc(prand_ctx* ctx, int gen, void* h_state, int dtype, vo
  * dtypes in one launch, replayed from a HIP graph.  Each task is cut into
  * sections that jump to their first output (the sectioning of "Multi-threaded
  * generation"), grouped into tiles; a first kernel computes every section's
- * start state, then two persistent kernels (MT19937 and GM/GQ; MRG32K3A and
- * LFSR113) work through their tile lists longest first, taking the next tile
- * from a device counter -- one after the other, each with as many wavefronts
- * as the chip holds, in either order, or side by side
- * (prand_batch_config.overlap).
+ * start state, then two kernels (MT19937 and GM/GQ; MRG32K3A and LFSR113) make
+ * the tiles, longest first -- one after the other, in either order, or side by
+ * side (prand_batch_config.overlap).
  * ------------------------------------------------------------------------ */
 typedef struct prand_task {
   int32_t gen;           /* enum prand_gen */

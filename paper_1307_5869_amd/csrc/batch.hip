@@ -4,10 +4,10 @@
 // and groups them into tiles (see k_batch.hip), family by family.  Every
 // MRG32K3A/LFSR113 and GM/GQ tile gets a slot in the batch's scratch area for
 // its sections' start states.  The tiles form three lists (MT19937 and
-// copies, MRG32K3A/LFSR113, GM/GQ), longest first by estimated time, which the
-// persistent kernels work through.  The launch -- counter reset and section
-// starts, then the two persistent kernels -- is captured once in a HIP graph
-// on a private stream and replayed on the caller's stream.  The autotuner
+// copies, MRG32K3A/LFSR113, GM/GQ), longest first by estimated time.  The launch --
+// counter reset and section starts, then the two generation kernels -- is
+// captured once in a HIP graph on a private stream and replayed on the
+// caller's stream.  The autotuner
 // times a small grid of (MRG32K3A/LFSR113 lane section, LDS chunk width of the
 // reg kernel, kernel order) on the actual task mix and re-times the best three
 // before it picks one.
@@ -35,10 +35,10 @@ struct prand_batch {
   BatchTask* d_tasks = nullptr;
   char* d_scratch = nullptr;
   uint32_t* d_order = nullptr;      // the lists, one after the other
-  uint32_t* d_counters = nullptr;   // a tile counter per list
+  uint32_t* d_counter = nullptr;    // of the tiles that reg has taken
   uint32_t n_list[kBatchLists] = {0, 0, 0};
   uint32_t off_list[kBatchLists] = {0, 0, 0};
-  uint32_t main_blocks = 0, reg_blocks = 0;
+  uint32_t reg_blocks = 0;
   hipStream_t cap = nullptr;
   hipStream_t side = nullptr;               // reg branch
   hipEvent_t ev[2] = {nullptr, nullptr};    // fork, join
@@ -219,7 +219,7 @@ int batch_plan(const prand_task* tasks, uint32_t ntasks, const prand_batch_confi
   }
   size_t total = 0;
   for (auto& w : work) total += w.size();
-  if (total > (1ull << 31)) return PRAND_ERANGE;   // tile counters stay far from wrapping
+  if (total > (1ull << 31)) return PRAND_ERANGE;   // 32-bit tile numbers
   plan.tiles.resize(total);
   plan.scratch_bytes = 0;
   plan.n.mtsec = 0;
@@ -272,36 +272,34 @@ void free_batch(prand_batch* b) {
   (void)hipFree(b->d_tasks);
   (void)hipFree(b->d_scratch);
   (void)hipFree(b->d_order);
-  (void)hipFree(b->d_counters);
+  (void)hipFree(b->d_counter);
   delete b;
 }
 
-// The batch's kernels: on stream a the tile counters are cleared and every
-// section jumped to its start (and the MT19937 section starts, when a task
-// is long enough to have sections); then the two persistent kernels run, each
-// with the whole chip's worth of workgroups, main then reg (mode 0) or reg
-// then main (mode 2), or side by side (mode 1): reg on a forked stream with
-// the share of the chip its work takes, main on stream a with the whole chip's
-// worth (those that do not fit at first are dispatched as the other's finish).
-hipError_t enqueue_persistent(prand_batch* b, hipStream_t a) {
+// The batch's kernels: on stream a the reg kernel's tile counter is cleared and
+// every section jumped to its start (and the MT19937 section starts, when a task
+// is long enough to have sections); then the two generation kernels run, main
+// with a workgroup or wavefront per tile, reg with the whole chip's worth of
+// workgroups that take tiles from the counter: main then reg (mode 0) or reg then
+// main (mode 2), or side by side (mode 1), reg on a forked stream with the share
+// of the chip its work takes.
+hipError_t enqueue_batch(prand_batch* b, hipStream_t a) {
   const DeviceTables& T = b->ctx->T;
   const uint32_t w = b->cfg.waves_per_block;
   const BatchCounts& n = b->n;
   const BatchTile* mt = b->d_tiles + n.with_starts();
-  hipError_t e = launch_batch_reset(b->d_counters, a);
+  hipError_t e = launch_batch_reset(b->d_counter, a);
   if (e == hipSuccess) e = launch_batch_starts(T, b->d_tiles, n.with_starts(), b->d_tasks, b->d_scratch, w, a);
   if (e == hipSuccess && n.mtsec) e = launch_batch_mt_starts(T, mt, n.mt + n.copy + n.cut, b->d_tasks, b->d_scratch, a);
   auto main = [&](hipStream_t st) {
     if (e == hipSuccess)
       e = launch_batch_main(T, b->d_tiles, b->d_order + b->off_list[kListMt], b->n_list[kListMt],
-                            b->d_order + b->off_list[kListGm], b->n_list[kListGm], b->d_tasks, b->d_scratch,
-                            b->d_counters, b->main_blocks, st);
+                            b->d_order + b->off_list[kListGm], b->n_list[kListGm], b->d_tasks, b->d_scratch, st);
   };
   auto reg = [&](hipStream_t st) {
     if (e == hipSuccess)
       e = launch_batch_reg_persistent((int)b->cfg.lds_chunk_words, b->d_tiles, b->d_order + b->off_list[kListReg],
-                                      b->n_list[kListReg], b->d_tasks, b->d_scratch, b->d_counters, w, b->reg_blocks,
-                                      st);
+                                      b->n_list[kListReg], b->d_tasks, b->d_scratch, b->d_counter, w, b->reg_blocks, st);
   };
   switch (b->cfg.overlap) {
     case 0:
@@ -417,15 +415,13 @@ int prand_batch_create(prand_ctx* c, const prand_task* h_tasks, uint32_t ntasks,
     total_order += b->n_list[l];
     all += plan.cost[l];
   }
-  // side by side, main gets the whole chip's worth and reg the share its work
-  // takes of the batch's (a tenth more, so that it rather finishes before
-  // main than after it); one after the other, each gets the whole chip
+  // side by side, reg gets the share of the chip that its work takes of the
+  // batch's (a tenth more, so that it rather finishes before main than after it)
   const double share = conf.overlap != 1 || all <= 0 ? 1.0 : std::min(1.0, 1.1 * plan.cost[kListReg] / all);
   const uint32_t full = batch_reg_blocks((int)conf.lds_chunk_words, conf.waves_per_block, c->num_cus);
   b->reg_blocks = std::max<uint32_t>(1, (uint32_t)std::ceil(share * full));
-  b->main_blocks = batch_main_blocks(c->num_cus);
   if (e == hipSuccess) e = hipMalloc((void**)&b->d_order, std::max<size_t>(1, total_order) * 4);
-  if (e == hipSuccess) e = hipMalloc((void**)&b->d_counters, 256);
+  if (e == hipSuccess) e = hipMalloc((void**)&b->d_counter, 256);
   for (int l = 0; l < kBatchLists && e == hipSuccess; l++)
     if (b->n_list[l])
       e = hipMemcpy(b->d_order + b->off_list[l], plan.order[l].data(), b->n_list[l] * 4, hipMemcpyHostToDevice);
@@ -460,13 +456,13 @@ int prand_batch_launch(prand_batch* b, void* stream) {
   DeviceGuard g(b->ctx->device);
   hipStream_t st = (hipStream_t)stream;
   if (!b->cfg.use_graph) {
-    hipError_t e = enqueue_persistent(b, st);
+    hipError_t e = enqueue_batch(b, st);
     return e == hipSuccess ? PRAND_OK : hipfail(b->ctx, e);
   }
   if (!b->exec) {
     hipError_t e = hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
-      hipError_t le = enqueue_persistent(b, b->cap);
+      hipError_t le = enqueue_batch(b, b->cap);
       e = hipStreamEndCapture(b->cap, &b->graph);
       if (e == hipSuccess) e = le;
     }

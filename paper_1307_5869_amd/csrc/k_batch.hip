@@ -9,20 +9,24 @@
 // independent: each starts from the task's state jumped to its first output.
 //
 // A batched launch (prand_batch_launch) is a chain of kernels on one stream:
-//  - batch_reset_kernel clears the tile counters;
 //  - batch_starts_kernel jumps every MRG32K3A/LFSR113/GM/GQ section to its
 //    start and writes the state to the batch's scratch area (the jump code
 //    needs many registers, so it runs apart from the generation loops);
 //    sections of long MT19937 tasks (batch.hip) get theirs from
 //    mt_section_start_kernel (k_mt19937.hip);
-//  - two persistent kernels, each launched with as many workgroups as the
-//    chip holds at once, which take the next tile of a list from a device
-//    counter until it is used up.  The lists are ordered longest first by
-//    the host (estimated time), so the long tiles start at once and the short
-//    ones fill the end.  batch_main_kernel runs MT19937 tasks and sections
-//    (and n = 0 copies) and the GM/GQ tiles, batch_reg_persistent_kernel
-//    MRG32K3A/LFSR113 (its LDS sized by the chunk width of the staging, the
-//    footprint the autotuner chooses).
+//  - batch_main_kernel runs MT19937 tasks and sections (and n = 0 copies), a
+//    workgroup each, and the GM/GQ tiles, a wavefront each, in the order of
+//    their lists, longest first (estimated time, by the host), so the long
+//    tiles start at once and the short ones fill the end;
+//  - batch_reg_persistent_kernel runs MRG32K3A/LFSR113 (its LDS sized by the
+//    chunk width of the staging, the footprint the autotuner chooses): as many
+//    workgroups as the chip holds at once, or fewer, which take the next tile of
+//    their list from a device counter (cleared by batch_reset_kernel) until it is
+//    used up.
+// A counter costs 15 ns a tile: main by one took 10.5 ms for 2000 tasks of
+// 10^3 .. 10^6 outputs in GM/GQ tiles of 256, 2.4 so; 10^7 GM19 numbers of one
+// task 203 us and 67; 2000 MT19937 tasks of 100 .. 1000 96 and 23 (2000 tasks of
+// 10^3 .. 10^7: 7.0 ms either way).
 // Each tile runs the same routines as the one-generator kernels; the GM/GQ ones
 // with the element type as a value, so that the kernel holds each generator's
 // code once.  2000 tasks of 10^3 .. 10^7 outputs of all generators: 20.9 ms with
@@ -243,9 +247,7 @@ __global__ void __launch_bounds__(mt::kGroup) batch_mt_kernel(const BatchTile* _
 }
 
 // ---------------------------------------------------------- persistent
-__global__ void batch_reset_kernel(uint32_t* counters) {
-  if (threadIdx.x < kBatchLists) counters[threadIdx.x] = 0;
-}
+__global__ void batch_reset_kernel(uint32_t* counter) { *counter = 0; }
 
 // the next entry of a tile list for this wavefront (uniform across it)
 __device__ __forceinline__ uint32_t next_tile(uint32_t* counter) {
@@ -291,38 +293,26 @@ __global__ void __launch_bounds__(256) batch_reg_persistent_kernel(const BatchTi
   }
 }
 
-// MT19937 tasks and sections (and n = 0 copies), then GM/GQ tiles: a workgroup
-// takes MT19937 tiles, whose chains are the longest of the batch, until that
-// list is used up, then each of its wavefronts GM/GQ tiles.  While it runs an
-// MT19937 tile its wavefronts issue before the GM/GQ ones they share a SIMD
-// with: they are few, and wait for one another at every turn.
+// MT19937 tasks and sections (and n = 0 copies), a workgroup each, then GM/GQ
+// tiles, a wavefront each.  The MT19937 ones, whose chains are the longest of the
+// batch, are dispatched first, and issue before the GM/GQ wavefronts they share a
+// SIMD with: they are few, and wait for one another at every turn.  first: the
+// launch's first workgroup of the batch's.
 __global__ void __launch_bounds__(mt::kGroup, 4)
     batch_main_kernel(const BatchTile* __restrict__ tiles, const uint32_t* __restrict__ mt_order, uint32_t nmt,
                       const uint32_t* __restrict__ gm_order, uint32_t ngm, const BatchTask* __restrict__ tasks,
-                      char* scratch, uint32_t* counters, const GmxTable* __restrict__ table) {
+                      char* scratch, uint32_t first, const GmxTable* __restrict__ table) {
   __shared__ uint32_t ring[mt::kRing];
   __shared__ uint32_t lds[4][gm::kGmxLds];
-  __shared__ uint32_t taken;
-  __builtin_amdgcn_s_setprio(3);
-  for (;;) {
-    if (threadIdx.x == 0) taken = atomicAdd(counters + kListMt, 1u);
-    __syncthreads();
-    const uint32_t k = __builtin_amdgcn_readfirstlane(taken);
-    if (k >= nmt) break;
-    const BatchTile tl = tiles[mt_order[k]];
+  const uint32_t b = first + blockIdx.x;
+  if (b < nmt) {
+    __builtin_amdgcn_s_setprio(3);
+    const BatchTile tl = tiles[mt_order[b]];
     mt_tile(tl, tasks[tl.task], scratch, ring);
-    __syncthreads();   // `taken` and the ring are read
+    return;
   }
-  __builtin_amdgcn_s_setprio(0);
-  uint32_t* mine = lds[threadIdx.x >> 6];
-  for (;;) {
-    const uint32_t k = next_tile(counters + kListGm);
-    if (k >= ngm) break;
-    const GmxTable* t = table;
-    asm volatile("" : "+s"(t));   // nothing of the eight generators' table addresses is kept across tiles
-    gm_tile(tiles + gm_order[k], tasks, scratch, t, mine);
-    wave_lds_sync();   // the next tile reuses this wavefront's LDS
-  }
+  const uint64_t k = (uint64_t)(b - nmt) * (mt::kGroup / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (k < ngm) gm_tile(tiles + gm_order[k], tasks, scratch, table, lds[threadIdx.x >> 6]);
 }
 
 uint32_t blocks_for(uint32_t ntiles, uint32_t waves) { return (ntiles + waves - 1) / waves; }
@@ -339,12 +329,10 @@ uint32_t resident_blocks(K kernel, uint32_t waves, int num_cus) {
 
 }  // namespace
 
-hipError_t launch_batch_reset(uint32_t* counters, hipStream_t st) {
-  hipLaunchKernelGGL(batch_reset_kernel, dim3(1), dim3(64), 0, st, counters);
+hipError_t launch_batch_reset(uint32_t* counter, hipStream_t st) {
+  hipLaunchKernelGGL(batch_reset_kernel, dim3(1), dim3(1), 0, st, counter);
   return hipGetLastError();
 }
-
-uint32_t batch_main_blocks(int num_cus) { return resident_blocks(batch_main_kernel, mt::kGroup / 64, num_cus); }
 
 uint32_t batch_reg_blocks(int cw, uint32_t waves, int num_cus) {
   return cw == 16 ? resident_blocks(batch_reg_persistent_kernel<16>, waves, num_cus)
@@ -353,28 +341,27 @@ uint32_t batch_reg_blocks(int cw, uint32_t waves, int num_cus) {
 
 hipError_t launch_batch_main(const DeviceTables& T, const BatchTile* tiles, const uint32_t* mt_order, uint32_t nmt,
                              const uint32_t* gm_order, uint32_t ngm, const BatchTask* tasks, char* scratch,
-                             uint32_t* counters, uint32_t blocks, hipStream_t st) {
-  if (!nmt && !ngm) return hipSuccess;
-  // no more workgroups than tiles need
-  constexpr uint32_t kWaves = mt::kGroup / 64;
-  blocks = (uint32_t)std::min<uint64_t>(blocks, (uint64_t)nmt + blocks_for(ngm, kWaves));
-  hipLaunchKernelGGL(batch_main_kernel, dim3(blocks), dim3(mt::kGroup), 0, st, tiles, mt_order, nmt, gm_order, ngm,
-                     tasks, scratch, counters, T.gmx);
-  return hipGetLastError();
+                             hipStream_t st) {
+  return launch_ranges((uint64_t)nmt + blocks_for(ngm, mt::kGroup / 64), mt::kGroup, 1,
+                       [&](uint64_t first, uint32_t, uint32_t blocks) {
+                         hipLaunchKernelGGL(batch_main_kernel, dim3(blocks), dim3(mt::kGroup), 0, st, tiles, mt_order,
+                                            nmt, gm_order, ngm, tasks, scratch, (uint32_t)first, T.gmx);
+                         return hipGetLastError();
+                       });
 }
 
 hipError_t launch_batch_reg_persistent(int cw, const BatchTile* tiles, const uint32_t* order, uint32_t n,
-                                       const BatchTask* tasks, char* scratch, uint32_t* counters, uint32_t waves,
+                                       const BatchTask* tasks, char* scratch, uint32_t* counter, uint32_t waves,
                                        uint32_t blocks, hipStream_t st) {
   if (!n) return hipSuccess;
   blocks = std::min<uint32_t>(blocks, blocks_for(n, waves));
   const dim3 grid(blocks), block(64 * waves);
   if (cw == 16)
     hipLaunchKernelGGL(batch_reg_persistent_kernel<16>, grid, block, 0, st, tiles, order, n, tasks, scratch,
-                       counters + kListReg);
+                       counter);
   else
     hipLaunchKernelGGL(batch_reg_persistent_kernel<32>, grid, block, 0, st, tiles, order, n, tasks, scratch,
-                       counters + kListReg);
+                       counter);
   return hipGetLastError();
 }
 

@@ -52,15 +52,15 @@ struct BatchCounts {
 };
 constexpr int kFamReg = 0, kFamGm = 1, kFamMt = 2, kFamCopy = 3, kFamCut = 4, kBatchFamilies = 5;
 
-// lists of the persistent launch: MT19937 and copies, MRG32K3A/LFSR113, GM/GQ
+// tile lists of a launch: MT19937 and copies, MRG32K3A/LFSR113, GM/GQ
 constexpr int kListMt = 0, kListReg = 1, kListGm = 2, kBatchLists = 3;
 
 struct BatchPlan {
   std::vector<BatchTile> tiles;
   BatchCounts n;
   uint64_t scratch_bytes = 0;
-  // tile indices of the persistent launch's lists, longest (estimated
-  // time) first, indexed by kList*, and the whole-chip time of each
+  // tile indices of the launch's lists, longest (estimated time) first,
+  // indexed by kList*, and the whole-chip time of each
   std::vector<uint32_t> order[kBatchLists];
   double cost[kBatchLists] = {0, 0, 0};
 };
@@ -91,18 +91,18 @@ hipError_t launch_batch_mt(const BatchTile* tiles, uint32_t ntiles, const BatchT
 // task state moved first * kMtSection outputs on (one workgroup each)
 hipError_t launch_batch_mt_starts(const DeviceTables& T, const BatchTile* tiles, uint32_t ntiles,
                                   const BatchTask* tasks, char* scratch, hipStream_t st);
-// persistent launch: one tile counter per list, cleared by a small kernel
-// (no memset node in a captured graph)
-hipError_t launch_batch_reset(uint32_t* counters, hipStream_t st);
-// workgroups of a persistent kernel resident on the chip at once (reg: of
+// the reg kernel's tile counter, cleared by a small kernel (no memset node in a
+// captured graph)
+hipError_t launch_batch_reset(uint32_t* counter, hipStream_t st);
+// workgroups of the persistent reg kernel resident on the chip at once (of
 // `waves` wavefronts, LDS chunk width cw = 16 or 32)
-uint32_t batch_main_blocks(int num_cus);
 uint32_t batch_reg_blocks(int cw, uint32_t waves, int num_cus);
+// MT19937 and copy tiles, then GM/GQ tiles
 hipError_t launch_batch_main(const DeviceTables& T, const BatchTile* tiles, const uint32_t* mt_order, uint32_t nmt,
                              const uint32_t* gm_order, uint32_t ngm, const BatchTask* tasks, char* scratch,
-                             uint32_t* counters, uint32_t blocks, hipStream_t st);
+                             hipStream_t st);
 hipError_t launch_batch_reg_persistent(int cw, const BatchTile* tiles, const uint32_t* order, uint32_t n,
-                                       const BatchTask* tasks, char* scratch, uint32_t* counters, uint32_t waves,
+                                       const BatchTask* tasks, char* scratch, uint32_t* counter, uint32_t waves,
                                        uint32_t blocks, hipStream_t st);
 // all of them on one stream: section starts, MT19937, GM/GQ, MRG32K3A/LFSR113
 hipError_t launch_batch_serial(const DeviceTables& T, const BatchTile* tiles, const BatchCounts& n,

@@ -1,6 +1,7 @@
-"""The batch autotuner: its pick is no slower than a default configuration,
-also where the tasks are few and short, and a cache file of a library with
-other plans is not taken."""
+"""How long batches take.  The autotuner's pick is no slower than a default
+configuration, also where the tasks are few and short, and a cache file of a
+library with other plans is not taken; a batch's tiles cost little by
+themselves, however many there are."""
 import numpy as np
 import pytest
 import torch
@@ -65,3 +66,19 @@ def test_cache_of_other_plans_is_not_taken(ctx, tmp_path, monkeypatch):
     path.write_text(f"{key}\t2 64 128 16 2\n")
     best = P.autotune(ctx, tasks)
     assert (best.waves_per_block, best.reg_section, best.gm_section, best.overlap) == (2, 64, 128, 2)
+
+
+def test_many_tiles_cost_little(ctx):
+    n = 10**7
+    tasks = _tasks(ctx, [(P.GM19, n)])
+    state, out = ctx.seed(P.GM19, 1), torch.empty(n, dtype=torch.float32, device="cuda")
+    single = 1e9
+    for _ in range(30):
+        a, z = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        ctx.generate(P.GM19, state, P.F32, out, n)
+        z.record()
+        z.synchronize()
+        single = min(single, a.elapsed_time(z))
+    # 10^4 tiles: 67 us and 57 by the single call; 203 with a counter they are taken from
+    assert _time(ctx, tasks, P.BatchConfig(use_graph=1)) <= 2.5 * single
