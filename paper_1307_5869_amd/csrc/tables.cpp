@@ -127,6 +127,18 @@ uint32_t f2_apply(const uint32_t* cols, uint32_t v) {
 }  // namespace
 
 namespace {
+// a matrix by the bytes of the word it is applied to
+struct F2Bytes {
+  uint32_t t[4][256];
+  explicit F2Bytes(const uint32_t* cols) {
+    for (int q = 0; q < 4; q++) {
+      t[q][0] = 0;
+      for (int x = 1; x < 256; x++) t[q][x] = t[q][x & (x - 1)] ^ cols[8 * q + __builtin_ctz(x)];
+    }
+  }
+  uint32_t apply(uint32_t v) const { return t[0][v & 255] ^ t[1][v >> 8 & 255] ^ t[2][v >> 16 & 255] ^ t[3][v >> 24]; }
+};
+
 // columns of T_c^(d 2^(e + 8 j)) for every byte position j < 8 and value d
 // (row [j][d], 128 words, the layout of the section tables)
 void lfsr_bytes(int e, uint32_t* out) {
@@ -138,11 +150,11 @@ void lfsr_bytes(int e, uint32_t* out) {
       std::memcpy(b, t, sizeof t);
     }
     for (int pos = 0; pos < 8; pos++) {
+      const F2Bytes by(b);
       for (int j = 0; j < 32; j++) m[j] = 1u << j;   // d = 0: identity
       for (int d = 0; d < 256; d++) {
         std::memcpy(out + (((size_t)pos * 256 + d) * 4 + c) * 32, m, sizeof m);
-        for (int j = 0; j < 32; j++) t[j] = f2_apply(b, m[j]);
-        std::memcpy(m, t, sizeof t);
+        for (int j = 0; j < 32; j++) m[j] = by.apply(m[j]);
       }
       std::memcpy(b, m, sizeof b);   // m = b^256
     }
@@ -286,7 +298,10 @@ bool balanced(__int128 v, int b, int n, int* d) {
 void gmx_digits(uint64_t a, uint64_t p, int b, int n, int* best) {
   int score = 1 << 30;
   int d[8];
-  for (int t = -40; t <= 40; t++) {
+  // `n` digits hold the values of magnitude below 2^(b n - 1) (1 + 2 / 2^b)
+  const __int128 reach = ((__int128)1 << (b * n - 1)) + ((__int128)1 << (b * n - b));
+  const int most = (int)(reach / p < 40 ? reach / p + 1 : 40);
+  for (int t = -most; t <= most; t++) {
     if (!balanced((__int128)a + (__int128)t * p, b, n, d)) continue;
     int s = 0;
     for (int m = 0; m < n; m++) s += d[m] > 0 ? 3 * d[m] : -d[m];
