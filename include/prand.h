@@ -190,11 +190,13 @@ int prand_generate(prand_ctx* ctx, int gen, void* h_state, int dtype, void* d_ou
 /* Fill the host array h_out with the next n outputs of one host state
    (rng_generate_array_, section "Multi-threaded generation of pseudorandom
    numbers with GPGPU"): the values are generated on the device exactly as
-   by prand_generate, in chunks of up to 2^26 values through one device
-   buffer allocated for the call, and copied to the host; h_state is
-   advanced by n.  Any n is accepted (the paper's version pads n to a
-   multiple of its section count on the device; here the sections need no
-   padding).  PRAND_ERANGE when n > 2^40.  Blocks. */
+   by prand_generate, in chunks of up to 64 MB, and copied to the host by way of
+   pinned buffers; h_state is advanced by n.  The context keeps the buffers
+   between calls (up to two sets of at most 64 MB of device and 6 MB of pinned
+   memory, freed with it); calls of several threads run side by side, only the
+   generation of their chunks is serialised.  Any n is accepted (the paper's
+   version pads n to a multiple of its section count on the device; here the
+   sections need no padding).  PRAND_ERANGE when n > 2^40.  Blocks. */
 int prand_generate_array(prand_ctx* ctx, int gen, void* h_state, int dtype, void* h_out, uint64_t n);
 
 /* Many independent streams (section "Multi-threaded generation of

@@ -384,6 +384,36 @@ __global__ void copy_state_kernel(uint32_t* dst, const uint32_t* src, uint32_t w
   for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) dst[i] = src[i];
 }
 
+void free_array_buffers(ArrayBuffers* b) {
+  if (!b) return;
+  (void)hipFree(b->dev);
+  (void)hipHostFree(b->pin);
+  for (hipEvent_t ev : b->ev)
+    if (ev) (void)hipEventDestroy(ev);
+  delete b;
+}
+
+// a set of the context's free ones, or a new one (null: out of memory); given
+// back at the end of its scope
+struct TakenBuffers {
+  prand_ctx* c;
+  ArrayBuffers* b = nullptr;
+  explicit TakenBuffers(prand_ctx* ctx) : c(ctx) {
+    std::lock_guard<std::mutex> lk(c->arr_mu);
+    for (ArrayBuffers*& f : c->arr_free)
+      if (!b && f) std::swap(b, f);
+    if (!b) b = new (std::nothrow) ArrayBuffers;
+  }
+  ~TakenBuffers() {
+    {
+      std::lock_guard<std::mutex> lk(c->arr_mu);
+      for (ArrayBuffers*& f : c->arr_free)
+        if (b && !f) std::swap(b, f);
+    }
+    free_array_buffers(b);   // more calls at once than sets are kept
+  }
+};
+
 // the host state in pinned slot 0 after `launch` on it, back to h_state (the
 // default stream; the caller holds mu)
 template <class F>
@@ -637,10 +667,7 @@ int prand_ctx_destroy(prand_ctx* c) {
   (void)hipFree(c->scratch);
   (void)hipFree(c->sec_buf);
   (void)hipHostFree(c->pin);
-  (void)hipFree(c->arr_dev);
-  (void)hipHostFree(c->arr_pin);
-  for (hipEvent_t ev : c->arr_ev)
-    if (ev) (void)hipEventDestroy(ev);
+  for (ArrayBuffers* b : c->arr_free) free_array_buffers(b);
   for (auto& v : c->sec_tabs)
     for (auto& t : v) (void)hipFree(t.second);
   delete c;
@@ -806,51 +833,53 @@ int prand_generate_array(prand_ctx* c, int gen, void* h_state, int dtype, void* 
   // CPU copies the one before on: 10^7 MRG32K3A f32 took 2.4 ms by one copy
   // into pageable memory, 1.5 so (the copying CPU's rate, 27 GB/s).  A call of
   // at most 256 KB is generated straight into a pinned buffer.
-  std::lock_guard<std::mutex> lk(c->arr_mu);
+  TakenBuffers taken(c);
+  ArrayBuffers* const b = taken.b;
+  if (!b) return PRAND_ENOMEM;
   const size_t es = elem_bytes(dtype);
   hipError_t e = hipSuccess;
-  if (!c->arr_pin) {
-    e = hipHostMalloc((void**)&c->arr_pin, kArrayPins * kArrayPinBytes, hipHostMallocMapped);
-    if (e != hipSuccess) c->arr_pin = nullptr;
+  if (!b->pin) {
+    e = hipHostMalloc((void**)&b->pin, kArrayPins * kArrayPinBytes, hipHostMallocMapped);
+    if (e != hipSuccess) b->pin = nullptr;
   }
-  for (hipEvent_t& ev : c->arr_ev)
+  for (hipEvent_t& ev : b->ev)
     if (e == hipSuccess && !ev) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
   const uint64_t chunk = std::min<uint64_t>(n, kArrayDevBytes / es);
   const bool direct = n * es <= (256u << 10);
-  if (e == hipSuccess && !direct && c->arr_dev_bytes < chunk * es) {
-    (void)hipFree(c->arr_dev);
-    c->arr_dev = nullptr;
-    c->arr_dev_bytes = 0;
-    e = hipMalloc(&c->arr_dev, chunk * es);
-    if (e == hipSuccess) c->arr_dev_bytes = chunk * es;
+  if (e == hipSuccess && !direct && b->dev_bytes < chunk * es) {
+    (void)hipFree(b->dev);
+    b->dev = nullptr;
+    b->dev_bytes = 0;
+    e = hipMalloc(&b->dev, chunk * es);
+    if (e == hipSuccess) b->dev_bytes = chunk * es;
   }
   if (e != hipSuccess) {
     (void)hipGetLastError();
     return e == hipErrorOutOfMemory ? PRAND_ENOMEM : hipfail(c, e);
   }
   if (direct) {
-    rc = generate_host_state(c, gen, h_state, dtype, c->arr_pin, n, nullptr, nullptr, 0);
-    if (rc == PRAND_OK) std::memcpy(h_out, c->arr_pin, n * es);
+    rc = generate_host_state(c, gen, h_state, dtype, b->pin, n, nullptr, nullptr, 0);
+    if (rc == PRAND_OK) std::memcpy(h_out, b->pin, n * es);
     return rc;
   }
   for (uint64_t done = 0; done < n && rc == PRAND_OK; done += chunk) {
     const uint64_t m = std::min(chunk, n - done);
-    rc = generate_host_state(c, gen, h_state, dtype, c->arr_dev, m, nullptr, nullptr, 0);
+    rc = generate_host_state(c, gen, h_state, dtype, b->dev, m, nullptr, nullptr, 0);
     if (rc != PRAND_OK) break;
     const size_t bytes = m * es, pieces = (bytes + kArrayPinBytes - 1) / kArrayPinBytes;
     char* const to = (char*)h_out + done * es;
     auto size_of = [&](size_t k) { return std::min(kArrayPinBytes, bytes - k * kArrayPinBytes); };
     auto start = [&](size_t k) {
       if (e == hipSuccess)
-        e = hipMemcpyAsync(c->arr_pin + (k % kArrayPins) * kArrayPinBytes, (char*)c->arr_dev + k * kArrayPinBytes,
+        e = hipMemcpyAsync(b->pin + (k % kArrayPins) * kArrayPinBytes, (char*)b->dev + k * kArrayPinBytes,
                            size_of(k), hipMemcpyDeviceToHost, nullptr);
-      if (e == hipSuccess) e = hipEventRecord(c->arr_ev[k % kArrayPins], nullptr);
+      if (e == hipSuccess) e = hipEventRecord(b->ev[k % kArrayPins], nullptr);
     };
     for (size_t k = 0; k < std::min<size_t>(pieces, kArrayPins); k++) start(k);
     for (size_t k = 0; k < pieces && e == hipSuccess; k++) {
-      e = hipEventSynchronize(c->arr_ev[k % kArrayPins]);
+      e = hipEventSynchronize(b->ev[k % kArrayPins]);
       if (e != hipSuccess) break;
-      std::memcpy(to + k * kArrayPinBytes, c->arr_pin + (k % kArrayPins) * kArrayPinBytes, size_of(k));
+      std::memcpy(to + k * kArrayPinBytes, b->pin + (k % kArrayPins) * kArrayPinBytes, size_of(k));
       if (k + kArrayPins < pieces) start(k + kArrayPins);
     }
     if (e != hipSuccess) {

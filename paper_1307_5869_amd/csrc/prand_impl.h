@@ -320,7 +320,16 @@ namespace prand {
 constexpr size_t kPinBytes = 8192, kPinOut = 4096;
 constexpr int kPinSlots = 2;
 constexpr size_t kArrayDevBytes = 64u << 20, kArrayPinBytes = 2u << 20;
-constexpr int kArrayPins = 3;
+constexpr int kArrayPins = 3, kArrayKept = 2;
+
+// what one prand_generate_array call works with: a device buffer of up to
+// kArrayDevBytes, pinned copy buffers and the events of their copies
+struct ArrayBuffers {
+  void* dev = nullptr;
+  size_t dev_bytes = 0;
+  char* pin = nullptr;
+  hipEvent_t ev[kArrayPins] = {};
+};
 static_assert(sizeof(MtState) <= kPinOut, "a state fits half a slot");
 }  // namespace prand
 
@@ -342,14 +351,11 @@ struct prand_ctx {
   // calls pass in (at 0) and get back (at kPinOut): slot 0 under mu, slot 1
   // under the allocation-free entry point's lock of the device
   char* pin = nullptr;
-  // prand_generate_array: device buffer and pinned copy buffers, kept between
-  // calls (at most kArrayDevBytes and kArrayPins kArrayPinBytes), and the
-  // events of the copies; guarded by arr_mu
+  // prand_generate_array: buffers that no call is using, kept between calls (up
+  // to kArrayKept sets; a call takes one, or makes its own); arr_mu guards the
+  // list alone, calls of several threads run side by side
   std::mutex arr_mu;
-  void* arr_dev = nullptr;
-  size_t arr_dev_bytes = 0;
-  char* arr_pin = nullptr;
-  hipEvent_t arr_ev[prand::kArrayPins] = {};
+  prand::ArrayBuffers* arr_free[prand::kArrayKept] = {};
   // section-start tables by section length, [0] MRG32K3A, [1] LFSR113
   // (built on first use, immutable afterwards, freed with the context)
   std::mutex sec_mu;
