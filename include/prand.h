@@ -95,10 +95,11 @@ int prand_last_hip_error(const prand_ctx* ctx);
 
 /* Create a context on HIP device `hip_device`: uploads the jump-ahead tables
    (the counterpart of the paper's rng_init_device_consts_, section "Function
-   call interface for MRG32K3A / MT19937"): matrix powers A^(2^j), B^(2^j) for
-   MRG32K3A, 32x32 F2 matrix powers for LFSR113, 2x2 matrix powers for GM/GQ,
-   and x^(2^j) mod phi for MT19937 (equation g_v; phi is computed once by
-   Berlekamp-Massey).  The MT19937 tables (656 MB: the ladder, the digit
+   call interface for MRG32K3A / MT19937"): the step matrices (A, B of
+   MRG32K3A, 32x32 over F2 for LFSR113, 2x2 for GM/GQ) at every power
+   d * 256^j, d < 256, of a 64-bit distance and at 2^j above it, and
+   x^(2^j) mod phi for MT19937 (equation g_v; phi is computed once by
+   Berlekamp-Massey).  The MT19937 tables (656 MB: the powers, the digit
    tables of block splitting and the 65536 precomputed top-16-bit states)
    are built when a call first needs them and are shared by all contexts on
    the same device, freed with the last of them.  *ctx is set to NULL on
@@ -180,10 +181,13 @@ int prand_init_streams_dev(prand_ctx* ctx, int gen, int variant, const void* d_b
    array_[float_|double_], section "Multi-threaded generation"): the array is
    cut into sections that jump to their start and fill in parallel; the
    result equals sequential generation for every n (no divisibility or
-   power-of-two condition).  h_state is advanced by n.  The section states
-   live in a device buffer the context keeps between calls (allocated, or
-   grown, only when a call needs more than any earlier one; freed with the
-   context); calls on one context are serialised.  Blocks. */
+   power-of-two condition).  h_state is advanced by n.  Only MT19937 needs
+   section states in memory: they live in a device buffer the context keeps
+   between calls (allocated, or grown, only when a call needs more than any
+   earlier one; freed with the context).  The other generators are one launch
+   whose lanes or wavefronts jump by themselves.  h_state goes and comes by way
+   of pinned memory of the context; calls on one context are serialised.
+   Blocks. */
 int prand_generate(prand_ctx* ctx, int gen, void* h_state, int dtype, void* d_out, uint64_t n,
                    void* stream);
 
@@ -217,14 +221,14 @@ int prand_generate_streams(prand_ctx* ctx, int gen, void* d_states, uint32_t cou
 
 /* prand_generate for callers that cannot allocate device memory (harnesses
    that forbid hipMalloc, tight serving loops): the same arguments, result
-   and blocking behaviour, but the section start states, their distances and
-   the copied-in state live in a static device array of 4 MiB per GPU
-   (PRAND_NOALLOC_SCRATCH_BYTES) instead of memory allocated per call, and no
-   hipMalloc, hipFree or allocating library routine is called.  The array is
-   reserved by the library on each device where a context is created and is
-   held until the process ends.  The section plan is limited to what fits in
-   it (at most 1663 MT19937, 7941 GM/GQ, 131048 MRG32K3A and 174730 LFSR113
-   sections); the output never depends on the plan.  PRAND_ERANGE when
+   and blocking behaviour, but what the call keeps in device memory (MT19937:
+   the copied-in state, the section start states and their distances; GM/GQ:
+   the copied-in state; MRG32K3A and LFSR113: nothing) lives in a static device
+   array of 4 MiB per GPU (PRAND_NOALLOC_SCRATCH_BYTES), and no hipMalloc,
+   hipFree or allocating library routine is called.  The array is reserved by
+   the library on each device where a context is created and is held until the
+   process ends.  It holds the 512 sections that an MT19937 call is cut into at
+   most, so the plans are those of prand_generate.  PRAND_ERANGE when
    n > 2^40.  MT19937 needs the context's jump tables: PRAND_ENOTREADY when no
    earlier MT19937 call on this context (for example prand_init_stream) has
    built them.  Every call on one GPU shares that GPU's array and keeps the

@@ -1,6 +1,6 @@
 // prand_generate_noalloc: the sectioned fill of prand_generate with its
-// scratch (section start states, their distances, the copied-in state) in a
-// file-scope device array instead of memory allocated per call.
+// scratch (the copied-in state; MT19937: section start states and their
+// distances too) in a file-scope device array instead of allocated memory.
 //
 // The array's name is a host-side stand-in in host code: its device address
 // is looked up once per device (hipGetSymbolAddress, from the context set-up

@@ -43,8 +43,8 @@ __device__ __forceinline__ void put_word(void* out, uint64_t i, uint32_t w, doub
 }
 
 // One lane's section: live lanes start from *in (jumped `start` outputs
-// ahead: by the jump matrix sec_mat when it is given, else through the
-// ladder), write `len` values at `out` (element pointer of the run) and, when
+// ahead: by the jump matrix sec_mat when it is given, else by the bytes of
+// the distance), write `len` values at `out` (element pointer of the run) and, when
 // `sout` is set, store the advanced state there.  All 64 lanes must call.
 // kJump = false: the caller guarantees start == 0 (no jump code is built).
 // unit: bytes that the chunks are aligned to (16: short runs, which then touch
